@@ -312,6 +312,9 @@ struct Layout {
     int32_t *kT = nullptr, *posT = nullptr;  // transposed position <-> incidence
     int32_t *ptrS, *itmS;
     int32_t *pos;   // s filter: kept entries before each member-list entry (nnz + 1)
+    // s filter: the kept items' candidate numbers (N + 1) and their items (N);
+    // null when not used
+    int32_t *crank = nullptr, *orig = nullptr;
     int32_t *xcol;  // batches: columns of the dual graphs' rows (XD)
     int64_t *cost, *tbase, *part64;
     int32_t *part32, *ntask, *start;
@@ -327,7 +330,10 @@ Tuning build_tuning(const Tuning &t, int64_t n_items) {
     return u;
 }
 
-Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64_t M, bool filt) {
+// ranks: with room for candidate numbers.  fixed: the arena is a fixed region,
+// where they must not make a build too large that fits without them.
+Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64_t M, bool filt,
+                   bool ranks = false, bool fixed = false) {
     Layout L{};
     L.err = A.take<int32_t>(4);
     L.queue = A.take<int32_t>(4);
@@ -351,6 +357,14 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
         L.ptrS = A.take<int32_t>(M + 1);
         L.pos = A.take<int32_t>(nnz + 1);
         L.itmS = A.take<int32_t>(nnz);
+        if (ranks && N + 1 <= nnz) {
+            // the sort's value buffers are idle once the lists are transposed
+            L.crank = L.rsV0;
+            L.orig = L.rsV1;
+        } else if (ranks && !fixed) {
+            L.crank = A.take<int32_t>(N + 1);
+            L.orig = A.take<int32_t>(N);
+        }
     }
     L.cost = A.take<int64_t>(N);
     L.ntask = A.take<int32_t>(N);
@@ -762,11 +776,14 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     const bool noprune = (flags & SLINE_NO_PRUNE) != 0;
     const bool filt = IS.s_max > 1 && !noprune;
     Arena sizing;
-    plan_layout(sizing, m, n, nnz, N, M, filt);
+    const bool fixed = c->fixed.base != nullptr;
+    // the intersections of the variants without visited skipping read items
+    const bool ranks = filt && N >= kRankMinItems && !IS.item_end && !(flags & SLINE_NO_VISITED);
+    plan_layout(sizing, m, n, nnz, N, M, filt, ranks, fixed);
     ensure_ws(c, sizing.off + 4096);
     Arena A;
     A.base = reinterpret_cast<char *>(c->ws);
-    const Layout L = plan_layout(A, m, n, nnz, N, M, filt);
+    const Layout L = plan_layout(A, m, n, nnz, N, M, filt, ranks, fixed);
 
     hip_check(c, launch_fill_i32(st, L.err, 4, 0), "zero flags");
     hip_check(c, launch_fill_i32(st, L.tcounts, 4, 0), "zero task counts");
@@ -801,7 +818,8 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
         // the task counts are written later: until then their array holds
         // the filter's per-item keep flags
         hip_check(c, launch_filter(st, ptrM, itmM, (int32_t)M, nnz, ptrI, (int32_t)N, s, IS.s_item,
-                                   L.ntask, L.pos, L.part32, L.ptrS, L.itmS, inv, L.start),
+                                   L.ntask, L.pos, L.part32, L.ptrS, L.itmS, inv, L.start,
+                                   L.crank, L.orig),
                   "filter");
         ptrS = L.ptrS;
         itmS = L.itmS;
@@ -835,8 +853,8 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
         hip_check(c, launch_mark_lookup(st, ptrI, memI, (int32_t)N, s, IS.s_item, IS.s_max, ptrS,
                                         L.start, L.cost, IS.full ? 0 : tu.tiny_max_wedges),
                   "lookup members");
-    hip_check(c, launch_task_count(st, L.cost, (int32_t)N, tu, ptrI, IS.item_end, IS.full ? 1 : 0,
-                                   L.ntask),
+    hip_check(c, launch_task_count(st, L.cost, (int32_t)N, tu, ptrI, L.crank, IS.item_end,
+                                   IS.full ? 1 : 0, L.ntask),
               "task count");
     hip_check(c, launch_scan_i32_to_i64(st, L.ntask, N, L.tbase, L.part64), "task scan");
     int64_t *h = c->host;
@@ -857,8 +875,8 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     Arena TA;
     TA.base = reinterpret_cast<char *>(c->ws2);
     const TaskLayout TL = plan_tasks(TA, T);
-    hip_check(c, launch_task_fill(st, L.cost, (int32_t)N, tu, ptrI, IS.item_end, IS.full ? 1 : 0,
-                                  L.tbase, TL.item, TL.part, TL.small,
+    hip_check(c, launch_task_fill(st, L.cost, (int32_t)N, tu, ptrI, L.crank, IS.item_end,
+                                  IS.full ? 1 : 0, L.tbase, TL.item, TL.part, TL.small,
                                   TL.small_item, TL.tiny, TL.tiny_item, TL.big, L.tcounts),
               "task fill");
     mark(c, 2);
@@ -882,6 +900,8 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     C.memI = memI;
     C.ptrS = ptrS;
     C.itmS = itmS;
+    C.crank = L.crank;
+    C.orig = L.orig;
     C.N = (int32_t)N;
     C.s = s;
     C.s_item = IS.s_item;
@@ -1514,7 +1534,7 @@ void plan_enqueue_prep(sline_batch_plan *p, hipStream_t st, int64_t t_cap) {
     hip_check(c, launch_mark_lookup(st, ptrI, memI, NI, p->s_min, p->K.s_item, INT32_MAX, L.ptrS,
                                     L.start, L.cost, tu.tiny_max_wedges),
               "lookup members");
-    hip_check(c, launch_task_count(st, L.cost, NI, tu, ptrI, p->K.iend, 0, L.ntask), "task count");
+    hip_check(c, launch_task_count(st, L.cost, NI, tu, ptrI, nullptr, p->K.iend, 0, L.ntask), "task count");
     hip_check(c, launch_scan_i32_to_i64(st, L.ntask, NI, L.tbase, L.part64), "task scan");
     if (t_cap >= 0)
         hip_check(c, launch_plan_guard(st, L.tbase + NI, t_cap, kErrPlanTasks, p->d_err), "task guard");
@@ -1529,8 +1549,8 @@ void plan_enqueue_count(sline_batch_plan *p, hipStream_t st, int64_t pair_cap) {
     const TaskLayout &TL = p->TL;
     const CountArgs &C = p->C;
     const int32_t NI = (int32_t)p->B.NI;
-    hip_check(c, launch_task_fill(st, L.cost, NI, C.tune, C.ptrI, p->K.iend, 0, L.tbase, TL.item,
-                                  TL.part, TL.small, TL.small_item, TL.tiny, TL.tiny_item, TL.big,
+    hip_check(c, launch_task_fill(st, L.cost, NI, C.tune, C.ptrI, nullptr, p->K.iend, 0, L.tbase,
+                                  TL.item, TL.part, TL.small, TL.small_item, TL.tiny, TL.tiny_item, TL.big,
                                   L.tcounts, p->d_err),
               "task fill");
     hip_check(c, launch_fill_i32(st, TL.need, p->t_cap, 0), "zero need flags");

@@ -53,7 +53,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "sline_internal.h"
+#include "sline_count.h"
 
 namespace sl {
 
@@ -61,23 +61,6 @@ namespace {
 
 constexpr int kR = 8;        // member cursors per thread held in registers
 constexpr int kPiece = 256;  // planned entries per piece of a long member run
-
-__device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
-// Wave index inside the workgroup, as a wave-uniform (scalar) value.
-__device__ __forceinline__ int wave_id() {
-    return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-}
-
-__device__ __forceinline__ int32_t wave_total(int32_t v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-    return v;
-}
-
-__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
 
 // first index p in [lo, hi) with arr[p] >= key (arr ascending), hi if none
 __device__ __forceinline__ int32_t lower_bound(const int32_t *arr, int32_t lo, int32_t hi,
@@ -505,36 +488,6 @@ __device__ __forceinline__ void insert_range(const CountArgs &A, const Smem &S, 
     }
 }
 
-// Where the pairs of item `item` at combined output position `pos` go: the
-// single output, or (batches written per graph) the arrays of the item's
-// graph at the position inside it, ids to be written less `shift`.
-struct OutDst {
-    int32_t *a, *b, *w;
-    int64_t base;
-    int32_t shift;
-};
-
-__device__ __forceinline__ OutDst out_dst(const CountArgs &A, int32_t item, int64_t pos) {
-    OutDst d{A.out_a, A.out_b, A.out_w, pos, 0};
-    const int32_t G = A.n_graphs;
-    if (G > 0) {
-        int32_t lo = 0, hi = G;  // g_ibase[lo] <= item < g_ibase[hi]
-        while (hi - lo > 1) {
-            const int32_t mid = (lo + hi) >> 1;
-            if (A.g_ibase[mid] <= item) lo = mid;
-            else hi = mid;
-        }
-        d.shift = (int32_t)A.g_ibase[lo];
-        if (A.g_out) {
-            d.a = A.g_out[lo];
-            d.b = A.g_out[G + lo];
-            d.w = A.g_out[2 * G + lo];
-            d.base = pos - A.g_off[lo];
-        }
-    }
-    return d;
-}
-
 // Zero table words [0, limit); `tab` is 16-byte aligned.
 template <int NT>
 __device__ __forceinline__ void tab_clear(uint32_t *tab, int32_t limit) {
@@ -566,18 +519,6 @@ __device__ __forceinline__ int32_t bucket_pairs(const uint4 &q, const Range &R, 
            packed_hits(q.w, R.psh, s);
 }
 
-// Sum over the wave of n (0 <= n < 32) and the sum over the lanes below this
-// one, from the ballots of its bits (nb = bits of n that can be set).
-__device__ __forceinline__ void wave_bits_prefix(int32_t n, int nb, int32_t &before, int32_t &step) {
-    before = 0;
-    step = 0;
-    for (int b = 0; b < nb; ++b) {
-        const uint64_t m = __ballot((n >> b) & 1);
-        before += (int32_t)lanes_below(m) << b;
-        step += (int32_t)__popcll(m) << b;
-    }
-}
-
 __device__ __forceinline__ void cswap(uint32_t &x, uint32_t &y) {
     const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
     x = lo;
@@ -586,40 +527,6 @@ __device__ __forceinline__ void cswap(uint32_t &x, uint32_t &y) {
 
 __device__ __forceinline__ bool bucket_full(const uint4 &q) {
     return q.x != 0u && q.y != 0u && q.z != 0u && q.w != 0u;
-}
-
-// Stage mode, thread 0 of a workgroup: room for `total` pairs in the pool and
-// `nrec` consecutive log records, taken from this workgroup's chunks (one
-// global atomic per new chunk; records of a chunk left unused stay zero, i.e.
-// empty).  Returns false if the pool or the log has no room left.
-__device__ __forceinline__ bool stage_reserve(const CountArgs &A, uint64_t *pool_cur,
-                                              int32_t *log_cur, int32_t total, int32_t nrec,
-                                              uint64_t &off, int32_t &rec) {
-    off = pool_cur[0];
-    rec = 0;
-    if (off + (uint64_t)total > pool_cur[1]) {
-        const uint64_t size = max((uint64_t)total, (uint64_t)A.pool_chunk);
-        off = atomicAdd(A.pool_head, (unsigned long long)size);
-        if (off + size <= (uint64_t)A.pool_cap) {
-            pool_cur[1] = off + size;
-        } else if (off + (uint64_t)total <= (uint64_t)A.pool_cap) {
-            pool_cur[1] = (uint64_t)A.pool_cap;
-        } else {
-            pool_cur[1] = 0;
-            return false;
-        }
-    }
-    pool_cur[0] = off + (uint64_t)total;
-    if (log_cur[0] + nrec > log_cur[1]) {
-        const int32_t size = max(nrec, A.log_chunk);
-        const int32_t r = atomicAdd(A.log_head, size);
-        log_cur[0] = r;
-        log_cur[1] = (int32_t)min((int64_t)r + size, (int64_t)A.log_cap);
-    }
-    rec = log_cur[0];
-    if (rec + nrec > log_cur[1]) return false;
-    log_cur[0] = rec + nrec;
-    return true;
 }
 
 // Extract the candidates with count >= s and return their number
@@ -743,7 +650,7 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
                         if (cnt >= s) {
                             const int32_t b = R.lo + (int32_t)(((uint32_t)(4 * bk + k) << R.psh) + j);
                             if (dst_a) dst_a[base + pos] = a - shift;
-                            dst_b[base + pos] = b - shift;
+                            dst_b[base + pos] = dst_a ? item_of(A.orig, b) - shift : b;
                             if (dst_w) dst_w[base + pos] = (int32_t)cnt;
                             ++pos;
                         }
@@ -756,7 +663,8 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
                 for (int k = 0; k < 4; ++k) {
                     if (ok[k]) {
                         if (dst_a) dst_a[base + pos] = a - shift;
-                        dst_b[base + pos] = R.lo + 4 * bk + k - shift;
+                        const int32_t b = R.lo + 4 * bk + k;
+                        dst_b[base + pos] = dst_a ? item_of(A.orig, b) - shift : b;
                         if (dst_w) dst_w[base + pos] = (int32_t)c[k];
                         ++pos;
                     }
@@ -829,7 +737,8 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
                     if (k < n) {
                         const int32_t p = pos + rank[k];
                         if (dst_a) dst_a[base + p] = a - shift;
-                        dst_b[base + p] = R.lo + (int32_t)tag[k] - 1 - shift;
+                        const int32_t b = R.lo + (int32_t)tag[k] - 1;
+                        dst_b[base + p] = dst_a ? item_of(A.orig, b) - shift : b;
                         if (dst_w) dst_w[base + p] = (int32_t)(key[k] & R.cmask);
                     }
                 }
@@ -922,10 +831,11 @@ __device__ __forceinline__ int64_t run_range(const CountArgs &A, const Smem &S, 
     return produced;
 }
 
-// Cursors of the thread's members for a walk starting at candidate lo.
+// Cursors of the thread's members for a walk starting at candidate lo (first:
+// the item's first candidate, where the back-pointers point).
 template <int NT>
-__device__ __forceinline__ void init_cursors(const CountArgs &A, int32_t a, int32_t lo, int32_t k0,
-                                             int32_t k1, int32_t (&cur)[kR], int32_t (&end)[kR],
+__device__ __forceinline__ void init_cursors(const CountArgs &A, int32_t first, int32_t lo,
+                                             int32_t k0, int32_t k1, int32_t (&cur)[kR], int32_t (&end)[kR],
                                              uint32_t &lookm) {
     lookm = 0;
 #pragma unroll
@@ -939,7 +849,7 @@ __device__ __forceinline__ void init_cursors(const CountArgs &A, int32_t a, int3
             const int32_t st = A.start[k];
             lookm |= (uint32_t)(st < 0) << i;
             int32_t c = st & kStartMask;
-            if (lo > (A.full ? 0 : a + 1)) c = lower_bound(A.itmS, c, e, lo);
+            if (lo > first) c = lower_bound(A.itmS, c, e, lo);
             cur[i] = c;
             end[i] = e;
         }
@@ -972,12 +882,10 @@ __device__ __forceinline__ int32_t task_parts(int64_t cost, int32_t small_max, i
     return (int32_t)min(P, (int64_t)INT32_MAX);
 }
 
-// Candidate span of item a: [a + 1, end) (product mode: [0, end)), end = its
-// graph's end (batches) or N.
-__device__ __forceinline__ int64_t item_span(const int32_t *item_end, int32_t N, int32_t full,
-                                             int32_t a) {
-    const int64_t e = item_end ? item_end[a] : N;
-    return e - (full ? 0 : (int64_t)a + 1);
+// Number of candidates of item a.
+__device__ __forceinline__ int64_t item_span(const int32_t *crank, const int32_t *item_end,
+                                             int32_t N, int32_t full, int32_t a) {
+    return (int64_t)cand_end(crank, item_end, N, a) - cand_first(crank, full, a);
 }
 
 // Sub-range p of P of the candidate range [first, N) of an item.
@@ -994,14 +902,6 @@ constexpr int kTaskPad = 64;
 constexpr int kTaskRunCap = 256;
 constexpr int kStack = 64;
 
-// A counting launch with nothing to do: the plan's bounds were exceeded (or
-// its input is malformed), or a fill pass that only recounts tasks flagged in
-// `need` while none is flagged.
-__device__ __forceinline__ bool count_idle(const CountArgs &A) {
-    if (A.abort && *A.abort != 0) return true;
-    return A.mode == kModeFill && A.need && A.need_count && *A.need_count == 0;
-}
-
 // --------------------------------------------------------------- small
 
 // SLOTS: home slots of the wave's table (Tuning::small_slots).
@@ -1017,6 +917,7 @@ __global__ __launch_bounds__(kWave) void k_count_small(CountArgs A) {
     __shared__ int32_t log_cur[2];
     const Smem S{tab, runs, taken, misc, stack, tab + LIM, pool_cur, log_cur};
     if (count_idle(A)) return;  // uniform: every thread reads the same words
+    use_ranks(A);
     if (threadIdx.x == 0) {
         pool_cur[0] = pool_cur[1] = 0;
         log_cur[0] = log_cur[1] = 0;
@@ -1036,10 +937,11 @@ __global__ __launch_bounds__(kWave) void k_count_small(CountArgs A) {
         const int32_t k0 = A.ptrI[a], k1 = A.ptrI[a + 1];
         int32_t cur[kR], end[kR];
         uint32_t lookm;
-        const int32_t nend = A.item_end ? A.item_end[a] : A.N;
-        init_cursors<kWave>(A, a, A.full ? 0 : a + 1, k0, k1, cur, end, lookm);
+        const int32_t first = cand_first(A.crank, A.full, a);
+        const int32_t nend = cand_end(A.crank, A.item_end, A.N, a);
+        init_cursors<kWave>(A, first, first, k0, k1, cur, end, lookm);
         const int64_t produced = run_range<kWave, kSmallPad, kSmallRunCap>(
-            A, S, a, A.s_item ? A.s_item[a] : A.s, nend, t, A.full ? 0 : a + 1, nend, want,
+            A, S, a, A.s_item ? A.s_item[a] : A.s, nend, t, first, nend, want,
             count_bits(k1 - k0), k0, k1, cur, end, lookm, passes);
         if (A.mode != kModeFill && threadIdx.x == 0) A.task_cnt[t] = (int32_t)produced;
         __syncthreads();
@@ -1066,6 +968,7 @@ __global__ __launch_bounds__(kTinyThreads) void k_count_tiny(CountArgs A) {
     __shared__ int32_t log_cur[2];
     __shared__ int32_t res[4];  // ok, offset low, offset high, first record
     if (count_idle(A)) return;
+    use_ranks(A);
     if (threadIdx.x == 0) {
         pool_cur[0] = pool_cur[1] = 0;
         log_cur[0] = log_cur[1] = 0;
@@ -1186,7 +1089,7 @@ __global__ __launch_bounds__(kTinyThreads) void k_count_tiny(CountArgs A) {
                 while (j < nc && col[j * NT] == b) ++j;
                 if (j - i >= sa) {
                     if (dst_a) dst_a[at + q] = a - shift;
-                    dst_b[at + q] = b - shift;
+                    dst_b[at + q] = dst_a ? item_of(A.orig, b) - shift : b;
                     if (dst_w) dst_w[at + q] = j - i;
                     ++q;
                 }
@@ -1214,6 +1117,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_tasks(CountArgs A) {
     __shared__ int32_t log_cur[2];
     const Smem S{tab, runs, taken, misc, stack, tab + LIM, pool_cur, log_cur};
     if (count_idle(A)) return;  // uniform: every thread reads the same words
+    use_ranks(A);
     if (threadIdx.x == 0) {
         pool_cur[0] = pool_cur[1] = 0;
         log_cur[0] = log_cur[1] = 0;
@@ -1233,27 +1137,28 @@ __global__ __launch_bounds__(NT, MINB) void k_count_tasks(CountArgs A) {
         const int32_t a = A.task_item[t0];
         const int32_t p0 = A.task_part[t0];
         const int32_t P = task_parts(A.cost[a], A.tune.small_max_wedges, A.tune.task_wedges,
-                                     item_span(A.item_end, A.N, A.full, a),
+                                     item_span(A.crank, A.item_end, A.N, A.full, a),
                                      A.ptrI[a + 1] - A.ptrI[a], A.tune.dense_min_wedges,
                                      SLOTS);
         const int32_t p1 = min(P, p0 + A.tune.group_parts);
         const int32_t k0 = A.ptrI[a], k1 = A.ptrI[a + 1];
         const int32_t cb = count_bits(k1 - k0);
         const int32_t sa = A.s_item ? A.s_item[a] : A.s;
-        const int32_t nend = A.item_end ? A.item_end[a] : A.N;
+        const int32_t first = cand_first(A.crank, A.full, a);
+        const int32_t nend = cand_end(A.crank, A.item_end, A.N, a);
         int32_t cur[kR], end[kR];
         uint32_t lookm = 0;
         bool fresh = true;  // cursors must be placed at the range start
         for (int32_t q = p0; q < p1; ++q) {
             int32_t lo, hi;
-            task_range(A.full ? 0 : a + 1, nend, q, P, lo, hi);
+            task_range(first, nend, q, P, lo, hi);
             const int32_t t = t0 + (q - p0);
             if (A.mode == kModeFill && A.need && !A.need[t]) {
                 fresh = true;
                 continue;
             }
             if (fresh) {
-                init_cursors<NT>(A, a, lo, k0, k1, cur, end, lookm);
+                init_cursors<NT>(A, first, lo, k0, k1, cur, end, lookm);
                 if (q == 0 && A.mode != kModeFill) {
                     // work figures of this kernel: the item's incidences and wedges
 #pragma unroll
@@ -1299,6 +1204,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_tasks(CountArgs A) {
 // What task_parts needs to know about the items besides their cost.
 struct PlanItems {
     const int32_t *ptrI;      // item lists (sizes)
+    const int32_t *crank;     // candidate numbers of the items, or null: their ids
     const int32_t *item_end;  // per item: end of its graph's items (batches), or null
     int32_t full;             // product mode
     int32_t dense_min;        // Tuning::dense_min_wedges
@@ -1307,12 +1213,13 @@ struct PlanItems {
 
 __device__ __forceinline__ int32_t plan_parts(const PlanItems &I, const int64_t *cost, int32_t N,
                                               int32_t small_max, int32_t target, int32_t a) {
-    return task_parts(cost[a], small_max, target, item_span(I.item_end, N, I.full, a),
+    return task_parts(cost[a], small_max, target, item_span(I.crank, I.item_end, N, I.full, a),
                       I.ptrI[a + 1] - I.ptrI[a], I.dense_min, I.slots);
 }
 
 __global__ void k_task_count(const int64_t *cost, int32_t N, int32_t small_max, int32_t target,
                              PlanItems I, int32_t *ntask) {
+    I.crank = ranks_or_null(I.crank, N);
     for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < N;
          a += (int64_t)gridDim.x * blockDim.x)
         ntask[a] = plan_parts(I, cost, N, small_max, target, (int32_t)a);
@@ -1333,6 +1240,7 @@ __global__ __launch_bounds__(256) void k_task_fill(const int64_t *cost, int32_t 
                                                    int32_t *groups, int32_t *counts,
                                                    int32_t chunk, const int32_t *abort) {
     if (abort && *abort != 0) return;
+    I.crank = ranks_or_null(I.crank, N);
     __shared__ int32_t sh[3];
     const int lane = lane_id();
     const int64_t lo = (int64_t)blockIdx.x * chunk;
@@ -1438,6 +1346,7 @@ constexpr int32_t kLaneRec = 32;
 
 __global__ __launch_bounds__(256) void k_stage_copy(CountArgs A, int32_t n_rec) {
     if (A.abort && *A.abort != 0) return;
+    use_ranks(A);
     if (n_rec < 0) n_rec = min(*A.log_head, A.log_cap);
     const int lane = lane_id();
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
@@ -1461,7 +1370,7 @@ __global__ __launch_bounds__(256) void k_stage_copy(CountArgs A, int32_t n_rec) 
         const OutDst od = out_dst(A, a, dst);
         for (int32_t i = 0; i < rec.n; ++i) {
             od.a[od.base + i] = a - od.shift;
-            od.b[od.base + i] = A.pool_b[rec.off + i] - od.shift;
+            od.b[od.base + i] = item_of(A.orig, A.pool_b[rec.off + i]) - od.shift;
             if (od.w) od.w[od.base + i] = A.pool_w[rec.off + i];
         }
     }
@@ -1490,7 +1399,7 @@ __global__ __launch_bounds__(256) void k_stage_copy(CountArgs A, int32_t n_rec) 
                 bv[u] = 0;
                 wv[u] = 0;
                 if (i < rec.n) {
-                    bv[u] = A.pool_b[rec.off + i];
+                    bv[u] = item_of(A.orig, A.pool_b[rec.off + i]);
                     if (od.w) wv[u] = A.pool_w[rec.off + i];
                 }
             }
@@ -1515,18 +1424,18 @@ inline int grid_for(int64_t work, int per_block, int cap) {
 }  // namespace
 
 hipError_t launch_task_count(hipStream_t st, const int64_t *cost, int32_t N, const Tuning &tu,
-                             const int32_t *ptrI, const int32_t *item_end, int32_t full,
-                             int32_t *ntask) {
+                             const int32_t *ptrI, const int32_t *crank, const int32_t *item_end,
+                             int32_t full, int32_t *ntask) {
     if (N <= 0) return hipSuccess;
-    const PlanItems I{ptrI, item_end, full, tu.dense_min_wedges, tu.task_slots};
+    const PlanItems I{ptrI, crank, item_end, full, tu.dense_min_wedges, tu.task_slots};
     k_task_count<<<grid_for(N, 256, 65536), 256, 0, st>>>(cost, N, tu.small_max_wedges,
                                                          tu.task_wedges, I, ntask);
     return hipGetLastError();
 }
 
 hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, int32_t N, const Tuning &tu,
-                            const int32_t *ptrI, const int32_t *item_end, int32_t full,
-                            const int64_t *tbase, int32_t *task_item, int32_t *task_part,
+                            const int32_t *ptrI, const int32_t *crank, const int32_t *item_end,
+                            int32_t full, const int64_t *tbase, int32_t *task_item, int32_t *task_part,
                             int32_t *small_tasks, int32_t *small_items, int32_t *tiny_tasks,
                             int32_t *tiny_items, int32_t *big_tasks, int32_t *counts,
                             const int32_t *abort) {
@@ -1534,7 +1443,7 @@ hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, int32_t N, cons
     const int64_t blocks = std::min<int64_t>(1024, ((int64_t)N + 255) / 256);
     const int32_t chunk = (int32_t)((((int64_t)N + blocks - 1) / blocks + 255) / 256 * 256);
     const int64_t grid = ((int64_t)N + chunk - 1) / chunk;
-    const PlanItems I{ptrI, item_end, full, tu.dense_min_wedges, tu.task_slots};
+    const PlanItems I{ptrI, crank, item_end, full, tu.dense_min_wedges, tu.task_slots};
     k_task_fill<<<(unsigned)grid, 256, 0, st>>>(cost, N, tu.small_max_wedges, tu.task_wedges,
                                                 tu.tiny_max_wedges, I,
                                                 std::max(1, tu.group_parts), tbase, task_item,

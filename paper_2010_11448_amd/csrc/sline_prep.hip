@@ -409,20 +409,30 @@ __global__ void k_filter_flags(const int32_t *itmM, int64_t nnz, const int32_t *
 // After the exclusive scan of the flags (pos[p], pos[nnz] = kept total): kept
 // entry p goes to itmS[pos[p]], and the item's own entry sets its
 // back-pointer start[inv[p]] to the position after it; ptrS[v] = pos[ptrM[v]].
+// Where ranks pay, itmS receives the items' ranks among the kept ones, and orig
+// the item of every rank.
 __global__ void k_filter_scatter(const int32_t *itmM, int64_t nnz, const int32_t *pos,
                                  const int32_t *ptrM, int32_t M, int32_t *ptrS, int32_t *itmS,
-                                 const int32_t *inv, int32_t *start) {
-    const int64_t n = nnz > (int64_t)M + 1 ? nnz : (int64_t)M + 1;
+                                 const int32_t *inv, int32_t *start, int32_t N,
+                                 const int32_t *crank, int32_t *orig) {
+    int64_t n = nnz > (int64_t)M + 1 ? nnz : (int64_t)M + 1;
+    if (crank && !ranks_pay(crank[N], N)) crank = nullptr;
+    if (crank && N > n) n = N;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
          p += (int64_t)gridDim.x * blockDim.x) {
         if (p < nnz) {
             const int32_t q = pos[p];
             if (pos[p + 1] != q) {
-                itmS[q] = itmM[p];
+                const int32_t it = itmM[p];
+                itmS[q] = crank ? crank[it] : it;
                 if (start) start[inv[p]] = q + 1;
             }
         }
         if (p <= M) ptrS[p] = pos[ptrM[p]];
+        if (crank && p < N) {
+            const int32_t r = crank[p];
+            if (crank[p + 1] != r) orig[r] = (int32_t)p;
+        }
     }
 }
 
@@ -727,19 +737,24 @@ hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int
 hipError_t launch_filter(hipStream_t st, const int32_t *ptrM, const int32_t *itmM, int32_t M,
                          int64_t nnz, const int32_t *ptrI, int32_t N, int32_t s,
                          const int32_t *s_item, int32_t *kept, int32_t *pos, int32_t *part32,
-                         int32_t *ptrS, int32_t *itmS, const int32_t *inv, int32_t *start) {
+                         int32_t *ptrS, int32_t *itmS, const int32_t *inv, int32_t *start,
+                         int32_t *crank, int32_t *orig) {
     if (M <= 0) return hipSuccess;
     if (nnz > 0) {
         k_item_kept<<<grid_for(N, 256, 65536), 256, 0, st>>>(ptrI, N, s, s_item, kept);
         k_filter_flags<<<grid_for(nnz, 256, 65536), 256, 0, st>>>(itmM, nnz, kept, pos);
         hipError_t e = hipGetLastError();
+        if (e == hipSuccess && crank) e = launch_scan_i32(st, kept, N, crank, part32);
         if (e != hipSuccess) return e;
+    } else {
+        crank = nullptr;  // no member lists to number
     }
     // in place: every scan thread reads its inputs before writing them
     hipError_t e = launch_scan_i32(st, pos, nnz, pos, part32);
     if (e != hipSuccess) return e;
-    k_filter_scatter<<<grid_for(std::max<int64_t>(nnz, (int64_t)M + 1), 256, 65536), 256, 0, st>>>(
-        itmM, nnz, pos, ptrM, M, ptrS, itmS, inv, start);
+    const int64_t most = std::max<int64_t>({nnz, (int64_t)M + 1, crank ? (int64_t)N : 0});
+    k_filter_scatter<<<grid_for(most, 256, 65536), 256, 0, st>>>(
+        itmM, nnz, pos, ptrM, M, ptrS, itmS, inv, start, N, crank, orig);
     return hipGetLastError();
 }
 
