@@ -208,10 +208,16 @@ __global__ void k_cc_hook(const int32_t *a, const int32_t *b, int64_t n, int32_t
     }
 }
 
+// Every node at its root.  The walk writes nothing on its way: a halving step
+// here could put back a grandparent read before the node's own thread had
+// stored the root.
 __global__ void k_cc_flatten(int32_t *p, int32_t N) {
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < N;
-         x += (int64_t)gridDim.x * blockDim.x)
-        st_rel(p + x, uf_root(p, (int32_t)x));
+         x += (int64_t)gridDim.x * blockDim.x) {
+        int32_t r = (int32_t)x;
+        for (int32_t up = ld_rel(p + r); up != r; up = ld_rel(p + r)) r = up;
+        st_rel(p + x, r);
+    }
 }
 
 // Roots that occur in a pair: one per component of the squeezed graph.
