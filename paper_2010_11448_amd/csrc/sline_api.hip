@@ -315,6 +315,7 @@ struct Layout {
     // s filter: the kept items' candidate numbers (N + 1) and their items (N);
     // null when not used
     int32_t *crank = nullptr, *orig = nullptr;
+    int32_t *bnd;   // bounds table of the direct counting path (nnz)
     int32_t *xcol;  // batches: columns of the dual graphs' rows (XD)
     int64_t *cost, *tbase, *part64;
     int32_t *part32, *ntask, *start;
@@ -337,8 +338,8 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
     Layout L{};
     L.err = A.take<int32_t>(4);
     L.queue = A.take<int32_t>(4);
-    L.tcounts = A.take<int32_t>(4);
-    L.totals = A.take<int64_t>(4);
+    L.tcounts = A.take<int32_t>(kKinds);
+    L.totals = A.take<int64_t>(3 + 1 + kKinds);  // cost totals, then the planner's sums
     L.passes = A.take<int64_t>(4);
     L.rowid = A.take<int32_t>(nnz);
     L.ptrT = A.take<int32_t>(n + 1);
@@ -357,8 +358,8 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
         L.ptrS = A.take<int32_t>(M + 1);
         L.pos = A.take<int32_t>(nnz + 1);
         L.itmS = A.take<int32_t>(nnz);
+        // the sort's buffers are idle once the lists are transposed
         if (ranks && N + 1 <= nnz) {
-            // the sort's value buffers are idle once the lists are transposed
             L.crank = L.rsV0;
             L.orig = L.rsV1;
         } else if (ranks && !fixed) {
@@ -366,6 +367,7 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
             L.orig = A.take<int32_t>(N);
         }
     }
+    L.bnd = L.rsK0;
     L.cost = A.take<int64_t>(N);
     L.ntask = A.take<int32_t>(N);
     L.tbase = A.take<int64_t>(N + 1);
@@ -382,9 +384,28 @@ struct TaskLayout {
     int32_t log_cap;
 };
 
-TaskLayout plan_tasks(Arena &A, int64_t T) {
+PlanItems plan_items(const Tuning &tu, const int32_t *ptrI, const int32_t *crank,
+                     const int32_t *item_end, int64_t N, int32_t s, const int32_t *s_item,
+                     bool full) {
+    PlanItems I{};
+    I.ptrI = ptrI;
+    I.crank = crank;
+    I.item_end = item_end;
+    I.s_item = s_item;
+    I.N = (int32_t)N;
+    I.s = s;
+    I.full = full ? 1 : 0;
+    I.small_max = tu.small_max_wedges;
+    I.target = tu.task_wedges;
+    I.dense_min = tu.dense_min_wedges;
+    I.slots = tu.task_slots;
+    return I;
+}
+
+// `more`: log records beyond two per task.
+TaskLayout plan_tasks(Arena &A, int64_t T, int64_t more) {
     TaskLayout L{};
-    L.log_cap = (int32_t)std::min<int64_t>(INT32_MAX - 1, 2 * T + 65536);
+    L.log_cap = (int32_t)std::min<int64_t>(INT32_MAX - 1, 2 * T + 65536 + more);
     L.pool_head = A.take<unsigned long long>(1);
     L.ctrs = A.take<int32_t>(4);  // [0] log head, [1] tasks flagged
     L.log = A.take<StageRec>(L.log_cap);
@@ -786,8 +807,8 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     const Layout L = plan_layout(A, m, n, nnz, N, M, filt, ranks, fixed);
 
     hip_check(c, launch_fill_i32(st, L.err, 4, 0), "zero flags");
-    hip_check(c, launch_fill_i32(st, L.tcounts, 4, 0), "zero task counts");
-    hip_check(c, launch_fill_i64(st, L.totals, 4, 0), "zero totals");
+    hip_check(c, launch_fill_i32(st, L.tcounts, kKinds, 0), "zero task counts");
+    hip_check(c, launch_fill_i64(st, L.totals, 3 + 1 + kKinds, 0), "zero totals");
     hip_check(c, launch_fill_i64(st, L.passes, 4, 0), "zero passes");
 
     mark(c, 0);
@@ -849,17 +870,18 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
                                L.tbase, L.part64, reinterpret_cast<unsigned long long *>(L.passes),
                                out, S);
     }
+    const PlanItems PI = plan_items(tu, ptrI, L.crank, IS.item_end, N, s, IS.s_item, IS.full);
     if (!(flags & SLINE_NO_SHORTCUT))
-        hip_check(c, launch_mark_lookup(st, ptrI, memI, (int32_t)N, s, IS.s_item, IS.s_max, ptrS,
-                                        L.start, L.cost, IS.full ? 0 : tu.tiny_max_wedges),
+        hip_check(c, launch_mark_lookup(st, PI, memI, IS.s_max, ptrS, L.start, L.cost,
+                                        IS.full ? 0 : tu.tiny_max_wedges),
                   "lookup members");
-    hip_check(c, launch_task_count(st, L.cost, (int32_t)N, tu, ptrI, L.crank, IS.item_end,
-                                   IS.full ? 1 : 0, L.ntask),
-              "task count");
+    hip_check(c, launch_task_count(st, L.cost, PI, tu.tiny_max_wedges, L.ntask, L.totals + 3), "task count");
     hip_check(c, launch_scan_i32_to_i64(st, L.ntask, N, L.tbase, L.part64), "task scan");
     int64_t *h = c->host;
     hip_check(c, hipMemcpyAsync(h + 0, L.tbase + N, sizeof(int64_t), hipMemcpyDeviceToHost, st), "read tasks");
-    hip_check(c, hipMemcpyAsync(h + 1, L.totals, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, st), "read totals");
+    hip_check(c, hipMemcpyAsync(h + 1, L.totals, (3 + 1 + kKinds) * sizeof(int64_t),
+                                hipMemcpyDeviceToHost, st),
+              "read totals");
     sync(c, "task plan");
     const int64_t T = h[0];
     S.n_kept = h[1];
@@ -869,16 +891,30 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
         set_err(c, "too many counting tasks (%s)", std::to_string(T).c_str());
         throw Fail{SLINE_ENOMEM};
     }
+    // every range of an item counted directly logs its pairs; in a fixed region
+    // as many of those records as leave most of the room to the staging pool
+    int64_t more = h[4];
+    uint32_t kinds = 0;
+    for (int k = 0; k < kKinds; ++k) kinds |= h[5 + k] > 0 ? 1u << k : 0u;
     Arena tsz;
-    plan_tasks(tsz, T);
+    if (c->fixed.base) {
+        Arena least;
+        plan_tasks(least, T, 0);
+        const int64_t room = (int64_t)c->fixed.size - (int64_t)(c->ws_bytes + least.off + 8192);
+        more = std::max<int64_t>(0, std::min<int64_t>(more, room / 4 / (int64_t)sizeof(StageRec)));
+    }
+    plan_tasks(tsz, T, more);
     ensure_ws2(c, tsz.off + 4096);
     Arena TA;
     TA.base = reinterpret_cast<char *>(c->ws2);
-    const TaskLayout TL = plan_tasks(TA, T);
-    hip_check(c, launch_task_fill(st, L.cost, (int32_t)N, tu, ptrI, L.crank, IS.item_end,
-                                  IS.full ? 1 : 0, L.tbase, TL.item, TL.part, TL.small,
-                                  TL.small_item, TL.tiny, TL.tiny_item, TL.big, L.tcounts),
+    const TaskLayout TL = plan_tasks(TA, T, more);
+    hip_check(c, launch_task_fill(st, L.cost, PI, tu.tiny_max_wedges, tu.group_parts, L.tbase,
+                                  TL.item, TL.part, TL.small, TL.small_item, TL.tiny, TL.tiny_item,
+                                  TL.big, (int32_t)T, L.tcounts),
               "task fill");
+    if ((kinds >> kKindFlat) & 1u)
+        hip_check(c, launch_flat_bounds(st, ptrS, itmS, (int32_t)M, L.crank, (int32_t)N, L.bnd),
+                  "list bounds");
     mark(c, 2);
     // 7. one counting pass: pairs per task, each range's pairs staged in a pool
     const int64_t want_pool = S.wedges / IS.s_min;  // every pair of L_s accounts for >= s wedges
@@ -918,6 +954,8 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     C.tiny_items = TL.tiny_item;
     C.big_tasks = TL.big;
     C.task_counts = L.tcounts;
+    C.kinds = kinds;
+    C.bnd = L.bnd;
     C.queue = L.queue;
     C.task_cnt = TL.cnt;
     C.task_off = nullptr;
@@ -949,7 +987,7 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     hip_check(c, hipMemcpyAsync(h + 4, L.passes, sizeof(int64_t), hipMemcpyDeviceToHost, st), "read passes");
     hip_check(c, hipMemcpyAsync(h + 9, L.passes + 1, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, st),
               "read task kernel work");
-    hip_check(c, hipMemcpyAsync(h + 12, L.tcounts, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, st),
+    hip_check(c, hipMemcpyAsync(h + 12, L.tcounts, kKinds * sizeof(int32_t), hipMemcpyDeviceToHost, st),
               "read task counts");
     hip_check(c, hipMemcpyAsync(h + 6, L.err, sizeof(int32_t), hipMemcpyDeviceToHost, st), "read flags");
     hip_check(c, hipMemcpyAsync(h + 7, TL.ctrs, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st), "read stage counters");
@@ -961,8 +999,8 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     S.heavy_nnz = h[9];
     S.heavy_wedges = h[10];
     S.heavy_pairs = h[11];
-    S.n_small = hb[0] + hb[2];  // one-wave and one-lane items
-    S.n_heavy = hb[1];
+    S.n_small = hb[kKindSmall] + hb[kKindTiny];  // one-wave and one-lane items
+    S.n_heavy = hb[kKindGroups] + hb[kKindFlat] + hb[kKindSieve1] + hb[kKindSieve4];
     S.n_pairs = total;
     if (c->profile) {
         S.ms_transpose = span_ms(c, 0, 1);
@@ -1494,6 +1532,17 @@ BatchDev plan_dev(sline_batch_plan *p) {
     return BatchDev{p->d_gr, p->ibase, p->dbase, p->dual_ids, p->zb, p->d_err};
 }
 
+// Tasks per item and their scan; bound: as many as a run at any larger s needs.
+void plan_enqueue_tasks(sline_batch_plan *p, hipStream_t st, bool bound) {
+    sline_ctx *c = p->c;
+    const Layout &L = p->L;
+    const PlanItems PI = plan_items(p->C.tune, p->K.ptrC, nullptr, p->K.iend, p->B.NI, p->s_min,
+                                    p->K.s_item, false);
+    hip_check(c, launch_task_count(st, L.cost, PI, p->C.tune.tiny_max_wedges, L.ntask, L.totals + 3,
+                                   bound ? 1 : 0), "task count");
+    hip_check(c, launch_scan_i32_to_i64(st, L.ntask, p->B.NI, L.tbase, L.part64), "task scan");
+}
+
 // Shape checks, combine stage, transposes, filter, costs, lookup-only members
 // and the task scan; with t_cap >= 0, the guard of the task count.
 void plan_enqueue_prep(sline_batch_plan *p, hipStream_t st, int64_t t_cap) {
@@ -1510,8 +1559,8 @@ void plan_enqueue_prep(sline_batch_plan *p, hipStream_t st, int64_t t_cap) {
     const int32_t NI = (int32_t)B.NI, MT = (int32_t)B.MT;
     const int32_t *ptrI = p->K.ptrC, *memI = p->K.memC;
     hip_check(c, launch_fill_i32(st, L.err, 4, 0), "zero flags");
-    hip_check(c, launch_fill_i32(st, L.tcounts, 4, 0), "zero task counts");
-    hip_check(c, launch_fill_i64(st, L.totals, 4, 0), "zero totals");
+    hip_check(c, launch_fill_i32(st, L.tcounts, kKinds, 0), "zero task counts");
+    hip_check(c, launch_fill_i64(st, L.totals, 3 + 1 + kKinds, 0), "zero totals");
     hip_check(c, launch_fill_i64(st, L.passes, 4, 0), "zero passes");
     // row ids, and the member order of every row (a primal graph's combined
     // ids keep its members' order); a violation stops the run's counting
@@ -1531,11 +1580,11 @@ void plan_enqueue_prep(sline_batch_plan *p, hipStream_t st, int64_t t_cap) {
                              L.start, L.totals, 0, 1),
               "cost");
     const Tuning &tu = p->C.tune;
-    hip_check(c, launch_mark_lookup(st, ptrI, memI, NI, p->s_min, p->K.s_item, INT32_MAX, L.ptrS,
-                                    L.start, L.cost, tu.tiny_max_wedges),
+    const PlanItems PI = plan_items(tu, ptrI, nullptr, p->K.iend, NI, p->s_min, p->K.s_item, false);
+    hip_check(c, launch_mark_lookup(st, PI, memI, INT32_MAX, L.ptrS, L.start, L.cost,
+                                    tu.tiny_max_wedges),
               "lookup members");
-    hip_check(c, launch_task_count(st, L.cost, NI, tu, ptrI, nullptr, p->K.iend, 0, L.ntask), "task count");
-    hip_check(c, launch_scan_i32_to_i64(st, L.ntask, NI, L.tbase, L.part64), "task scan");
+    plan_enqueue_tasks(p, st, t_cap < 0);
     if (t_cap >= 0)
         hip_check(c, launch_plan_guard(st, L.tbase + NI, t_cap, kErrPlanTasks, p->d_err), "task guard");
 }
@@ -1548,11 +1597,15 @@ void plan_enqueue_count(sline_batch_plan *p, hipStream_t st, int64_t pair_cap) {
     const Layout &L = p->L;
     const TaskLayout &TL = p->TL;
     const CountArgs &C = p->C;
-    const int32_t NI = (int32_t)p->B.NI;
-    hip_check(c, launch_task_fill(st, L.cost, NI, C.tune, C.ptrI, nullptr, p->K.iend, 0, L.tbase,
-                                  TL.item, TL.part, TL.small, TL.small_item, TL.tiny, TL.tiny_item, TL.big,
-                                  L.tcounts, p->d_err),
+    const PlanItems PI = plan_items(C.tune, C.ptrI, nullptr, p->K.iend, p->B.NI, p->s_min,
+                                    p->K.s_item, false);
+    hip_check(c, launch_task_fill(st, L.cost, PI, C.tune.tiny_max_wedges, C.tune.group_parts,
+                                  L.tbase, TL.item, TL.part, TL.small, TL.small_item, TL.tiny,
+                                  TL.tiny_item, TL.big, (int32_t)p->t_cap, L.tcounts, p->d_err),
               "task fill");
+    hip_check(c, launch_flat_bounds(st, L.ptrS, L.itmS, (int32_t)p->B.MT, nullptr,
+                                    (int32_t)p->B.NI, L.bnd),
+              "list bounds");
     hip_check(c, launch_fill_i32(st, TL.need, p->t_cap, 0), "zero need flags");
     hip_check(c, launch_fill_i32(st, reinterpret_cast<int32_t *>(TL.log),
                                  (int64_t)TL.log_cap * (int64_t)(sizeof(StageRec) / 4), 0),
@@ -1622,6 +1675,8 @@ CountArgs plan_count_args(sline_batch_plan *p) {
     C.tiny_items = TL.tiny_item;
     C.big_tasks = TL.big;
     C.task_counts = L.tcounts;
+    C.kinds = ~0u;
+    C.bnd = L.bnd;
     C.queue = L.queue;
     C.task_cnt = TL.cnt;
     C.task_off = nullptr;
@@ -1801,7 +1856,8 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
         p->L = plan_layout(A, B.NI, B.MT, B.ZT, B.NI, B.MT, true);
         p->C.ptrI = p->K.ptrC;
     }
-    // 3. one run of the preparation, without guards: the task count
+    // 3. one run of the preparation, without guards: the tasks that this run
+    // or one at a larger s can need
     if (G > 0) {
         plan_enqueue_prep(p, st, -1);
         int64_t *h = p->host;
@@ -1809,18 +1865,18 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
             hip_check(c, hipMemcpyAsync(h + 0, p->L.tbase + B.NI, sizeof(int64_t),
                                         hipMemcpyDeviceToHost, st),
                       "read tasks");
-            hip_check(c, hipMemcpyAsync(h + 1, p->L.totals, 3 * sizeof(int64_t),
+            hip_check(c, hipMemcpyAsync(h + 1, p->L.totals, 4 * sizeof(int64_t),
                                         hipMemcpyDeviceToHost, st),
                       "read totals");
         }
-        hip_check(c, hipMemcpyAsync(h + 4, p->d_err, sizeof(int32_t), hipMemcpyDeviceToHost, st),
+        hip_check(c, hipMemcpyAsync(h + 5, p->d_err, sizeof(int32_t), hipMemcpyDeviceToHost, st),
                   "read flags");
         sync(c, "batch plan tasks");
-        const int32_t e = reinterpret_cast<const int32_t *>(h + 4)[0];
+        const int32_t e = reinterpret_cast<const int32_t *>(h + 5)[0];
         if (e) return plan_csr_error(c, e);
     }
     if (B.ZT > 0) {
-        const int64_t T = p->host[0], wedges = p->host[3];
+        const int64_t T = p->host[0], wedges = p->host[3], ranges = p->host[4];
         if (T >= INT32_MAX) {
             set_err(c, "too many counting tasks (%s)", std::to_string(T).c_str());
             return SLINE_ENOMEM;
@@ -1828,16 +1884,17 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
         p->t_cap = std::max<int64_t>(T, 1);
         {
             Arena sz;
-            (void)plan_tasks(sz, p->t_cap);
+            (void)plan_tasks(sz, p->t_cap, ranges);
             Arena A;
             A.base = reinterpret_cast<char *>(plan_alloc(p, sz.off + 4096, "the task arrays"));
-            p->TL = plan_tasks(A, p->t_cap);
+            p->TL = plan_tasks(A, p->t_cap, ranges);
         }
         // 4. one counting pass with a pool of W_s / s_min pairs (every pair
         // of L_s takes at least s wedges): the pair count
         plan_pool(p, wedges / p->s_min);
         void *first_pool = p->pool;
         p->C = plan_count_args(p);
+        plan_enqueue_tasks(p, st, false);
         plan_enqueue_count(p, st, -1);
         int64_t *h = p->host;
         hip_check(c, hipMemcpyAsync(h + 0, p->TL.off + p->t_cap, sizeof(int64_t),

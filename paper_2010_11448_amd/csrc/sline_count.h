@@ -25,36 +25,9 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Candidate numbers (see ranks_pay): a kernel drops crank and orig at its start
-// when the build does not use ranks; a candidate's number is then its item's id.
-__device__ __forceinline__ const int32_t *ranks_or_null(const int32_t *crank, int32_t N) {
-    return crank && ranks_pay(crank[N], N) ? crank : nullptr;
-}
-
 __device__ __forceinline__ void use_ranks(CountArgs &A) {
     A.crank = ranks_or_null(A.crank, A.N);
     if (!A.crank) A.orig = nullptr;
-}
-
-__device__ __forceinline__ int32_t cand_of(const int32_t *crank, int32_t item) {
-    return crank ? crank[item] : item;
-}
-
-// First candidate of item a: the one after a (product mode: 0).
-__device__ __forceinline__ int32_t cand_first(const int32_t *crank, int32_t full, int32_t a) {
-    return full ? 0 : cand_of(crank, a) + 1;
-}
-
-// One past the last candidate of item a: the end of its graph (batches) or of
-// all items.
-__device__ __forceinline__ int32_t cand_end(const int32_t *crank, const int32_t *item_end,
-                                            int32_t N, int32_t a) {
-    return cand_of(crank, item_end ? item_end[a] : N);
-}
-
-// The item a candidate stands for.
-__device__ __forceinline__ int32_t item_of(const int32_t *orig, int32_t cand) {
-    return orig ? orig[cand] : cand;
 }
 
 // Where the pairs of item `item` at combined output position `pos` go: the
@@ -140,6 +113,95 @@ __device__ __forceinline__ bool count_idle(const CountArgs &A) {
     if (A.abort && *A.abort != 0) return true;
     return A.mode == kModeFill && A.need && A.need_count && *A.need_count == 0;
 }
+
+// Inclusive sum over the lanes up to this one.
+__device__ __forceinline__ int32_t wave_incl(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+
+__device__ __forceinline__ int32_t lane63(int32_t v) { return __builtin_amdgcn_readlane(v, 63); }
+
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// The wedges of an item (or of one range of it), numbered 0, 1, ... over its
+// members' list parts one after the other, one part per thread at most.  A bit
+// per wedge marks where a part begins: a wave reads the bits of 64 wedges, and
+// the count of the bits up to a lane's own is that lane's part.  Every lane of
+// every load then has a wedge, whatever the parts' lengths are.
+template <int NT, int CHUNKS>
+struct WedgeMap {
+    static constexpr int NW = NT / kWave;
+    int32_t *adj;     // NT: list position less wedge number, per part that has wedges
+    uint64_t *marks;  // CHUNKS, all zero when a window is marked
+    int32_t *wlen, *wpart;  // NW each
+    int32_t *before0;
+
+    // Number the parts: this thread's is [b, b + len).  One barrier inside.
+    __device__ __forceinline__ void number(int32_t b, int32_t len, int32_t &off, int32_t &rank,
+                                           int32_t &total) const {
+        const int32_t incl = wave_incl(len);
+        const uint64_t has = __ballot(len > 0);
+        off = incl - len;
+        rank = (int32_t)lanes_below(has);
+        total = lane63(incl);
+        if (NW > 1) {
+            const int wid = wave_id();
+            if (lane_id() == 0) {
+                wlen[wid] = total;
+                wpart[wid] = __popcll(has);
+            }
+            __syncthreads();
+            total = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                if (w < wid) {
+                    off += wlen[w];
+                    rank += wpart[w];
+                }
+                total += wlen[w];
+            }
+        }
+        if (len > 0) adj[rank] = b - off;
+    }
+    // Mark the parts of the window that starts at wedge w0.
+    __device__ __forceinline__ void mark(int32_t w0, int32_t off, int32_t len, int32_t rank) const {
+        const int32_t in = off - w0;
+        if (len > 0 && in >= 0 && in < CHUNKS * kWave)
+            atomicOr(reinterpret_cast<uint32_t *>(marks) + (in >> 5), 1u << (in & 31));
+        // parts that begin before the window
+        if (len > 0 && in <= 0 && in + len > 0) *before0 = in < 0 ? rank : rank - 1;
+    }
+    // Parts that begin before chunk c0 of the window.
+    __device__ __forceinline__ int32_t parts_before(int32_t c0) const {
+        int32_t n = 0;
+        if (c0 > 0) {
+#pragma unroll
+            for (int i = 0; i < (CHUNKS + kWave - 1) / kWave; ++i) {
+                const int c = i * kWave + lane_id();
+                if (c < c0) n += __popcll(marks[c]);
+            }
+            n = lane63(wave_incl(n));
+        }
+        return uniform(*before0) + n;
+    }
+    // The candidate of this lane's wedge of chunk c (ok: it has one), and the
+    // parts so far.
+    __device__ __forceinline__ int32_t wedge(const int32_t *itmS, int32_t w0, int32_t c, bool ok,
+                                             int32_t &before) const {
+        const uint64_t raw = marks[c];
+        const uint64_t m = ((uint64_t)(uint32_t)uniform((int32_t)(raw >> 32)) << 32) |
+                           (uint32_t)uniform((int32_t)raw);
+        const int32_t q = before + (int32_t)(m & 1u) + (int32_t)lanes_below(m >> 1);
+        before += __popcll(m);
+        return ok ? itmS[adj[q] + w0 + c * kWave + lane_id()] : -1;
+    }
+};
 
 }  // namespace
 

@@ -42,8 +42,10 @@
 // behind a barrier, and only add to keys already in the table: a candidate
 // whose overlap reaches s lies in at least one list that inserts it.
 //
-// Two kernels: k_count_small (one wave per item with W_a <= small_max) and
-// k_count_tasks (one workgroup per task group).  Normally one counting pass
+// Kernels: k_count_small (one wave per item with W_a <= small_max), k_count_tasks
+// (one workgroup per task group), k_count_tiny (one lane per item), k_count_sieve
+// (s > 1, up to a few thousand wedges) and k_count_flat (sline_flat.hip: wedges
+// dense in their candidate range).  Normally one counting pass
 // stages every extracted range's (b, w) in a pool and logs where it goes;
 // after the exclusive scan of the pairs per task, k_stage_copy moves each
 // range to its task's offset, writing (a, b, w).  Tasks that found no room in
@@ -950,6 +952,199 @@ __global__ __launch_bounds__(kWave) void k_count_small(CountArgs A) {
         atomicAdd((unsigned long long *)A.passes, (unsigned long long)passes);
 }
 
+// --------------------------------------------------------------- sieve
+
+// s > 1, a few thousand wedges: most candidates are met once and are no pair.
+// A first walk sets, for every wedge, a bit chosen by the candidate (its low
+// bits) in `seen`, and where that was set already, in `twice`; a second walk
+// inserts only the wedges whose `twice` bit is set into the hash table, which
+// counts them exactly, every wedge of a pair among them.  (Two candidates that
+// share a bit only bring wedges that stay below s.)  The wedges let through
+// are collected first, so that a table step has a wedge in every lane.
+//
+// What bounds it: instructions, about 25 per 64 wedges and walk and 30 per 64
+// wedges let through, and below that the list reads' latency.  So a small item
+// gets a single wave, whose barriers cost nothing and whose per-item steps are
+// not repeated by other waves; its table, bits and lists take 10.7 KB of LDS, 15
+// waves per CU.  A larger one gets four.
+constexpr int kSieveList = 5 * kWave;  // wedges a wave collects
+
+template <int NT, int MINB>
+__global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
+    constexpr int NW = NT / kWave;
+    constexpr int LIM = NT * 16, SLOTS = LIM - kTaskPad;   // table words, home slots
+    constexpr int CHUNKS = NT * kSieveWedges / kWave;
+    constexpr uint32_t BITS = LIM * 32;
+    constexpr int RUNCAP = NT;  // extraction: one bucket entry per bucket of a wave's block
+    static_assert(NW * kSieveList * sizeof(int32_t) >= RUNCAP * sizeof(int2), "list area");
+    __shared__ __align__(16) uint32_t tab[LIM + kWave];  // first walk: `seen`; then the table
+    __shared__ __align__(16) uint32_t twice[LIM];
+    __shared__ __align__(16) int32_t list[NW * kSieveList];
+    __shared__ int32_t adj[NT];
+    __shared__ uint64_t marks[CHUNKS];
+    __shared__ int32_t wlen[NW], wpart[NW], before0;
+    __shared__ int2 stack[kStack];
+    __shared__ int32_t misc[kMiscWave + NW];
+    __shared__ uint64_t pool_cur[2];
+    __shared__ int32_t log_cur[2];
+    if (count_idle(A)) return;  // uniform: every thread reads the same words
+    const bool one = NT == kSieveSmall;
+    const int32_t n_tasks = A.task_counts[one ? kKindSieve1 : kKindSieve4];
+    if ((int32_t)blockIdx.x >= n_tasks) return;
+    use_ranks(A);
+    const int32_t *const tasks = (one ? A.small_tasks : A.tiny_tasks) + (A.n_tasks - 1);
+    const int tid = threadIdx.x, lane = lane_id(), wid = wave_id();
+    const Smem S{tab, reinterpret_cast<int2 *>(list), nullptr, misc, stack, tab + LIM, pool_cur,
+                 log_cur};
+    const WedgeMap<NT, CHUNKS> map{adj, marks, wlen, wpart, &before0};
+    if (tid == 0) {
+        pool_cur[0] = pool_cur[1] = 0;
+        log_cur[0] = log_cur[1] = 0;
+    }
+    tab_clear<NT>(tab, LIM);
+    tab_clear<NT>(twice, LIM);
+    for (int i = tid; i < CHUNKS; i += NT) marks[i] = 0;
+    int64_t my_wedges = 0, my_nnz = 0, my_pairs = 0, passes = 0;  // thread 0's are used
+    __syncthreads();
+    for (int32_t r = blockIdx.x; r < n_tasks; r += gridDim.x) {
+        const int32_t t = tasks[-r];
+        if (A.mode == kModeFill && A.need && !A.need[t]) continue;
+        const int32_t a = A.task_item[t];
+        const int32_t k0 = A.ptrI[a], size = A.ptrI[a + 1] - k0;
+        const int32_t first = cand_first(A.crank, 0, a);
+        const int32_t nend = cand_end(A.crank, A.item_end, A.N, a);
+        const int32_t s = A.s_item ? A.s_item[a] : A.s;
+        int32_t b = 0, len = 0;
+        if (tid < size) {
+            const int32_t v = A.memI[k0 + tid];
+            b = A.start[k0 + tid] & kStartMask;
+            len = max(A.ptrS[v + 1] - b, 0);
+        }
+        int32_t off, rank, total;
+        map.number(b, len, off, rank, total);
+        map.mark(0, off, len, rank);
+        __syncthreads();
+        const int32_t nch = (total + kWave - 1) / kWave, cpw = (nch + NW - 1) / NW;
+        const int32_t c0 = min(nch, wid * cpw), c1 = min(nch, c0 + cpw);
+        const int32_t parts0 = c0 < c1 ? map.parts_before(c0) : 0;
+        // call body(j) with four candidates per lane (-1: none), over the wave's chunks
+        auto walk = [&](auto body) {
+            int32_t before = parts0;
+            for (int32_t c = c0; c < c1; c += 4) {
+                int32_t j[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    j[u] = -1;
+                    if (c + u < c1)
+                        j[u] = map.wedge(A.itmS, 0, c + u, (c + u) * kWave + lane < total, before);
+                }
+                body(j);
+            }
+        };
+        // home slots: a pair takes two wedges at least
+        const int32_t want =
+            min(SLOTS, max(kWave, (total / 2 + kWave - 1) / kWave * kWave));
+        const int32_t cb = count_bits(size);
+        // a range that direct counters fit needs no sieve
+        const bool sieve = make_range(first, nend, want, kTaskPad, cb).mul != 0;
+        if (sieve) {
+            walk([&](const int32_t (&j)[4]) {
+                uint32_t old[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t h = (uint32_t)j[u] & (BITS - 1u);
+                    old[u] = atomicOr(j[u] >= 0 ? &tab[h >> 5] : S.spare + lane, 1u << (h & 31u));
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t h = (uint32_t)j[u] & (BITS - 1u), bit = 1u << (h & 31u);
+                    if (j[u] >= 0 && (old[u] & bit)) atomicOr(&twice[h >> 5], bit);
+                }
+            });
+            __syncthreads();
+            tab_clear<NT>(tab, LIM);
+        }
+        if (tid == 0) {
+            stack[0] = make_int2(first, nend);
+            misc[kMiscDepth] = 1;
+            misc[kMiscOverflow] = 0;
+        }
+        __syncthreads();
+        int32_t produced = 0;
+        for (;;) {
+            const int32_t depth = misc[kMiscDepth];
+            const int2 top = depth ? stack[depth - 1] : make_int2(0, 0);
+            if (depth == 0) break;
+            const Range R = make_range(top.x, top.y, want, kTaskPad, cb);
+            bool split = too_wide(R);
+            if (!split) {
+                ++passes;
+                int32_t *const mine = list + wid * kSieveList;
+                int32_t n = 0;  // wedges collected
+                bool ok = true;
+                walk([&](const int32_t (&j)[4]) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t h = (uint32_t)j[u] & (BITS - 1u);
+                        bool in = j[u] >= R.lo && j[u] < R.hi;
+                        if (sieve) in = in && ((twice[h >> 5] >> (h & 31u)) & 1u);
+                        const uint64_t m = __ballot(in);
+                        if (in) mine[n + (int32_t)lanes_below(m)] = j[u];
+                        n += __popcll(m);
+                        if (n >= 4 * kWave) {
+                            ok &= tab_add4(tab, S.spare, R, mine[lane], mine[kWave + lane],
+                                           mine[2 * kWave + lane], mine[3 * kWave + lane]);
+                            n -= 4 * kWave;
+                            if (lane < n) mine[lane] = mine[4 * kWave + lane];
+                        }
+                    }
+                });
+                if (n > 0) {
+                    int32_t j[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        j[u] = u * kWave + lane < n ? mine[u * kWave + lane] : INT32_MAX;
+                    ok &= tab_add4(tab, S.spare, R, j[0], j[1], j[2], j[3]);
+                }
+                if (!ok) misc[kMiscOverflow] = 1;
+                __syncthreads();
+                split = misc[kMiscOverflow] != 0;
+                if (!split) produced += tab_extract<NT, RUNCAP>(A, S, R, a, s, t, produced);
+                else tab_clear<NT>(tab, R.limit);
+            }
+            __syncthreads();
+            if (tid == 0) {
+                int32_t d = depth - 1;
+                if (split) {
+                    const int32_t mid = (int32_t)(((int64_t)top.x + top.y) / 2);
+                    stack[d] = make_int2(mid, top.y);
+                    stack[d + 1] = make_int2(top.x, mid);
+                    d += 2;
+                    misc[kMiscOverflow] = 0;
+                }
+                misc[kMiscDepth] = d;
+            }
+            __syncthreads();
+        }
+        if (sieve) tab_clear<NT>(twice, LIM);
+        for (int i = tid; i < CHUNKS; i += NT) marks[i] = 0;
+        if (A.mode != kModeFill) {
+            if (tid == 0) A.task_cnt[t] = produced;
+            my_wedges += total;
+            my_nnz += size;
+            my_pairs += produced;
+        }
+        __syncthreads();
+    }
+    if (tid == 0 && A.passes && A.mode != kModeFill) {
+        unsigned long long *wk = (unsigned long long *)A.passes;
+        if (passes) atomicAdd(&wk[0], (unsigned long long)passes);
+        if (my_nnz) atomicAdd(&wk[1], (unsigned long long)my_nnz);
+        if (my_wedges) atomicAdd(&wk[2], (unsigned long long)my_wedges);
+        if (my_pairs) atomicAdd(&wk[3], (unsigned long long)my_pairs);
+    }
+}
+
 // --------------------------------------------------------------- tiny
 
 // One lane per tiny item: a single-task item with a planning cost of at most
@@ -1201,136 +1396,158 @@ __global__ __launch_bounds__(NT, MINB) void k_count_tasks(CountArgs A) {
 
 // ----------------------------------------------------------- task lists
 
-// What task_parts needs to know about the items besides their cost.
-struct PlanItems {
-    const int32_t *ptrI;      // item lists (sizes)
-    const int32_t *crank;     // candidate numbers of the items, or null: their ids
-    const int32_t *item_end;  // per item: end of its graph's items (batches), or null
-    int32_t full;             // product mode
-    int32_t dense_min;        // Tuning::dense_min_wedges
-    int32_t slots;            // Tuning::task_slots
-};
-
-__device__ __forceinline__ int32_t plan_parts(const PlanItems &I, const int64_t *cost, int32_t N,
-                                              int32_t small_max, int32_t target, int32_t a) {
-    return task_parts(cost[a], small_max, target, item_span(I.crank, I.item_end, N, I.full, a),
-                      I.ptrI[a + 1] - I.ptrI[a], I.dense_min, I.slots);
+__device__ __forceinline__ int32_t plan_parts(const PlanItems &I, int64_t cost, int32_t a) {
+    return task_parts(cost, I.small_max, I.target,
+                      item_span(I.crank, I.item_end, I.N, I.full, a), I.ptrI[a + 1] - I.ptrI[a],
+                      I.dense_min, I.slots);
 }
 
-__global__ void k_task_count(const int64_t *cost, int32_t N, int32_t small_max, int32_t target,
-                             PlanItems I, int32_t *ntask) {
-    I.crank = ranks_or_null(I.crank, N);
-    for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < N;
-         a += (int64_t)gridDim.x * blockDim.x)
-        ntask[a] = plan_parts(I, cost, N, small_max, target, (int32_t)a);
+// A tiny item: one task, a planning cost of at most tiny_max and at most
+// kTinyCap members, outside product mode (see k_count_tiny).
+__device__ __forceinline__ bool is_tiny(const PlanItems &I, int32_t a, int64_t c,
+                                        int32_t tiny_max) {
+    return c <= tiny_max && !I.full && I.ptrI[a + 1] - I.ptrI[a] <= kTinyCap;
 }
 
-// counts[0] small tasks, counts[1] task groups
+// Tasks of item a and the kind of kernel that counts them.
+__device__ __forceinline__ int32_t item_tasks(const PlanItems &I, int32_t a, int64_t c,
+                                              int32_t tiny_max, int32_t &kind, int32_t &ranges) {
+    const int32_t direct = direct_tasks(I, a, c, kind, ranges);
+    if (direct > 0) return direct;
+    kind = c > I.small_max ? kKindGroups : is_tiny(I, a, c, tiny_max) ? kKindTiny : kKindSmall;
+    return plan_parts(I, c, a);
+}
+
+__global__ __launch_bounds__(256) void k_task_count(const int64_t *cost, PlanItems I,
+                                                    int32_t tiny_max, int32_t bound,
+                                                    int32_t *ntask, int64_t *sums) {
+    I.crank = ranks_or_null(I.crank, I.N);
+    __shared__ int32_t sh[1 + kKinds];
+    if (threadIdx.x < 1 + kKinds) sh[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < I.N;
+         base += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t i = base + threadIdx.x;
+        int32_t kind = -1, r = 0;
+        if (i < I.N) {
+            const int32_t a = (int32_t)i;
+            const int64_t c = cost[a];
+            int32_t n = item_tasks(I, a, c, tiny_max, kind, r);
+            if (n == 0) kind = -1;
+            // at a larger s the item's cost is no higher, but its ranges may
+            // come to have too few wedges to be counted directly, and the
+            // other way round; either way it has at most one task per
+            // `target` wedges
+            if (bound && c > 0)
+                n = max(n, (int32_t)min((c + I.target - 1) / I.target, (int64_t)INT32_MAX));
+            ntask[a] = n;
+        }
+        r = wave_total(r);
+        if (lane_id() == 0 && r) atomicAdd(&sh[0], r);
+#pragma unroll
+        for (int k = 0; k < kKinds; ++k) {
+            const int32_t n = (int32_t)__popcll(__ballot(kind == k));
+            if (lane_id() == 0 && n) atomicAdd(&sh[1 + k], n);
+        }
+    }
+    __syncthreads();
+    // one atomic per sum and block (same-address atomics serialize)
+    if (threadIdx.x < 1 + kKinds && sh[threadIdx.x])
+        atomicAdd((unsigned long long *)&sums[threadIdx.x], (unsigned long long)sh[threadIdx.x]);
+}
+
+// counts[kind] receives the length of each kind's list.
+//
 // Each workgroup fills the tasks of a contiguous chunk of items.  The slots
 // of the two lists are claimed with one global atomic per list and workgroup
 // (same-address atomics serialize), then handed out inside the workgroup
 // with LDS atomics, one per wave and step.
-__global__ __launch_bounds__(256) void k_task_fill(const int64_t *cost, int32_t N,
-                                                   int32_t small_max, int32_t target,
-                                                   int32_t tiny_max, PlanItems I,
-                                                   int32_t group, const int64_t *tbase,
-                                                   int32_t *task_item, int32_t *task_part,
-                                                   int32_t *small_tasks, int32_t *small_items,
-                                                   int32_t *tiny_tasks, int32_t *tiny_items,
-                                                   int32_t *groups, int32_t *counts,
-                                                   int32_t chunk, const int32_t *abort) {
+__global__ __launch_bounds__(256) void k_task_fill(
+    const int64_t *cost, PlanItems I, int32_t tiny_max, int32_t group, const int64_t *tbase,
+    int32_t *task_item, int32_t *task_part, int32_t *small_tasks, int32_t *small_items,
+    int32_t *tiny_tasks, int32_t *tiny_items, int32_t *groups, int32_t cap, int32_t *counts,
+    int32_t chunk, const int32_t *abort) {
     if (abort && *abort != 0) return;
-    I.crank = ranks_or_null(I.crank, N);
-    __shared__ int32_t sh[3];
+    I.crank = ranks_or_null(I.crank, I.N);
+    const int32_t N = I.N;
+    __shared__ int32_t sh[kKinds];
     const int lane = lane_id();
     const int64_t lo = (int64_t)blockIdx.x * chunk;
     const int64_t hi = lo + chunk < N ? lo + chunk : N;
-    if (threadIdx.x == 0) sh[0] = sh[1] = sh[2] = 0;
+    if (threadIdx.x < kKinds) sh[threadIdx.x] = 0;
     __syncthreads();
-    // a tiny item: one task, a planning cost of at most tiny_max and at most
-    // kTinyCap members, outside product mode (see k_count_tiny)
-    auto is_tiny = [&](int64_t a, int64_t c) {
-        return c <= tiny_max && !I.full && I.ptrI[a + 1] - I.ptrI[a] <= kTinyCap;
+    // list entries of n tasks of a kind: task groups hold several
+    auto entries = [&](int32_t kind, int32_t n) {
+        return kind == kKindGroups ? (n + group - 1) / group : n;
     };
     // pass 1: list entries of the chunk
-    int32_t ns = 0, ng = 0, nt = 0;
+    int32_t ne[kKinds] = {};
     for (int64_t a = lo + threadIdx.x; a < hi; a += blockDim.x) {
-        const int64_t c = cost[a];
-        const int32_t P = plan_parts(I, cost, N, small_max, target, (int32_t)a);
-        if (P == 0) continue;
-        if (c <= small_max) {
-            if (is_tiny(a, c)) ++nt;
-            else ++ns;
-        } else {
-            ng += (P + group - 1) / group;
-        }
+        int32_t kind, ranges;
+        const int32_t n = item_tasks(I, (int32_t)a, cost[a], tiny_max, kind, ranges);
+        const int32_t e = entries(kind, n);
+#pragma unroll
+        for (int k = 0; k < kKinds; ++k) ne[k] += k == kind ? e : 0;
     }
-    ns = wave_total(ns);
-    ng = wave_total(ng);
-    nt = wave_total(nt);
-    if (lane == 0) {
-        if (ns) atomicAdd(&sh[0], ns);
-        if (ng) atomicAdd(&sh[1], ng);
-        if (nt) atomicAdd(&sh[2], nt);
+#pragma unroll
+    for (int k = 0; k < kKinds; ++k) {
+        const int32_t n = wave_total(ne[k]);
+        if (lane == 0 && n) atomicAdd(&sh[k], n);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        sh[0] = sh[0] ? atomicAdd(&counts[0], sh[0]) : 0;
-        sh[1] = sh[1] ? atomicAdd(&counts[1], sh[1]) : 0;
-        sh[2] = sh[2] ? atomicAdd(&counts[2], sh[2]) : 0;
-    }
+    if (threadIdx.x < kKinds && sh[threadIdx.x])
+        sh[threadIdx.x] = atomicAdd(&counts[threadIdx.x], sh[threadIdx.x]);
     __syncthreads();
     // pass 2: tasks, and the list entries at the claimed slots
     for (int64_t base = lo + (threadIdx.x & ~(kWave - 1)); base < hi; base += blockDim.x) {
         const int64_t a = base + lane;
-        int64_t c = 0;
-        int32_t P = 0;
+        int32_t n = 0, kind = -1, ranges;
         int64_t t0 = 0;
         if (a < hi) {
-            c = cost[a];
-            P = plan_parts(I, cost, N, small_max, target, (int32_t)a);
-            if (P > 0) t0 = tbase[a];
+            n = item_tasks(I, (int32_t)a, cost[a], tiny_max, kind, ranges);
+            if (n > 0) t0 = tbase[a];
         }
-        for (int32_t p = 0; p < P; ++p) {
+        for (int32_t p = 0; p < n; ++p) {
             task_item[t0 + p] = (int32_t)a;
             task_part[t0 + p] = p;
         }
-        const bool one = P > 0 && c <= small_max;
-        const bool tiny = one && is_tiny(a, c);
-        const bool small = one && !tiny;
-        const int32_t G = (P > 0 && !one) ? (P + group - 1) / group : 0;
-        const uint64_t sm = __ballot(small), tm = __ballot(tiny);
-        int32_t sbase = 0, tbase0 = 0;
-        if (lane == 0 && sm) sbase = atomicAdd(&sh[0], (int32_t)__popcll(sm));
-        if (lane == 0 && tm) tbase0 = atomicAdd(&sh[2], (int32_t)__popcll(tm));
-        sbase = __shfl(sbase, 0, kWave);
-        tbase0 = __shfl(tbase0, 0, kWave);
-        if (small) {
-            const int32_t q = sbase + (int32_t)lanes_below(sm);
-            small_tasks[q] = (int32_t)t0;
-            small_items[q] = (int32_t)a;
-        }
-        if (tiny) {
-            const int32_t q = tbase0 + (int32_t)lanes_below(tm);
-            tiny_tasks[q] = (int32_t)t0;
-            tiny_items[q] = (int32_t)a;
-        }
-        int32_t incl = G;  // inclusive prefix of G over the wave
+        // this lane's first entry in the list of its kind
+        int32_t at = 0;
 #pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int32_t u = __shfl_up(incl, d, kWave);
-            if (lane >= d) incl += u;
+        for (int k = 0; k < kKinds; ++k) {
+            const bool is = n > 0 && kind == k;
+            const uint64_t m = __ballot(is);
+            if (m == 0) continue;
+            const bool several = k == kKindGroups || k == kKindFlat;
+            const int32_t e = is ? entries(k, n) : 0;
+            const int32_t incl = several ? wave_incl(e) : (int32_t)lanes_below(m) + e;
+            const int32_t tot = several ? lane63(incl) : (int32_t)__popcll(m);
+            int32_t first = 0;
+            if (lane == 0) first = atomicAdd(&sh[k], tot);
+            first = uniform(first);
+            if (is) at = first + incl - e;
         }
-        const int32_t tot = __shfl(incl, kWave - 1, kWave);
-        int32_t gbase = 0;
-        if (lane == kWave - 1 && tot) gbase = atomicAdd(&sh[1], tot);
-        gbase = __shfl(gbase, kWave - 1, kWave);
-        const int32_t at = gbase + incl - G;
-        for (int32_t g = 0; g < G; ++g) groups[at + g] = (int32_t)(t0 + (int64_t)g * group);
+        if (n == 0) continue;
+        if (kind == kKindSmall) {
+            small_tasks[at] = (int32_t)t0;
+            small_items[at] = (int32_t)a;
+        } else if (kind == kKindTiny) {
+            tiny_tasks[at] = (int32_t)t0;
+            tiny_items[at] = (int32_t)a;
+        } else if (kind == kKindSieve1) {
+            small_tasks[cap - 1 - at] = (int32_t)t0;
+        } else if (kind == kKindSieve4) {
+            tiny_tasks[cap - 1 - at] = (int32_t)t0;
+        } else if (kind == kKindFlat) {
+            for (int32_t p = 0; p < n; ++p) groups[cap - 1 - (at + p)] = (int32_t)(t0 + p);
+        } else {
+            for (int32_t g = 0; g * group < n; ++g)
+                groups[at + g] = (int32_t)(t0 + (int64_t)g * group);
+        }
     }
 }
 
-__global__ void k_reset_queue(int32_t *q) { *q = 0; }
+__global__ void k_reset_queue(int32_t *q) { q[0] = q[1] = 0; }
 
 // One wave per staged range (grid-stride): pool -> final (a, b, w).
 // A record as the stage pass wrote it, checked all the same: it guards the
@@ -1423,64 +1640,71 @@ inline int grid_for(int64_t work, int per_block, int cap) {
 
 }  // namespace
 
-hipError_t launch_task_count(hipStream_t st, const int64_t *cost, int32_t N, const Tuning &tu,
-                             const int32_t *ptrI, const int32_t *crank, const int32_t *item_end,
-                             int32_t full, int32_t *ntask) {
-    if (N <= 0) return hipSuccess;
-    const PlanItems I{ptrI, crank, item_end, full, tu.dense_min_wedges, tu.task_slots};
-    k_task_count<<<grid_for(N, 256, 65536), 256, 0, st>>>(cost, N, tu.small_max_wedges,
-                                                         tu.task_wedges, I, ntask);
+hipError_t launch_task_count(hipStream_t st, const int64_t *cost, const PlanItems &I,
+                             int32_t tiny_max, int32_t *ntask, int64_t *sums, int32_t bound) {
+    if (I.N <= 0) return hipSuccess;
+    k_task_count<<<grid_for(I.N, 256, 2048), 256, 0, st>>>(cost, I, tiny_max, bound, ntask, sums);
     return hipGetLastError();
 }
 
-hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, int32_t N, const Tuning &tu,
-                            const int32_t *ptrI, const int32_t *crank, const int32_t *item_end,
-                            int32_t full, const int64_t *tbase, int32_t *task_item, int32_t *task_part,
-                            int32_t *small_tasks, int32_t *small_items, int32_t *tiny_tasks,
-                            int32_t *tiny_items, int32_t *big_tasks, int32_t *counts,
+hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, const PlanItems &I,
+                            int32_t tiny_max, int32_t group, const int64_t *tbase,
+                            int32_t *task_item, int32_t *task_part, int32_t *small_tasks,
+                            int32_t *small_items, int32_t *tiny_tasks, int32_t *tiny_items,
+                            int32_t *big_tasks, int32_t cap, int32_t *counts,
                             const int32_t *abort) {
-    if (N <= 0) return hipSuccess;
-    const int64_t blocks = std::min<int64_t>(1024, ((int64_t)N + 255) / 256);
-    const int32_t chunk = (int32_t)((((int64_t)N + blocks - 1) / blocks + 255) / 256 * 256);
-    const int64_t grid = ((int64_t)N + chunk - 1) / chunk;
-    const PlanItems I{ptrI, crank, item_end, full, tu.dense_min_wedges, tu.task_slots};
-    k_task_fill<<<(unsigned)grid, 256, 0, st>>>(cost, N, tu.small_max_wedges, tu.task_wedges,
-                                                tu.tiny_max_wedges, I,
-                                                std::max(1, tu.group_parts), tbase, task_item,
-                                                task_part, small_tasks, small_items, tiny_tasks,
-                                                tiny_items, big_tasks, counts, chunk, abort);
+    if (I.N <= 0) return hipSuccess;
+    const int64_t blocks = std::min<int64_t>(1024, ((int64_t)I.N + 255) / 256);
+    const int32_t chunk = (int32_t)((((int64_t)I.N + blocks - 1) / blocks + 255) / 256 * 256);
+    const int64_t grid = ((int64_t)I.N + chunk - 1) / chunk;
+    k_task_fill<<<(unsigned)grid, 256, 0, st>>>(cost, I, tiny_max, std::max(1, group), tbase,
+                                                task_item, task_part, small_tasks, small_items,
+                                                tiny_tasks, tiny_items, big_tasks, cap, counts,
+                                                chunk, abort);
     return hipGetLastError();
 }
 
 hipError_t launch_count(hipStream_t st, const CountArgs &A, hipEvent_t mid) {
     if (A.N <= 0) return hipSuccess;
-    if (A.tune.tiny_max_wedges > 0 && !A.full) {
+    const auto any = [&](int kind) { return ((A.kinds >> kind) & 1u) != 0; };
+    if (any(kKindTiny) && A.tune.tiny_max_wedges > 0 && !A.full) {
         // LDS (the 32 KB candidate buffer) allows four workgroups per CU
         k_count_tiny<<<std::max(1, A.n_cu * 4), kTinyThreads, 0, st>>>(A);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
     }
-    const int gs = std::max(1, A.n_cu * A.tune.small_grid_per_cu);
-    switch (A.tune.small_slots) {
-    case 512: k_count_small<512><<<gs, kWave, 0, st>>>(A); break;
-    case 2048: k_count_small<2048><<<gs, kWave, 0, st>>>(A); break;
-    default: k_count_small<1024><<<gs, kWave, 0, st>>>(A); break;
+    if (any(kKindSmall)) {
+        const int gs = std::max(1, A.n_cu * A.tune.small_grid_per_cu);
+        switch (A.tune.small_slots) {
+        case 512: k_count_small<512><<<gs, kWave, 0, st>>>(A); break;
+        case 2048: k_count_small<2048><<<gs, kWave, 0, st>>>(A); break;
+        default: k_count_small<1024><<<gs, kWave, 0, st>>>(A); break;
+        }
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_reset_queue<<<1, 1, 0, st>>>(A.queue);
+    if (any(kKindGroups) || any(kKindFlat)) k_reset_queue<<<1, 1, 0, st>>>(A.queue);
     if (mid) {
         e = hipEventRecord(mid, st);
         if (e != hipSuccess) return e;
     }
-    const int gh = std::max(1, A.n_cu * A.tune.task_grid_per_cu);
-    switch (A.tune.task_slots) {
-    case 4480: k_count_tasks<4480, 4, 256><<<gh, 256, 0, st>>>(A); break;
-    case 13440: k_count_tasks<13440, 2, 256><<<gh, 256, 0, st>>>(A); break;
-    // twice the table and twice the threads: two workgroups per CU keep
-    // four waves per SIMD, as four of 256 threads do
-    case 17920: k_count_tasks<17920, 4, 512><<<gh, 512, 0, st>>>(A); break;
-    default: k_count_tasks<8960, 4, 256><<<gh, 256, 0, st>>>(A); break;
+    if (any(kKindFlat)) {
+        e = launch_count_flat(st, A);
+        if (e != hipSuccess) return e;
+    }
+    // LDS allows 15 one-wave and four 256-thread workgroups per CU
+    if (any(kKindSieve4))
+        k_count_sieve<kSieveLarge, 4><<<std::max(1, A.n_cu * 4), kSieveLarge, 0, st>>>(A);
+    if (any(kKindSieve1))
+        k_count_sieve<kSieveSmall, 4><<<std::max(1, A.n_cu * 15), kSieveSmall, 0, st>>>(A);
+    if (any(kKindGroups)) {
+        const int gh = std::max(1, A.n_cu * A.tune.task_grid_per_cu);
+        switch (A.tune.task_slots) {
+        case 4480: k_count_tasks<4480, 4, 256><<<gh, 256, 0, st>>>(A); break;
+        case 13440: k_count_tasks<13440, 2, 256><<<gh, 256, 0, st>>>(A); break;
+        // twice the table and twice the threads: two workgroups per CU keep
+        // four waves per SIMD, as four of 256 threads do
+        case 17920: k_count_tasks<17920, 4, 512><<<gh, 512, 0, st>>>(A); break;
+        default: k_count_tasks<8960, 4, 256><<<gh, 256, 0, st>>>(A); break;
+        }
     }
     return hipGetLastError();
 }

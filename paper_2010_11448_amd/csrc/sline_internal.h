@@ -57,6 +57,167 @@ constexpr int kTinyCap = 32;
 constexpr int kTinyMaxCost = 10;
 constexpr int kTinyThreads = 256;
 
+// Candidate numbers.  A build that filters by s may number its kept items 0, 1,
+// ... in id order and let the member lists hold those ranks: the candidates
+// of an item then lie in a range with no items that cannot be in a pair, so
+// the range is cut into fewer tables.  The price is a look-up per pair to
+// turn ranks back into items (on the 10^6-item power-law graph, 4 of 74 ms
+// at s = 2, where 99.98 % of the items are kept; at s = 8, 15 % kept, the
+// build takes 18.9 instead of 21.7 ms, and 12.4 instead of 13.8 on the dual
+// side).  Ranks are used when at most three in four items are kept (crank[N]
+// counts them; every kernel derives the same answer from it), in builds of one
+// graph with kRankMinItems items or more: a smaller one fits a few tables
+// anyhow, and so does each graph of a batch (128 lognormal graphs of up to
+// 200,000 hyperedges: 11.1 ms with ranks, 10.7 without).
+constexpr int64_t kRankMinItems = 1 << 17;
+__host__ __device__ inline bool ranks_pay(int64_t kept, int64_t N) { return kept * 4 <= N * 3; }
+
+// A kernel drops crank (and orig) at its start when the build does not use ranks;
+// a candidate's number is then its item's id.
+__device__ __forceinline__ const int32_t *ranks_or_null(const int32_t *crank, int32_t N) {
+    return crank && ranks_pay(crank[N], N) ? crank : nullptr;
+}
+
+__device__ __forceinline__ int32_t cand_of(const int32_t *crank, int32_t item) {
+    return crank ? crank[item] : item;
+}
+
+// First candidate of item a: the one after a (product mode: 0).
+__device__ __forceinline__ int32_t cand_first(const int32_t *crank, int32_t full, int32_t a) {
+    return full ? 0 : cand_of(crank, a) + 1;
+}
+
+// One past the last candidate of item a: the end of its graph (batches) or of
+// all items.
+__device__ __forceinline__ int32_t cand_end(const int32_t *crank, const int32_t *item_end,
+                                            int32_t N, int32_t a) {
+    return cand_of(crank, item_end ? item_end[a] : N);
+}
+
+// The item a candidate stands for.
+__device__ __forceinline__ int32_t item_of(const int32_t *orig, int32_t cand) {
+    return orig ? orig[cand] : cand;
+}
+
+// Direct counting (sline_flat.hip): an item's candidate range is cut into
+// ranges of kFlatBlock << k candidates that fit kFlatWords words of counters
+// wide enough for the item's size: 4 bits (k = 2), 8 (k = 1) or 16 (k = 0).
+constexpr int32_t kFlatWords = 15360;
+constexpr int32_t kFlatBlock = kFlatWords * 2;
+constexpr int32_t kFlatMaxSize = 65535;      // members of an item at most
+constexpr int32_t kFlatTaskWedges = 1 << 16; // a task's share of a heavy item
+// With s = 1, items of at most kFlatKeep wedges and kFlatThreads members keep
+// their wedges in registers and take one bit per candidate, in ranges of
+// kKeepWidth.
+constexpr int32_t kFlatThreads = 512;
+constexpr int32_t kFlatKeep = 32 * kFlatThreads;
+constexpr int32_t kKeepWidth = kFlatWords / 2 * 32;
+constexpr int32_t kKeepRanks = kFlatWords / 4;  // pairs of a range counted at a time
+
+// Sieved counting (k_count_sieve): with s > 1, an item of at most
+// kSieveWedges * threads wedges and a member per thread is counted by one
+// workgroup of kSieveSmall or kSieveLarge threads.
+constexpr int32_t kSieveSmall = 64, kSieveLarge = 256;
+constexpr int32_t kSieveWedges = 32;
+
+// Blocks that hold `cands` candidates.
+__device__ __forceinline__ int32_t flat_blocks(int32_t cands) {
+    return (int32_t)(((int64_t)cands + kFlatBlock - 1) / kFlatBlock);
+}
+
+struct FlatShape {
+    int32_t base;    // first candidate of the first range
+    int32_t width;   // candidates per range
+    int32_t ranges;
+    uint32_t lbits;  // 1 << lbits bits per counter
+};
+
+// Ranges of an item with candidates [first, nend) and `size` members: one
+// that starts at its first candidate, or several that start at a block.
+__device__ __forceinline__ FlatShape flat_shape(int32_t first, int32_t nend, int32_t size) {
+    FlatShape f;
+    f.lbits = size < 16 ? 2u : size < 256 ? 3u : 4u;
+    f.width = kFlatBlock << (4u - f.lbits);
+    f.base = first;
+    f.ranges = 1;
+    if ((int64_t)nend - first > f.width) {
+        f.base = first / kFlatBlock * kFlatBlock;
+        f.ranges = (int32_t)(((int64_t)nend - f.base + f.width - 1) / f.width);
+    }
+    return f;
+}
+
+// Whether an item keeps its wedges in registers, and its ranges then.
+__device__ __forceinline__ bool flat_keeps(int32_t s, int64_t cost, int32_t size) {
+    return s == 1 && cost <= kFlatKeep && size <= kFlatThreads;
+}
+
+__device__ __forceinline__ int32_t keep_ranges(int32_t first, int32_t nend) {
+    return (int32_t)(((int64_t)nend - first + kKeepWidth - 1) / kKeepWidth);
+}
+
+// Ranges of a task of an item with `cost` wedges.
+__device__ __forceinline__ int32_t flat_ranges_per_task(const FlatShape &f, int64_t cost) {
+    const int64_t parts = (cost + kFlatTaskWedges - 1) / kFlatTaskWedges;
+    return parts >= f.ranges ? 1 : (int32_t)((f.ranges + parts - 1) / parts);
+}
+
+// What the task planner needs to know about the items besides their cost.
+struct PlanItems {
+    const int32_t *ptrI;      // item lists (sizes)
+    const int32_t *crank;     // candidate numbers of the items, or null: their ids
+    const int32_t *item_end;  // per item: end of its graph's items (batches), or null
+    const int32_t *s_item;    // per-item s (batches), or null: s
+    int32_t N, s;
+    int32_t full;             // product mode
+    int32_t small_max;        // Tuning::small_max_wedges
+    int32_t target;           // Tuning::task_wedges
+    int32_t dense_min;        // Tuning::dense_min_wedges
+    int32_t slots;            // Tuning::task_slots
+};
+
+// How an item is counted.  The lists of its tasks are counts[kind] long.
+enum : int32_t {
+    kKindSmall = 0,   // one wave, hash table
+    kKindGroups = 1,  // workgroup task groups, hash table
+    kKindTiny = 2,    // one lane
+    kKindFlat = 3,    // direct counters
+    kKindSieve1 = 4,  // sieved, kSieveSmall threads
+    kKindSieve4 = 5,  // sieved, kSieveLarge threads
+    kKinds = 6,
+};
+
+// Tasks of item a when every wedge of it is counted by one of the kernels
+// without hashed wedge lists (kind: which; ranges: those that stage their pairs
+// by themselves), 0 when it is not.  `cost` is W_a, or the lowered planning
+// cost of an item that was not to be counted so by its W_a (and is not by less).
+__device__ __forceinline__ int32_t direct_tasks(const PlanItems &I, int32_t a, int64_t cost,
+                                                int32_t &kind, int32_t &ranges) {
+    ranges = 0;
+    kind = kKindFlat;
+    if (cost <= I.small_max || I.dense_min <= 0 || I.full) return 0;
+    const int32_t size = I.ptrI[a + 1] - I.ptrI[a];
+    const int32_t s = I.s_item ? I.s_item[a] : I.s;
+    if (s > 1 && cost <= kSieveWedges * kSieveLarge && size <= kSieveLarge) {
+        const bool one = cost <= kSieveWedges * kSieveSmall && size <= kSieveSmall;
+        kind = one ? kKindSieve1 : kKindSieve4;
+        return 1;
+    }
+    if (size > kFlatMaxSize) return 0;
+    const int32_t first = cand_first(I.crank, 0, a), nend = cand_end(I.crank, I.item_end, I.N, a);
+    if (flat_keeps(s, cost, size)) {
+        const int32_t n = keep_ranges(first, nend);
+        if (cost * 16 < (int64_t)I.dense_min * n) return 0;
+        ranges = n + (int32_t)(cost / kKeepRanks);
+        return 1;
+    }
+    const FlatShape f = flat_shape(first, nend, size);
+    if (cost * 8 < (int64_t)I.dense_min * f.ranges) return 0;
+    const int32_t per = flat_ranges_per_task(f, cost);
+    ranges = f.ranges;
+    return (f.ranges + per - 1) / per;
+}
+
 // ------------------------------------------------------------ launchers
 // Every launcher enqueues on `st` and returns the launch status.
 
@@ -95,21 +256,6 @@ hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int
                             const int32_t *rowid, int32_t *const rsK[2], int32_t *const rsV[2],
                             int32_t *hist, int32_t *part32, int32_t *ptrT, int32_t *colT,
                             int32_t *kT, int32_t *posT);
-
-// Candidate numbers.  A build that filters by s may number its kept items 0, 1,
-// ... in id order and let the member lists hold those ranks: the candidates
-// of an item then lie in a range with no items that cannot be in a pair, so
-// the range is cut into fewer tables.  The price is a look-up per pair to
-// turn ranks back into items (on the 10^6-item power-law graph, 4 of 74 ms
-// at s = 2, where 99.98 % of the items are kept; at s = 8, 15 % kept, the
-// build takes 18.9 instead of 21.7 ms, and 12.4 instead of 13.8 on the dual
-// side).  Ranks are used when at most three in four items are kept (crank[N]
-// counts them; every kernel derives the same answer from it), in builds of one
-// graph with kRankMinItems items or more: a smaller one fits a few tables
-// anyhow, and so does each graph of a batch (128 lognormal graphs of up to
-// 200,000 hyperedges: 11.1 ms with ranks, 10.7 without).
-constexpr int64_t kRankMinItems = 1 << 17;
-__host__ __device__ inline bool ranks_pay(int64_t kept, int64_t N) { return kept * 4 <= N * 3; }
 
 // s filter: N_s(v) = the items of N(v) with |S| >= s (s_item[it] for item it
 // when s_item is given), every list in its order, written to itmS with list
@@ -157,30 +303,44 @@ constexpr int32_t kMaxLookup = 15;  // lookup-only members per item at most
 // s_item (nullable) gives each item its own s (batches); s_max is the largest.
 // Items with at most kTinyCap members and at most tiny_max wedges (0: none)
 // are left as they are: the one-lane path counts every wedge of them.
-hipError_t launch_mark_lookup(hipStream_t st, const int32_t *ptrI, const int32_t *memI, int32_t N,
-                              int32_t s, const int32_t *s_item, int32_t s_max,
-                              const int32_t *ptrS, int32_t *start, int64_t *cost,
+// So are items that count every wedge another way (direct_tasks).
+hipError_t launch_mark_lookup(hipStream_t st, const PlanItems &I, const int32_t *memI,
+                              int32_t s_max, const int32_t *ptrS, int32_t *start, int64_t *cost,
                               int32_t tiny_max);
 
-// Tasks: item a with W_a wedges becomes P_a tasks (equal sub-ranges of its
+// Tasks: item a with W_a wedges becomes P_a tasks (sub-ranges of its
 // candidate range); ntask[a] = P_a.  Task t of item a (t = tbase[a] + p) is
 // listed in small_tasks, with its item in small_items (W_a <= small_max), or
 // in big_tasks; counts[0] / [1]
 // receive the list lengths.
-hipError_t launch_task_count(hipStream_t st, const int64_t *cost, int32_t N, const Tuning &tu,
-                             const int32_t *ptrI, const int32_t *crank, const int32_t *item_end,
-                             int32_t full, int32_t *ntask);
+// sums (zeroed by the caller): [0] receives the ranges of the items counted
+// directly, each of which stages its pairs by itself, [1 + kind] the items of
+// each kind.
+// bound != 0: instead of P_a, no fewer tasks than the item can come to have in a
+// replay of the same lists at any larger s.
+hipError_t launch_task_count(hipStream_t st, const int64_t *cost, const PlanItems &I,
+                             int32_t tiny_max, int32_t *ntask, int64_t *sums,
+                             int32_t bound = 0);
 // big_tasks receives, per group of up to group_parts consecutive tasks of an
 // item, the index of the group's first task; counts[1] = number of groups.
 // With `abort` given, the kernel does nothing while *abort != 0.
 // Tiny one-task items (Tuning::tiny_max_wedges) go to tiny_tasks /
 // tiny_items instead of the small lists; counts[2] receives their number.
-hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, int32_t N, const Tuning &tu,
-                            const int32_t *ptrI, const int32_t *crank, const int32_t *item_end,
-                            int32_t full, const int64_t *tbase, int32_t *task_item, int32_t *task_part,
-                            int32_t *small_tasks, int32_t *small_items, int32_t *tiny_tasks,
-                            int32_t *tiny_items, int32_t *big_tasks, int32_t *counts,
+// The tasks of items counted without hashed wedge lists go to the ends of three
+// lists, each with `cap` entries, room for every task: big_tasks[cap - 1 - i] for
+// i < counts[kKindFlat], small_tasks (kKindSieve1) and tiny_tasks (kKindSieve4)
+// likewise.
+hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, const PlanItems &I,
+                            int32_t tiny_max, int32_t group, const int64_t *tbase,
+                            int32_t *task_item, int32_t *task_part, int32_t *small_tasks,
+                            int32_t *small_items, int32_t *tiny_tasks, int32_t *tiny_items,
+                            int32_t *big_tasks, int32_t cap, int32_t *counts,
                             const int32_t *abort = nullptr);
+
+// Positions of the multiples of kFlatBlock candidates in the long lists (bnd:
+// as many entries as itmS), for the items counted directly.
+hipError_t launch_flat_bounds(hipStream_t st, const int32_t *ptrS, const int32_t *itmS, int32_t M,
+                              const int32_t *crank, int32_t N, int32_t *bnd);
 
 // Counting-kernel modes.
 enum : int32_t {
@@ -216,8 +376,10 @@ struct CountArgs {
     const int32_t *small_tasks, *big_tasks;
     const int32_t *small_items;  // item of each small task
     const int32_t *tiny_tasks, *tiny_items;  // tiny tasks (one lane each) and their items
-    const int32_t *task_counts;  // [0] small tasks, [1] task groups, [2] tiny tasks
-    int32_t *queue;              // big-task queue head (reset by the launcher)
+    const int32_t *task_counts;  // list lengths by kind
+    uint32_t kinds;              // bit per kind that has items (all set where the host cannot know)
+    const int32_t *bnd;          // bounds table of the direct path (launch_flat_bounds)
+    int32_t *queue;              // queue heads: task groups, direct tasks (reset by the launcher)
     int32_t *task_cnt;           // count mode: pairs per task
     const int64_t *task_off;     // fill mode: output offset per task (nullptr = count mode)
     int32_t *out_a, *out_b, *out_w;  // out_w null: weights not written (SLINE_NO_WEIGHTS)
@@ -254,6 +416,8 @@ struct CountArgs {
 };
 // `mid` (may be null) is recorded between the one-wave kernel and the task kernel.
 hipError_t launch_count(hipStream_t st, const CountArgs &a, hipEvent_t mid = nullptr);
+// The direct counting kernel alone (launch_count calls it).
+hipError_t launch_count_flat(hipStream_t st, const CountArgs &a);
 
 // ---------------------------------------------------------------- batches
 // One graph of a batch (a device array of these drives the batch kernels).

@@ -505,18 +505,20 @@ __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t
 constexpr int kKeysPerLane = 4;
 
 template <int W>
-__global__ __launch_bounds__(256) void k_mark_lookup(const int32_t *ptrI, const int32_t *memI,
-                                                     int32_t N, int32_t s_all,
-                                                     const int32_t *s_item, const int32_t *ptrS,
+__global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t *memI,
+                                                     const int32_t *ptrS,
                                                      int32_t *start, int64_t *cost,
                                                      int32_t tiny_max) {
-    for_rows<W, kGroup * kKeysPerLane>(ptrI, N, [&](int64_t a, int gl) {
-        const int32_t b = ptrI[a], e = ptrI[a + 1];
-        const int32_t s = s_item ? s_item[a] : s_all;
+    I.crank = ranks_or_null(I.crank, I.N);
+    for_rows<W, kGroup * kKeysPerLane>(I.ptrI, I.N, [&](int64_t a, int gl) {
+        const int32_t b = I.ptrI[a], e = I.ptrI[a + 1];
+        const int32_t s = I.s_item ? I.s_item[a] : I.s;
         if (e - b < s) return;
         // a tiny item by its exact wedges stays tiny: it is counted one per
         // lane, every wedge, so lookup-only members would change nothing
         if (e - b <= kTinyCap && cost[a] <= tiny_max) return;
+        int32_t kind, ranges;
+        if (direct_tasks(I, (int32_t)a, cost[a], kind, ranges) > 0) return;
         const int32_t rounds = min(min(s - 1, kMaxLookup), e - b - 1);
         int64_t flagged = 0;
         if (e - b <= W * kKeysPerLane) {
@@ -566,7 +568,9 @@ __global__ __launch_bounds__(256) void k_mark_lookup(const int32_t *ptrI, const 
         }
         if (gl == 0 && flagged) {
             const int64_t w = cost[a];
-            cost[a] = max(w - flagged, (w + 2) / 3);
+            // an item with too many wedges for the sieve keeps more than those
+            const int64_t least = min(w, (int64_t)kSieveWedges * kSieveLarge + 1);
+            cost[a] = max(max(w - flagged, (w + 2) / 3), w > least ? least : (int64_t)0);
         }
     });
 }
@@ -772,17 +776,16 @@ hipError_t launch_cost(hipStream_t st, const int32_t *ptrI, const int32_t *memI,
     return hipGetLastError();
 }
 
-hipError_t launch_mark_lookup(hipStream_t st, const int32_t *ptrI, const int32_t *memI, int32_t N,
-                              int32_t s, const int32_t *s_item, int32_t s_max,
-                              const int32_t *ptrS, int32_t *start, int64_t *cost,
+hipError_t launch_mark_lookup(hipStream_t st, const PlanItems &I, const int32_t *memI,
+                              int32_t s_max, const int32_t *ptrS, int32_t *start, int64_t *cost,
                               int32_t tiny_max) {
-    if (N <= 0 || s_max <= 1) return hipSuccess;
-    k_mark_lookup<kGroup><<<grid_for((int64_t)N * kGroup, 256, 65536), 256, 0, st>>>(
-        ptrI, memI, N, s, s_item, ptrS, start, cost, tiny_max);
+    if (I.N <= 0 || s_max <= 1) return hipSuccess;
+    k_mark_lookup<kGroup><<<grid_for((int64_t)I.N * kGroup, 256, 65536), 256, 0, st>>>(
+        I, memI, ptrS, start, cost, tiny_max);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_mark_lookup<kWave><<<grid_for(N, 256, 4096), 256, 0, st>>>(
-        ptrI, memI, N, s, s_item, ptrS, start, cost, tiny_max);
+    k_mark_lookup<kWave><<<grid_for(I.N, 256, 4096), 256, 0, st>>>(I, memI, ptrS, start, cost,
+                                                                  tiny_max);
     return hipGetLastError();
 }
 

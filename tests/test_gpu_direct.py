@@ -1,0 +1,86 @@
+"""The counting kernels without hashed wedge lists, at the sizes where they turn:
+the wedges and members a sieved item may have, more pairs than its table holds,
+the widths of direct counters and of a range, tasks of several ranges, more
+members than threads, and (s = 1) the pairs counted at a time."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2010_11448_amd import gen
+
+from helpers import assert_same, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    from paper_2010_11448_amd import sline
+
+    assert torch.cuda.is_available()
+    c = sline.Context(0)
+    yield c
+    c.close()
+
+
+def hub(T: int, k: int, r: int, N: int, seed: int) -> gen.Hypergraph:
+    """Item 0 has k members; T of the N items after it, the last one among them,
+    hold r of these (neighbours, cyclically) and all hold two vertices of their
+    own, so nearly every item is kept up to s = 2.  Item 0 has r T wedges and T
+    candidates that overlap it in r; members lie in about r T / k items."""
+    st = gen.Stream(seed)
+    at = np.sort(1 + np.argsort(st.uniform(N - 1), kind="stable")[:T - 1])
+    at = np.append(at, N)
+    first = st.integers(0, k - 1, T)
+    shared = np.sort((first[:, None] + np.arange(r)) % k, axis=1)
+    sizes = np.full(N + 1, 2, dtype=np.int64)
+    sizes[0] = k
+    sizes[at] += r
+    rp = np.zeros(N + 2, dtype=np.int32)
+    rp[1:] = np.cumsum(sizes)
+    col = np.empty(rp[-1], dtype=np.int32)
+    col[:k] = np.arange(k)
+    end = rp[2:]
+    col[end - 2] = k + 2 * np.arange(N)
+    col[end - 1] = k + 2 * np.arange(N) + 1
+    for q in range(r):
+        col[rp[at] + q] = shared[:, q]
+    return gen.Hypergraph(rp, col, N + 1, k + 2 * N)
+
+
+CASES = [
+    # sieved, one wave or four: wedges, members, pairs beyond the table
+    (1024, 64, 2, 50000), (1025, 64, 2, 50000), (600, 65, 2, 50000), (1000, 8, 2, 9000),
+    (4096, 256, 2, 70000), (4097, 256, 2, 70000), (1500, 257, 2, 70000), (4090, 40, 2, 200000),
+    (700, 6, 5, 700), (2000, 12, 4, 2000),
+    # direct counters of 4, 8 and 16 bits, one range and two
+    (9000, 15, 3, 122880), (9000, 15, 3, 122882), (9000, 16, 3, 61440), (9000, 16, 3, 61442),
+    (9000, 255, 3, 61442), (9000, 256, 3, 30720), (9000, 256, 3, 30722), (9000, 300, 3, 245800),
+    # several tasks, more members than threads
+    (45000, 90, 3, 400000), (30000, 1100, 4, 40000),
+    # s = 1: wedges kept, a range and two, pairs counted at a time
+    (8192, 30, 2, 9000), (8193, 30, 2, 9000), (3840, 30, 2, 245760), (3841, 30, 2, 245762),
+]
+
+
+@pytest.mark.parametrize("T,k,r,N", CASES, ids=["-".join(map(str, c)) for c in CASES])
+def test_hub(ctx, T, k, r, N):
+    import torch
+
+    g = hub(T, k, r, N, seed=T + k + N)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    base = ctx.tuning()
+    for s in sorted({1, 2, r, r + 1}):
+        ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, threads=8)
+        for stage in (base["stage_max_bytes"], 0):
+            what = f"T={T} k={k} r={r} N={N} s={s} stage={stage}"
+            print(f"case: {what}", flush=True)
+            ctx.set_tuning(stage_max_bytes=stage)
+            try:
+                assert_same(ctx.build(rp, col, g.n_vertices, s), ref, what)
+            finally:
+                ctx.set_tuning(**base)
