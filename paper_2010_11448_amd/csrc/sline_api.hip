@@ -325,8 +325,9 @@ struct Layout {
 // the items outnumber the lanes of the resident one-wave workgroups several
 // times over (a lane walks its item's lists one entry after another).
 constexpr int64_t kTinyMinItems = 1 << 15;
-Tuning build_tuning(const Tuning &t, int64_t n_items) {
+Tuning build_tuning(const Tuning &t, int64_t n_items, int64_t nnz) {
     Tuning u = t;
+    if (nnz >= kDirectMaxNnz) u.dense_min_wedges = 0;
     if (n_items < kTinyMinItems) u.tiny_max_wedges = 0;
     return u;
 }
@@ -846,7 +847,7 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
         itmS = L.itmS;
     }
     // 6. wedge counts, tasks
-    const Tuning tu = build_tuning(c->tune, N);
+    const Tuning tu = build_tuning(c->tune, N, nnz);
     if (!filt && !IS.full)
         hip_check(c, launch_start_from_map(st, nnz, map, L.start), "back-pointers");
     // degree-based pruning (Sec. IV-C) unless switched off: items smaller
@@ -1829,7 +1830,7 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
     const sline_status rb = batch_bases(c, p->gr, nnz, p->B);
     if (rb != SLINE_OK) return rb;
     const BatchBases &B = p->B;
-    p->C.tune = build_tuning(c->tune, B.NI);
+    p->C.tune = build_tuning(c->tune, B.NI, B.ZT);
     if (G > 0) {
         hip_check(c, hipMemcpyAsync(p->d_gr, p->gr.data(), sizeof(BatchGraph) * G,
                                     hipMemcpyHostToDevice, st),

@@ -130,76 +130,155 @@ __device__ __forceinline__ int32_t lane63(int32_t v) { return __builtin_amdgcn_r
 __device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // The wedges of an item (or of one range of it), numbered 0, 1, ... over its
-// members' list parts one after the other, one part per thread at most.  A bit
-// per wedge marks where a part begins: a wave reads the bits of 64 wedges, and
-// the count of the bits up to a lane's own is that lane's part.  Every lane of
+// members' list parts one after the other.  A bit per wedge marks where a part
+// begins: the count of the bits up to a wedge's own is its part.  Every lane of
 // every load then has a wedge, whatever the parts' lengths are.
+//
+// A window of CHUNKS * 64 wedges is shared out to the waves, a run of 64-wedge
+// chunks each; a lane holds the bits of one chunk of its wave's run, so taking
+// a chunk reads no memory but the part's position.  With up to 64 parts
+// (narrow) every wave numbers all of them by itself, in its own area: no
+// barrier.  With more, each thread has one part and two barriers order them.
 template <int NT, int CHUNKS>
 struct WedgeMap {
-    static constexpr int NW = NT / kWave;
-    int32_t *adj;     // NT: list position less wedge number, per part that has wedges
-    uint64_t *marks;  // CHUNKS, all zero when a window is marked
-    int32_t *wlen, *wpart;  // NW each
-    int32_t *before0;
+    static constexpr int NW = NT / kWave, PER = CHUNKS / NW;
+    static_assert(PER <= kWave && PER * NW == CHUNKS, "a lane per chunk of a run");
 
-    // Number the parts: this thread's is [b, b + len).  One barrier inside.
-    __device__ __forceinline__ void number(int32_t b, int32_t len, int32_t &off, int32_t &rank,
-                                           int32_t &total) const {
-        const int32_t incl = wave_incl(len);
-        const uint64_t has = __ballot(len > 0);
-        off = incl - len;
+    int32_t *adj_all;     // NT: list position less wedge number, per part that has wedges
+    uint32_t *marks_all;  // 2 * CHUNKS words, all zero between windows
+    int32_t *sh;          // 3 * NW
+    bool narrow;
+    int32_t *adj;
+    int32_t off, len, rank, total;  // this thread's part, and all wedges
+
+    // a run: the bits of chunk c0 + lane, the parts before it and the list
+    // position of its first wedge; the chunks that lie in one part (bit per
+    // chunk), chunks and wedges of the run
+    struct Run {
+        uint32_t lo, hi;
+        int32_t base, pos;
+        uint64_t whole;
+        int32_t nc, t0, n;
+    };
+
+    // Which member this thread looks after: narrow maps have one per lane.
+    __device__ __forceinline__ int member() const { return narrow ? lane_id() : (int)threadIdx.x; }
+
+    // Number the parts: this thread's is [b, b + n).
+    __device__ __forceinline__ void number(int32_t b, int32_t n) {
+        len = n;
+        const int32_t incl = wave_incl(n);
+        const uint64_t has = __ballot(n > 0);
+        off = incl - n;
         rank = (int32_t)lanes_below(has);
         total = lane63(incl);
-        if (NW > 1) {
+        adj = adj_all;
+        if (narrow) {
+            adj += wave_id() * kWave;
+        } else if (NW > 1) {
             const int wid = wave_id();
             if (lane_id() == 0) {
-                wlen[wid] = total;
-                wpart[wid] = __popcll(has);
+                sh[wid] = total;
+                sh[NW + wid] = __popcll(has);
             }
             __syncthreads();
             total = 0;
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
-                if (w < wid) {
-                    off += wlen[w];
-                    rank += wpart[w];
-                }
-                total += wlen[w];
+                const int32_t l = uniform(sh[w]), c = uniform(sh[NW + w]);
+                off += w < wid ? l : 0;
+                rank += w < wid ? c : 0;
+                total += l;
             }
         }
-        if (len > 0) adj[rank] = b - off;
+        if (n > 0) adj[rank] = b - off;
     }
-    // Mark the parts of the window that starts at wedge w0.
-    __device__ __forceinline__ void mark(int32_t w0, int32_t off, int32_t len, int32_t rank) const {
-        const int32_t in = off - w0;
-        if (len > 0 && in >= 0 && in < CHUNKS * kWave)
-            atomicOr(reinterpret_cast<uint32_t *>(marks) + (in >> 5), 1u << (in & 31));
-        // parts that begin before the window
-        if (len > 0 && in <= 0 && in + len > 0) *before0 = in < 0 ? rank : rank - 1;
-    }
-    // Parts that begin before chunk c0 of the window.
-    __device__ __forceinline__ int32_t parts_before(int32_t c0) const {
-        int32_t n = 0;
-        if (c0 > 0) {
+
+    // The wave's run of the window that starts at wedge w0 < total.
+    __device__ __forceinline__ Run window(int32_t w0) {
+        const int lane = lane_id(), wid = wave_id();
+        const int32_t n = min(total - w0, CHUNKS * kWave);
+        const int32_t nch = (n + kWave - 1) / kWave, cpw = (nch + NW - 1) / NW;
+        const int32_t c0 = min(nch, wid * cpw);
+        Run r;
+        r.nc = min(nch, c0 + cpw) - c0;
+        r.t0 = w0 + c0 * kWave;
+        r.n = min(n - c0 * kWave, r.nc * kWave);
+        uint32_t *marks = marks_all;
+        int32_t before;
+        if (narrow) {
+            marks += wid * 2 * PER;
+            const int32_t in = off - r.t0;
+            if (len > 0 && in >= 0 && in < r.n) atomicOr(marks + (in >> 5), 1u << (in & 31));
+            before = (int32_t)__popcll(__ballot(len > 0 && in < 0)) - 1;
+        } else {
+            const int32_t in = off - w0;
+            if (len > 0 && in >= 0 && in < n) atomicOr(marks + (in >> 5), 1u << (in & 31));
+            // parts up to the wedge before each run
 #pragma unroll
-            for (int i = 0; i < (CHUNKS + kWave - 1) / kWave; ++i) {
-                const int c = i * kWave + lane_id();
-                if (c < c0) n += __popcll(marks[c]);
+            for (int w = 0; w < NW; ++w) {
+                const int32_t d = in - w * cpw * kWave;
+                if (len > 0 && d <= 0 && d + len > 0) sh[2 * NW + w] = d < 0 ? rank : rank - 1;
             }
-            n = lane63(wave_incl(n));
+            __syncthreads();
+            marks += 2 * c0;
+            before = uniform(sh[2 * NW + wid]);
         }
-        return uniform(*before0) + n;
+        __builtin_amdgcn_wave_barrier();
+        r.lo = r.hi = 0u;
+        if (lane < r.nc) {
+            uint2 *const m = reinterpret_cast<uint2 *>(marks) + lane;
+            const uint2 v = *m;
+            *m = make_uint2(0u, 0u);
+            r.lo = v.x;
+            r.hi = v.y;
+        }
+        const int32_t pop = __popc(r.lo) + __popc(r.hi);
+        r.base = before + wave_incl(pop) - pop;
+        r.pos = 0;
+        if (lane < r.nc) r.pos = adj[r.base + (int32_t)(r.lo & 1u)] + r.t0 + lane * kWave;
+        r.whole = __ballot(((r.lo & ~1u) | r.hi) == 0u);
+        return r;
     }
-    // The candidate of this lane's wedge of chunk c (ok: it has one), and the
-    // parts so far.
-    __device__ __forceinline__ int32_t wedge(const int32_t *itmS, int32_t w0, int32_t c, bool ok,
-                                             int32_t &before) const {
-        const uint64_t raw = marks[c];
-        const uint64_t m = ((uint64_t)(uint32_t)uniform((int32_t)(raw >> 32)) << 32) |
-                           (uint32_t)uniform((int32_t)raw);
-        const int32_t q = before + (int32_t)(m & 1u) + (int32_t)lanes_below(m >> 1);
-        before += __popcll(m);
-        return ok ? itmS[adj[q] + w0 + c * kWave + lane_id()] : -1;
+
+    // List positions of the wedges of chunk u < nc of the run (a lane past the
+    // run's end gets its last wedge's).
+    __device__ __forceinline__ int32_t position(const Run &r, int32_t u, bool full) const {
+        if (full && ((r.whole >> u) & 1u))
+            return __builtin_amdgcn_readlane(r.pos, u) + lane_id();
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int32_t)r.lo, u);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int32_t)r.hi, u);
+        const uint64_t m = ((uint64_t)hi << 32) | lo;
+        const int32_t q = __builtin_amdgcn_readlane(r.base, u) + (int32_t)(lo & 1u) +
+                          (int32_t)lanes_below(m >> 1);
+        return adj[q] + r.t0 + (full ? u * kWave + lane_id() : min(u * kWave + lane_id(), r.n - 1));
+    }
+
+    // A list entry; positions lie below 2^30, so a 32-bit offset reaches it.
+    static __device__ __forceinline__ int32_t entry(const int32_t *itmS, int32_t p) {
+        return *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(itmS) +
+                                                  ((uint32_t)p << 2));
+    }
+
+    // Candidates of chunks u0 .. u0 + K - 1 of the run, -1 past its end.
+    template <int K>
+    __device__ __forceinline__ void load(const int32_t *itmS, const Run &r, int32_t u0,
+                                         int32_t (&j)[K]) const {
+        int32_t p[K];
+        if ((u0 + K) * kWave <= r.n) {
+#pragma unroll
+            for (int v = 0; v < K; ++v) p[v] = position(r, u0 + v, true);
+#pragma unroll
+            for (int v = 0; v < K; ++v) j[v] = entry(itmS, p[v]);
+        } else {
+#pragma unroll
+            for (int v = 0; v < K; ++v) p[v] = position(r, min(u0 + v, r.nc - 1), false);
+#pragma unroll
+            for (int v = 0; v < K; ++v) {
+                j[v] = entry(itmS, p[v]);
+                if ((u0 + v) * kWave + lane_id() >= r.n) j[v] = -1;
+            }
+        }
     }
 };
 

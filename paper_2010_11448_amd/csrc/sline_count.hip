@@ -974,6 +974,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
     constexpr int NW = NT / kWave;
     constexpr int LIM = NT * 16, SLOTS = LIM - kTaskPad;   // table words, home slots
     constexpr int CHUNKS = NT * kSieveWedges / kWave;
+    constexpr int kLoad = 8;  // chunks a wave loads at a time
     constexpr uint32_t BITS = LIM * 32;
     constexpr int RUNCAP = NT;  // extraction: one bucket entry per bucket of a wave's block
     static_assert(NW * kSieveList * sizeof(int32_t) >= RUNCAP * sizeof(int2), "list area");
@@ -981,8 +982,8 @@ __global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
     __shared__ __align__(16) uint32_t twice[LIM];
     __shared__ __align__(16) int32_t list[NW * kSieveList];
     __shared__ int32_t adj[NT];
-    __shared__ uint64_t marks[CHUNKS];
-    __shared__ int32_t wlen[NW], wpart[NW], before0;
+    __shared__ __align__(8) uint32_t marks[2 * CHUNKS];
+    __shared__ int32_t msh[3 * NW];
     __shared__ int2 stack[kStack];
     __shared__ int32_t misc[kMiscWave + NW];
     __shared__ uint64_t pool_cur[2];
@@ -996,14 +997,17 @@ __global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
     const int tid = threadIdx.x, lane = lane_id(), wid = wave_id();
     const Smem S{tab, reinterpret_cast<int2 *>(list), nullptr, misc, stack, tab + LIM, pool_cur,
                  log_cur};
-    const WedgeMap<NT, CHUNKS> map{adj, marks, wlen, wpart, &before0};
+    WedgeMap<NT, CHUNKS> map;
+    map.adj_all = adj;
+    map.marks_all = marks;
+    map.sh = msh;
     if (tid == 0) {
         pool_cur[0] = pool_cur[1] = 0;
         log_cur[0] = log_cur[1] = 0;
     }
     tab_clear<NT>(tab, LIM);
     tab_clear<NT>(twice, LIM);
-    for (int i = tid; i < CHUNKS; i += NT) marks[i] = 0;
+    for (int i = tid; i < 2 * CHUNKS; i += NT) marks[i] = 0;
     int64_t my_wedges = 0, my_nnz = 0, my_pairs = 0, passes = 0;  // thread 0's are used
     __syncthreads();
     for (int32_t r = blockIdx.x; r < n_tasks; r += gridDim.x) {
@@ -1014,30 +1018,22 @@ __global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
         const int32_t first = cand_first(A.crank, 0, a);
         const int32_t nend = cand_end(A.crank, A.item_end, A.N, a);
         const int32_t s = A.s_item ? A.s_item[a] : A.s;
+        map.narrow = NT == kWave || size <= kWave;
+        const int32_t k = map.member();
         int32_t b = 0, len = 0;
-        if (tid < size) {
-            const int32_t v = A.memI[k0 + tid];
-            b = A.start[k0 + tid] & kStartMask;
+        if (k < size) {
+            const int32_t v = A.memI[k0 + k];
+            b = A.start[k0 + k] & kStartMask;
             len = max(A.ptrS[v + 1] - b, 0);
         }
-        int32_t off, rank, total;
-        map.number(b, len, off, rank, total);
-        map.mark(0, off, len, rank);
-        __syncthreads();
-        const int32_t nch = (total + kWave - 1) / kWave, cpw = (nch + NW - 1) / NW;
-        const int32_t c0 = min(nch, wid * cpw), c1 = min(nch, c0 + cpw);
-        const int32_t parts0 = c0 < c1 ? map.parts_before(c0) : 0;
-        // call body(j) with four candidates per lane (-1: none), over the wave's chunks
+        map.number(b, len);
+        const int32_t total = map.total;
+        const auto run = map.window(0);
+        // call body(j) with kLoad candidates per lane (-1: none), over the wave's chunks
         auto walk = [&](auto body) {
-            int32_t before = parts0;
-            for (int32_t c = c0; c < c1; c += 4) {
-                int32_t j[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    j[u] = -1;
-                    if (c + u < c1)
-                        j[u] = map.wedge(A.itmS, 0, c + u, (c + u) * kWave + lane < total, before);
-                }
+            for (int32_t u = 0; u < run.nc; u += kLoad) {
+                int32_t j[kLoad];
+                map.load(A.itmS, run, u, j);
                 body(j);
             }
         };
@@ -1048,17 +1044,18 @@ __global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
         // a range that direct counters fit needs no sieve
         const bool sieve = make_range(first, nend, want, kTaskPad, cb).mul != 0;
         if (sieve) {
-            walk([&](const int32_t (&j)[4]) {
-                uint32_t old[4];
+            walk([&](const int32_t (&j)[kLoad]) {
+                uint32_t old[kLoad];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kLoad; ++u) {
                     const uint32_t h = (uint32_t)j[u] & (BITS - 1u);
-                    old[u] = atomicOr(j[u] >= 0 ? &tab[h >> 5] : S.spare + lane, 1u << (h & 31u));
+                    if (j[u] >= 0) old[u] = atomicOr(&tab[h >> 5], 1u << (h & 31u));
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t h = (uint32_t)j[u] & (BITS - 1u), bit = 1u << (h & 31u);
-                    if (j[u] >= 0 && (old[u] & bit)) atomicOr(&twice[h >> 5], bit);
+                for (int u = 0; u < kLoad; ++u) {
+                    const uint32_t h = (uint32_t)j[u] & (BITS - 1u);
+                    if (j[u] >= 0 && __builtin_amdgcn_ubfe(old[u], h, 1u))
+                        atomicOr(&twice[h >> 5], 1u << (h & 31u));
                 }
             });
             __syncthreads();
@@ -1082,23 +1079,32 @@ __global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
                 int32_t *const mine = list + wid * kSieveList;
                 int32_t n = 0;  // wedges collected
                 bool ok = true;
-                walk([&](const int32_t (&j)[4]) {
+                walk([&](const int32_t (&j)[kLoad]) {
+                    uint32_t w[kLoad];
+                    if (sieve) {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const uint32_t h = (uint32_t)j[u] & (BITS - 1u);
+                        for (int u = 0; u < kLoad; ++u)
+                            w[u] = twice[((uint32_t)j[u] & (BITS - 1u)) >> 5];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kLoad; ++u) {
                         bool in = j[u] >= R.lo && j[u] < R.hi;
-                        if (sieve) in = in && ((twice[h >> 5] >> (h & 31u)) & 1u);
+                        if (sieve) in = in && __builtin_amdgcn_ubfe(w[u], (uint32_t)j[u], 1u);
                         const uint64_t m = __ballot(in);
+                        if (m == 0) continue;
                         if (in) mine[n + (int32_t)lanes_below(m)] = j[u];
                         n += __popcll(m);
                         if (n >= 4 * kWave) {
+                            __builtin_amdgcn_wave_barrier();
                             ok &= tab_add4(tab, S.spare, R, mine[lane], mine[kWave + lane],
                                            mine[2 * kWave + lane], mine[3 * kWave + lane]);
                             n -= 4 * kWave;
                             if (lane < n) mine[lane] = mine[4 * kWave + lane];
+                            __builtin_amdgcn_wave_barrier();
                         }
                     }
                 });
+                __builtin_amdgcn_wave_barrier();
                 if (n > 0) {
                     int32_t j[4];
 #pragma unroll
@@ -1127,7 +1133,6 @@ __global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
             __syncthreads();
         }
         if (sieve) tab_clear<NT>(twice, LIM);
-        for (int i = tid; i < CHUNKS; i += NT) marks[i] = 0;
         if (A.mode != kModeFill) {
             if (tid == 0) A.task_cnt[t] = produced;
             my_wedges += total;

@@ -84,13 +84,14 @@ struct FlatTask {
 
 __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
     constexpr int NT = kFlatThreads, NW = NT / kWave;
-    constexpr int kKeep = kFlatKeep / NT;  // wedges a lane holds at a time
+    constexpr int kKeep = kFlatKeep / NT;  // wedges a lane holds (s = 1)
+    constexpr int kLoad = 8;               // chunks a wave loads at a time
     __shared__ __align__(16) uint32_t ctr[kFlatWords + kWave];  // + a spare word per lane
     __shared__ __align__(16) uint4 bmp[kFlatWords / 16];        // a bit per candidate
-    __shared__ int32_t adj[NT];               // list position less wedge number, per part
-    __shared__ uint64_t marks[kFlatChunks];   // first wedges of the parts
-    __shared__ int32_t wlen[NW], wpart[NW], wtot[NW];
-    __shared__ int32_t sh_task, sh_before, sh_hits, sh_ok;
+    __shared__ int32_t adj[NT];  // the wedge map's positions; hits while pairs are written
+    __shared__ __align__(8) uint32_t marks[2 * kFlatChunks];
+    __shared__ int32_t msh[3 * NW], wtot[NW];
+    __shared__ int32_t sh_task, sh_hits, sh_ok;
     __shared__ uint64_t sh_off, pool_cur[2];
     __shared__ int32_t log_cur[2];
     if (count_idle(A)) return;  // uniform: every thread reads the same words
@@ -102,19 +103,22 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
     uint4 *const c4 = reinterpret_cast<uint4 *>(ctr);
     for (int i = tid; i < kFlatWords / 4; i += NT) c4[i] = make_uint4(0u, 0u, 0u, 0u);
     for (int i = tid; i < kFlatWords / 16; i += NT) bmp[i] = make_uint4(0u, 0u, 0u, 0u);
-    for (int i = tid; i < kFlatChunks; i += NT) marks[i] = 0;
+    for (int i = tid; i < 2 * kFlatChunks; i += NT) marks[i] = 0;
     if (tid == 0) {
         pool_cur[0] = pool_cur[1] = 0;
         log_cur[0] = log_cur[1] = 0;
         sh_hits = 0;
-        sh_before = atomicAdd(A.queue + 1, 2);
+        sh_task = atomicAdd(A.queue + 1, 2);
     }
     int64_t passes = 0, my_wedges = 0, my_nnz = 0, my_pairs = 0;  // thread 0's are used
     __syncthreads();
-    int32_t r = sh_before, r1 = r + 1;  // this task and the next in the list
+    int32_t r = sh_task, r1 = r + 1;  // this task and the next in the list
     __syncthreads();
 
-    const WedgeMap<NT, kFlatChunks> map{adj, marks, wlen, wpart, &sh_before};
+    WedgeMap<NT, kFlatChunks> map;
+    map.adj_all = adj;
+    map.marks_all = marks;
+    map.sh = msh;
     auto load_task = [&](int32_t q) {
         FlatTask d{};
         if (q < n_flat) {
@@ -156,7 +160,8 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
     while (r < n_flat) {
         int32_t r2 = 0;
         if (tid == 0) r2 = atomicAdd(A.queue + 1, 1);
-        FlatMember mem = load_member(cur.k0 + tid, cur.k0 + cur.size);
+        map.narrow = uniform(cur.size) <= kWave;
+        FlatMember mem = load_member(cur.k0 + map.member(), cur.k0 + cur.size);
         FlatTask nxt = load_task(r1);
         const int32_t t = uniform(cur.t), a = uniform(cur.a), s = uniform(cur.s);
         const int32_t k0 = uniform(cur.k0), k1 = k0 + uniform(cur.size);
@@ -170,8 +175,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
         const bool skip = A.mode == kModeFill && A.need && !A.need[t];
         // bits per counter as a shift, counters per word as a shift
         const uint32_t lb = F.lbits, psh = 5u - lb;
-        const uint32_t pm = (1u << psh) - 1u, cm = (1u << (1u << lb)) - 1u;
-        const bool keep = flat_keeps(s, cost, k1 - k0);
+                const bool keep = flat_keeps(s, cost, k1 - k0);
         if (part == 0 && A.mode != kModeFill) {
             my_wedges += cost;
             my_nnz += k1 - k0;
@@ -179,21 +183,28 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
         load_list(mem, F.ranges > 1 && !keep);
         int32_t produced = 0;
         int32_t hits = 0;  // pairs found by this wave
+        const uint32_t s_1 = (uint32_t)s - 1u;
 
-        // Count four wedges, x = candidate - first of the range (>= span: none).
-        auto count4 = [&](const uint32_t (&x)[4], uint32_t span) {
-            uint32_t old[4];
+        // Count wedges, x = candidate - first of the range (>= span: none).
+        auto count = [&](const int32_t (&j)[kLoad], int32_t lo, uint32_t span) {
+            uint32_t x[kLoad], old[kLoad];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                old[u] = atomicAdd(&ctr[x[u] < span ? x[u] >> psh : (uint32_t)(kFlatWords + lane)],
-                                   1u << ((x[u] & pm) << lb));
+            for (int u = 0; u < kLoad; ++u) {
+                x[u] = (uint32_t)(j[u] - lo);
+                if (x[u] < span)
+                    old[u] = atomicAdd(&ctr[x[u] >> psh], 1u << ((x[u] << lb) & 31u));
+            }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t was = (old[u] >> ((x[u] & pm) << lb)) & cm;
-                const bool hit = x[u] < span && was + 1u == (uint32_t)s;
-                if (hit)
-                    atomicOr(reinterpret_cast<uint32_t *>(bmp) + (x[u] >> 5), 1u << (x[u] & 31u));
-                hits += __popcll(__ballot(hit));
+            for (int u = 0; u < kLoad; ++u) {
+                const bool hit =
+                    x[u] < span && __builtin_amdgcn_ubfe(old[u], x[u] << lb, 1u << lb) == s_1;
+                const uint64_t m = __ballot(hit);
+                if (m) {
+                    if (hit)
+                        atomicOr(reinterpret_cast<uint32_t *>(bmp) + (x[u] >> 5),
+                                 1u << (x[u] & 31u));
+                    hits += __popcll(m);
+                }
             }
         };
         // Thread 0: room for `total` pairs of the task.
@@ -270,20 +281,39 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
 #pragma unroll
             for (int i = 0; i < IT; ++i) {
                 const int32_t incl = wave_incl(np[i]);
-                int64_t o = d.at + incl - np[i];
-                d.at += lane63(incl);
+                const int32_t all = lane63(incl);
+                int32_t o = incl - np[i];
                 const uint32_t x0 = (uint32_t)(q0 + i * kWave + lane) << 7;
                 uint32_t word = w[i].x, rest = 0;
-                for (int32_t n = np[i]; n > 0; --n) {
+                auto next = [&]() {  // the lane's next pair
                     while (word == 0u) {
                         ++rest;
                         word = rest == 1u ? w[i].y : rest == 2u ? w[i].z : w[i].w;
                     }
                     const uint32_t x = x0 + rest * 32u + (uint32_t)__builtin_ctz(word);
                     word &= word - 1u;
-                    put(d, o, lo + (int32_t)x, (int32_t)((ctr[x >> psh] >> ((x & pm) << lb)) & cm));
-                    ++o;
+                    return x;
+                };
+                auto value = [&](uint32_t x) {
+                    return (int32_t)__builtin_amdgcn_ubfe(ctr[x >> psh], x << lb, 1u << lb);
+                };
+                if (all <= kWave) {
+                    // few: line them up, a pair per lane
+                    int32_t *const line = adj + wid * kWave;
+                    for (int32_t n = np[i]; n > 0; --n) line[o++] = (int32_t)next();
+                    __builtin_amdgcn_wave_barrier();
+                    if (lane < all) {
+                        const uint32_t x = (uint32_t)line[lane];
+                        put(d, d.at + lane, lo + (int32_t)x, value(x));
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                } else {
+                    for (int32_t n = np[i]; n > 0; --n) {
+                        const uint32_t x = next();
+                        put(d, d.at + o++, lo + (int32_t)x, value(x));
+                    }
                 }
+                d.at += all;
             }
         };
 
@@ -298,19 +328,18 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
             uint16_t *const pre = reinterpret_cast<uint16_t *>(bmp);  // bits before each 64
             uint16_t *const cnt = pre + kFlatWords / 4;
             const uint64_t *const set64 = reinterpret_cast<const uint64_t *>(set);
-            const int32_t len = max(mem.en - mem.st, 0);
-            int32_t off, rank, total;
-            map.number(mem.st, len, off, rank, total);
-            map.mark(0, off, len, rank);
-            __syncthreads();
-            const int32_t nch = (total + kWave - 1) / kWave, cpw = (nch + NW - 1) / NW;
-            const int32_t c0 = min(nch, wid * cpw), n = min(nch, c0 + cpw) - c0;
+            map.number(mem.st, max(mem.en - mem.st, 0));
+            const auto run = map.window(0);
+            const int32_t n = run.nc;
             int32_t j[kKeep];
-            int32_t before = n > 0 ? map.parts_before(c0) : 0;
 #pragma unroll
-            for (int u = 0; u < kKeep; ++u) {
-                j[u] = -1;
-                if (u < n) j[u] = map.wedge(A.itmS, 0, c0 + u, (c0 + u) * kWave + lane < total, before);
+            for (int u = 0; u < kKeep; u += kLoad) {
+                int32_t part[kLoad];
+#pragma unroll
+                for (int v = 0; v < kLoad; ++v) part[v] = -1;
+                if (u < n) map.load(A.itmS, run, u, part);
+#pragma unroll
+                for (int v = 0; v < kLoad; ++v) j[u + v] = part[v];
             }
             const int32_t np = keep_ranges(first, nend);
             for (int32_t p = 0; p < np; ++p) {
@@ -332,8 +361,6 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
                 if (lane == 0 && hits) atomicAdd(&sh_hits, hits);
                 hits = 0;
                 __syncthreads();
-                if (p == 0)
-                    for (int i = tid; i < kFlatChunks; i += NT) marks[i] = 0;
                 const int32_t ranks = sh_hits;
                 if (ranks > 0) {
                     // bits before each 64 candidates: eight of those per thread
@@ -435,40 +462,28 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
                         b = max(b, ahead);
                         ahead = e = A.bnd[mem.row + blk1];
                     }
-                    const int32_t len = max(e - b, 0);
-                    int32_t off, rank, total;
-                    map.number(b, len, off, rank, total);
-                    if (total == 0) __syncthreads();  // wlen is written again
-                    for (int32_t w0 = 0; w0 < total; w0 += kFlatChunks * kWave) {
-                        if (w0 > 0) __syncthreads();  // the marks are clear
-                        map.mark(w0, off, len, rank);
-                        __syncthreads();
-                        // a run of chunks for each wave
-                        const int32_t n = min(total - w0, kFlatChunks * kWave);
-                        const int32_t nch = (n + kWave - 1) / kWave, cpw = (nch + NW - 1) / NW;
-                        const int32_t c0 = min(nch, wid * cpw), mine = min(nch, c0 + cpw) - c0;
-                        int32_t j[kKeep];
-                        int32_t before = mine > 0 ? map.parts_before(c0) : 0;
-#pragma unroll
-                        for (int u = 0; u < kKeep; ++u) {
-                            j[u] = -1;
-                            if (u < mine)
-                                j[u] = map.wedge(A.itmS, w0, c0 + u, (c0 + u) * kWave + lane < n, before);
+                    map.number(b, max(e - b, 0));
+                    for (int32_t w0 = 0; w0 < map.total; w0 += kFlatChunks * kWave) {
+                        const auto run = map.window(w0);
+                        if (run.nc > 0) {
+                            int32_t ja[kLoad], jb[kLoad];
+                            map.load(A.itmS, run, 0, ja);
+                            // the next chunks are loaded while these are counted
+                            for (int32_t u = 0; u < run.nc; u += 2 * kLoad) {
+                                if (u + kLoad < run.nc) map.load(A.itmS, run, u + kLoad, jb);
+                                count(ja, lo, span);
+                                if (u + kLoad >= run.nc) break;
+                                if (u + 2 * kLoad < run.nc) map.load(A.itmS, run, u + 2 * kLoad, ja);
+                                count(jb, lo, span);
+                            }
                         }
-#pragma unroll
-                        for (int u0 = 0; u0 < kKeep; u0 += 4) {
-                            if (u0 >= mine) break;
-                            uint32_t x[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) x[u] = (uint32_t)(j[u0 + u] - lo);
-                            count4(x, span);
-                        }
-                        if (lane == 0 && hits) atomicAdd(&sh_hits, hits);
-                        hits = 0;
-                        __syncthreads();
-                        for (int i = tid; i < kFlatChunks; i += NT) marks[i] = 0;
+                        if (!map.narrow) __syncthreads();  // the map is used again
                     }
+                    if (!map.narrow && map.total == 0) __syncthreads();
                 }
+                if (lane == 0 && hits) atomicAdd(&sh_hits, hits);
+                hits = 0;
+                __syncthreads();
                 const int32_t nq = (int32_t)((span + 127u) >> 7), qpw = (nq + NW - 1) / NW;
                 const int32_t q0 = min(nq, wid * qpw), q1 = min(nq, q0 + qpw);
                 const int32_t found = sh_hits;  // written before the last barrier
@@ -479,6 +494,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
                 // a quad's counters are 1 << lb times four words
                 for (int32_t i = (q0 << lb) + lane; i < (q1 << lb); i += kWave)
                     c4[i] = make_uint4(0u, 0u, 0u, 0u);
+                __syncthreads();
             }
         }
         if (!skip && A.mode != kModeFill && tid == 0) {

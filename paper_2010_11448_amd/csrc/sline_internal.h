@@ -120,6 +120,10 @@ constexpr int32_t kKeepRanks = kFlatWords / 4;  // pairs of a range counted at a
 constexpr int32_t kSieveSmall = 64, kSieveLarge = 256;
 constexpr int32_t kSieveWedges = 32;
 
+// The list positions of all these kernels fit a 32-bit byte offset: builds with
+// this many incidences or more use the hashed kernels alone.
+constexpr int64_t kDirectMaxNnz = (int64_t)1 << 30;
+
 // Blocks that hold `cands` candidates.
 __device__ __forceinline__ int32_t flat_blocks(int32_t cands) {
     return (int32_t)(((int64_t)cands + kFlatBlock - 1) / kFlatBlock);
