@@ -351,7 +351,6 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
     L.rsK1 = A.take<int32_t>(nnz);
     L.rsV0 = A.take<int32_t>(nnz);
     L.rsV1 = A.take<int32_t>(nnz);
-    L.rsHist = A.take<int32_t>(transpose_hist(nnz));
     const int64_t pmax = scan_partials(std::max<int64_t>({n, N, M, m, nnz}) + 1);
     L.part32 = A.take<int32_t>(pmax);
     L.part64 = A.take<int64_t>(pmax);
@@ -372,7 +371,8 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
     L.cost = A.take<int64_t>(N);
     L.ntask = A.take<int32_t>(N);
     L.tbase = A.take<int64_t>(N + 1);
-    L.start = A.take<int32_t>(nnz);
+    L.start = A.take<int32_t>(std::max(nnz, transpose_hist(nnz)));
+    L.rsHist = L.start;  // written once the lists are transposed
     return L;
 }
 

@@ -251,7 +251,6 @@ hipError_t launch_start_from_map(hipStream_t st, int64_t nnz, const int32_t *map
 // (member, incidence) pairs; rsK / rsV are two pairs of nnz-entry buffers,
 // hist holds transpose_hist(nnz) counts and part32 the partials of their
 // scan.
-int64_t transpose_tiles(int64_t nnz);
 int64_t transpose_hist(int64_t nnz);
 // Radix passes of a transpose over members in [0, n); its sorted members end
 // in rsK[(passes - 1) & 1].

@@ -235,6 +235,45 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const TI *in, int64_
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = partial[blockIdx.x] + tot;
 }
 
+// Short scans: one workgroup, one launch instead of three (which cost about
+// 2.5 us each, more than a pass over 16K entries takes here).
+constexpr int kScanOneThreads = 1024;
+constexpr int64_t kScanOneMax = 16384;
+
+template <typename TI, typename TO>
+__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const TI *in, int64_t n, TO *out) {
+    constexpr int NW = kScanOneThreads / kWave;
+    __shared__ TO sh[NW];
+    const int lane = lane_id(), wid = threadIdx.x / kWave;
+    TO carry = 0;
+    for (int64_t c = 0; c < n; c += kScanOneThreads * kScanItems) {
+        const int64_t base = c + (int64_t)threadIdx.x * kScanItems;
+        TO v[kScanItems];
+        TO s = 0;
+#pragma unroll
+        for (int q = 0; q < kScanItems; ++q) {
+            v[q] = base + q < n ? (TO)in[base + q] : (TO)0;
+            s += v[q];
+        }
+        const TO incl = wave_incl_scan(s);
+        if (lane == kWave - 1) sh[wid] = incl;
+        __syncthreads();
+        TO run = carry + incl - s;
+        for (int w = 0; w < NW; ++w) {
+            const TO x = sh[w];
+            if (w < wid) run += x;
+            carry += x;
+        }
+#pragma unroll
+        for (int q = 0; q < kScanItems; ++q) {
+            if (base + q < n) out[base + q] = run;
+            run += v[q];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[n] = carry;
+}
+
 template <typename TO>
 __global__ void k_zero_total(TO *out) { out[0] = 0; }
 
@@ -257,41 +296,46 @@ __global__ void k_start_from_map(int64_t nnz, const int32_t *map, int32_t *start
 
 // ------------------------------------------------ transpose by radix sort
 // The transpose is a stable sort of the incidences (v = col[k], k) by member
-// v: least significant digit first, kRsBits bits per pass.  A pass counts
-// the digits of each tile of kRsTile keys (k_rs_hist), scans the counts
-// bin by bin across tiles, and moves every key to its bin's place
-// (k_rs_scatter).  Inside a tile, thread t holds kRsItems consecutive keys
-// and counts them per bin in its own LDS counters; a block scan of the
-// counters in (bin, thread) order gives every key its place, so equal
-// digits keep their order within the tile, and the bin-major offsets keep
-// the order of the tiles.
-constexpr int kRsBits = 4;
+// v: least significant digit first, digits of up to kRsBits bits, all of about
+// the same width.  A pass counts the digits of each tile of keys (k_rs_hist),
+// scans the counts bin by bin across tiles, and moves every key to its bin's
+// place (k_rs_scatter).  Inside a tile a wave takes 64 consecutive keys at a
+// time: ballots of the digit's bits give every lane the lanes with its digit,
+// so its place among them, and one of them advances the wave's own counter of
+// the digit; equal digits keep their order in the wave, and the scan over
+// (digit, wave) keeps it in the tile.
+//
+// What bounds it: memory, 20 B per key and pass, the last pass's scattered maps
+// and the ballots; so few passes of wide digits.  10^7 keys of 21 bits, counts,
+// scans and moves: 3 passes of 7 bits 0.43 ms, 6 of 4 bits (counters per
+// thread) 0.68 ms.  22,000 keys of 13 bits: 2 passes 25 us, 4 passes 100 us.
+constexpr int kRsBits = 8;
 constexpr int kRsBins = 1 << kRsBits;
 constexpr int kRsThreads = 256;
-constexpr int kRsItems = 8;
-constexpr int kRsTile = kRsThreads * kRsItems;
+constexpr int kRsWaves = kRsThreads / kWave;
+// Keys per thread: with fewer keys than kRsFewKeys, smaller tiles fill more CUs.
+constexpr int kRsItems = 16, kRsItemsFew = 4;
+constexpr int64_t kRsFewKeys = 1 << 19;
 
 // Digit counts of each tile, bin-major: hist[bin * ntiles + tile].
+template <int ITEMS>
 __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const int32_t *keys, int64_t n, int shift,
-                                                        int32_t *hist, int32_t ntiles) {
-    __shared__ int32_t h[kRsBins];
-    if (threadIdx.x < kRsBins) h[threadIdx.x] = 0;
+                                                        int bits, int32_t *hist, int32_t ntiles) {
+    __shared__ int32_t h[kRsWaves][kRsBins];
+    const int t = threadIdx.x, w = t / kWave;
+    for (int i = 0; i < kRsWaves; ++i) h[i][t] = 0;
     __syncthreads();
-    const int lane = lane_id();
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    int32_t mine = 0;  // lane b < kRsBins: this wave's count of digit b
-    for (int i = threadIdx.x & ~(kWave - 1); i < kRsTile; i += kRsThreads) {
-        const int64_t p = base + i + lane;
-        const int32_t d = p < n ? (int32_t)(((uint32_t)keys[p] >> shift) & (kRsBins - 1)) : -1;
+    const int64_t base = (int64_t)blockIdx.x * kRsThreads * ITEMS;
+    const uint32_t mask = (1u << bits) - 1u;
 #pragma unroll
-        for (int b = 0; b < kRsBins; ++b) {
-            const int32_t cb = (int32_t)__popcll(__ballot(d == b));
-            if (lane == b) mine += cb;
-        }
+    for (int i = 0; i < ITEMS; ++i) {
+        const int64_t p = base + i * kRsThreads + t;
+        if (p < n) atomicAdd(&h[w][((uint32_t)keys[p] >> shift) & mask], 1);
     }
-    if (lane < kRsBins && mine) atomicAdd(&h[lane], mine);
     __syncthreads();
-    if (threadIdx.x < kRsBins) hist[threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
+    int32_t c = 0;
+    for (int i = 0; i < kRsWaves; ++i) c += h[i][t];
+    if (t <= (int)mask) hist[(int64_t)t * ntiles + blockIdx.x] = c;
 }
 
 // Move the keys of each tile to their place: off[bin * ntiles + tile] is the
@@ -299,66 +343,81 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const int32_t *keys, int
 // of key p is p.  The last pass writes, instead of the values, the final
 // maps: kT[q] = value (the incidence), colT[q] = rowid[value] (its item),
 // posT[value] = q (kT, posT may be null).
+template <int ITEMS>
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
-    const int32_t *kin, const int32_t *vin, int64_t n, int shift, const int32_t *off,
+    const int32_t *kin, const int32_t *vin, int64_t n, int shift, int bits, const int32_t *off,
     int32_t ntiles, int32_t *kout, int32_t *vout, int32_t last, const int32_t *rowid,
     int32_t *colT, int32_t *kT, int32_t *posT) {
-    __shared__ int32_t cnt[kRsBins * kRsThreads];  // [bin][thread]
-    __shared__ int32_t sk[kRsTile], sv[kRsTile];   // the tile in sorted order
-    __shared__ int32_t sh[kRsThreads / kWave + 1];
-    __shared__ int32_t bin_start[kRsBins];
-    const int t = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * kRsTile + (int64_t)t * kRsItems;
-    int32_t key[kRsItems], val[kRsItems], dig[kRsItems];
+    constexpr int TILE = kRsThreads * ITEMS;
+    __shared__ int32_t cnt[kRsWaves][kRsBins];  // keys of a digit so far; then their place
+    __shared__ int32_t sk[TILE], sv[TILE];      // the tile in sorted order
+    __shared__ int32_t sh[kScanThreads / kWave + 1];
+    __shared__ int32_t dst[kRsBins];            // output slot less tile position, per digit
+    const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
+    const uint32_t mask = (1u << bits) - 1u;
+    for (int i = 0; i < kRsWaves; ++i) cnt[i][t] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * TILE;
+    const int64_t mine = base + (int64_t)w * ITEMS * kWave + lane;
+    int32_t key[ITEMS], val[ITEMS], rank[ITEMS];
 #pragma unroll
-    for (int b = 0; b < kRsBins; ++b) cnt[b * kRsThreads + t] = 0;
-#pragma unroll
-    for (int i = 0; i < kRsItems; ++i) {
-        const int64_t p = base + i;
-        dig[i] = -1;
+    for (int i = 0; i < ITEMS; ++i) {
+        const int64_t p = mine + i * kWave;
+        key[i] = 0;
+        val[i] = (int32_t)p;
         if (p < n) {
             key[i] = kin[p];
-            val[i] = vin ? vin[p] : (int32_t)p;
-            dig[i] = (int32_t)(((uint32_t)key[i] >> shift) & (kRsBins - 1));
-            cnt[dig[i] * kRsThreads + t] += 1;
+            if (vin) val[i] = vin[p];
         }
     }
-    __syncthreads();
-    // exclusive scan of the counters in (bin, thread) order: thread t takes
-    // entries [t * kRsBins, (t + 1) * kRsBins) of the flattened array
-    int32_t loc[kRsBins];
-    int32_t sum = 0;
 #pragma unroll
-    for (int j = 0; j < kRsBins; ++j) {
-        loc[j] = cnt[t * kRsBins + j];
-        sum += loc[j];
+    for (int i = 0; i < ITEMS; ++i) {
+        const bool ok = mine + i * kWave < n;
+        const uint32_t d = ((uint32_t)key[i] >> shift) & mask;
+        uint64_t same = __ballot(ok);
+        for (int b = 0; b < bits; ++b) {
+            const bool set = (d >> b) & 1u;
+            const uint64_t m = __ballot(set);
+            same &= set ? m : ~m;
+        }
+        const int32_t below = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+        const int32_t before = ok ? cnt[w][d] : 0;
+        rank[i] = before + below;
+        __builtin_amdgcn_wave_barrier();  // every lane has read its counter
+        if (ok && below == 0) cnt[w][d] = before + __popcll(same);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    int32_t c[kRsWaves], sum = 0;  // thread t: digit t
+#pragma unroll
+    for (int i = 0; i < kRsWaves; ++i) {
+        c[i] = cnt[i][t];
+        sum += c[i];
     }
     int32_t total;
     int32_t run = block_excl_scan<int32_t>(sum, sh, total);
+    dst[t] = (t <= (int)mask ? off[(int64_t)t * ntiles + blockIdx.x] : 0) - run;
 #pragma unroll
-    for (int j = 0; j < kRsBins; ++j) {
-        cnt[t * kRsBins + j] = run;
-        run += loc[j];
+    for (int i = 0; i < kRsWaves; ++i) {
+        cnt[i][t] = run;
+        run += c[i];
     }
     __syncthreads();
-    if (t < kRsBins) bin_start[t] = cnt[t * kRsThreads];
-    __syncthreads();
-    // place the keys in tile order, then write each bin's run with
-    // consecutive lanes
 #pragma unroll
-    for (int i = 0; i < kRsItems; ++i) {
-        if (dig[i] < 0) continue;
-        const int32_t r = cnt[dig[i] * kRsThreads + t]++;
+    for (int i = 0; i < ITEMS; ++i) {
+        if (mine + i * kWave >= n) continue;
+        const int32_t r = cnt[w][((uint32_t)key[i] >> shift) & mask] + rank[i];
         sk[r] = key[i];
         sv[r] = val[i];
     }
     __syncthreads();
-    const int64_t tile0 = (int64_t)blockIdx.x * kRsTile;
-    const int32_t tn = (int32_t)(n - tile0 < kRsTile ? n - tile0 : kRsTile);
+    // each bin's run with consecutive lanes
+    const int32_t tn = (int32_t)(n - base < TILE ? n - base : TILE);
+#pragma unroll 4
     for (int32_t j = t; j < tn; j += kRsThreads) {
         const int32_t k = sk[j], v = sv[j];
-        const int32_t b = (int32_t)(((uint32_t)k >> shift) & (kRsBins - 1));
-        const int32_t q = off[b * ntiles + blockIdx.x] + (j - bin_start[b]);
+        const int32_t q = dst[((uint32_t)k >> shift) & mask] + j;
         kout[q] = k;
         if (!last) {
             vout[q] = v;
@@ -669,6 +728,10 @@ static hipError_t scan_impl(hipStream_t st, const TI *in, int64_t n, TO *out, TO
         k_zero_total<TO><<<1, 1, 0, st>>>(out);
         return hipGetLastError();
     }
+    if (n <= kScanOneMax) {
+        k_scan_one<TI, TO><<<1, kScanOneThreads, 0, st>>>(in, n, out);
+        return hipGetLastError();
+    }
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
     k_scan_reduce<TI, TO><<<(unsigned)nb, kScanThreads, 0, st>>>(in, n, partial);
     k_scan_partials<TO><<<1, kScanThreads, 0, st>>>(partial, nb);
@@ -700,15 +763,20 @@ hipError_t launch_start_from_map(hipStream_t st, int64_t nnz, const int32_t *map
 
 
 
-int64_t transpose_tiles(int64_t nnz) { return (nnz + kRsTile - 1) / kRsTile; }
+static int64_t rs_tiles(int64_t nnz) {
+    const int64_t tile = (int64_t)kRsThreads * (nnz < kRsFewKeys ? kRsItemsFew : kRsItems);
+    return (nnz + tile - 1) / tile;
+}
 
-int64_t transpose_hist(int64_t nnz) { return (int64_t)kRsBins * transpose_tiles(nnz) + 1; }
+int64_t transpose_hist(int64_t nnz) { return (int64_t)kRsBins * rs_tiles(nnz) + 1; }
 
-int transpose_passes(int32_t n) {
+static int key_bits(int32_t n) {
     int bits = 0;
     while (bits < 31 && ((int64_t)1 << bits) < (int64_t)n) ++bits;
-    return std::max(1, (bits + kRsBits - 1) / kRsBits);
+    return std::max(1, bits);
 }
+
+int transpose_passes(int32_t n) { return (key_bits(n) + kRsBits - 1) / kRsBits; }
 
 hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int32_t n,
                             const int32_t *rowid, int32_t *const rsK[2], int32_t *const rsV[2],
@@ -716,21 +784,24 @@ hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int
                             int32_t *kT, int32_t *posT) {
     if (nnz <= 0) return launch_fill_i32(st, ptrT, (int64_t)n + 1, 0);
     const int passes = transpose_passes(n);
-    const int32_t ntiles = (int32_t)transpose_tiles(nnz);
+    const int32_t ntiles = (int32_t)rs_tiles(nnz);
+    const bool few = nnz < kRsFewKeys;
+    const int total = key_bits(n), width = (total + passes - 1) / passes;
     hipError_t e = hipSuccess;
     for (int p = 0; p < passes && e == hipSuccess; ++p) {
         const int32_t *kin = p == 0 ? col : rsK[(p - 1) & 1];
         const int32_t *vin = p == 0 ? nullptr : rsV[(p - 1) & 1];
         const int last = p == passes - 1;
-        k_rs_hist<<<ntiles, kRsThreads, 0, st>>>(kin, nnz, p * kRsBits, hist, ntiles);
+        const int shift = p * width, bits = std::min(width, total - shift);
+        if (few) k_rs_hist<kRsItemsFew><<<ntiles, kRsThreads, 0, st>>>(kin, nnz, shift, bits, hist, ntiles);
+        else k_rs_hist<kRsItems><<<ntiles, kRsThreads, 0, st>>>(kin, nnz, shift, bits, hist, ntiles);
         e = hipGetLastError();
-        if (e == hipSuccess) e = launch_scan_i32(st, hist, (int64_t)kRsBins * ntiles, hist, part32);
-        if (e == hipSuccess) {
-            k_rs_scatter<<<ntiles, kRsThreads, 0, st>>>(kin, vin, nnz, p * kRsBits, hist, ntiles,
-                                                       rsK[p & 1], rsV[p & 1], last, rowid, colT,
-                                                       kT, posT);
-            e = hipGetLastError();
-        }
+        if (e == hipSuccess) e = launch_scan_i32(st, hist, (int64_t)ntiles << bits, hist, part32);
+        if (e != hipSuccess) break;
+        auto *const scatter = few ? k_rs_scatter<kRsItemsFew> : k_rs_scatter<kRsItems>;
+        scatter<<<ntiles, kRsThreads, 0, st>>>(kin, vin, nnz, shift, bits, hist, ntiles, rsK[p & 1],
+                                               rsV[p & 1], last, rowid, colT, kT, posT);
+        e = hipGetLastError();
     }
     if (e != hipSuccess) return e;
     k_rs_bounds<<<grid_for(nnz + 1, 256, 65536), 256, 0, st>>>(rsK[(passes - 1) & 1], nnz, n,
