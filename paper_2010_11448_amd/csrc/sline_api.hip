@@ -135,7 +135,7 @@ struct sline_ctx {
         size_t size = 0;
         size_t used = 0;
     } fixed;
-    bool pool_fixed = false;  // c->pool lies in the fixed region: never freed
+    bool pool_fixed = false;  // c->pool lies in the fixed region or in ws2: not freed
 };
 
 namespace {
@@ -237,7 +237,7 @@ void sync(sline_ctx *c, const char *where) { hip_check(c, hipStreamSynchronize(c
 
 void release_pool(sline_ctx *c) {
     if (c->pool_fixed) {
-        // a pool inside the fixed region is not the allocator's to free
+        // a pool inside the fixed region or the workspace is not to be freed
         c->pool = nullptr;
         c->pool_bytes = 0;
         c->pool_fixed = false;
@@ -253,9 +253,19 @@ void release_pool(sline_ctx *c) {
 // Staging pool for `want` pairs (`pair_bytes` each: 8 with weights, 4
 // without), halving on failure; returns the pairs it holds (0: none, count
 // the pairs in a separate pass instead).
-int64_t acquire_pool(sline_ctx *c, int64_t want, int64_t pair_bytes) {
+// A pool of at most kKeptPool bytes lies behind the task arrays at `kept`, in
+// memory the context keeps (an allocation and a release per build otherwise).
+constexpr int64_t kKeptPool = 32 << 20;
+
+int64_t acquire_pool(sline_ctx *c, int64_t want, int64_t pair_bytes, void *kept) {
     release_pool(c);
     int64_t cap = std::min<int64_t>(want, c->tune.stage_max_bytes / pair_bytes);
+    if (kept && cap > 0) {
+        c->pool = kept;
+        c->pool_bytes = (size_t)(cap * pair_bytes);
+        c->pool_fixed = true;
+        return cap;
+    }
     if (c->fixed.base) {
         // whatever the fixed region has left after the task arrays (tasks
         // that find no room are counted again in the fill pass)
@@ -306,6 +316,7 @@ double span_ms(sline_ctx *c, int i, int j) {
 
 struct Layout {
     int32_t *err, *queue, *tcounts;
+    int64_t n_flags;  // words from err to the end of passes, zeroed together
     int64_t *totals, *passes;
     int32_t *rowid, *ptrT, *colT;
     int32_t *rsK0, *rsK1, *rsV0, *rsV1, *rsHist;  // transpose (radix sort) buffers
@@ -325,6 +336,10 @@ struct Layout {
 // the items outnumber the lanes of the resident one-wave workgroups several
 // times over (a lane walks its item's lists one entry after another).
 constexpr int64_t kTinyMinItems = 1 << 15;
+// Staging pools below kPoolSlackMax pairs get room to spare (see build_core).
+constexpr int64_t kPoolSlackMax = 1 << 27;
+constexpr int64_t kPoolChunkMin = 256;   // pairs a workgroup reserves at least
+constexpr int64_t kPoolSlackTasks = 16384;
 Tuning build_tuning(const Tuning &t, int64_t n_items, int64_t nnz) {
     Tuning u = t;
     if (nnz >= kDirectMaxNnz) u.dense_min_wedges = 0;
@@ -342,6 +357,7 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
     L.tcounts = A.take<int32_t>(kKinds);
     L.totals = A.take<int64_t>(3 + 1 + kKinds);  // cost totals, then the planner's sums
     L.passes = A.take<int64_t>(4);
+    L.n_flags = reinterpret_cast<int32_t *>(L.passes + 4) - L.err;
     L.rowid = A.take<int32_t>(nnz);
     L.ptrT = A.take<int32_t>(n + 1);
     L.colT = A.take<int32_t>(nnz);
@@ -383,6 +399,7 @@ struct TaskLayout {
     unsigned long long *pool_head;
     StageRec *log;
     int32_t log_cap;
+    int64_t n_zero;  // words from pool_head to the end of need, zeroed together
 };
 
 PlanItems plan_items(const Tuning &tu, const int32_t *ptrI, const int32_t *crank,
@@ -411,6 +428,7 @@ TaskLayout plan_tasks(Arena &A, int64_t T, int64_t more) {
     L.ctrs = A.take<int32_t>(4);  // [0] log head, [1] tasks flagged
     L.log = A.take<StageRec>(L.log_cap);
     L.need = A.take<int32_t>(T);
+    L.n_zero = L.need + T - reinterpret_cast<int32_t *>(L.pool_head);
     L.item = A.take<int32_t>(T);
     L.part = A.take<int32_t>(T);
     L.small = A.take<int32_t>(T);
@@ -446,11 +464,14 @@ void ensure_ws2(sline_ctx *c, size_t bytes) {
     c->ws2_bytes = want;
 }
 
-void transpose(sline_ctx *c, const Layout &L, const int32_t *col, int32_t n, int64_t nnz) {
+// kT and posT: the position maps wanted, or null (each is a scattered write of
+// every incidence).
+void transpose(sline_ctx *c, const Layout &L, const int32_t *col, int32_t n, int64_t nnz,
+               int32_t *kT, int32_t *posT) {
     int32_t *const rk[2] = {L.rsK0, L.rsK1};
     int32_t *const rv[2] = {L.rsV0, L.rsV1};
     hip_check(c, launch_transpose(c->stream, col, nnz, n, L.rowid, rk, rv, L.rsHist, L.part32,
-                                  L.ptrT, L.colT, L.kT, L.posT),
+                                  L.ptrT, L.colT, kT, posT),
               "transpose");
 }
 
@@ -742,6 +763,13 @@ sline_status noalloc_impl(sline_ctx *c, const sline_csr &H, int32_t s, int32_t d
     return r;
 }
 
+// The member checks as read back at `flags`.
+bool bad_members(sline_ctx *c, const int64_t *flags) {
+    if (!(reinterpret_cast<const int32_t *>(flags)[0] & (kErrColRange | kErrColOrder))) return false;
+    set_err(c, "col_idx: members must lie in [0, n_vertices) and increase strictly within a row");
+    return true;
+}
+
 sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dual, uint32_t flags,
                         sline_edges *out, const ItemS &IS) {
     c->profile = (flags & SLINE_PROFILE) != 0;
@@ -756,21 +784,12 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     int64_t nnz = 0;
     // 1. row_ptr check and nnz
     {
-        ensure_ws(c, 4096);
-        int32_t *err = reinterpret_cast<int32_t *>(c->ws);
-        hip_check(c, launch_fill_i32(st, err, 4, 0), "zero flags");
+        int32_t *hp = reinterpret_cast<int32_t *>(c->host);
+        hp[0] = hp[1] = 0;
         if (m > 0) {
-            hip_check(c, launch_check_rowptr(st, H.row_ptr, (int32_t)m, err), "row_ptr check");
-            hip_check(c, hipMemcpyAsync(c->host, H.row_ptr + m, sizeof(int32_t), hipMemcpyDeviceToHost, st),
-                      "read nnz");
-        } else {
-            reinterpret_cast<int32_t *>(c->host)[0] = 0;
+            hip_check(c, launch_check_rowptr(st, H.row_ptr, (int32_t)m, hp), "row_ptr check");
+            sync(c, "row_ptr check");
         }
-        hip_check(c, hipMemcpyAsync(reinterpret_cast<int32_t *>(c->host) + 1, err, sizeof(int32_t),
-                                    hipMemcpyDeviceToHost, st),
-                  "read flags");
-        sync(c, "row_ptr check");
-        const int32_t *hp = reinterpret_cast<const int32_t *>(c->host);
         nnz = hp[0];
         if (hp[1] != 0 || nnz < 0) {
             set_err(c, "row_ptr must start at 0 and never decrease");
@@ -807,31 +826,26 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     A.base = reinterpret_cast<char *>(c->ws);
     const Layout L = plan_layout(A, m, n, nnz, N, M, filt, ranks, fixed);
 
-    hip_check(c, launch_fill_i32(st, L.err, 4, 0), "zero flags");
-    hip_check(c, launch_fill_i32(st, L.tcounts, kKinds, 0), "zero task counts");
-    hip_check(c, launch_fill_i64(st, L.totals, 3 + 1 + kKinds, 0), "zero totals");
-    hip_check(c, launch_fill_i64(st, L.passes, 4, 0), "zero passes");
+    hip_check(c, launch_fill_i32(st, L.err, L.n_flags, 0), "zero flags and totals");
 
     mark(c, 0);
     // 2. row ids and member checks (range checks always: they guard every later index)
     hip_check(c, launch_rows(st, H.row_ptr, H.col_idx, (int32_t)m, (int32_t)n, nnz,
                              (flags & SLINE_SKIP_VALIDATE) ? 0 : 1, L.rowid, L.err),
               "row check");
-    // 3. transpose (bad members are skipped by every kernel and reported below)
-    transpose(c, L, H.col_idx, (int32_t)n, nnz);
-    hip_check(c, hipMemcpyAsync(c->host, L.err, sizeof(int32_t), hipMemcpyDeviceToHost, st), "read flags");
-    sync(c, "member check");
-    if (reinterpret_cast<const int32_t *>(c->host)[0] & (kErrColRange | kErrColOrder)) {
-        set_err(c, "col_idx: members must lie in [0, n_vertices) and increase strictly within a row");
-        return SLINE_EINVAL;
-    }
+    // 3. transpose (until the flags are read back below, no kernel indexes by a
+    // member that may be bad)
+    // back-pointer maps: the filter wants the item incidence of a member-list
+    // position (inv), a build without a filter the position of an incidence (map)
+    const bool want_kT = filt != (dual != 0);
+    transpose(c, L, H.col_idx, (int32_t)n, nnz, want_kT ? L.kT : nullptr,
+              want_kT || IS.full ? nullptr : L.posT);
     mark(c, 1);
     // 4. roles
     const int32_t *ptrI = dual ? L.ptrT : H.row_ptr;
     const int32_t *memI = dual ? L.colT : H.col_idx;
     const int32_t *ptrM = dual ? H.row_ptr : L.ptrT;
     const int32_t *itmM = dual ? H.col_idx : L.colT;
-    // back-pointer maps: item incidence -> member-list position, and back
     const int32_t *map = dual ? L.kT : L.posT;
     const int32_t *inv = dual ? L.posT : L.kT;
     // 5. s filter
@@ -841,7 +855,7 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
         // the filter's per-item keep flags
         hip_check(c, launch_filter(st, ptrM, itmM, (int32_t)M, nnz, ptrI, (int32_t)N, s, IS.s_item,
                                    L.ntask, L.pos, L.part32, L.ptrS, L.itmS, inv, L.start,
-                                   L.crank, L.orig),
+                                   L.crank, L.orig, L.err),
                   "filter");
         ptrS = L.ptrS;
         itmS = L.itmS;
@@ -854,15 +868,18 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     // than s get no cost and are never walked from
     hip_check(c, launch_cost(st, ptrI, memI, (int32_t)N, noprune ? 1 : s,
                              noprune ? nullptr : IS.s_item, ptrS, itmS, L.cost, L.start,
-                             L.totals, IS.full ? 1 : 0, IS.full ? 0 : 1),
+                             L.totals, IS.full ? 1 : 0, IS.full ? 0 : 1, L.err),
               "cost");
     if (flags & SLINE_NO_VISITED) {
         // one set intersection per wedge instead of the counter table
         hip_check(c, launch_fill_i64(st, L.passes, 4, 0), "zero counters");
         int64_t *h = c->host;
-        hip_check(c, hipMemcpyAsync(h + 1, L.totals, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, st),
-                  "read totals");
+        Report R;
+        R.add(h + 1, L.totals, 3 * sizeof(int64_t));
+        R.add(h + 20, L.err, sizeof(int32_t));
+        hip_check(c, launch_report(st, R), "read totals");
         sync(c, "wedge totals");
+        if (bad_members(c, h + 20)) return SLINE_EINVAL;
         S.n_kept = h[1];
         S.nnz_kept = h[2];
         S.wedges = h[3];
@@ -872,18 +889,27 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
                                out, S);
     }
     const PlanItems PI = plan_items(tu, ptrI, L.crank, IS.item_end, N, s, IS.s_item, IS.full);
-    if (!(flags & SLINE_NO_SHORTCUT))
-        hip_check(c, launch_mark_lookup(st, PI, memI, IS.s_max, ptrS, L.start, L.cost,
-                                        IS.full ? 0 : tu.tiny_max_wedges),
-                  "lookup members");
-    hip_check(c, launch_task_count(st, L.cost, PI, tu.tiny_max_wedges, L.ntask, L.totals + 3), "task count");
-    hip_check(c, launch_scan_i32_to_i64(st, L.ntask, N, L.tbase, L.part64), "task scan");
     int64_t *h = c->host;
-    hip_check(c, hipMemcpyAsync(h + 0, L.tbase + N, sizeof(int64_t), hipMemcpyDeviceToHost, st), "read tasks");
-    hip_check(c, hipMemcpyAsync(h + 1, L.totals, (3 + 1 + kKinds) * sizeof(int64_t),
-                                hipMemcpyDeviceToHost, st),
-              "read totals");
-    sync(c, "task plan");
+    auto plan_and_read = [&]() {
+        hip_check(c, launch_task_count(st, L.cost, PI, tu.tiny_max_wedges, L.ntask, L.totals + 3),
+                  "task count");
+        hip_check(c, launch_scan_i32_to_i64(st, L.ntask, N, L.tbase, L.part64), "task scan");
+        Report R;
+        R.add(h + 0, L.tbase + N, sizeof(int64_t));
+        R.add(h + 1, L.totals, (3 + 1 + kKinds) * sizeof(int64_t));
+        R.add(h + 20, L.err, sizeof(int32_t));
+        hip_check(c, launch_report(st, R), "read task plan");
+        sync(c, "task plan");
+    };
+    plan_and_read();
+    if (bad_members(c, h + 20)) return SLINE_EINVAL;
+    if (h[5 + kKindGroups] > 0 && IS.s_max > 1 && !IS.full && !(flags & SLINE_NO_SHORTCUT)) {
+        // lookup-only members help the task kernel alone: its items are planned
+        // again by what is left to insert
+        hip_check(c, launch_mark_lookup(st, PI, memI, ptrS, L.start, L.cost), "lookup members");
+        hip_check(c, launch_fill_i64(st, L.totals + 3, 1 + kKinds, 0), "zero plan sums");
+        plan_and_read();
+    }
     const int64_t T = h[0];
     S.n_kept = h[1];
     S.nnz_kept = h[2];
@@ -905,10 +931,25 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
         more = std::max<int64_t>(0, std::min<int64_t>(more, room / 4 / (int64_t)sizeof(StageRec)));
     }
     plan_tasks(tsz, T, more);
-    ensure_ws2(c, tsz.off + 4096);
+    c->no_weights = (flags & SLINE_NO_WEIGHTS) != 0;
+    const int64_t pair_bytes = c->no_weights ? 4 : 8;
+    // Staging pool: every pair of L_s accounts for >= s wedges.  Nearly that many
+    // are possible (s = 1, or few wedges), and each workgroup may leave part of
+    // its chunk unused: with less than an eighth and a smallest chunk per task
+    // to spare, such a build would count tasks twice.  The product route counts
+    // and fills in two passes (symbolic, then numeric), as SpGEMM does: its
+    // product is too large to stage as well.
+    int64_t want_pool = IS.full ? 0 : S.wedges / IS.s_min;
+    if (want_pool > 0 && want_pool < kPoolSlackMax)
+        want_pool += want_pool / 8 + kPoolChunkMin * std::min<int64_t>(T, kPoolSlackTasks);
+    const int64_t kept_pool =
+        std::min<int64_t>(want_pool * pair_bytes, c->tune.stage_max_bytes / pair_bytes * pair_bytes);
+    const bool keep_pool = !c->fixed.base && kept_pool > 0 && kept_pool <= kKeptPool;
+    ensure_ws2(c, tsz.off + 4096 + (keep_pool ? align256((size_t)kept_pool) : 0));
     Arena TA;
     TA.base = reinterpret_cast<char *>(c->ws2);
     const TaskLayout TL = plan_tasks(TA, T, more);
+    void *const pool_at = keep_pool ? TA.take<char>(kept_pool) : nullptr;
     hip_check(c, launch_task_fill(st, L.cost, PI, tu.tiny_max_wedges, tu.group_parts, L.tbase,
                                   TL.item, TL.part, TL.small, TL.small_item, TL.tiny, TL.tiny_item,
                                   TL.big, (int32_t)T, L.tcounts),
@@ -918,19 +959,11 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
                   "list bounds");
     mark(c, 2);
     // 7. one counting pass: pairs per task, each range's pairs staged in a pool
-    const int64_t want_pool = S.wedges / IS.s_min;  // every pair of L_s accounts for >= s wedges
-    // the product route counts and fills in two passes (symbolic, then
-    // numeric), as SpGEMM does: its product is too large to stage as well
-    c->no_weights = (flags & SLINE_NO_WEIGHTS) != 0;
-    const int64_t pool_cap =
-        (want_pool > 0 && !IS.full) ? acquire_pool(c, want_pool, c->no_weights ? 4 : 8) : 0;
-    hip_check(c, launch_fill_i32(st, TL.need, T, 0), "zero flags");
-    // unused records of a reserved log chunk must read as empty
-    hip_check(c, launch_fill_i32(st, reinterpret_cast<int32_t *>(TL.log),
-                                 (int64_t)TL.log_cap * (int64_t)(sizeof(StageRec) / 4), 0),
-              "zero log");
-    hip_check(c, launch_fill_i32(st, TL.ctrs, 4, 0), "zero counters");
-    hip_check(c, launch_fill_i64(st, reinterpret_cast<int64_t *>(TL.pool_head), 1, 0), "zero pool head");
+    const int64_t pool_cap = want_pool > 0 ? acquire_pool(c, want_pool, pair_bytes, pool_at) : 0;
+    // counters, need flags, and the log: unused records of a reserved log chunk
+    // must read as empty
+    hip_check(c, launch_fill_i32(st, reinterpret_cast<int32_t *>(TL.pool_head), TL.n_zero, 0),
+              "zero task arrays");
     CountArgs C{};
     C.mode = pool_cap > 0 ? kModeStage : kModeCount;
     C.ptrI = ptrI;
@@ -969,7 +1002,8 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     {
         // chunks small enough that every resident workgroup gets several
         const int64_t groups = (int64_t)c->n_cu * (tu.small_grid_per_cu + tu.task_grid_per_cu);
-        C.pool_chunk = std::max<int64_t>(256, std::min<int64_t>(1 << 16, pool_cap / (8 * groups)));
+        C.pool_chunk =
+            std::max<int64_t>(kPoolChunkMin, std::min<int64_t>(1 << 16, pool_cap / (8 * groups)));
         C.log_chunk = (int32_t)std::max<int64_t>(
             1, std::min<int64_t>(256, (int64_t)TL.log_cap / (8 * groups)));
     }
@@ -984,14 +1018,16 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     mark(c, 3);
     hip_check(c, launch_scan_i32_to_i64(st, TL.cnt, T, TL.off, TL.part64), "pair scan");
     mark(c, 4);
-    hip_check(c, hipMemcpyAsync(h + 0, TL.off + T, sizeof(int64_t), hipMemcpyDeviceToHost, st), "read total");
-    hip_check(c, hipMemcpyAsync(h + 4, L.passes, sizeof(int64_t), hipMemcpyDeviceToHost, st), "read passes");
-    hip_check(c, hipMemcpyAsync(h + 9, L.passes + 1, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, st),
-              "read task kernel work");
-    hip_check(c, hipMemcpyAsync(h + 12, L.tcounts, kKinds * sizeof(int32_t), hipMemcpyDeviceToHost, st),
-              "read task counts");
-    hip_check(c, hipMemcpyAsync(h + 6, L.err, sizeof(int32_t), hipMemcpyDeviceToHost, st), "read flags");
-    hip_check(c, hipMemcpyAsync(h + 7, TL.ctrs, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st), "read stage counters");
+    {
+        Report R;
+        R.add(h + 0, TL.off + T, sizeof(int64_t));
+        R.add(h + 4, L.passes, sizeof(int64_t));
+        R.add(h + 9, L.passes + 1, 3 * sizeof(int64_t));
+        R.add(h + 12, L.tcounts, kKinds * sizeof(int32_t));
+        R.add(h + 6, L.err, sizeof(int32_t));
+        R.add(h + 7, TL.ctrs, 2 * sizeof(int32_t));
+        hip_check(c, launch_report(st, R), "read counts");
+    }
     sync(c, "count pass");
     const int64_t total = h[0];
     const int32_t *hb = reinterpret_cast<const int32_t *>(h + 12);
@@ -1487,6 +1523,7 @@ struct sline_batch_plan {
     std::vector<int32_t> s_plan;       // each graph's planned s
     BatchBases B;
     int32_t s_min = 1;
+    bool groups = true;  // the task kernel has items (its lookup-only members are marked)
     std::vector<std::pair<void *, size_t>> mem;  // device allocations
     // device views
     BatchGraph *d_gr = nullptr;
@@ -1559,17 +1596,14 @@ void plan_enqueue_prep(sline_batch_plan *p, hipStream_t st, int64_t t_cap) {
     const Layout &L = p->L;
     const int32_t NI = (int32_t)B.NI, MT = (int32_t)B.MT;
     const int32_t *ptrI = p->K.ptrC, *memI = p->K.memC;
-    hip_check(c, launch_fill_i32(st, L.err, 4, 0), "zero flags");
-    hip_check(c, launch_fill_i32(st, L.tcounts, kKinds, 0), "zero task counts");
-    hip_check(c, launch_fill_i64(st, L.totals, 3 + 1 + kKinds, 0), "zero totals");
-    hip_check(c, launch_fill_i64(st, L.passes, 4, 0), "zero passes");
+    hip_check(c, launch_fill_i32(st, L.err, L.n_flags, 0), "zero flags and totals");
     // row ids, and the member order of every row (a primal graph's combined
     // ids keep its members' order); a violation stops the run's counting
     hip_check(c, launch_rows(st, ptrI, memI, NI, MT, B.ZT, 1, L.rowid, p->d_err), "row ids");
     int32_t *const rk[2] = {L.rsK0, L.rsK1};
     int32_t *const rv[2] = {L.rsV0, L.rsV1};
     hip_check(c, launch_transpose(st, memI, B.ZT, MT, L.rowid, rk, rv, L.rsHist, L.part32, L.ptrT,
-                                  L.colT, L.kT, L.posT),
+                                  L.colT, L.kT, nullptr),
               "transpose");
     // every item carries its graph's s; the filter, the costs and the
     // lookup-only members read them per item, so a run's s need not be the
@@ -1582,9 +1616,8 @@ void plan_enqueue_prep(sline_batch_plan *p, hipStream_t st, int64_t t_cap) {
               "cost");
     const Tuning &tu = p->C.tune;
     const PlanItems PI = plan_items(tu, ptrI, nullptr, p->K.iend, NI, p->s_min, p->K.s_item, false);
-    hip_check(c, launch_mark_lookup(st, PI, memI, INT32_MAX, L.ptrS, L.start, L.cost,
-                                    tu.tiny_max_wedges),
-              "lookup members");
+    if (p->groups)
+        hip_check(c, launch_mark_lookup(st, PI, memI, L.ptrS, L.start, L.cost), "lookup members");
     plan_enqueue_tasks(p, st, t_cap < 0);
     if (t_cap >= 0)
         hip_check(c, launch_plan_guard(st, L.tbase + NI, t_cap, kErrPlanTasks, p->d_err), "task guard");
@@ -1607,13 +1640,8 @@ void plan_enqueue_count(sline_batch_plan *p, hipStream_t st, int64_t pair_cap) {
     hip_check(c, launch_flat_bounds(st, L.ptrS, L.itmS, (int32_t)p->B.MT, nullptr,
                                     (int32_t)p->B.NI, L.bnd),
               "list bounds");
-    hip_check(c, launch_fill_i32(st, TL.need, p->t_cap, 0), "zero need flags");
-    hip_check(c, launch_fill_i32(st, reinterpret_cast<int32_t *>(TL.log),
-                                 (int64_t)TL.log_cap * (int64_t)(sizeof(StageRec) / 4), 0),
-              "zero log");
-    hip_check(c, launch_fill_i32(st, TL.ctrs, 4, 0), "zero counters");
-    hip_check(c, launch_fill_i64(st, reinterpret_cast<int64_t *>(TL.pool_head), 1, 0),
-              "zero pool head");
+    hip_check(c, launch_fill_i32(st, reinterpret_cast<int32_t *>(TL.pool_head), TL.n_zero, 0),
+              "zero task arrays");
     // tasks beyond this run's count must add no pairs to the scan
     hip_check(c, launch_fill_i32(st, TL.cnt, p->t_cap, 0), "zero pair counts");
     hip_check(c, launch_count(st, C), "count pass");
@@ -1866,18 +1894,19 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
             hip_check(c, hipMemcpyAsync(h + 0, p->L.tbase + B.NI, sizeof(int64_t),
                                         hipMemcpyDeviceToHost, st),
                       "read tasks");
-            hip_check(c, hipMemcpyAsync(h + 1, p->L.totals, 4 * sizeof(int64_t),
+            hip_check(c, hipMemcpyAsync(h + 1, p->L.totals, (3 + 1 + kKinds) * sizeof(int64_t),
                                         hipMemcpyDeviceToHost, st),
                       "read totals");
         }
-        hip_check(c, hipMemcpyAsync(h + 5, p->d_err, sizeof(int32_t), hipMemcpyDeviceToHost, st),
+        hip_check(c, hipMemcpyAsync(h + 15, p->d_err, sizeof(int32_t), hipMemcpyDeviceToHost, st),
                   "read flags");
         sync(c, "batch plan tasks");
-        const int32_t e = reinterpret_cast<const int32_t *>(h + 5)[0];
+        const int32_t e = reinterpret_cast<const int32_t *>(h + 15)[0];
         if (e) return plan_csr_error(c, e);
     }
     if (B.ZT > 0) {
         const int64_t T = p->host[0], wedges = p->host[3], ranges = p->host[4];
+        p->groups = p->host[5 + kKindGroups] > 0;
         if (T >= INT32_MAX) {
             set_err(c, "too many counting tasks (%s)", std::to_string(T).c_str());
             return SLINE_ENOMEM;
@@ -2351,14 +2380,11 @@ int64_t validate_csr(sline_ctx *c, const sline_csr &H, uint32_t flags) {
     int32_t *err = reinterpret_cast<int32_t *>(T0.get(64, "flags"));
     hip_check(c, launch_fill_i32(st, err, 4, 0), "zero flags");
     int32_t *h = reinterpret_cast<int32_t *>(c->host);
-    h[0] = 0;
+    h[0] = h[1] = 0;
     if (m > 0) {
-        hip_check(c, launch_check_rowptr(st, H.row_ptr, (int32_t)m, err), "row_ptr check");
-        hip_check(c, hipMemcpyAsync(h, H.row_ptr + m, sizeof(int32_t), hipMemcpyDeviceToHost, st),
-                  "read nnz");
+        hip_check(c, launch_check_rowptr(st, H.row_ptr, (int32_t)m, h), "row_ptr check");
+        sync(c, "row_ptr check");
     }
-    hip_check(c, hipMemcpyAsync(h + 1, err, sizeof(int32_t), hipMemcpyDeviceToHost, st), "read flags");
-    sync(c, "row_ptr check");
     const int64_t nnz = h[0];
     if (h[1] != 0 || nnz < 0) {
         set_err(c, "row_ptr must start at 0 and never decrease");

@@ -1407,11 +1407,13 @@ __device__ __forceinline__ int32_t plan_parts(const PlanItems &I, int64_t cost, 
                       I.dense_min, I.slots);
 }
 
-// A tiny item: one task, a planning cost of at most tiny_max and at most
-// kTinyCap members, outside product mode (see k_count_tiny).
+// A tiny item: one task, at most kTinyCap members and tiny_max wedges, or with
+// s > 2, where few pairs are left to write, three times as many, outside
+// product mode (see k_count_tiny).
 __device__ __forceinline__ bool is_tiny(const PlanItems &I, int32_t a, int64_t c,
                                         int32_t tiny_max) {
-    return c <= tiny_max && !I.full && I.ptrI[a + 1] - I.ptrI[a] <= kTinyCap;
+    if (I.full || c > 3 * tiny_max || I.ptrI[a + 1] - I.ptrI[a] > kTinyCap) return false;
+    return c <= tiny_max || (I.s_item ? I.s_item[a] : I.s) > 2;
 }
 
 // Tasks of item a and the kind of kernel that counts them.

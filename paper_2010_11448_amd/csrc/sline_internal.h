@@ -225,7 +225,25 @@ __device__ __forceinline__ int32_t direct_tasks(const PlanItems &I, int32_t a, i
 // ------------------------------------------------------------ launchers
 // Every launcher enqueues on `st` and returns the launch status.
 
-hipError_t launch_check_rowptr(hipStream_t st, const int32_t *rp, int32_t m, int32_t *err);
+// seen (host memory the device can write, seen[1] zeroed by the caller): [0]
+// receives row_ptr[m], [1] becomes 1 if row_ptr[0] != 0 or row_ptr decreases.
+hipError_t launch_check_rowptr(hipStream_t st, const int32_t *rp, int32_t m, int32_t *seen);
+
+// A read-back: up to kMost runs of 32-bit words copied to host memory by one
+// launch (a copy per run would cost a launch each).
+struct Report {
+    static constexpr int kMost = 6;
+    int32_t n = 0;
+    const int32_t *src[kMost];
+    int32_t *dst[kMost];
+    int32_t words[kMost];
+    void add(void *to, const void *from, int32_t bytes) {
+        src[n] = static_cast<const int32_t *>(from);
+        dst[n] = static_cast<int32_t *>(to);
+        words[n++] = bytes / 4;
+    }
+};
+hipError_t launch_report(hipStream_t st, const Report &R);
 hipError_t launch_rows(hipStream_t st, const int32_t *rp, const int32_t *col, int32_t m,
                        int32_t n, int64_t nnz, int check_order, int32_t *rowid, int32_t *err);
 
@@ -267,6 +285,7 @@ hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int
 // With start given, the back-pointer of every kept entry is written as well:
 // start[inv[p]] = (its position in itmS) + 1, inv mapping member-list
 // positions to item incidences.
+// With err given, nothing is read while kErrColRange is set in *err.
 // kept (N entries, scratch) receives each item's keep flag first.  With crank
 // given (N + 1 entries), crank[it] = kept items before it, and where ranks pay
 // (ranks_pay), itmS holds ranks and orig[rank] (up to N entries) their items.
@@ -274,7 +293,8 @@ hipError_t launch_filter(hipStream_t st, const int32_t *ptrM, const int32_t *itm
                          int64_t nnz, const int32_t *ptrI, int32_t N, int32_t s,
                          const int32_t *s_item, int32_t *kept, int32_t *pos, int32_t *part32,
                          int32_t *ptrS, int32_t *itmS, const int32_t *inv, int32_t *start,
-                         int32_t *crank = nullptr, int32_t *orig = nullptr);
+                         int32_t *crank = nullptr, int32_t *orig = nullptr,
+                         const int32_t *err = nullptr);
 
 // Per-item exact wedge count W_a, the back-pointer start[k] (first item > a
 // in N_s(v) for member incidence k of a kept item a) and the run totals:
@@ -284,7 +304,7 @@ hipError_t launch_filter(hipStream_t st, const int32_t *ptrM, const int32_t *itm
 hipError_t launch_cost(hipStream_t st, const int32_t *ptrI, const int32_t *memI, int32_t N,
                        int32_t s, const int32_t *s_item, const int32_t *ptrS, const int32_t *itmS,
                        int64_t *cost, int32_t *start, int64_t *totals, int32_t full = 0,
-                       int32_t have_start = 0);
+                       int32_t have_start = 0, const int32_t *err = nullptr);
 
 // Keep the entries (a, b, w) with b > a and w >= s of a row-sorted product,
 // in order: pass 1 (out_a == nullptr) counts per block into cnt, pass 2 writes
@@ -303,13 +323,10 @@ hipError_t launch_product_filter(hipStream_t st, const int32_t *a, const int32_t
 // cost max(W_a - flagged wedges, W_a / 3).
 constexpr int32_t kStartMask = 0x7fffffff;
 constexpr int32_t kMaxLookup = 15;  // lookup-only members per item at most
-// s_item (nullable) gives each item its own s (batches); s_max is the largest.
-// Items with at most kTinyCap members and at most tiny_max wedges (0: none)
-// are left as they are: the one-lane path counts every wedge of them.
-// So are items that count every wedge another way (direct_tasks).
+// Only items that k_count_tasks counts are marked: every other kernel counts all
+// wedges, and would gain nothing.
 hipError_t launch_mark_lookup(hipStream_t st, const PlanItems &I, const int32_t *memI,
-                              int32_t s_max, const int32_t *ptrS, int32_t *start, int64_t *cost,
-                              int32_t tiny_max);
+                              const int32_t *ptrS, int32_t *start, int64_t *cost);
 
 // Tasks: item a with W_a wedges becomes P_a tasks (sub-ranges of its
 // candidate range); ntask[a] = P_a.  Task t of item a (t = tbase[a] + p) is

@@ -79,7 +79,7 @@ inline int grid_for(int64_t work, int per_block, int cap = 1 << 20) {
 // ------------------------------------------------------------- checks
 
 // Short rows are walked by groups of kGroup lanes (eight rows per wave);
-// longer rows by whole waves, in a second launch that looks at 64 rows at a
+// longer rows by whole waves, in a second loop that looks at 64 rows at a
 // time and takes the long ones in turn.  Short means at most 32 entries.
 constexpr int kGroup = 8;
 
@@ -100,9 +100,9 @@ __device__ __forceinline__ uint64_t group_max(uint64_t v) {
     return v;
 }
 
-// Call body(a, gl) for the rows a this launch owns: with W < kWave, every
-// row of at most SHORT entries, by a group of W lanes (gl = lane in the
-// group); with W == kWave, every longer row, by the whole wave.
+// Call body(a, gl) for the rows a of one kind: with W < kWave, every row of at
+// most SHORT entries, by a group of W lanes (gl = lane in the group); with
+// W == kWave, every longer row, by the whole wave.
 template <int W, int SHORT, typename Body>
 __device__ __forceinline__ void for_rows(const int32_t *ptrI, int64_t N, Body body) {
     const int lane = lane_id();
@@ -112,7 +112,7 @@ __device__ __forceinline__ void for_rows(const int32_t *ptrI, int64_t N, Body bo
         constexpr int G = kWave / W;
         const int gl = lane & (W - 1);
         for (int64_t a = wave * G + lane / W; a < N; a += nwaves * G) {
-            if (ptrI[a + 1] - ptrI[a] > SHORT) continue;  // the whole-wave launch takes it
+            if (ptrI[a + 1] - ptrI[a] > SHORT) continue;  // the whole-wave loop takes it
             body(a, gl);
         }
     } else {
@@ -128,20 +128,34 @@ __device__ __forceinline__ void for_rows(const int32_t *ptrI, int64_t N, Body bo
     }
 }
 
-__global__ void k_check_rowptr(const int32_t *rp, int32_t m, int32_t *err) {
+// Every row in one launch: body(a, gl, W), W lanes to a row, gl this lane's place.
+template <int SHORT, typename Body>
+__device__ __forceinline__ void for_all_rows(const int32_t *ptrI, int64_t N, Body body) {
+    for_rows<kGroup, SHORT>(ptrI, N, [&](int64_t a, int gl) { body(a, gl, kGroup); });
+    for_rows<kWave, SHORT>(ptrI, N, [&](int64_t a, int gl) { body(a, gl, kWave); });
+}
+
+// row_ptr checks; seen (host memory): [0] = row_ptr[m], [1] = 1 if one failed.
+__global__ void k_check_rowptr(const int32_t *rp, int32_t m, int32_t *seen) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0 && rp[0] != 0) atomicOr(err, kErrRowPtr0);
-    if (i < m && rp[i] > rp[i + 1]) atomicOr(err, kErrRowPtrOrder);
+    if (i == 0) seen[0] = rp[m];
+    if ((i == 0 && rp[0] != 0) || (i < m && rp[i] > rp[i + 1])) seen[1] = 1;
+}
+
+// Device words to host memory, one launch for all of a read-back.
+__global__ __launch_bounds__(kWave) void k_report(Report R) {
+    for (int i = 0; i < R.n; ++i)
+        for (int32_t w = threadIdx.x; w < R.words[i]; w += kWave)
+            R.dst[i][w] = R.src[i][w];
 }
 
 // One wave per row (grid-stride): the row id of every incidence, member range
 // checks and, when asked, the strictly-increasing check of each row.
-template <int W>
 __global__ __launch_bounds__(256) void k_rows(const int32_t *rp, const int32_t *col, int32_t m,
                                               int32_t n, int64_t nnz, int check_order,
                                               int32_t *rowid, int32_t *err) {
     int32_t bad = 0;
-    for_rows<W, 32>(rp, m, [&](int64_t i, int gl) {
+    for_all_rows<32>(rp, m, [&](int64_t i, int gl, int W) {
         int64_t b = rp[i], e = rp[i + 1];
         if (b < 0) b = 0;
         if (e > nnz) e = nnz;
@@ -236,9 +250,9 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const TI *in, int64_
 }
 
 // Short scans: one workgroup, one launch instead of three (which cost about
-// 2.5 us each, more than a pass over 16K entries takes here).
+// 2.5 us each, as much as 20,000 entries take here).
 constexpr int kScanOneThreads = 1024;
-constexpr int64_t kScanOneMax = 16384;
+constexpr int64_t kScanOneMax = 65536;
 
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const TI *in, int64_t n, TO *out) {
@@ -445,6 +459,9 @@ __global__ void k_rs_bounds(const int32_t *sk, int64_t nnz, int32_t n, int32_t *
 
 // -------------------------------------------------------- s filtering
 
+// Member-list entries below which the filter compares sizes entry by entry.
+constexpr int64_t kFilterFew = 1 << 20;
+
 // The s filter as a stream compaction: the filtered lists N_s(v), one after
 // the other, are the kept entries of the member lists in their order, so the
 // position of a kept entry is the number of kept entries before it.
@@ -458,8 +475,20 @@ __global__ void k_item_kept(const int32_t *ptrI, int32_t N, int32_t s, const int
         kept[it] = (ptrI[it + 1] - ptrI[it]) >= (s_item ? s_item[it] : s) ? 1 : 0;
 }
 
+// kept null: the sizes are compared here (short inputs, whose list bounds stay
+// in cache: one launch less).
 __global__ void k_filter_flags(const int32_t *itmM, int64_t nnz, const int32_t *kept,
-                               int32_t *keep) {
+                               const int32_t *ptrI, int32_t s, const int32_t *s_item,
+                               int32_t *keep, const int32_t *err) {
+    if (err && (*err & kErrColRange)) return;  // items that index nothing
+    if (!kept) {
+        for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz;
+             p += (int64_t)gridDim.x * blockDim.x) {
+            const int32_t it = itmM[p];
+            keep[p] = (ptrI[it + 1] - ptrI[it]) >= (s_item ? s_item[it] : s) ? 1 : 0;
+        }
+        return;
+    }
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz;
          p += (int64_t)gridDim.x * blockDim.x)
         keep[p] = kept[itmM[p]];
@@ -473,7 +502,8 @@ __global__ void k_filter_flags(const int32_t *itmM, int64_t nnz, const int32_t *
 __global__ void k_filter_scatter(const int32_t *itmM, int64_t nnz, const int32_t *pos,
                                  const int32_t *ptrM, int32_t M, int32_t *ptrS, int32_t *itmS,
                                  const int32_t *inv, int32_t *start, int32_t N,
-                                 const int32_t *crank, int32_t *orig) {
+                                 const int32_t *crank, int32_t *orig, const int32_t *err) {
+    if (err && (*err & kErrColRange)) return;
     int64_t n = nnz > (int64_t)M + 1 ? nnz : (int64_t)M + 1;
     if (crank && !ranks_pay(crank[N], N)) crank = nullptr;
     if (crank && N > n) n = N;
@@ -499,14 +529,15 @@ __global__ void k_filter_scatter(const int32_t *itmM, int64_t nnz, const int32_t
 // items with |S_a| < s.  For every member incidence k of a kept item,
 // start[k] = index in itmS of the first item > a in N_s(v) (the back-pointer
 // where a's walk over v begins).  totals: kept items, their incidences, W.
-template <int W>
 __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t *memI,
                                               int32_t N, int32_t s, const int32_t *s_item,
                                               const int32_t *ptrS, const int32_t *itmS,
                                               int64_t *cost, int32_t *start, int64_t *totals,
-                                              int32_t full, int32_t have_start) {
+                                              int32_t full, int32_t have_start,
+                                              const int32_t *err) {
+    if (err && (*err & kErrColRange)) return;  // members that index nothing
     int64_t kept = 0, kept_nnz = 0, wedges = 0;  // counted by each row's first lane
-    for_rows<W, 32>(ptrI, N, [&](int64_t a, int gl) {
+    for_all_rows<32>(ptrI, N, [&](int64_t a, int gl, int W) {
         const int32_t b = ptrI[a], e = ptrI[a + 1];
         if (e - b < (s_item ? s_item[a] : s)) {
             if (gl == 0) cost[a] = 0;
@@ -525,7 +556,7 @@ __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t
             }
             c += hi - st;
         }
-        c = group_sum<W>(c);
+        c = W == kWave ? wave_sum(c) : group_sum<kGroup>(c);
         if (gl == 0) {
             cost[a] = c;
             kept += 1;
@@ -563,19 +594,17 @@ __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t
 // incidence k is the one that flags it.
 constexpr int kKeysPerLane = 4;
 
-template <int W>
 __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t *memI,
                                                      const int32_t *ptrS,
-                                                     int32_t *start, int64_t *cost,
-                                                     int32_t tiny_max) {
+                                                     int32_t *start, int64_t *cost) {
     I.crank = ranks_or_null(I.crank, I.N);
-    for_rows<W, kGroup * kKeysPerLane>(I.ptrI, I.N, [&](int64_t a, int gl) {
+    for_all_rows<kGroup * kKeysPerLane>(I.ptrI, I.N, [&](int64_t a, int gl, int W) {
+        auto best_of = [&](uint64_t v) { return W == kWave ? group_max<kWave>(v) : group_max<kGroup>(v); };
         const int32_t b = I.ptrI[a], e = I.ptrI[a + 1];
         const int32_t s = I.s_item ? I.s_item[a] : I.s;
         if (e - b < s) return;
-        // a tiny item by its exact wedges stays tiny: it is counted one per
-        // lane, every wedge, so lookup-only members would change nothing
-        if (e - b <= kTinyCap && cost[a] <= tiny_max) return;
+        // only items that the task kernel counts: the others count every wedge
+        if (cost[a] <= I.small_max) return;
         int32_t kind, ranges;
         if (direct_tasks(I, (int32_t)a, cost[a], kind, ranges) > 0) return;
         const int32_t rounds = min(min(s - 1, kMaxLookup), e - b - 1);
@@ -597,7 +626,7 @@ __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t 
                 uint64_t best = 0;
 #pragma unroll
                 for (int i = 0; i < kKeysPerLane; ++i) best = key[i] > best ? key[i] : best;
-                best = group_max<W>(best);
+                best = best_of(best);
                 if ((best >> 32) == 0) break;  // no member with candidates left
                 const int32_t k = INT32_MAX - (int32_t)(uint32_t)best;
 #pragma unroll
@@ -619,7 +648,7 @@ __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t 
                 const uint64_t key = ((uint64_t)(uint32_t)c << 32) | (uint32_t)(INT32_MAX - k);
                 best = key > best ? key : best;
             }
-            best = group_max<W>(best);
+            best = best_of(best);
             if ((best >> 32) == 0) break;  // no member with candidates left
             const int32_t k = INT32_MAX - (int32_t)(uint32_t)best;
             if ((k - b) % W == gl) start[k] |= (int32_t)0x80000000u;
@@ -684,20 +713,21 @@ hipError_t launch_product_filter(hipStream_t st, const int32_t *a, const int32_t
     return hipGetLastError();
 }
 
-hipError_t launch_check_rowptr(hipStream_t st, const int32_t *rp, int32_t m, int32_t *err) {
-    k_check_rowptr<<<grid_for((int64_t)m + 1, 256), 256, 0, st>>>(rp, m, err);
+hipError_t launch_check_rowptr(hipStream_t st, const int32_t *rp, int32_t m, int32_t *seen) {
+    k_check_rowptr<<<grid_for((int64_t)m + 1, 256), 256, 0, st>>>(rp, m, seen);
+    return hipGetLastError();
+}
+
+hipError_t launch_report(hipStream_t st, const Report &R) {
+    k_report<<<1, kWave, 0, st>>>(R);
     return hipGetLastError();
 }
 
 hipError_t launch_rows(hipStream_t st, const int32_t *rp, const int32_t *col, int32_t m,
                        int32_t n, int64_t nnz, int check_order, int32_t *rowid, int32_t *err) {
     if (m <= 0) return hipSuccess;
-    k_rows<kGroup><<<grid_for((int64_t)m * kGroup, 256, 65536), 256, 0, st>>>(
-        rp, col, m, n, nnz, check_order, rowid, err);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_rows<kWave><<<grid_for(m, 256, 4096), 256, 0, st>>>(rp, col, m, n, nnz, check_order, rowid,
-                                                         err);
+    k_rows<<<grid_for((int64_t)m * kGroup, 256, 16384), 256, 0, st>>>(rp, col, m, n, nnz,
+                                                                     check_order, rowid, err);
     return hipGetLastError();
 }
 
@@ -813,11 +843,13 @@ hipError_t launch_filter(hipStream_t st, const int32_t *ptrM, const int32_t *itm
                          int64_t nnz, const int32_t *ptrI, int32_t N, int32_t s,
                          const int32_t *s_item, int32_t *kept, int32_t *pos, int32_t *part32,
                          int32_t *ptrS, int32_t *itmS, const int32_t *inv, int32_t *start,
-                         int32_t *crank, int32_t *orig) {
+                         int32_t *crank, int32_t *orig, const int32_t *err) {
     if (M <= 0) return hipSuccess;
     if (nnz > 0) {
-        k_item_kept<<<grid_for(N, 256, 65536), 256, 0, st>>>(ptrI, N, s, s_item, kept);
-        k_filter_flags<<<grid_for(nnz, 256, 65536), 256, 0, st>>>(itmM, nnz, kept, pos);
+        const bool few = !crank && nnz < kFilterFew;
+        if (!few) k_item_kept<<<grid_for(N, 256, 65536), 256, 0, st>>>(ptrI, N, s, s_item, kept);
+        k_filter_flags<<<grid_for(nnz, 256, 65536), 256, 0, st>>>(itmM, nnz, few ? nullptr : kept,
+                                                                 ptrI, s, s_item, pos, err);
         hipError_t e = hipGetLastError();
         if (e == hipSuccess && crank) e = launch_scan_i32(st, kept, N, crank, part32);
         if (e != hipSuccess) return e;
@@ -829,34 +861,25 @@ hipError_t launch_filter(hipStream_t st, const int32_t *ptrM, const int32_t *itm
     if (e != hipSuccess) return e;
     const int64_t most = std::max<int64_t>({nnz, (int64_t)M + 1, crank ? (int64_t)N : 0});
     k_filter_scatter<<<grid_for(most, 256, 65536), 256, 0, st>>>(
-        itmM, nnz, pos, ptrM, M, ptrS, itmS, inv, start, N, crank, orig);
+        itmM, nnz, pos, ptrM, M, ptrS, itmS, inv, start, N, crank, orig, err);
     return hipGetLastError();
 }
 
 hipError_t launch_cost(hipStream_t st, const int32_t *ptrI, const int32_t *memI, int32_t N,
                        int32_t s, const int32_t *s_item, const int32_t *ptrS, const int32_t *itmS,
                        int64_t *cost, int32_t *start, int64_t *totals, int32_t full,
-                       int32_t have_start) {
+                       int32_t have_start, const int32_t *err) {
     if (N <= 0) return hipSuccess;
-    k_cost<kGroup><<<grid_for((int64_t)N * kGroup, 256, 4096), 256, 0, st>>>(
-        ptrI, memI, N, s, s_item, ptrS, itmS, cost, start, totals, full, have_start);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_cost<kWave><<<grid_for(N, 256, 1024), 256, 0, st>>>(
-        ptrI, memI, N, s, s_item, ptrS, itmS, cost, start, totals, full, have_start);
+    k_cost<<<grid_for((int64_t)N * kGroup, 256, 4096), 256, 0, st>>>(
+        ptrI, memI, N, s, s_item, ptrS, itmS, cost, start, totals, full, have_start, err);
     return hipGetLastError();
 }
 
 hipError_t launch_mark_lookup(hipStream_t st, const PlanItems &I, const int32_t *memI,
-                              int32_t s_max, const int32_t *ptrS, int32_t *start, int64_t *cost,
-                              int32_t tiny_max) {
-    if (I.N <= 0 || s_max <= 1) return hipSuccess;
-    k_mark_lookup<kGroup><<<grid_for((int64_t)I.N * kGroup, 256, 65536), 256, 0, st>>>(
-        I, memI, ptrS, start, cost, tiny_max);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_mark_lookup<kWave><<<grid_for(I.N, 256, 4096), 256, 0, st>>>(I, memI, ptrS, start, cost,
-                                                                  tiny_max);
+                              const int32_t *ptrS, int32_t *start, int64_t *cost) {
+    if (I.N <= 0) return hipSuccess;
+    k_mark_lookup<<<grid_for((int64_t)I.N * kGroup, 256, 16384), 256, 0, st>>>(I, memI, ptrS, start,
+                                                                              cost);
     return hipGetLastError();
 }
 
