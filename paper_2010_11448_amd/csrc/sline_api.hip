@@ -86,7 +86,7 @@ struct sline_ctx {
     size_t ws_bytes = 0;
     void *ws2 = nullptr;  // task arrays
     size_t ws2_bytes = 0;
-    int64_t *host = nullptr;  // pinned read-back area (64 int64)
+    int64_t *host = nullptr;  // pinned read-back area (128 int64)
 
     // counting work kept after SLINE_ECAPACITY for an immediate retry
     struct Pending {
@@ -338,8 +338,7 @@ struct Layout {
 constexpr int64_t kTinyMinItems = 1 << 15;
 // Staging pools below kPoolSlackMax pairs get room to spare (see build_core).
 constexpr int64_t kPoolSlackMax = 1 << 27;
-constexpr int64_t kPoolChunkMin = 256;   // pairs a workgroup reserves at least
-constexpr int64_t kPoolSlackTasks = 16384;
+constexpr int64_t kLogPerWg = 32;  // log records for each workgroup's chunks
 Tuning build_tuning(const Tuning &t, int64_t n_items, int64_t nnz) {
     Tuning u = t;
     if (nnz >= kDirectMaxNnz) u.dense_min_wedges = 0;
@@ -354,10 +353,10 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
     Layout L{};
     L.err = A.take<int32_t>(4);
     L.queue = A.take<int32_t>(4);
-    L.tcounts = A.take<int32_t>(kKinds);
-    L.totals = A.take<int64_t>(3 + 1 + kKinds);  // cost totals, then the planner's sums
-    L.passes = A.take<int64_t>(4);
-    L.n_flags = reinterpret_cast<int32_t *>(L.passes + 4) - L.err;
+    L.tcounts = A.take<int32_t>(kKinds * kCountStride);
+    L.totals = A.take<int64_t>(kSumRows * kTotalCols);
+    L.passes = A.take<int64_t>(kSumRows * kStatCols);
+    L.n_flags = reinterpret_cast<int32_t *>(L.passes + kSumRows * kStatCols) - L.err;
     L.rowid = A.take<int32_t>(nnz);
     L.ptrT = A.take<int32_t>(n + 1);
     L.colT = A.take<int32_t>(nnz);
@@ -875,7 +874,7 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
         hip_check(c, launch_fill_i64(st, L.passes, 4, 0), "zero counters");
         int64_t *h = c->host;
         Report R;
-        R.add(h + 1, L.totals, 3 * sizeof(int64_t));
+        R.add_rows(h + 1, L.totals, kTotalCols, 3);
         R.add(h + 20, L.err, sizeof(int32_t));
         hip_check(c, launch_report(st, R), "read totals");
         sync(c, "wedge totals");
@@ -896,33 +895,36 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
         hip_check(c, launch_scan_i32_to_i64(st, L.ntask, N, L.tbase, L.part64), "task scan");
         Report R;
         R.add(h + 0, L.tbase + N, sizeof(int64_t));
-        R.add(h + 1, L.totals, (3 + 1 + kKinds) * sizeof(int64_t));
+        R.add_rows(h + 1, L.totals, kTotalCols, 3 + 1 + kKinds);
         R.add(h + 20, L.err, sizeof(int32_t));
         hip_check(c, launch_report(st, R), "read task plan");
         sync(c, "task plan");
     };
     plan_and_read();
     if (bad_members(c, h + 20)) return SLINE_EINVAL;
+    S.n_kept = h[1];
+    S.nnz_kept = h[2];
+    S.wedges = h[3];
     if (h[5 + kKindGroups] > 0 && IS.s_max > 1 && !IS.full && !(flags & SLINE_NO_SHORTCUT)) {
         // lookup-only members help the task kernel alone: its items are planned
         // again by what is left to insert
         hip_check(c, launch_mark_lookup(st, PI, memI, ptrS, L.start, L.cost), "lookup members");
-        hip_check(c, launch_fill_i64(st, L.totals + 3, 1 + kKinds, 0), "zero plan sums");
+        hip_check(c, launch_fill_i64(st, L.totals, kSumRows * kTotalCols, 0), "zero plan sums");
         plan_and_read();
     }
     const int64_t T = h[0];
-    S.n_kept = h[1];
-    S.nnz_kept = h[2];
-    S.wedges = h[3];
     if (T >= INT32_MAX) {
         set_err(c, "too many counting tasks (%s)", std::to_string(T).c_str());
         throw Fail{SLINE_ENOMEM};
     }
     // every range of an item counted directly logs its pairs; in a fixed region
     // as many of those records as leave most of the room to the staging pool
-    int64_t more = h[4];
-    uint32_t kinds = 0;
-    for (int k = 0; k < kKinds; ++k) kinds |= h[5 + k] > 0 ? 1u << k : 0u;
+    CountArgs C{};
+    C.tune = tu;
+    C.n_cu = c->n_cu;
+    const int64_t wgs = set_grids(C, h + 5);
+    // and some for each workgroup's chunk
+    int64_t more = h[4] + kLogPerWg * wgs;
     Arena tsz;
     if (c->fixed.base) {
         Arena least;
@@ -935,13 +937,13 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     const int64_t pair_bytes = c->no_weights ? 4 : 8;
     // Staging pool: every pair of L_s accounts for >= s wedges.  Nearly that many
     // are possible (s = 1, or few wedges), and each workgroup may leave part of
-    // its chunk unused: with less than an eighth and a smallest chunk per task
-    // to spare, such a build would count tasks twice.  The product route counts
+    // its chunk unused: with less than an eighth and two smallest chunks each to
+    // spare, such a build would count tasks twice.  The product route counts
     // and fills in two passes (symbolic, then numeric), as SpGEMM does: its
     // product is too large to stage as well.
     int64_t want_pool = IS.full ? 0 : S.wedges / IS.s_min;
     if (want_pool > 0 && want_pool < kPoolSlackMax)
-        want_pool += want_pool / 8 + kPoolChunkMin * std::min<int64_t>(T, kPoolSlackTasks);
+        want_pool += want_pool / 8 + 2 * kPoolChunkMin * wgs;
     const int64_t kept_pool =
         std::min<int64_t>(want_pool * pair_bytes, c->tune.stage_max_bytes / pair_bytes * pair_bytes);
     const bool keep_pool = !c->fixed.base && kept_pool > 0 && kept_pool <= kKeptPool;
@@ -954,7 +956,7 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
                                   TL.item, TL.part, TL.small, TL.small_item, TL.tiny, TL.tiny_item,
                                   TL.big, (int32_t)T, L.tcounts),
               "task fill");
-    if ((kinds >> kKindFlat) & 1u)
+    if (C.grid[kKindFlat] > 0)
         hip_check(c, launch_flat_bounds(st, ptrS, itmS, (int32_t)M, L.crank, (int32_t)N, L.bnd),
                   "list bounds");
     mark(c, 2);
@@ -964,7 +966,6 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     // must read as empty
     hip_check(c, launch_fill_i32(st, reinterpret_cast<int32_t *>(TL.pool_head), TL.n_zero, 0),
               "zero task arrays");
-    CountArgs C{};
     C.mode = pool_cap > 0 ? kModeStage : kModeCount;
     C.ptrI = ptrI;
     C.memI = memI;
@@ -981,6 +982,7 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     C.start = L.start;
     C.task_item = TL.item;
     C.task_part = TL.part;
+    C.tbase = L.tbase;
     C.n_tasks = (int32_t)T;
     C.small_tasks = TL.small;
     C.small_items = TL.small_item;
@@ -988,7 +990,6 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     C.tiny_items = TL.tiny_item;
     C.big_tasks = TL.big;
     C.task_counts = L.tcounts;
-    C.kinds = kinds;
     C.bnd = L.bnd;
     C.queue = L.queue;
     C.task_cnt = TL.cnt;
@@ -999,21 +1000,12 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     C.pool_head = TL.pool_head;
     C.log = TL.log;
     C.log_cap = TL.log_cap;
-    {
-        // chunks small enough that every resident workgroup gets several
-        const int64_t groups = (int64_t)c->n_cu * (tu.small_grid_per_cu + tu.task_grid_per_cu);
-        C.pool_chunk =
-            std::max<int64_t>(kPoolChunkMin, std::min<int64_t>(1 << 16, pool_cap / (8 * groups)));
-        C.log_chunk = (int32_t)std::max<int64_t>(
-            1, std::min<int64_t>(256, (int64_t)TL.log_cap / (8 * groups)));
-    }
+    set_chunks(C);
     C.log_head = TL.ctrs;
     C.need = TL.need;
     C.need_count = TL.ctrs + 1;
     C.passes = L.passes;
     C.err = L.err;
-    C.tune = tu;
-    C.n_cu = c->n_cu;
     hip_check(c, launch_count(st, C, c->profile ? c->ev[7] : nullptr), "count pass");
     mark(c, 3);
     hip_check(c, launch_scan_i32_to_i64(st, TL.cnt, T, TL.off, TL.part64), "pair scan");
@@ -1021,23 +1013,26 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     {
         Report R;
         R.add(h + 0, TL.off + T, sizeof(int64_t));
-        R.add(h + 4, L.passes, sizeof(int64_t));
-        R.add(h + 9, L.passes + 1, 3 * sizeof(int64_t));
-        R.add(h + 12, L.tcounts, kKinds * sizeof(int32_t));
+        R.add_rows(h + 9, L.passes, kStatCols, 4);
+        R.add(h + 16, L.tcounts, kKinds * kCountStride * sizeof(int32_t));
         R.add(h + 6, L.err, sizeof(int32_t));
         R.add(h + 7, TL.ctrs, 2 * sizeof(int32_t));
         hip_check(c, launch_report(st, R), "read counts");
     }
     sync(c, "count pass");
     const int64_t total = h[0];
-    const int32_t *hb = reinterpret_cast<const int32_t *>(h + 12);
+    auto listed = [&](int kind) {
+        return reinterpret_cast<const int32_t *>(h + 16)[kind * kCountStride];
+    };
     const int32_t *hc = reinterpret_cast<const int32_t *>(h + 7);
-    S.passes = h[4];
-    S.heavy_nnz = h[9];
-    S.heavy_wedges = h[10];
-    S.heavy_pairs = h[11];
-    S.n_small = hb[kKindSmall] + hb[kKindTiny];  // one-wave and one-lane items
-    S.n_heavy = hb[kKindGroups] + hb[kKindFlat] + hb[kKindSieve1] + hb[kKindSieve4];
+    S.passes = h[9];
+    S.heavy_nnz = h[10];
+    S.heavy_wedges = h[11];
+    S.heavy_pairs = h[12];
+    // one-wave and one-lane items, and the others
+    S.n_small = listed(kKindSmall) + listed(kKindTiny) + listed(kKindMini);
+    S.n_heavy =
+        listed(kKindGroups) + listed(kKindFlat) + listed(kKindSieve1) + listed(kKindSieve4);
     S.n_pairs = total;
     if (c->profile) {
         S.ms_transpose = span_ms(c, 0, 1);
@@ -1050,7 +1045,9 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
         set_err(c, "internal error: counting table overflow");
         return SLINE_EDEVICE;
     }
-    c->fill_records = C.mode == kModeStage ? std::min(hc[0], TL.log_cap) : 0;
+    c->fill_records = C.mode == kModeStage
+                          ? (int32_t)std::min<int64_t>((int64_t)C.log_own + hc[0], TL.log_cap)
+                          : 0;
     c->fill_need = C.mode == kModeStage ? hc[1] : -1;
     c->stats = S;
     C.task_off = TL.off;
@@ -1697,6 +1694,7 @@ CountArgs plan_count_args(sline_batch_plan *p) {
     C.start = L.start;
     C.task_item = TL.item;
     C.task_part = TL.part;
+    C.tbase = L.tbase;
     C.n_tasks = (int32_t)p->t_cap;
     C.small_tasks = TL.small;
     C.small_items = TL.small_item;
@@ -1704,7 +1702,6 @@ CountArgs plan_count_args(sline_batch_plan *p) {
     C.tiny_items = TL.tiny_item;
     C.big_tasks = TL.big;
     C.task_counts = L.tcounts;
-    C.kinds = ~0u;
     C.bnd = L.bnd;
     C.queue = L.queue;
     C.task_cnt = TL.cnt;
@@ -1723,11 +1720,8 @@ CountArgs plan_count_args(sline_batch_plan *p) {
     C.n_cu = p->c->n_cu;
     C.abort = p->d_err;
     C.mode = p->pool_cap > 0 ? kModeStage : kModeCount;
-    const int64_t groups =
-        (int64_t)C.n_cu * (C.tune.small_grid_per_cu + C.tune.task_grid_per_cu);
-    C.pool_chunk = std::max<int64_t>(256, std::min<int64_t>(1 << 16, p->pool_cap / (8 * groups)));
-    C.log_chunk =
-        (int32_t)std::max<int64_t>(1, std::min<int64_t>(256, (int64_t)TL.log_cap / (8 * groups)));
+    (void)set_grids(C, nullptr);
+    set_chunks(C);
     return C;
 }
 
@@ -1894,9 +1888,9 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
             hip_check(c, hipMemcpyAsync(h + 0, p->L.tbase + B.NI, sizeof(int64_t),
                                         hipMemcpyDeviceToHost, st),
                       "read tasks");
-            hip_check(c, hipMemcpyAsync(h + 1, p->L.totals, (3 + 1 + kKinds) * sizeof(int64_t),
-                                        hipMemcpyDeviceToHost, st),
-                      "read totals");
+            Report R;
+            R.add_rows(h + 1, p->L.totals, kTotalCols, 3 + 1 + kKinds);
+            hip_check(c, launch_report(st, R), "read totals");
         }
         hip_check(c, hipMemcpyAsync(h + 15, p->d_err, sizeof(int32_t), hipMemcpyDeviceToHost, st),
                   "read flags");
@@ -1914,10 +1908,13 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
         p->t_cap = std::max<int64_t>(T, 1);
         {
             Arena sz;
-            (void)plan_tasks(sz, p->t_cap, ranges);
+            CountArgs all = p->C;
+            all.n_cu = c->n_cu;
+            const int64_t more = ranges + kLogPerWg * set_grids(all, nullptr);
+            (void)plan_tasks(sz, p->t_cap, more);
             Arena A;
             A.base = reinterpret_cast<char *>(plan_alloc(p, sz.off + 4096, "the task arrays"));
-            p->TL = plan_tasks(A, p->t_cap, ranges);
+            p->TL = plan_tasks(A, p->t_cap, more);
         }
         // 4. one counting pass with a pool of W_s / s_min pairs (every pair
         // of L_s takes at least s wedges): the pair count
@@ -1945,8 +1942,8 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
         // the chunks left partly used at the end (one per workgroup, at most
         // an eighth of the pool in all); tasks that still find no room are
         // counted again by the fill pass
-        const int64_t groups =
-            (int64_t)c->n_cu * (p->C.tune.small_grid_per_cu + p->C.tune.task_grid_per_cu);
+        CountArgs all = p->C;
+        const int64_t groups = set_grids(all, nullptr);
         const int64_t keep = std::min<int64_t>(p->pool_cap, total * 7 / 3 + 512 * groups);
         if (first_pool && keep < p->pool_cap) {
             plan_drop_last(p, first_pool);
@@ -2026,11 +2023,10 @@ sline_status plan_run_impl(sline_batch_plan *p, const int32_t *s, sline_edges *o
     if (p->B.ZT > 0) {
         hip_check(c, hipMemcpyAsync(w + 1, p->L.err, sizeof(int32_t), hipMemcpyDeviceToHost, st),
                   "read flags");
-        hip_check(c, hipMemcpyAsync(w + 2, p->L.totals, 3 * sizeof(int64_t), hipMemcpyDeviceToHost,
-                                    st),
-                  "read totals");
-        hip_check(c, hipMemcpyAsync(w + 5, p->L.passes, sizeof(int64_t), hipMemcpyDeviceToHost, st),
-                  "read passes");
+        Report R;
+        R.add_rows(w + 2, p->L.totals, kTotalCols, 3);
+        R.add_rows(w + 5, p->L.passes, kStatCols, 1);
+        hip_check(c, launch_report(st, R), "read totals");
     } else {
         w[1] = 0;
     }
@@ -2895,7 +2891,7 @@ sline_status sline_create(sline_ctx **ctx, int device, void *hip_stream, const s
     // set-up of sline_build_noalloc: this device's address of the scratch
     // array (a failure is reported by that entry point, not here)
     (void)scratch_address(device);
-    if (hipHostMalloc((void **)&c->host, 64 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void **)&c->host, 128 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         delete c;
         return SLINE_EDEVICE;

@@ -72,8 +72,32 @@ __device__ __forceinline__ void wave_bits_prefix(int32_t n, int nb, int32_t &bef
     }
 }
 
+// Thread 0 of a workgroup of a kind's kernel, at its start: its own first chunks
+// of the pool and the log, if it has some (a small build needs no others, and
+// so no atomics on the heads).
+__device__ __forceinline__ void stage_begin(const CountArgs &A, int kind, uint64_t *pool_cur,
+                                            int32_t *log_cur) {
+    const bool own = A.mode == kModeStage && A.pool_own > 0;
+    pool_cur[0] = pool_cur[1] = 0;
+    log_cur[0] = log_cur[1] = 0;
+    pool_cur[2] = (uint64_t)A.pool_chunk[kind];
+    log_cur[2] = A.log_chunk[kind];
+    if (own) {
+        pool_cur[0] = (uint64_t)A.pool_first[kind] + (uint64_t)blockIdx.x * pool_cur[2];
+        pool_cur[1] = pool_cur[0] + pool_cur[2];
+        log_cur[0] = A.log_first[kind] + (int32_t)blockIdx.x * log_cur[2];
+        log_cur[1] = log_cur[0] + log_cur[2];
+    }
+}
+
+// The row of A.passes a workgroup adds to.
+__device__ __forceinline__ unsigned long long *stat_row(const CountArgs &A) {
+    return (unsigned long long *)A.passes + (blockIdx.x % kSumRows) * kStatCols;
+}
+
 // Stage mode, thread 0 of a workgroup: room for `total` pairs in the pool and
-// `nrec` consecutive log records, taken from this workgroup's chunks (one
+// `nrec` consecutive log records, taken from this workgroup's chunks (pool_cur and
+// log_cur: next, end and size of a chunk, see stage_begin; one
 // global atomic per new chunk; records of a chunk left unused stay zero, i.e.
 // empty).  Returns false if the pool or the log has no room left.
 __device__ __forceinline__ bool stage_reserve(const CountArgs &A, uint64_t *pool_cur,
@@ -82,8 +106,8 @@ __device__ __forceinline__ bool stage_reserve(const CountArgs &A, uint64_t *pool
     off = pool_cur[0];
     rec = 0;
     if (off + (uint64_t)total > pool_cur[1]) {
-        const uint64_t size = max((uint64_t)total, (uint64_t)A.pool_chunk);
-        off = atomicAdd(A.pool_head, (unsigned long long)size);
+        const uint64_t size = max((uint64_t)total, pool_cur[2]);
+        off = (uint64_t)A.pool_own + atomicAdd(A.pool_head, (unsigned long long)size);
         if (off + size <= (uint64_t)A.pool_cap) {
             pool_cur[1] = off + size;
         } else if (off + (uint64_t)total <= (uint64_t)A.pool_cap) {
@@ -95,8 +119,8 @@ __device__ __forceinline__ bool stage_reserve(const CountArgs &A, uint64_t *pool
     }
     pool_cur[0] = off + (uint64_t)total;
     if (log_cur[0] + nrec > log_cur[1]) {
-        const int32_t size = max(nrec, A.log_chunk);
-        const int32_t r = atomicAdd(A.log_head, size);
+        const int32_t size = max(nrec, log_cur[2]);
+        const int32_t r = A.log_own + atomicAdd(A.log_head, size);
         log_cur[0] = r;
         log_cur[1] = (int32_t)min((int64_t)r + size, (int64_t)A.log_cap);
     }

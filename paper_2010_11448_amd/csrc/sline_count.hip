@@ -43,8 +43,8 @@
 // whose overlap reaches s lies in at least one list that inserts it.
 //
 // Kernels: k_count_small (one wave per item with W_a <= small_max), k_count_tasks
-// (one workgroup per task group), k_count_tiny (one lane per item), k_count_sieve
-// (s > 1, up to a few thousand wedges) and k_count_flat (sline_flat.hip: wedges
+// (one workgroup per task group), k_count_tiny (one lane per item), k_count_item
+// (whole items of up to a few thousand wedges) and k_count_flat (sline_flat.hip: wedges
 // dense in their candidate range).  Normally one counting pass
 // stages every extracted range's (b, w) in a pool and logs where it goes;
 // after the exclusive scan of the pairs per task, k_stage_copy moves each
@@ -322,8 +322,8 @@ struct Smem {
     int32_t *misc;       // see kMisc*
     int2 *stack;         // ranges still to process
     uint32_t *spare;     // one word per lane, past the table (targets of idle atomics)
-    uint64_t *pool_cur;  // [next, end) of this workgroup's pool chunk
-    int32_t *log_cur;    // [next, end) of this workgroup's log chunk
+    uint64_t *pool_cur;  // this workgroup's pool chunk (see stage_begin)
+    int32_t *log_cur;    // and log chunk
 };
 
 // misc words: run pieces, overflow flag, stack depth, staging reservation
@@ -915,17 +915,16 @@ __global__ __launch_bounds__(kWave) void k_count_small(CountArgs A) {
     __shared__ int32_t taken[kSmallRunCap];
     __shared__ int2 stack[kStack];
     __shared__ int32_t misc[kMiscWave + 1];
-    __shared__ uint64_t pool_cur[2];
-    __shared__ int32_t log_cur[2];
+    __shared__ uint64_t pool_cur[3];
+    __shared__ int32_t log_cur[3];
     const Smem S{tab, runs, taken, misc, stack, tab + LIM, pool_cur, log_cur};
     if (count_idle(A)) return;  // uniform: every thread reads the same words
     use_ranks(A);
     if (threadIdx.x == 0) {
-        pool_cur[0] = pool_cur[1] = 0;
-        log_cur[0] = log_cur[1] = 0;
+        stage_begin(A, kKindSmall, pool_cur, log_cur);
     }
     tab_clear<kWave>(tab, LIM);
-    const int32_t n_small = A.task_counts[0];
+    const int32_t n_small = A.task_counts[kKindSmall * kCountStride];
     int64_t passes = 0;
     __syncthreads();
     for (int32_t r = blockIdx.x; r < n_small; r += gridDim.x) {
@@ -949,51 +948,78 @@ __global__ __launch_bounds__(kWave) void k_count_small(CountArgs A) {
         __syncthreads();
     }
     if (threadIdx.x == 0 && passes && A.passes)
-        atomicAdd((unsigned long long *)A.passes, (unsigned long long)passes);
+        atomicAdd(stat_row(A), (unsigned long long)passes);
 }
 
-// --------------------------------------------------------------- sieve
+// ---------------------------------------------------------- whole items
 
-// s > 1, a few thousand wedges: most candidates are met once and are no pair.
-// A first walk sets, for every wedge, a bit chosen by the candidate (its low
-// bits) in `seen`, and where that was set already, in `twice`; a second walk
-// inserts only the wedges whose `twice` bit is set into the hash table, which
-// counts them exactly, every wedge of a pair among them.  (Two candidates that
-// share a bit only bring wedges that stay below s.)  The wedges let through
-// are collected first, so that a table step has a wedge in every lane.
+// An item counted at once by one workgroup, all its wedges through a wedge map.
 //
-// What bounds it: instructions, about 25 per 64 wedges and walk and 30 per 64
-// wedges let through, and below that the list reads' latency.  So a small item
-// gets a single wave, whose barriers cost nothing and whose per-item steps are
-// not repeated by other waves; its table, bits and lists take 10.7 KB of LDS, 15
-// waves per CU.  A larger one gets four.
+// With up to kMiniWedges wedges (KIND kKindMini) every wedge goes into the hash
+// table in one step of a wave.  With more and s > 1 most candidates are met
+// once and are no pair, so they are sieved: a first walk sets, for every
+// wedge, a bit chosen by the candidate (its low bits) in `seen`, and where that
+// was set already, in `twice`; a second walk inserts only the wedges whose
+// `twice` bit is set, which counts them exactly, every wedge of a pair among
+// them.  (Two candidates that share a bit only bring wedges that stay below
+// s.)  The wedges let through are collected first, so that a table step has a
+// wedge in every lane.
+//
+// What bounds it: the chain of reads from an item to its wedges (item, list
+// bounds, members, their lists, candidates), then instructions, about 25 per
+// 64 wedges and walk and 30 per 64 wedges let through.  So the next item's
+// part of the chain is read while this one is counted, and small items get a
+// single wave, whose barriers cost nothing and whose per-item steps are not
+// repeated by other waves: 4 KB of LDS for up to 256 wedges, 10.8 KB (15 waves
+// per CU) for up to 2048, 40 KB and four waves for up to 8192.
 constexpr int kSieveList = 5 * kWave;  // wedges a wave collects
 
-template <int NT, int MINB>
-__global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
+// What the counting needs of an item.
+struct ItemDesc {
+    int32_t a, t, k0, size, first, nend, s;
+};
+
+__device__ __forceinline__ ItemDesc item_desc(const CountArgs &A, int32_t a) {
+    ItemDesc d{};
+    d.a = a;
+    if (a >= 0) {
+        d.t = (int32_t)A.tbase[a];
+        d.k0 = A.ptrI[a];
+        d.size = A.ptrI[a + 1] - d.k0;
+        d.first = cand_first(A.crank, 0, a);
+        d.nend = cand_end(A.crank, A.item_end, A.N, a);
+        d.s = A.s_item ? A.s_item[a] : A.s;
+    }
+    return d;
+}
+
+template <int KIND, int NT, int LIM, int CHUNKS, int MINB>
+__global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
     constexpr int NW = NT / kWave;
-    constexpr int LIM = NT * 16, SLOTS = LIM - kTaskPad;   // table words, home slots
-    constexpr int CHUNKS = NT * kSieveWedges / kWave;
-    constexpr int kLoad = 8;  // chunks a wave loads at a time
-    constexpr uint32_t BITS = LIM * 32;
-    constexpr int RUNCAP = NT;  // extraction: one bucket entry per bucket of a wave's block
-    static_assert(NW * kSieveList * sizeof(int32_t) >= RUNCAP * sizeof(int2), "list area");
+    constexpr bool SIEVE = KIND != kKindMini;
+    constexpr int SLOTS = LIM - kTaskPad;  // home slots of the LIM table words
+    constexpr int kLoad = SIEVE ? 8 : 4;   // chunks a wave loads at a time
+    constexpr int RUNCAP = ((LIM / 4 / NW + kWave - 1) / kWave * kWave) * NW * 2 / 8;
+    constexpr int LISTS = SIEVE ? NW * kSieveList : RUNCAP * 2;
+    static_assert(LISTS * sizeof(int32_t) >= RUNCAP * sizeof(int2), "list area");
+    static_assert(!SIEVE || (LIM & (LIM - 1)) == 0, "bits are chosen by a mask");
     __shared__ __align__(16) uint32_t tab[LIM + kWave];  // first walk: `seen`; then the table
-    __shared__ __align__(16) uint32_t twice[LIM];
-    __shared__ __align__(16) int32_t list[NW * kSieveList];
+    __shared__ __align__(16) uint32_t twice[SIEVE ? LIM : 4];
+    __shared__ __align__(16) int32_t list[LISTS];
     __shared__ int32_t adj[NT];
     __shared__ __align__(8) uint32_t marks[2 * CHUNKS];
     __shared__ int32_t msh[3 * NW];
     __shared__ int2 stack[kStack];
     __shared__ int32_t misc[kMiscWave + NW];
-    __shared__ uint64_t pool_cur[2];
-    __shared__ int32_t log_cur[2];
+    __shared__ uint64_t pool_cur[3];
+    __shared__ int32_t log_cur[3];
     if (count_idle(A)) return;  // uniform: every thread reads the same words
-    const bool one = NT == kSieveSmall;
-    const int32_t n_tasks = A.task_counts[one ? kKindSieve1 : kKindSieve4];
-    if ((int32_t)blockIdx.x >= n_tasks) return;
+    const int32_t n_items = A.task_counts[KIND * kCountStride];
+    if ((int32_t)blockIdx.x >= n_items) return;
     use_ranks(A);
-    const int32_t *const tasks = (one ? A.small_tasks : A.tiny_tasks) + (A.n_tasks - 1);
+    const int32_t *const items =
+        (KIND == kKindMini ? A.small_items : KIND == kKindSieve1 ? A.small_tasks : A.tiny_tasks) +
+        (A.n_tasks - 1);
     const int tid = threadIdx.x, lane = lane_id(), wid = wave_id();
     const Smem S{tab, reinterpret_cast<int2 *>(list), nullptr, misc, stack, tab + LIM, pool_cur,
                  log_cur};
@@ -1002,151 +1028,192 @@ __global__ __launch_bounds__(NT, MINB) void k_count_sieve(CountArgs A) {
     map.marks_all = marks;
     map.sh = msh;
     if (tid == 0) {
-        pool_cur[0] = pool_cur[1] = 0;
-        log_cur[0] = log_cur[1] = 0;
+        stage_begin(A, KIND, pool_cur, log_cur);
     }
     tab_clear<NT>(tab, LIM);
-    tab_clear<NT>(twice, LIM);
+    if (SIEVE) tab_clear<NT>(twice, LIM);
     for (int i = tid; i < 2 * CHUNKS; i += NT) marks[i] = 0;
     int64_t my_wedges = 0, my_nnz = 0, my_pairs = 0, passes = 0;  // thread 0's are used
-    __syncthreads();
-    for (int32_t r = blockIdx.x; r < n_tasks; r += gridDim.x) {
-        const int32_t t = tasks[-r];
-        if (A.mode == kModeFill && A.need && !A.need[t]) continue;
-        const int32_t a = A.task_item[t];
-        const int32_t k0 = A.ptrI[a], size = A.ptrI[a + 1] - k0;
-        const int32_t first = cand_first(A.crank, 0, a);
-        const int32_t nend = cand_end(A.crank, A.item_end, A.N, a);
-        const int32_t s = A.s_item ? A.s_item[a] : A.s;
-        map.narrow = NT == kWave || size <= kWave;
+    const int32_t stride = (int32_t)gridDim.x;
+    auto item_at = [&](int64_t q) { return q < n_items ? items[-q] : -1; };
+    // a member's list (v, -1: none) and the first entry of the walk
+    auto load_member = [&](const ItemDesc &d, int32_t &v, int32_t &b) {
+        map.narrow = NT == kWave || uniform(d.size) <= kWave;
         const int32_t k = map.member();
-        int32_t b = 0, len = 0;
-        if (k < size) {
-            const int32_t v = A.memI[k0 + k];
-            b = A.start[k0 + k] & kStartMask;
-            len = max(A.ptrS[v + 1] - b, 0);
+        v = -1;
+        b = 0;
+        if (k < d.size) {
+            v = A.memI[d.k0 + k];
+            b = A.start[d.k0 + k] & kStartMask;
         }
-        map.number(b, len);
-        const int32_t total = map.total;
-        const auto run = map.window(0);
-        // call body(j) with kLoad candidates per lane (-1: none), over the wave's chunks
-        auto walk = [&](auto body) {
-            for (int32_t u = 0; u < run.nc; u += kLoad) {
-                int32_t j[kLoad];
-                map.load(A.itmS, run, u, j);
-                body(j);
-            }
-        };
-        // home slots: a pair takes two wedges at least
-        const int32_t want =
-            min(SLOTS, max(kWave, (total / 2 + kWave - 1) / kWave * kWave));
-        const int32_t cb = count_bits(size);
-        // a range that direct counters fit needs no sieve
-        const bool sieve = make_range(first, nend, want, kTaskPad, cb).mul != 0;
-        if (sieve) {
-            walk([&](const int32_t (&j)[kLoad]) {
-                uint32_t old[kLoad];
-#pragma unroll
-                for (int u = 0; u < kLoad; ++u) {
-                    const uint32_t h = (uint32_t)j[u] & (BITS - 1u);
-                    if (j[u] >= 0) old[u] = atomicOr(&tab[h >> 5], 1u << (h & 31u));
+    };
+    auto load_end = [&](int32_t v) { return v >= 0 ? A.ptrS[v + 1] : 0; };
+    int64_t r = blockIdx.x;
+    ItemDesc cur = item_desc(A, item_at(r));
+    int32_t ahead = item_at(r + stride);  // the next item
+    int32_t v, b;
+    load_member(cur, v, b);
+    int32_t e = load_end(v);
+    __syncthreads();
+    for (; r < n_items; r += stride) {
+        const ItemDesc nxt = item_desc(A, ahead);
+        ahead = item_at(r + 2 * (int64_t)stride);
+        const int32_t t = uniform(cur.t), a = uniform(cur.a), s = uniform(cur.s);
+        const int32_t size = uniform(cur.size);
+        const int32_t first = uniform(cur.first), nend = uniform(cur.nend);
+        const bool skip = A.mode == kModeFill && A.need && !A.need[t];
+        map.narrow = NT == kWave || size <= kWave;
+        int32_t nv = -1, nb = 0, ne = 0;
+        if (!skip) {
+            map.number(b, max(e - b, 0));
+            const int32_t total = map.total;
+            const auto run = map.window(0);
+            int32_t j[kLoad];
+            if (run.nc > 0) map.load(A.itmS, run, 0, j);
+            const bool narrow = map.narrow;
+            load_member(nxt, nv, nb);
+            map.narrow = narrow;
+            // call body(j) with kLoad candidates per lane (-1: none), over the
+            // wave's chunks; the first ones are loaded
+            auto walk = [&](bool again, auto body) {
+                for (int32_t u = 0; u < run.nc; u += kLoad) {
+                    if (u > 0 || again) map.load(A.itmS, run, u, j);
+                    body();
                 }
+            };
+            // home slots: two per candidate, and a pair takes two wedges at least
+            const int32_t slots = SIEVE && s > 1 ? total / 2 : 2 * total;
+            const int32_t want =
+                min(SLOTS, max(kWave, (slots + kWave - 1) / kWave * kWave));
+            const int32_t cb = count_bits(size);
+            // a range that direct counters fit needs no sieve
+            const bool sieve =
+                SIEVE && s > 1 && make_range(first, nend, want, kTaskPad, cb).mul != 0;
+            // bits: 16 per wedge, a power of two
+            const int32_t words =
+                min(LIM, max(kWave, 1 << (32 - __clz(max(total, 2) / 2 - 1))));
+            const uint32_t bmask = (uint32_t)words * 32u - 1u;
+            if (sieve) {
+                walk(false, [&]() {
+                    uint32_t old[kLoad];
 #pragma unroll
-                for (int u = 0; u < kLoad; ++u) {
-                    const uint32_t h = (uint32_t)j[u] & (BITS - 1u);
-                    if (j[u] >= 0 && __builtin_amdgcn_ubfe(old[u], h, 1u))
-                        atomicOr(&twice[h >> 5], 1u << (h & 31u));
-                }
-            });
-            __syncthreads();
-            tab_clear<NT>(tab, LIM);
-        }
-        if (tid == 0) {
-            stack[0] = make_int2(first, nend);
-            misc[kMiscDepth] = 1;
-            misc[kMiscOverflow] = 0;
-        }
-        __syncthreads();
-        int32_t produced = 0;
-        for (;;) {
-            const int32_t depth = misc[kMiscDepth];
-            const int2 top = depth ? stack[depth - 1] : make_int2(0, 0);
-            if (depth == 0) break;
-            const Range R = make_range(top.x, top.y, want, kTaskPad, cb);
-            bool split = too_wide(R);
-            if (!split) {
-                ++passes;
-                int32_t *const mine = list + wid * kSieveList;
-                int32_t n = 0;  // wedges collected
-                bool ok = true;
-                walk([&](const int32_t (&j)[kLoad]) {
-                    uint32_t w[kLoad];
-                    if (sieve) {
-#pragma unroll
-                        for (int u = 0; u < kLoad; ++u)
-                            w[u] = twice[((uint32_t)j[u] & (BITS - 1u)) >> 5];
+                    for (int u = 0; u < kLoad; ++u) {
+                        const uint32_t h = (uint32_t)j[u] & bmask;
+                        if (j[u] >= 0) old[u] = atomicOr(&tab[h >> 5], 1u << (h & 31u));
                     }
 #pragma unroll
                     for (int u = 0; u < kLoad; ++u) {
-                        bool in = j[u] >= R.lo && j[u] < R.hi;
-                        if (sieve) in = in && __builtin_amdgcn_ubfe(w[u], (uint32_t)j[u], 1u);
-                        const uint64_t m = __ballot(in);
-                        if (m == 0) continue;
-                        if (in) mine[n + (int32_t)lanes_below(m)] = j[u];
-                        n += __popcll(m);
-                        if (n >= 4 * kWave) {
-                            __builtin_amdgcn_wave_barrier();
-                            ok &= tab_add4(tab, S.spare, R, mine[lane], mine[kWave + lane],
-                                           mine[2 * kWave + lane], mine[3 * kWave + lane]);
-                            n -= 4 * kWave;
-                            if (lane < n) mine[lane] = mine[4 * kWave + lane];
-                            __builtin_amdgcn_wave_barrier();
-                        }
+                        const uint32_t h = (uint32_t)j[u] & bmask;
+                        if (j[u] >= 0 && __builtin_amdgcn_ubfe(old[u], h, 1u))
+                            atomicOr(&twice[h >> 5], 1u << (h & 31u));
                     }
                 });
-                __builtin_amdgcn_wave_barrier();
-                if (n > 0) {
-                    int32_t j[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        j[u] = u * kWave + lane < n ? mine[u * kWave + lane] : INT32_MAX;
-                    ok &= tab_add4(tab, S.spare, R, j[0], j[1], j[2], j[3]);
-                }
-                if (!ok) misc[kMiscOverflow] = 1;
                 __syncthreads();
-                split = misc[kMiscOverflow] != 0;
-                if (!split) produced += tab_extract<NT, RUNCAP>(A, S, R, a, s, t, produced);
-                else tab_clear<NT>(tab, R.limit);
+                tab_clear<NT>(tab, words);
             }
-            __syncthreads();
+            ne = load_end(nv);
             if (tid == 0) {
-                int32_t d = depth - 1;
-                if (split) {
-                    const int32_t mid = (int32_t)(((int64_t)top.x + top.y) / 2);
-                    stack[d] = make_int2(mid, top.y);
-                    stack[d + 1] = make_int2(top.x, mid);
-                    d += 2;
-                    misc[kMiscOverflow] = 0;
-                }
-                misc[kMiscDepth] = d;
+                stack[0] = make_int2(first, nend);
+                misc[kMiscDepth] = 1;
+                misc[kMiscOverflow] = 0;
             }
             __syncthreads();
+            int32_t produced = 0;
+            // the first walk left j at the run's last chunks
+            bool again = sieve && run.nc > kLoad;
+            for (;;) {
+                const int32_t depth = misc[kMiscDepth];
+                const int2 top = depth ? stack[depth - 1] : make_int2(0, 0);
+                if (depth == 0) break;
+                const Range R = make_range(top.x, top.y, want, kTaskPad, cb);
+                bool split = too_wide(R);
+                if (!split) {
+                    ++passes;
+                    bool ok = true;
+                    if (SIEVE) {
+                        int32_t *const mine = list + wid * kSieveList;
+                        int32_t n = 0;  // wedges collected
+                        walk(again, [&]() {
+                            uint32_t w[kLoad];
+                            if (sieve) {
+#pragma unroll
+                                for (int u = 0; u < kLoad; ++u)
+                                    w[u] = twice[((uint32_t)j[u] & bmask) >> 5];
+                            }
+#pragma unroll
+                            for (int u = 0; u < kLoad; ++u) {
+                                bool in = j[u] >= R.lo && j[u] < R.hi;
+                                if (sieve) in = in && __builtin_amdgcn_ubfe(w[u], (uint32_t)j[u], 1u);
+                                const uint64_t m = __ballot(in);
+                                if (m == 0) continue;
+                                if (in) mine[n + (int32_t)lanes_below(m)] = j[u];
+                                n += __popcll(m);
+                                if (n >= 4 * kWave) {
+                                    __builtin_amdgcn_wave_barrier();
+                                    ok &= tab_add4(tab, S.spare, R, mine[lane], mine[kWave + lane],
+                                                   mine[2 * kWave + lane], mine[3 * kWave + lane]);
+                                    n -= 4 * kWave;
+                                    if (lane < n) mine[lane] = mine[4 * kWave + lane];
+                                    __builtin_amdgcn_wave_barrier();
+                                }
+                            }
+                        });
+                        again = run.nc > kLoad;
+                        __builtin_amdgcn_wave_barrier();
+                        if (n > 0) {
+                            int32_t x[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+                                x[u] = u * kWave + lane < n ? mine[u * kWave + lane] : INT32_MAX;
+                            ok &= tab_add4(tab, S.spare, R, x[0], x[1], x[2], x[3]);
+                        }
+                    } else {
+                        if (run.nc > 0) ok &= tab_add4(tab, S.spare, R, j[0], j[1], j[2], j[3]);
+                    }
+                    if (!ok) misc[kMiscOverflow] = 1;
+                    __syncthreads();
+                    split = misc[kMiscOverflow] != 0;
+                    if (!split) produced += tab_extract<NT, RUNCAP>(A, S, R, a, s, t, produced);
+                    else tab_clear<NT>(tab, R.limit);
+                }
+                __syncthreads();
+                if (tid == 0) {
+                    int32_t d = depth - 1;
+                    if (split) {
+                        const int32_t mid = (int32_t)(((int64_t)top.x + top.y) / 2);
+                        stack[d] = make_int2(mid, top.y);
+                        stack[d + 1] = make_int2(top.x, mid);
+                        d += 2;
+                        misc[kMiscOverflow] = 0;
+                    }
+                    misc[kMiscDepth] = d;
+                }
+                __syncthreads();
+            }
+            if (sieve) tab_clear<NT>(twice, words);
+            if (A.mode != kModeFill) {
+                if (tid == 0) A.task_cnt[t] = produced;
+                my_wedges += total;
+                my_nnz += size;
+                my_pairs += produced;
+            }
+            __syncthreads();
+        } else {
+            load_member(nxt, nv, nb);
+            ne = load_end(nv);
         }
-        if (sieve) tab_clear<NT>(twice, LIM);
-        if (A.mode != kModeFill) {
-            if (tid == 0) A.task_cnt[t] = produced;
-            my_wedges += total;
-            my_nnz += size;
-            my_pairs += produced;
-        }
-        __syncthreads();
+        cur = nxt;
+        b = nb;
+        e = ne;
     }
     if (tid == 0 && A.passes && A.mode != kModeFill) {
-        unsigned long long *wk = (unsigned long long *)A.passes;
+        unsigned long long *wk = stat_row(A);
         if (passes) atomicAdd(&wk[0], (unsigned long long)passes);
-        if (my_nnz) atomicAdd(&wk[1], (unsigned long long)my_nnz);
-        if (my_wedges) atomicAdd(&wk[2], (unsigned long long)my_wedges);
-        if (my_pairs) atomicAdd(&wk[3], (unsigned long long)my_pairs);
+        if (KIND != kKindMini) {  // work figures: the kernels of heavier items
+            if (my_nnz) atomicAdd(&wk[1], (unsigned long long)my_nnz);
+            if (my_wedges) atomicAdd(&wk[2], (unsigned long long)my_wedges);
+            if (my_pairs) atomicAdd(&wk[3], (unsigned long long)my_pairs);
+        }
     }
 }
 
@@ -1164,18 +1231,17 @@ __global__ __launch_bounds__(kTinyThreads) void k_count_tiny(CountArgs A) {
     constexpr int NT = kTinyThreads;
     __shared__ int32_t buf[kTinyCap * NT];  // column of lane i: buf[q * NT + i]
     __shared__ int32_t red[2][NT / kWave];
-    __shared__ uint64_t pool_cur[2];
-    __shared__ int32_t log_cur[2];
+    __shared__ uint64_t pool_cur[3];
+    __shared__ int32_t log_cur[3];
     __shared__ int32_t res[4];  // ok, offset low, offset high, first record
     if (count_idle(A)) return;
     use_ranks(A);
     if (threadIdx.x == 0) {
-        pool_cur[0] = pool_cur[1] = 0;
-        log_cur[0] = log_cur[1] = 0;
+        stage_begin(A, kKindTiny, pool_cur, log_cur);
     }
     const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
     int32_t *col = buf + tid;
-    const int32_t n_tiny = A.task_counts[2];
+    const int32_t n_tiny = A.task_counts[kKindTiny * kCountStride];
     __syncthreads();
     for (int32_t base = blockIdx.x * NT; base < n_tiny; base += gridDim.x * NT) {
         const int32_t r = base + tid;
@@ -1313,17 +1379,16 @@ __global__ __launch_bounds__(NT, MINB) void k_count_tasks(CountArgs A) {
     __shared__ int2 stack[kStack];
     __shared__ int32_t misc[kMiscWave + NT / kWave];
     __shared__ int32_t sh_task;
-    __shared__ uint64_t pool_cur[2];
-    __shared__ int32_t log_cur[2];
+    __shared__ uint64_t pool_cur[3];
+    __shared__ int32_t log_cur[3];
     const Smem S{tab, runs, taken, misc, stack, tab + LIM, pool_cur, log_cur};
     if (count_idle(A)) return;  // uniform: every thread reads the same words
     use_ranks(A);
     if (threadIdx.x == 0) {
-        pool_cur[0] = pool_cur[1] = 0;
-        log_cur[0] = log_cur[1] = 0;
+        stage_begin(A, kKindGroups, pool_cur, log_cur);
     }
     tab_clear<NT>(tab, LIM);
-    const int32_t n_groups = A.task_counts[1];
+    const int32_t n_groups = A.task_counts[kKindGroups * kCountStride];
     int64_t passes = 0;
     int64_t my_wedges = 0, my_nnz = 0, my_pairs = 0;
     __syncthreads();
@@ -1380,7 +1445,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_tasks(CountArgs A) {
     }
     if (A.passes && A.mode != kModeFill) {
         // one atomic per counter and workgroup (same-address atomics serialize)
-        unsigned long long *wk = (unsigned long long *)A.passes;
+        unsigned long long *wk = stat_row(A);
         int64_t w = my_wedges;
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) w += __shfl_xor(w, d, kWave);
@@ -1396,7 +1461,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_tasks(CountArgs A) {
         }
     }
     if (threadIdx.x == 0 && passes && A.passes)
-        atomicAdd((unsigned long long *)A.passes, (unsigned long long)passes);
+        atomicAdd(stat_row(A), (unsigned long long)passes);
 }
 
 // ----------------------------------------------------------- task lists
@@ -1419,9 +1484,12 @@ __device__ __forceinline__ bool is_tiny(const PlanItems &I, int32_t a, int64_t c
 // Tasks of item a and the kind of kernel that counts them.
 __device__ __forceinline__ int32_t item_tasks(const PlanItems &I, int32_t a, int64_t c,
                                               int32_t tiny_max, int32_t &kind, int32_t &ranges) {
+    ranges = 0;
+    kind = kKindTiny;
+    if (c > 0 && c <= I.small_max && is_tiny(I, a, c, tiny_max)) return 1;
     const int32_t direct = direct_tasks(I, a, c, kind, ranges);
     if (direct > 0) return direct;
-    kind = c > I.small_max ? kKindGroups : is_tiny(I, a, c, tiny_max) ? kKindTiny : kKindSmall;
+    kind = c > I.small_max ? kKindGroups : kKindSmall;
     return plan_parts(I, c, a);
 }
 
@@ -1460,10 +1528,11 @@ __global__ __launch_bounds__(256) void k_task_count(const int64_t *cost, PlanIte
     __syncthreads();
     // one atomic per sum and block (same-address atomics serialize)
     if (threadIdx.x < 1 + kKinds && sh[threadIdx.x])
-        atomicAdd((unsigned long long *)&sums[threadIdx.x], (unsigned long long)sh[threadIdx.x]);
+        atomicAdd((unsigned long long *)&sums[(blockIdx.x % kSumRows) * kTotalCols + threadIdx.x],
+                  (unsigned long long)sh[threadIdx.x]);
 }
 
-// counts[kind] receives the length of each kind's list.
+// counts[kind * kCountStride] receives the length of each kind's list.
 //
 // Each workgroup fills the tasks of a contiguous chunk of items.  The slots
 // of the two lists are claimed with one global atomic per list and workgroup
@@ -1503,7 +1572,7 @@ __global__ __launch_bounds__(256) void k_task_fill(
     }
     __syncthreads();
     if (threadIdx.x < kKinds && sh[threadIdx.x])
-        sh[threadIdx.x] = atomicAdd(&counts[threadIdx.x], sh[threadIdx.x]);
+        sh[threadIdx.x] = atomicAdd(&counts[threadIdx.x * kCountStride], sh[threadIdx.x]);
     __syncthreads();
     // pass 2: tasks, and the list entries at the claimed slots
     for (int64_t base = lo + (threadIdx.x & ~(kWave - 1)); base < hi; base += blockDim.x) {
@@ -1542,9 +1611,11 @@ __global__ __launch_bounds__(256) void k_task_fill(
             tiny_tasks[at] = (int32_t)t0;
             tiny_items[at] = (int32_t)a;
         } else if (kind == kKindSieve1) {
-            small_tasks[cap - 1 - at] = (int32_t)t0;
+            small_tasks[cap - 1 - at] = (int32_t)a;
         } else if (kind == kKindSieve4) {
-            tiny_tasks[cap - 1 - at] = (int32_t)t0;
+            tiny_tasks[cap - 1 - at] = (int32_t)a;
+        } else if (kind == kKindMini) {
+            small_items[cap - 1 - at] = (int32_t)a;
         } else if (kind == kKindFlat) {
             for (int32_t p = 0; p < n; ++p) groups[cap - 1 - (at + p)] = (int32_t)(t0 + p);
         } else {
@@ -1571,7 +1642,7 @@ constexpr int32_t kLaneRec = 32;
 __global__ __launch_bounds__(256) void k_stage_copy(CountArgs A, int32_t n_rec) {
     if (A.abort && *A.abort != 0) return;
     use_ranks(A);
-    if (n_rec < 0) n_rec = min(*A.log_head, A.log_cap);
+    if (n_rec < 0) n_rec = min(A.log_own + *A.log_head, A.log_cap);
     const int lane = lane_id();
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
@@ -1673,37 +1744,38 @@ hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, const PlanItems
 
 hipError_t launch_count(hipStream_t st, const CountArgs &A, hipEvent_t mid) {
     if (A.N <= 0) return hipSuccess;
-    const auto any = [&](int kind) { return ((A.kinds >> kind) & 1u) != 0; };
-    if (any(kKindTiny) && A.tune.tiny_max_wedges > 0 && !A.full) {
-        // LDS (the 32 KB candidate buffer) allows four workgroups per CU
-        k_count_tiny<<<std::max(1, A.n_cu * 4), kTinyThreads, 0, st>>>(A);
-    }
-    if (any(kKindSmall)) {
-        const int gs = std::max(1, A.n_cu * A.tune.small_grid_per_cu);
+    const int32_t *g = A.grid;
+    if (g[kKindTiny] > 0 && A.tune.tiny_max_wedges > 0 && !A.full)
+        k_count_tiny<<<g[kKindTiny], kTinyThreads, 0, st>>>(A);
+    if (g[kKindSmall] > 0) {
         switch (A.tune.small_slots) {
-        case 512: k_count_small<512><<<gs, kWave, 0, st>>>(A); break;
-        case 2048: k_count_small<2048><<<gs, kWave, 0, st>>>(A); break;
-        default: k_count_small<1024><<<gs, kWave, 0, st>>>(A); break;
+        case 512: k_count_small<512><<<g[kKindSmall], kWave, 0, st>>>(A); break;
+        case 2048: k_count_small<2048><<<g[kKindSmall], kWave, 0, st>>>(A); break;
+        default: k_count_small<1024><<<g[kKindSmall], kWave, 0, st>>>(A); break;
         }
     }
+    if (g[kKindMini] > 0)
+        k_count_item<kKindMini, kWave, 2 * kMiniWedges + kTaskPad, kMiniWedges / kWave, 5>
+            <<<g[kKindMini], kWave, 0, st>>>(A);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (any(kKindGroups) || any(kKindFlat)) k_reset_queue<<<1, 1, 0, st>>>(A.queue);
+    if (g[kKindGroups] > 0 || g[kKindFlat] > 0) k_reset_queue<<<1, 1, 0, st>>>(A.queue);
     if (mid) {
         e = hipEventRecord(mid, st);
         if (e != hipSuccess) return e;
     }
-    if (any(kKindFlat)) {
+    if (g[kKindFlat] > 0) {
         e = launch_count_flat(st, A);
         if (e != hipSuccess) return e;
     }
-    // LDS allows 15 one-wave and four 256-thread workgroups per CU
-    if (any(kKindSieve4))
-        k_count_sieve<kSieveLarge, 4><<<std::max(1, A.n_cu * 4), kSieveLarge, 0, st>>>(A);
-    if (any(kKindSieve1))
-        k_count_sieve<kSieveSmall, 4><<<std::max(1, A.n_cu * 15), kSieveSmall, 0, st>>>(A);
-    if (any(kKindGroups)) {
-        const int gh = std::max(1, A.n_cu * A.tune.task_grid_per_cu);
+    if (g[kKindSieve4] > 0)
+        k_count_item<kKindSieve4, kSieveLarge, kSieveLarge * 16, kSieveLarge * kSieveWedges / kWave, 4>
+            <<<g[kKindSieve4], kSieveLarge, 0, st>>>(A);
+    if (g[kKindSieve1] > 0)
+        k_count_item<kKindSieve1, kSieveSmall, kSieveSmall * 16, kSieveSmall * kSieveWedges / kWave, 4>
+            <<<g[kKindSieve1], kSieveSmall, 0, st>>>(A);
+    if (g[kKindGroups] > 0) {
+        const int gh = g[kKindGroups];
         switch (A.tune.task_slots) {
         case 4480: k_count_tasks<4480, 4, 256><<<gh, 256, 0, st>>>(A); break;
         case 13440: k_count_tasks<13440, 2, 256><<<gh, 256, 0, st>>>(A); break;
@@ -1714,6 +1786,48 @@ hipError_t launch_count(hipStream_t st, const CountArgs &A, hipEvent_t mid) {
         }
     }
     return hipGetLastError();
+}
+
+int32_t set_grids(CountArgs &A, const int64_t *items) {
+    // workgroups a CU holds: tiny four (32 KB of LDS each), item kernels 20 of one
+    // wave (registers), 15 and four (LDS), direct counters two; the hashed
+    // kernels as tuned
+    const int per_cu[kKinds] = {A.tune.small_grid_per_cu, A.tune.task_grid_per_cu, 4, 2, 15, 4, 20};
+    int32_t total = 0;
+    for (int k = 0; k < kKinds; ++k) {
+        int64_t g = std::max(1, A.n_cu * per_cu[k]);
+        if (items) {
+            const int64_t n = k == kKindTiny ? (items[k] + kTinyThreads - 1) / kTinyThreads : items[k];
+            // items in groups or ranges take several workgroups each
+            if (n == 0 || (k != kKindGroups && k != kKindFlat)) g = std::min(g, n);
+        }
+        A.grid[k] = (int32_t)g;
+        total += (int32_t)g;
+    }
+    return total;
+}
+
+void set_chunks(CountArgs &A) {
+    // Chunks so small that a kind's workgroups hold a share of pool and log: 1/16
+    // for the kernels whose ranges bring many pairs (so that what is left of a
+    // chunk when the next range does not fit it is little), 1/64 for the others.
+    int64_t pool = 0, log = 0;
+    for (int k = 0; k < kKinds; ++k) {
+        const bool big = k == kKindGroups || k == kKindFlat || k == kKindSieve4;
+        const int64_t parts = (big ? 16 : 64) * std::max<int64_t>(A.grid[k], 1);
+        A.pool_chunk[k] =
+            std::max<int64_t>(kPoolChunkMin, std::min<int64_t>(1 << 16, A.pool_cap / parts));
+        A.log_chunk[k] =
+            (int32_t)std::max<int64_t>(8, std::min<int64_t>(256, (int64_t)A.log_cap / parts));
+        A.pool_first[k] = pool;
+        A.log_first[k] = (int32_t)log;
+        pool += A.pool_chunk[k] * A.grid[k];
+        log += (int64_t)A.log_chunk[k] * A.grid[k];
+    }
+    // first chunks without atomics, where that leaves room for others
+    const bool fits = A.mode == kModeStage && pool * 2 <= A.pool_cap && log * 2 <= A.log_cap;
+    A.pool_own = fits ? pool : 0;
+    A.log_own = fits ? (int32_t)log : 0;
 }
 
 hipError_t launch_stage_copy(hipStream_t st, const CountArgs &A, int32_t n_rec) {

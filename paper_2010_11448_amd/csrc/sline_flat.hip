@@ -92,10 +92,10 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
     __shared__ __align__(8) uint32_t marks[2 * kFlatChunks];
     __shared__ int32_t msh[3 * NW], wtot[NW];
     __shared__ int32_t sh_task, sh_hits, sh_ok;
-    __shared__ uint64_t sh_off, pool_cur[2];
-    __shared__ int32_t log_cur[2];
+    __shared__ uint64_t sh_off, pool_cur[3];
+    __shared__ int32_t log_cur[3];
     if (count_idle(A)) return;  // uniform: every thread reads the same words
-    const int32_t n_flat = A.task_counts[kKindFlat];
+    const int32_t n_flat = A.task_counts[kKindFlat * kCountStride];
     if (n_flat == 0) return;
     use_ranks(A);
     const int tid = threadIdx.x, lane = lane_id(), wid = wave_id();
@@ -105,8 +105,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
     for (int i = tid; i < kFlatWords / 16; i += NT) bmp[i] = make_uint4(0u, 0u, 0u, 0u);
     for (int i = tid; i < 2 * kFlatChunks; i += NT) marks[i] = 0;
     if (tid == 0) {
-        pool_cur[0] = pool_cur[1] = 0;
-        log_cur[0] = log_cur[1] = 0;
+        stage_begin(A, kKindFlat, pool_cur, log_cur);
         sh_hits = 0;
         sh_task = atomicAdd(A.queue + 1, 2);
     }
@@ -508,7 +507,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
         cur = nxt;
     }
     if (tid == 0 && A.passes && A.mode != kModeFill) {
-        unsigned long long *wk = (unsigned long long *)A.passes;
+        unsigned long long *wk = stat_row(A);
         if (passes) atomicAdd(&wk[0], (unsigned long long)passes);
         if (my_nnz) atomicAdd(&wk[1], (unsigned long long)my_nnz);
         if (my_wedges) atomicAdd(&wk[2], (unsigned long long)my_wedges);
@@ -527,7 +526,7 @@ hipError_t launch_flat_bounds(hipStream_t st, const int32_t *ptrS, const int32_t
 }
 
 hipError_t launch_count_flat(hipStream_t st, const CountArgs &A) {
-    k_count_flat<<<std::max(1, A.n_cu * 2), kFlatThreads, 0, st>>>(A);
+    k_count_flat<<<A.grid[kKindFlat], kFlatThreads, 0, st>>>(A);
     return hipGetLastError();
 }
 

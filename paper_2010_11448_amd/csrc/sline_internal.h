@@ -114,11 +114,14 @@ constexpr int32_t kFlatKeep = 32 * kFlatThreads;
 constexpr int32_t kKeepWidth = kFlatWords / 2 * 32;
 constexpr int32_t kKeepRanks = kFlatWords / 4;  // pairs of a range counted at a time
 
-// Sieved counting (k_count_sieve): with s > 1, an item of at most
-// kSieveWedges * threads wedges and a member per thread is counted by one
-// workgroup of kSieveSmall or kSieveLarge threads.
+// Flat-table counting by one workgroup per item (k_count_item): up to kMiniWedges
+// wedges in one step of a wave; sieved, with s > 1, up to kSieveWedges * threads
+// (kSieveSmall or kSieveLarge threads); with s = 1, where nothing can be
+// sieved out, up to kOnesWedges.  A member per thread, in a wave per lane.
+constexpr int32_t kMiniWedges = 256;
 constexpr int32_t kSieveSmall = 64, kSieveLarge = 256;
 constexpr int32_t kSieveWedges = 32;
+constexpr int32_t kOnesWedges = 480;
 
 // The list positions of all these kernels fit a 32-bit byte offset: builds with
 // this many incidences or more use the hashed kernels alone.
@@ -188,7 +191,8 @@ enum : int32_t {
     kKindFlat = 3,    // direct counters
     kKindSieve1 = 4,  // sieved, kSieveSmall threads
     kKindSieve4 = 5,  // sieved, kSieveLarge threads
-    kKinds = 6,
+    kKindMini = 6,    // one wave, every wedge at once
+    kKinds = 7,
 };
 
 // Tasks of item a when every wedge of it is counted by one of the kernels
@@ -198,15 +202,19 @@ enum : int32_t {
 __device__ __forceinline__ int32_t direct_tasks(const PlanItems &I, int32_t a, int64_t cost,
                                                 int32_t &kind, int32_t &ranges) {
     ranges = 0;
-    kind = kKindFlat;
-    if (cost <= I.small_max || I.dense_min <= 0 || I.full) return 0;
+    if (cost <= 0 || I.dense_min <= 0 || I.full) return 0;
     const int32_t size = I.ptrI[a + 1] - I.ptrI[a];
     const int32_t s = I.s_item ? I.s_item[a] : I.s;
-    if (s > 1 && cost <= kSieveWedges * kSieveLarge && size <= kSieveLarge) {
-        const bool one = cost <= kSieveWedges * kSieveSmall && size <= kSieveSmall;
-        kind = one ? kKindSieve1 : kKindSieve4;
-        return 1;
+    if (size <= kSieveSmall) {
+        kind = kKindMini;
+        if (cost <= kMiniWedges) return 1;
+        kind = kKindSieve1;
+        if (cost <= (s > 1 ? kSieveWedges * kSieveSmall : kOnesWedges)) return 1;
     }
+    kind = kKindSieve4;
+    if (cost <= I.small_max) return 0;
+    if (s > 1 && cost <= kSieveWedges * kSieveLarge && size <= kSieveLarge) return 1;
+    kind = kKindFlat;
     if (size > kFlatMaxSize) return 0;
     const int32_t first = cand_first(I.crank, 0, a), nend = cand_end(I.crank, I.item_end, I.N, a);
     if (flat_keeps(s, cost, size)) {
@@ -229,6 +237,14 @@ __device__ __forceinline__ int32_t direct_tasks(const PlanItems &I, int32_t a, i
 // receives row_ptr[m], [1] becomes 1 if row_ptr[0] != 0 or row_ptr decreases.
 hipError_t launch_check_rowptr(hipStream_t st, const int32_t *rp, int32_t m, int32_t *seen);
 
+// Counters that every workgroup adds to are kept in kSumRows rows of a cache line
+// or more, added up when they are read: atomics on one address take about 10 ns
+// each, one after the other (12,000 of them at the end of a kernel: 0.1 ms).
+constexpr int kSumRows = 64;
+constexpr int kTotalCols = 16;  // cost totals [0..2], the planner's sums [3..]
+constexpr int kStatCols = 8;    // table passes, task kernel incidences, wedges, pairs
+constexpr int kCountStride = 16;  // words between two kinds' list lengths
+
 // A read-back: up to kMost runs of 32-bit words copied to host memory by one
 // launch (a copy per run would cost a launch each).
 struct Report {
@@ -237,6 +253,17 @@ struct Report {
     const int32_t *src[kMost];
     int32_t *dst[kMost];
     int32_t words[kMost];
+    // sums over kSumRows rows of int64: `vals` columns of rows of `cols`
+    int n_sums = 0;
+    const int64_t *rows[2];
+    int64_t *sums[2];
+    int32_t cols[2], vals[2];
+    void add_rows(int64_t *to, const int64_t *from, int32_t row_cols, int32_t n_vals) {
+        rows[n_sums] = from;
+        sums[n_sums] = to;
+        cols[n_sums] = row_cols;
+        vals[n_sums++] = n_vals;
+    }
     void add(void *to, const void *from, int32_t bytes) {
         src[n] = static_cast<const int32_t *>(from);
         dst[n] = static_cast<int32_t *>(to);
@@ -333,8 +360,8 @@ hipError_t launch_mark_lookup(hipStream_t st, const PlanItems &I, const int32_t 
 // listed in small_tasks, with its item in small_items (W_a <= small_max), or
 // in big_tasks; counts[0] / [1]
 // receive the list lengths.
-// sums (zeroed by the caller): [0] receives the ranges of the items counted
-// directly, each of which stages its pairs by itself, [1 + kind] the items of
+// sums (kSumRows rows of kTotalCols, zeroed by the caller): [0] receives the ranges
+// of the items counted directly, each of which stages its pairs by itself, [1 + kind] the items of
 // each kind.
 // bound != 0: instead of P_a, no fewer tasks than the item can come to have in a
 // replay of the same lists at any larger s.
@@ -346,10 +373,10 @@ hipError_t launch_task_count(hipStream_t st, const int64_t *cost, const PlanItem
 // With `abort` given, the kernel does nothing while *abort != 0.
 // Tiny one-task items (Tuning::tiny_max_wedges) go to tiny_tasks /
 // tiny_items instead of the small lists; counts[2] receives their number.
-// The tasks of items counted without hashed wedge lists go to the ends of three
-// lists, each with `cap` entries, room for every task: big_tasks[cap - 1 - i] for
-// i < counts[kKindFlat], small_tasks (kKindSieve1) and tiny_tasks (kKindSieve4)
-// likewise.
+// Items of the other kinds go to the ends of the lists, each with `cap` entries,
+// room for every task: big_tasks[cap - 1 - i] holds task i < counts[kKindFlat];
+// small_tasks (kKindSieve1), tiny_tasks (kKindSieve4) and small_items
+// (kKindMini) hold items in the same way.
 hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, const PlanItems &I,
                             int32_t tiny_max, int32_t group, const int64_t *tbase,
                             int32_t *task_item, int32_t *task_part, int32_t *small_tasks,
@@ -392,12 +419,13 @@ struct CountArgs {
     const int64_t *cost;         // W_a per item
     const int32_t *start;        // back-pointers per item incidence (see launch_cost)
     const int32_t *task_item, *task_part;
+    const int64_t *tbase;        // first task of each item
     int32_t n_tasks;
     const int32_t *small_tasks, *big_tasks;
     const int32_t *small_items;  // item of each small task
     const int32_t *tiny_tasks, *tiny_items;  // tiny tasks (one lane each) and their items
-    const int32_t *task_counts;  // list lengths by kind
-    uint32_t kinds;              // bit per kind that has items (all set where the host cannot know)
+    const int32_t *task_counts;  // list lengths: task_counts[kind * kCountStride]
+    int32_t grid[kKinds];        // workgroups per kind (0: no items)
     const int32_t *bnd;          // bounds table of the direct path (launch_flat_bounds)
     int32_t *queue;              // queue heads: task groups, direct tasks (reset by the launcher)
     int32_t *task_cnt;           // count mode: pairs per task
@@ -407,16 +435,21 @@ struct CountArgs {
     // room are flagged in need[] (need_count counts them) for a fill pass
     int32_t *pool_b, *pool_w;    // pool_w null: weights not staged
     int64_t pool_cap;
-    int64_t pool_chunk;          // pool pairs a workgroup reserves at a time
+    // Pool pairs and log records a workgroup reserves at a time, by kind.  The
+    // workgroups' first chunks lie at pool_first / log_first of their kind, one
+    // after the other, pool_own pairs and log_own records in all (0: none are
+    // set aside).
+    int64_t pool_chunk[kKinds], pool_first[kKinds], pool_own;
+    int32_t log_chunk[kKinds], log_first[kKinds], log_own;
     unsigned long long *pool_head;
     StageRec *log;
     int32_t log_cap;
-    int32_t log_chunk;           // log records a workgroup reserves at a time
     int32_t *log_head;
     int32_t *need;
     int32_t *need_count;
-    int64_t *passes;             // [0] table passes; task kernel work: [1] incidences,
-                                 // [2] wedges, [3] pairs (count and stage modes)
+    int64_t *passes;             // kSumRows rows of kStatCols: [0] table passes; task kernel
+                                 // work: [1] incidences, [2] wedges, [3] pairs (count and
+                                 // stage modes)
     int32_t *err;
     Tuning tune;
     int32_t n_cu;
@@ -434,6 +467,12 @@ struct CountArgs {
     // nothing (the plan's bounds were exceeded, or its input is malformed).
     const int32_t *abort;
 };
+constexpr int64_t kPoolChunkMin = 256;   // pairs a workgroup reserves at least
+// Workgroups per kind for `items` items of each (null: not known, the most that
+// are useful); returns their number.  Needs tune and n_cu.
+int32_t set_grids(CountArgs &a, const int64_t *items);
+// Chunks of pool and log for the grids, pool_cap, log_cap and mode.
+void set_chunks(CountArgs &a);
 // `mid` (may be null) is recorded between the one-wave kernel and the task kernel.
 hipError_t launch_count(hipStream_t st, const CountArgs &a, hipEvent_t mid = nullptr);
 // The direct counting kernel alone (launch_count calls it).

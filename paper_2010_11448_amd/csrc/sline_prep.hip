@@ -147,6 +147,14 @@ __global__ __launch_bounds__(kWave) void k_report(Report R) {
     for (int i = 0; i < R.n; ++i)
         for (int32_t w = threadIdx.x; w < R.words[i]; w += kWave)
             R.dst[i][w] = R.src[i][w];
+    for (int i = 0; i < R.n_sums; ++i) {
+        static_assert(kSumRows == kWave, "a lane per row");
+        const int64_t *row = R.rows[i] + (int64_t)threadIdx.x * R.cols[i];
+        for (int32_t v = 0; v < R.vals[i]; ++v) {
+            const int64_t s = wave_sum(row[v]);
+            if (threadIdx.x == 0) R.sums[i][v] = s;
+        }
+    }
 }
 
 // One wave per row (grid-stride): the row id of every incidence, member range
@@ -226,11 +234,23 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_partials(TA *partial, int
     }
 }
 
-template <typename TI, typename TO>
+// SUMS: partial holds the tiles' sums, not yet scanned, and every workgroup adds
+// up those before its own (few tiles: less than a launch to scan them costs).
+constexpr int64_t kScanSumTiles = 1024;
+
+template <typename TI, typename TO, bool SUMS>
 __global__ __launch_bounds__(kScanThreads) void k_scan_down(const TI *in, int64_t n,
                                                             const TO *partial, TO *out) {
     __shared__ TO sh[kScanThreads / kWave + 1];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    TO before = 0;
+    if (SUMS) {
+        TO s = 0;
+        for (int i = threadIdx.x; i < (int)blockIdx.x; i += kScanThreads) s += partial[i];
+        block_excl_scan<TO>(s, sh, before);
+    } else {
+        before = partial[blockIdx.x];
+    }
     TO v[kScanItems];
     TO s = 0;
 #pragma unroll
@@ -240,19 +260,19 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const TI *in, int64_
     }
     TO tot;
     TO ex = block_excl_scan<TO>(s, sh, tot);
-    TO run = partial[blockIdx.x] + ex;
+    TO run = before + ex;
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
         if (base + q < n) out[base + q] = run;
         run += v[q];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = partial[blockIdx.x] + tot;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = before + tot;
 }
 
 // Short scans: one workgroup, one launch instead of three (which cost about
 // 2.5 us each, as much as 20,000 entries take here).
 constexpr int kScanOneThreads = 1024;
-constexpr int64_t kScanOneMax = 65536;
+constexpr int64_t kScanOneMax = 16384;
 
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const TI *in, int64_t n, TO *out) {
@@ -528,7 +548,8 @@ __global__ void k_filter_scatter(const int32_t *itmM, int64_t nnz, const int32_t
 // W_a = sum over members v of the number of kept items b > a in N_s(v); 0 for
 // items with |S_a| < s.  For every member incidence k of a kept item,
 // start[k] = index in itmS of the first item > a in N_s(v) (the back-pointer
-// where a's walk over v begins).  totals: kept items, their incidences, W.
+// where a's walk over v begins).  totals (in rows): kept items, their
+// incidences, W.
 __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t *memI,
                                               int32_t N, int32_t s, const int32_t *s_item,
                                               const int32_t *ptrS, const int32_t *itmS,
@@ -579,7 +600,9 @@ __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t
     if (threadIdx.x < 3) {
         int64_t t = 0;
         for (int w = 0; w < 256 / kWave; ++w) t += red[threadIdx.x][w];
-        if (t) atomicAdd((unsigned long long *)&totals[threadIdx.x], (unsigned long long)t);
+        if (t)
+            atomicAdd((unsigned long long *)&totals[(blockIdx.x % kSumRows) * kTotalCols + threadIdx.x],
+                      (unsigned long long)t);
     }
 }
 
@@ -764,8 +787,12 @@ static hipError_t scan_impl(hipStream_t st, const TI *in, int64_t n, TO *out, TO
     }
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
     k_scan_reduce<TI, TO><<<(unsigned)nb, kScanThreads, 0, st>>>(in, n, partial);
-    k_scan_partials<TO><<<1, kScanThreads, 0, st>>>(partial, nb);
-    k_scan_down<TI, TO><<<(unsigned)nb, kScanThreads, 0, st>>>(in, n, partial, out);
+    if (nb <= kScanSumTiles) {
+        k_scan_down<TI, TO, true><<<(unsigned)nb, kScanThreads, 0, st>>>(in, n, partial, out);
+    } else {
+        k_scan_partials<TO><<<1, kScanThreads, 0, st>>>(partial, nb);
+        k_scan_down<TI, TO, false><<<(unsigned)nb, kScanThreads, 0, st>>>(in, n, partial, out);
+    }
     return hipGetLastError();
 }
 
