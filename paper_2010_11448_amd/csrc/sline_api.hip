@@ -2724,7 +2724,7 @@ sline_status squeeze_impl(sline_ctx *c, int32_t N, const sline_edges *L, uint32_
     sline_graph g{};
     auto plan = [&](Arena &A, int32_t *&err, int32_t *&flag, int32_t *&newid, int32_t *&p32,
                     int64_t *&fwd, int32_t *&deg, int64_t *&off, int64_t *&p64, SortBufs &B,
-                    int32_t *&colT, int32_t *&kT) {
+                    int32_t *&w0, int32_t *&w1) {
         err = A.take<int32_t>(4);
         flag = A.take<int32_t>((int64_t)N + 1);
         newid = A.take<int32_t>((int64_t)N + 1);
@@ -2734,18 +2734,18 @@ sline_status squeeze_impl(sline_ctx *c, int32_t N, const sline_edges *L, uint32_
         off = A.take<int64_t>((int64_t)N + 1);
         p64 = A.take<int64_t>(scan_partials((int64_t)N + 1));
         B = plan_sort(A, std::max<int64_t>(n, 1), N);
-        colT = A.take<int32_t>(std::max<int64_t>(n, 1));
-        kT = A.take<int32_t>(std::max<int64_t>(n, 1));
+        w0 = A.take<int32_t>(std::max<int64_t>(n, 1));
+        w1 = A.take<int32_t>(std::max<int64_t>(n, 1));
     };
-    int32_t *err, *flag, *newid, *p32, *deg, *colT, *kT;
+    int32_t *err, *flag, *newid, *p32, *deg, *w0, *w1;
     int64_t *fwd, *off, *p64;
     SortBufs B{};
     Arena sz;
-    plan(sz, err, flag, newid, p32, fwd, deg, off, p64, B, colT, kT);
+    plan(sz, err, flag, newid, p32, fwd, deg, off, p64, B, w0, w1);
     TempBlock T(c);
     Arena A;
     A.base = T.get(sz.off, "squeeze");
-    plan(A, err, flag, newid, p32, fwd, deg, off, p64, B, colT, kT);
+    plan(A, err, flag, newid, p32, fwd, deg, off, p64, B, w0, w1);
     hip_check(c, launch_fill_i32(st, err, 4, 0), "zero flags");
     hip_check(c, launch_fill_i32(st, flag, (int64_t)N + 1, 0), "zero flags");
     // 1. items present (and the pairs checked: ids in range, a < b, sorted)
@@ -2781,16 +2781,19 @@ sline_status squeeze_impl(sline_ctx *c, int32_t N, const sline_edges *L, uint32_
             throw Fail{SLINE_ENOMEM};
         }
         hip_check(c, launch_old_ids(st, flag, newid, N, g.old_id), "old ids");
-        // 3. the pairs by second item (transpose), by first item (runs)
-        hip_check(c, launch_transpose(st, L->b, n, N, L->a, B.rsK, B.rsV, B.hist, B.part32, B.ptrT,
-                                      colT, kT, nullptr),
+        // 3. the pairs by second item (sorted with their first items and weights),
+        // by first item (runs)
+        int32_t *const rsW[2] = {w0, w1};
+        hip_check(c, launch_sort_values(st, L->b, L->a, weights ? L->w : nullptr, n, N, B.rsK, B.rsV,
+                                        rsW, B.hist, B.part32, B.ptrT),
                   "pairs by second item");
+        const int at = (transpose_passes(N) - 1) & 1;
         hip_check(c, launch_run_starts(st, L->a, n, N, fwd), "pairs by first item");
         // 4. degrees, row pointers, rows
         hip_check(c, launch_degrees(st, fwd, B.ptrT, N, deg), "degrees");
         hip_check(c, launch_scan_i32_to_i64(st, deg, N, off, p64), "row offsets");
-        hip_check(c, launch_row_ptr(st, flag, newid, off, N, g.n_nodes, g.row_ptr), "row pointers");
-        hip_check(c, launch_adj_fill(st, N, flag, newid, off, B.ptrT, colT, kT, fwd, L->b,
+        hip_check(c, launch_row_ptr(st, flag, newid, off, fwd, B.ptrT, N, g.n_nodes, g.row_ptr), "row pointers");
+        hip_check(c, launch_adj_fill(st, n, newid, off, B.rsK[at], B.rsV[at], rsW[at], fwd, L->a, L->b,
                                      weights ? L->w : nullptr, g.col, g.w),
                   "adjacency");
         sync(c, "adjacency");

@@ -305,6 +305,14 @@ hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int
                             int32_t *hist, int32_t *part32, int32_t *ptrT, int32_t *colT,
                             int32_t *kT, int32_t *posT);
 
+// The same sort of keys that carry a value v, and w if not null: with p =
+// transpose_passes(n) - 1, the sorted values end in rsV[p & 1] and rsW[p & 1], and
+// ptr[x] (n + 1 entries) is the first key >= x.
+hipError_t launch_sort_values(hipStream_t st, const int32_t *key, const int32_t *v,
+                              const int32_t *w, int64_t nnz, int32_t n, int32_t *const rsK[2],
+                              int32_t *const rsV[2], int32_t *const rsW[2], int32_t *hist,
+                              int32_t *part32, int32_t *ptr);
+
 // s filter: N_s(v) = the items of N(v) with |S| >= s (s_item[it] for item it
 // when s_item is given), every list in its order, written to itmS with list
 // pointers ptrS (M + 1 entries).  pos (nnz + 1 entries) receives the kept
@@ -553,12 +561,17 @@ hipError_t launch_old_ids(hipStream_t st, const int32_t *flag, const int32_t *ne
 hipError_t launch_run_starts(hipStream_t st, const int32_t *a, int64_t n, int32_t N, int64_t *ptr);
 hipError_t launch_degrees(hipStream_t st, const int64_t *fwd, const int32_t *ptrT, int32_t N,
                           int32_t *deg);
-hipError_t launch_row_ptr(hipStream_t st, const int32_t *flag, const int32_t *newid,
-                          const int64_t *off, int32_t N, int32_t n_nodes, int64_t *row_ptr);
-hipError_t launch_adj_fill(hipStream_t st, int32_t N, const int32_t *flag, const int32_t *newid,
-                           const int64_t *off, const int32_t *ptrT, const int32_t *colT,
-                           const int32_t *kT, const int64_t *fwd, const int32_t *b,
-                           const int32_t *w, int32_t *ocol, int32_t *ow);
+// Row pointers from off; then off[x] and fwd[x] (from launch_run_starts) are
+// what launch_adj_fill adds to a pair's position for its slot: bwd and fwd there.
+hipError_t launch_row_ptr(hipStream_t st, const int32_t *flag, const int32_t *newid, int64_t *off,
+                          int64_t *fwd, const int32_t *ptrT, int32_t N, int32_t n_nodes,
+                          int64_t *row_ptr);
+// Neighbours (and weights, ow may be null) of all rows: n pairs (a, b, w), and
+// the same sorted by second item as (y, c, v).
+hipError_t launch_adj_fill(hipStream_t st, int64_t n, const int32_t *newid, const int64_t *bwd,
+                           const int32_t *y, const int32_t *c, const int32_t *v, const int64_t *fwd,
+                           const int32_t *a, const int32_t *b, const int32_t *w, int32_t *ocol,
+                           int32_t *ow);
 hipError_t launch_iota(hipStream_t st, int32_t *p, int64_t n);
 // comp[x] = smallest item of x's component in the graph of the pairs.
 hipError_t launch_components(hipStream_t st, const int32_t *a, const int32_t *b, int64_t n,

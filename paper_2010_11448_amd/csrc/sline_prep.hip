@@ -343,9 +343,12 @@ __global__ void k_start_from_map(int64_t nnz, const int32_t *map, int32_t *start
 // and the ballots; so few passes of wide digits.  10^7 keys of 21 bits, counts,
 // scans and moves: 3 passes of 7 bits 0.43 ms, 6 of 4 bits (counters per
 // thread) 0.68 ms.  22,000 keys of 13 bits: 2 passes 25 us, 4 passes 100 us.
-constexpr int kRsBits = 8;
+// 9 bits, as keys of 17 and 18 bits then take two passes and not three: 4.5*10^7
+// of 18 bits with two values 1.14 ms (three passes with one value 1.44).
+constexpr int kRsBits = 9;
 constexpr int kRsBins = 1 << kRsBits;
 constexpr int kRsThreads = 256;
+static_assert(kRsBins == 2 * kRsThreads, "two digits per thread");
 constexpr int kRsWaves = kRsThreads / kWave;
 // Keys per thread: with fewer keys than kRsFewKeys, smaller tiles fill more CUs.
 constexpr int kRsItems = 16, kRsItemsFew = 4;
@@ -357,7 +360,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const int32_t *keys, int
                                                         int bits, int32_t *hist, int32_t ntiles) {
     __shared__ int32_t h[kRsWaves][kRsBins];
     const int t = threadIdx.x, w = t / kWave;
-    for (int i = 0; i < kRsWaves; ++i) h[i][t] = 0;
+    for (int i = 0; i < kRsWaves; ++i) h[i][t] = h[i][t + kRsThreads] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kRsThreads * ITEMS;
     const uint32_t mask = (1u << bits) - 1u;
@@ -367,33 +370,36 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const int32_t *keys, int
         if (p < n) atomicAdd(&h[w][((uint32_t)keys[p] >> shift) & mask], 1);
     }
     __syncthreads();
-    int32_t c = 0;
-    for (int i = 0; i < kRsWaves; ++i) c += h[i][t];
-    if (t <= (int)mask) hist[(int64_t)t * ntiles + blockIdx.x] = c;
+    for (int d = t; d <= (int)mask; d += kRsThreads) {
+        int32_t c = 0;
+        for (int i = 0; i < kRsWaves; ++i) c += h[i][d];
+        hist[(int64_t)d * ntiles + blockIdx.x] = c;
+    }
 }
 
 // Move the keys of each tile to their place: off[bin * ntiles + tile] is the
 // first output slot of the tile's keys with that digit.  vin null: the value
-// of key p is p.  The last pass writes, instead of the values, the final
-// maps: kT[q] = value (the incidence), colT[q] = rowid[value] (its item),
-// posT[value] = q (kT, posT may be null).
-template <int ITEMS>
+// of key p is p.  With `last`, the values become the final maps instead: kT[q] =
+// value (the incidence), colT[q] = rowid[value] (its item), posT[value] = q (kT,
+// posT may be null).  TWO: a second value moves along (win to wout).
+template <int ITEMS, bool TWO>
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
-    const int32_t *kin, const int32_t *vin, int64_t n, int shift, int bits, const int32_t *off,
-    int32_t ntiles, int32_t *kout, int32_t *vout, int32_t last, const int32_t *rowid,
-    int32_t *colT, int32_t *kT, int32_t *posT) {
+    const int32_t *kin, const int32_t *vin, const int32_t *win, int64_t n, int shift, int bits,
+    const int32_t *off, int32_t ntiles, int32_t *kout, int32_t *vout, int32_t *wout, int32_t last,
+    const int32_t *rowid, int32_t *colT, int32_t *kT, int32_t *posT) {
     constexpr int TILE = kRsThreads * ITEMS;
     __shared__ int32_t cnt[kRsWaves][kRsBins];  // keys of a digit so far; then their place
     __shared__ int32_t sk[TILE], sv[TILE];      // the tile in sorted order
+    __shared__ int32_t sw[TWO ? TILE : 1];
     __shared__ int32_t sh[kScanThreads / kWave + 1];
     __shared__ int32_t dst[kRsBins];            // output slot less tile position, per digit
     const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
     const uint32_t mask = (1u << bits) - 1u;
-    for (int i = 0; i < kRsWaves; ++i) cnt[i][t] = 0;
+    for (int i = 0; i < kRsWaves; ++i) cnt[i][t] = cnt[i][t + kRsThreads] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * TILE;
     const int64_t mine = base + (int64_t)w * ITEMS * kWave + lane;
-    int32_t key[ITEMS], val[ITEMS], rank[ITEMS];
+    int32_t key[ITEMS], val[ITEMS], two[TWO ? ITEMS : 1], rank[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int64_t p = mine + i * kWave;
@@ -402,6 +408,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
         if (p < n) {
             key[i] = kin[p];
             if (vin) val[i] = vin[p];
+            if (TWO) two[i] = win[p];
         }
     }
 #pragma unroll
@@ -423,19 +430,19 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    int32_t c[kRsWaves], sum = 0;  // thread t: digit t
-#pragma unroll
-    for (int i = 0; i < kRsWaves; ++i) {
-        c[i] = cnt[i][t];
-        sum += c[i];
-    }
+    // thread t: digits 2 t and 2 t + 1
+    int32_t sum = 0;
+    for (int d = 2 * t; d < 2 * t + 2; ++d)
+        for (int i = 0; i < kRsWaves; ++i) sum += cnt[i][d];
     int32_t total;
     int32_t run = block_excl_scan<int32_t>(sum, sh, total);
-    dst[t] = (t <= (int)mask ? off[(int64_t)t * ntiles + blockIdx.x] : 0) - run;
-#pragma unroll
-    for (int i = 0; i < kRsWaves; ++i) {
-        cnt[i][t] = run;
-        run += c[i];
+    for (int d = 2 * t; d < 2 * t + 2; ++d) {
+        dst[d] = (d <= (int)mask ? off[(int64_t)d * ntiles + blockIdx.x] : 0) - run;
+        for (int i = 0; i < kRsWaves; ++i) {
+            const int32_t c = cnt[i][d];
+            cnt[i][d] = run;
+            run += c;
+        }
     }
     __syncthreads();
 #pragma unroll
@@ -444,6 +451,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
         const int32_t r = cnt[w][((uint32_t)key[i] >> shift) & mask] + rank[i];
         sk[r] = key[i];
         sv[r] = val[i];
+        if (TWO) sw[r] = two[i];
     }
     __syncthreads();
     // each bin's run with consecutive lanes
@@ -455,6 +463,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
         kout[q] = k;
         if (!last) {
             vout[q] = v;
+            if (TWO) wout[q] = sw[j];
         } else {
             if (kT) kT[q] = v;
             if (posT) posT[v] = q;
@@ -835,34 +844,68 @@ static int key_bits(int32_t n) {
 
 int transpose_passes(int32_t n) { return (key_bits(n) + kRsBits - 1) / kRsBits; }
 
-hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int32_t n,
-                            const int32_t *rowid, int32_t *const rsK[2], int32_t *const rsV[2],
-                            int32_t *hist, int32_t *part32, int32_t *ptrT, int32_t *colT,
-                            int32_t *kT, int32_t *posT) {
-    if (nnz <= 0) return launch_fill_i32(st, ptrT, (int64_t)n + 1, 0);
+// The passes of a sort of `keys` in [0, n), each counted, scanned and moved.
+// `move(p, few, ntiles, shift, bits)` launches the scatter of pass p.
+template <typename Move>
+static hipError_t rs_passes(hipStream_t st, const int32_t *keys, int64_t nnz, int32_t n,
+                            int32_t *const rsK[2], int32_t *hist, int32_t *part32, Move move) {
     const int passes = transpose_passes(n);
     const int32_t ntiles = (int32_t)rs_tiles(nnz);
     const bool few = nnz < kRsFewKeys;
     const int total = key_bits(n), width = (total + passes - 1) / passes;
     hipError_t e = hipSuccess;
     for (int p = 0; p < passes && e == hipSuccess; ++p) {
-        const int32_t *kin = p == 0 ? col : rsK[(p - 1) & 1];
-        const int32_t *vin = p == 0 ? nullptr : rsV[(p - 1) & 1];
-        const int last = p == passes - 1;
+        const int32_t *kin = p == 0 ? keys : rsK[(p - 1) & 1];
         const int shift = p * width, bits = std::min(width, total - shift);
-        if (few) k_rs_hist<kRsItemsFew><<<ntiles, kRsThreads, 0, st>>>(kin, nnz, shift, bits, hist, ntiles);
-        else k_rs_hist<kRsItems><<<ntiles, kRsThreads, 0, st>>>(kin, nnz, shift, bits, hist, ntiles);
+        auto *const count = few ? k_rs_hist<kRsItemsFew> : k_rs_hist<kRsItems>;
+        count<<<ntiles, kRsThreads, 0, st>>>(kin, nnz, shift, bits, hist, ntiles);
         e = hipGetLastError();
         if (e == hipSuccess) e = launch_scan_i32(st, hist, (int64_t)ntiles << bits, hist, part32);
         if (e != hipSuccess) break;
-        auto *const scatter = few ? k_rs_scatter<kRsItemsFew> : k_rs_scatter<kRsItems>;
-        scatter<<<ntiles, kRsThreads, 0, st>>>(kin, vin, nnz, shift, bits, hist, ntiles, rsK[p & 1],
-                                               rsV[p & 1], last, rowid, colT, kT, posT);
+        move(p, p == passes - 1, few, kin, ntiles, shift, bits);
         e = hipGetLastError();
     }
+    return e;
+}
+
+hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int32_t n,
+                            const int32_t *rowid, int32_t *const rsK[2], int32_t *const rsV[2],
+                            int32_t *hist, int32_t *part32, int32_t *ptrT, int32_t *colT,
+                            int32_t *kT, int32_t *posT) {
+    if (nnz <= 0) return launch_fill_i32(st, ptrT, (int64_t)n + 1, 0);
+    const hipError_t e = rs_passes(
+        st, col, nnz, n, rsK, hist, part32,
+        [&](int p, int last, bool few, const int32_t *kin, int32_t ntiles, int shift, int bits) {
+            auto *const move = few ? k_rs_scatter<kRsItemsFew, false> : k_rs_scatter<kRsItems, false>;
+            move<<<ntiles, kRsThreads, 0, st>>>(kin, p == 0 ? nullptr : rsV[(p - 1) & 1], nullptr,
+                                                nnz, shift, bits, hist, ntiles, rsK[p & 1],
+                                                rsV[p & 1], nullptr, last, rowid, colT, kT, posT);
+        });
     if (e != hipSuccess) return e;
-    k_rs_bounds<<<grid_for(nnz + 1, 256, 65536), 256, 0, st>>>(rsK[(passes - 1) & 1], nnz, n,
-                                                               ptrT);
+    k_rs_bounds<<<grid_for(nnz + 1, 256, 65536), 256, 0, st>>>(rsK[(transpose_passes(n) - 1) & 1],
+                                                               nnz, n, ptrT);
+    return hipGetLastError();
+}
+
+hipError_t launch_sort_values(hipStream_t st, const int32_t *key, const int32_t *v,
+                              const int32_t *w, int64_t nnz, int32_t n, int32_t *const rsK[2],
+                              int32_t *const rsV[2], int32_t *const rsW[2], int32_t *hist,
+                              int32_t *part32, int32_t *ptr) {
+    if (nnz <= 0) return launch_fill_i32(st, ptr, (int64_t)n + 1, 0);
+    const hipError_t e = rs_passes(
+        st, key, nnz, n, rsK, hist, part32,
+        [&](int p, int, bool few, const int32_t *kin, int32_t ntiles, int shift, int bits) {
+            const int32_t *vin = p == 0 ? v : rsV[(p - 1) & 1];
+            const int32_t *win = p == 0 || !w ? w : rsW[(p - 1) & 1];
+            auto *const move = w ? (few ? k_rs_scatter<kRsItemsFew, true> : k_rs_scatter<kRsItems, true>)
+                                 : (few ? k_rs_scatter<kRsItemsFew, false> : k_rs_scatter<kRsItems, false>);
+            move<<<ntiles, kRsThreads, 0, st>>>(kin, vin, win, nnz, shift, bits, hist, ntiles,
+                                                rsK[p & 1], rsV[p & 1], rsW[p & 1], 0, nullptr,
+                                                nullptr, nullptr, nullptr);
+        });
+    if (e != hipSuccess) return e;
+    k_rs_bounds<<<grid_for(nnz + 1, 256, 65536), 256, 0, st>>>(rsK[(transpose_passes(n) - 1) & 1],
+                                                               nnz, n, ptr);
     return hipGetLastError();
 }
 
