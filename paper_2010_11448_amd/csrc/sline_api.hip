@@ -316,6 +316,7 @@ double span_ms(sline_ctx *c, int i, int j) {
 
 struct Layout {
     int32_t *err, *queue, *tcounts;
+    int32_t *n_lists;  // kept incidences of a primal build (in err's words)
     int64_t n_flags;  // words from err to the end of passes, zeroed together
     int64_t *totals, *passes;
     int32_t *rowid, *ptrT, *colT;
@@ -348,10 +349,11 @@ Tuning build_tuning(const Tuning &t, int64_t n_items, int64_t nnz) {
 
 // ranks: with room for candidate numbers.  fixed: the arena is a fixed region,
 // where they must not make a build too large that fits without them.
-Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64_t M, bool filt,
-                   bool ranks = false, bool fixed = false) {
+Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64_t M, bool dual,
+                   bool filt, bool ranks = false, bool fixed = false) {
     Layout L{};
     L.err = A.take<int32_t>(4);
+    L.n_lists = L.err + 1;
     L.queue = A.take<int32_t>(4);
     L.tcounts = A.take<int32_t>(kKinds * kCountStride);
     L.totals = A.take<int64_t>(kSumRows * kTotalCols);
@@ -361,7 +363,7 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
     L.ptrT = A.take<int32_t>(n + 1);
     L.colT = A.take<int32_t>(nnz);
     L.kT = A.take<int32_t>(nnz);
-    L.posT = A.take<int32_t>(nnz);
+    L.posT = A.take<int32_t>(std::max(nnz, transpose_hist(nnz)));
     L.rsK0 = A.take<int32_t>(nnz);
     L.rsK1 = A.take<int32_t>(nnz);
     L.rsV0 = A.take<int32_t>(nnz);
@@ -373,10 +375,11 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
         L.ptrS = A.take<int32_t>(M + 1);
         L.pos = A.take<int32_t>(nnz + 1);
         L.itmS = A.take<int32_t>(nnz);
-        // the sort's buffers are idle once the lists are transposed
+        // dual: the sort's buffers are idle once the lists are transposed;
+        // primal: what the dual side's transposed lists and flags would take
         if (ranks && N + 1 <= nnz) {
-            L.crank = L.rsV0;
-            L.orig = L.rsV1;
+            L.crank = dual ? L.rsV0 : L.pos;
+            L.orig = dual ? L.rsV1 : L.colT;
         } else if (ranks && !fixed) {
             L.crank = A.take<int32_t>(N + 1);
             L.orig = A.take<int32_t>(N);
@@ -387,7 +390,8 @@ Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64
     L.ntask = A.take<int32_t>(N);
     L.tbase = A.take<int64_t>(N + 1);
     L.start = A.take<int32_t>(std::max(nnz, transpose_hist(nnz)));
-    L.rsHist = L.start;  // written once the lists are transposed
+    // written once the lists are transposed; a primal build writes both at once
+    L.rsHist = dual ? L.start : L.posT;
     return L;
 }
 
@@ -472,6 +476,16 @@ void transpose(sline_ctx *c, const Layout &L, const int32_t *col, int32_t n, int
     hip_check(c, launch_transpose(c->stream, col, nnz, n, L.rowid, rk, rv, L.rsHist, L.part32,
                                   L.ptrT, L.colT, kT, posT),
               "transpose");
+}
+
+// The filtered member lists of a primal build, from the row ids (which are used up).
+void member_lists(sline_ctx *c, hipStream_t st, const Layout &L, const int32_t *col, int32_t n,
+                  int64_t nnz, int32_t *itm, int32_t *start) {
+    int32_t *const rk[2] = {L.rsK0, L.rsK1};
+    int32_t *const rv[2] = {L.rsV0, L.rsV1};
+    hip_check(c, launch_member_lists(st, col, L.rowid, nnz, n, rk, rv, L.kT, L.rsHist, L.part32,
+                                     L.n_lists, L.ptrT, itm, start),
+              "member lists");
 }
 
 bool same_call(const sline_ctx::Pending &p, const sline_csr &H, int32_t s, int32_t dual,
@@ -819,50 +833,64 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     const bool fixed = c->fixed.base != nullptr;
     // the intersections of the variants without visited skipping read items
     const bool ranks = filt && N >= kRankMinItems && !IS.item_end && !(flags & SLINE_NO_VISITED);
-    plan_layout(sizing, m, n, nnz, N, M, filt, ranks, fixed);
+    plan_layout(sizing, m, n, nnz, N, M, dual != 0, filt, ranks, fixed);
     ensure_ws(c, sizing.off + 4096);
     Arena A;
     A.base = reinterpret_cast<char *>(c->ws);
-    const Layout L = plan_layout(A, m, n, nnz, N, M, filt, ranks, fixed);
+    const Layout L = plan_layout(A, m, n, nnz, N, M, dual != 0, filt, ranks, fixed);
 
     hip_check(c, launch_fill_i32(st, L.err, L.n_flags, 0), "zero flags and totals");
 
     mark(c, 0);
-    // 2. row ids and member checks (range checks always: they guard every later index)
-    hip_check(c, launch_rows(st, H.row_ptr, H.col_idx, (int32_t)m, (int32_t)n, nnz,
-                             (flags & SLINE_SKIP_VALIDATE) ? 0 : 1, L.rowid, L.err),
-              "row check");
-    // 3. transpose (until the flags are read back below, no kernel indexes by a
-    // member that may be bad)
-    // back-pointer maps: the filter wants the item incidence of a member-list
-    // position (inv), a build without a filter the position of an incidence (map)
-    const bool want_kT = filt != (dual != 0);
-    transpose(c, L, H.col_idx, (int32_t)n, nnz, want_kT ? L.kT : nullptr,
-              want_kT || IS.full ? nullptr : L.posT);
-    mark(c, 1);
-    // 4. roles
+    // 2. row ids and member checks (range checks always: they guard every later index;
+    // until the flags are read back below, no kernel indexes by a member that
+    // may be bad)
+    const int check_order = (flags & SLINE_SKIP_VALIDATE) ? 0 : 1;
     const int32_t *ptrI = dual ? L.ptrT : H.row_ptr;
     const int32_t *memI = dual ? L.colT : H.col_idx;
-    const int32_t *ptrM = dual ? H.row_ptr : L.ptrT;
-    const int32_t *itmM = dual ? H.col_idx : L.colT;
-    const int32_t *map = dual ? L.kT : L.posT;
-    const int32_t *inv = dual ? L.posT : L.kT;
-    // 5. s filter
-    const int32_t *ptrS = ptrM, *itmS = itmM;
-    if (filt) {
-        // the task counts are written later: until then their array holds
-        // the filter's per-item keep flags
-        hip_check(c, launch_filter(st, ptrM, itmM, (int32_t)M, nnz, ptrI, (int32_t)N, s, IS.s_item,
-                                   L.ntask, L.pos, L.part32, L.ptrS, L.itmS, inv, L.start,
-                                   L.crank, L.orig, L.err),
-                  "filter");
-        ptrS = L.ptrS;
-        itmS = L.itmS;
+    const int32_t *ptrS, *itmS;
+    if (!dual) {
+        // 3. the member lists of the kept items' incidences alone (s filter: an
+        // item's size is known), with the back-pointers
+        ptrS = L.ptrT;
+        int32_t *const itm = filt ? L.itmS : L.colT;
+        itmS = itm;
+        if (L.crank)
+            hip_check(c, launch_ranks(st, ptrI, (int32_t)N, s, L.ntask, L.crank, L.part32), "ranks");
+        hip_check(c, launch_rows(st, H.row_ptr, H.col_idx, (int32_t)m, (int32_t)n, nnz, check_order,
+                                 L.rowid, L.err, filt ? s : 0, filt ? IS.s_item : nullptr, L.crank),
+                  "row check");
+        member_lists(c, st, L, H.col_idx, (int32_t)n, nnz, itm, IS.full ? nullptr : L.start);
+        if (L.crank)
+            hip_check(c, launch_rank_items(st, L.crank, (int32_t)N, L.orig), "items of ranks");
+        mark(c, 1);
+    } else {
+        hip_check(c, launch_rows(st, H.row_ptr, H.col_idx, (int32_t)m, (int32_t)n, nnz, check_order,
+                                 L.rowid, L.err),
+                  "row check");
+        // 3. transpose; the filter wants the item incidence of a member-list
+        // position (posT), a build without a filter the position of an incidence (kT)
+        transpose(c, L, H.col_idx, (int32_t)n, nnz, filt || IS.full ? nullptr : L.kT,
+                  filt ? L.posT : nullptr);
+        mark(c, 1);
+        ptrS = H.row_ptr;
+        itmS = H.col_idx;
+        // 4. s filter
+        if (filt) {
+            // the task counts are written later: until then their array holds
+            // the filter's per-item keep flags
+            hip_check(c, launch_filter(st, H.row_ptr, H.col_idx, (int32_t)M, nnz, ptrI, (int32_t)N, s,
+                                       L.ntask, L.pos, L.part32, L.ptrS, L.itmS, L.posT, L.start,
+                                       L.crank, L.orig, L.err),
+                      "filter");
+            ptrS = L.ptrS;
+            itmS = L.itmS;
+        } else if (!IS.full) {
+            hip_check(c, launch_start_from_map(st, nnz, L.kT, L.start), "back-pointers");
+        }
     }
     // 6. wedge counts, tasks
     const Tuning tu = build_tuning(c->tune, N, nnz);
-    if (!filt && !IS.full)
-        hip_check(c, launch_start_from_map(st, nnz, map, L.start), "back-pointers");
     // degree-based pruning (Sec. IV-C) unless switched off: items smaller
     // than s get no cost and are never walked from
     hip_check(c, launch_cost(st, ptrI, memI, (int32_t)N, noprune ? 1 : s,
@@ -1595,26 +1623,21 @@ void plan_enqueue_prep(sline_batch_plan *p, hipStream_t st, int64_t t_cap) {
     const int32_t *ptrI = p->K.ptrC, *memI = p->K.memC;
     hip_check(c, launch_fill_i32(st, L.err, L.n_flags, 0), "zero flags and totals");
     // row ids, and the member order of every row (a primal graph's combined
-    // ids keep its members' order); a violation stops the run's counting
-    hip_check(c, launch_rows(st, ptrI, memI, NI, MT, B.ZT, 1, L.rowid, p->d_err), "row ids");
-    int32_t *const rk[2] = {L.rsK0, L.rsK1};
-    int32_t *const rv[2] = {L.rsV0, L.rsV1};
-    hip_check(c, launch_transpose(st, memI, B.ZT, MT, L.rowid, rk, rv, L.rsHist, L.part32, L.ptrT,
-                                  L.colT, L.kT, nullptr),
-              "transpose");
+    // ids keep its members' order); a violation stops the run's counting.
     // every item carries its graph's s; the filter, the costs and the
     // lookup-only members read them per item, so a run's s need not be the
     // planned one
-    hip_check(c, launch_filter(st, L.ptrT, L.colT, MT, B.ZT, ptrI, NI, p->s_min, p->K.s_item,
-                               L.ntask, L.pos, L.part32, L.ptrS, L.itmS, L.kT, L.start),
-              "filter");
-    hip_check(c, launch_cost(st, ptrI, memI, NI, p->s_min, p->K.s_item, L.ptrS, L.itmS, L.cost,
+    hip_check(c, launch_rows(st, ptrI, memI, NI, MT, B.ZT, 1, L.rowid, p->d_err, p->s_min,
+                             p->K.s_item),
+              "row ids");
+    member_lists(c, st, L, memI, MT, B.ZT, L.itmS, L.start);
+    hip_check(c, launch_cost(st, ptrI, memI, NI, p->s_min, p->K.s_item, L.ptrT, L.itmS, L.cost,
                              L.start, L.totals, 0, 1),
               "cost");
     const Tuning &tu = p->C.tune;
     const PlanItems PI = plan_items(tu, ptrI, nullptr, p->K.iend, NI, p->s_min, p->K.s_item, false);
     if (p->groups)
-        hip_check(c, launch_mark_lookup(st, PI, memI, L.ptrS, L.start, L.cost), "lookup members");
+        hip_check(c, launch_mark_lookup(st, PI, memI, L.ptrT, L.start, L.cost), "lookup members");
     plan_enqueue_tasks(p, st, t_cap < 0);
     if (t_cap >= 0)
         hip_check(c, launch_plan_guard(st, L.tbase + NI, t_cap, kErrPlanTasks, p->d_err), "task guard");
@@ -1634,7 +1657,7 @@ void plan_enqueue_count(sline_batch_plan *p, hipStream_t st, int64_t pair_cap) {
                                   L.tbase, TL.item, TL.part, TL.small, TL.small_item, TL.tiny,
                                   TL.tiny_item, TL.big, (int32_t)p->t_cap, L.tcounts, p->d_err),
               "task fill");
-    hip_check(c, launch_flat_bounds(st, L.ptrS, L.itmS, (int32_t)p->B.MT, nullptr,
+    hip_check(c, launch_flat_bounds(st, L.ptrT, L.itmS, (int32_t)p->B.MT, nullptr,
                                     (int32_t)p->B.NI, L.bnd),
               "list bounds");
     hip_check(c, launch_fill_i32(st, reinterpret_cast<int32_t *>(TL.pool_head), TL.n_zero, 0),
@@ -1683,7 +1706,7 @@ CountArgs plan_count_args(sline_batch_plan *p) {
     CountArgs C = p->C;  // keeps the tuning
     C.ptrI = p->K.ptrC;
     C.memI = p->K.memC;
-    C.ptrS = L.ptrS;
+    C.ptrS = L.ptrT;
     C.itmS = L.itmS;
     C.N = (int32_t)p->B.NI;
     C.s = p->s_min;
@@ -1872,11 +1895,11 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
     if (B.ZT > 0) {
         Arena sz;
         (void)plan_combine(sz, B);
-        (void)plan_layout(sz, B.NI, B.MT, B.ZT, B.NI, B.MT, true);
+        (void)plan_layout(sz, B.NI, B.MT, B.ZT, B.NI, B.MT, false, true);
         Arena A;
         A.base = reinterpret_cast<char *>(plan_alloc(p, sz.off + 4096, "the batch arrays"));
         p->K = plan_combine(A, B);
-        p->L = plan_layout(A, B.NI, B.MT, B.ZT, B.NI, B.MT, true);
+        p->L = plan_layout(A, B.NI, B.MT, B.ZT, B.NI, B.MT, false, true);
         p->C.ptrI = p->K.ptrC;
     }
     // 3. one run of the preparation, without guards: the tasks that this run

@@ -271,8 +271,19 @@ struct Report {
     }
 };
 hipError_t launch_report(hipStream_t st, const Report &R);
+// Checks of the rows, and the row of every incidence: rowid[k] = i, or -1 in rows
+// of fewer than s entries (s_item[i] when given); with crank, the row's rank
+// instead of i, where ranks pay.
 hipError_t launch_rows(hipStream_t st, const int32_t *rp, const int32_t *col, int32_t m,
-                       int32_t n, int64_t nnz, int check_order, int32_t *rowid, int32_t *err);
+                       int32_t n, int64_t nnz, int check_order, int32_t *rowid, int32_t *err,
+                       int32_t s = 0, const int32_t *s_item = nullptr,
+                       const int32_t *crank = nullptr);
+// crank[it] (N + 1 entries) = items of at least s members before it; kept: N
+// entries of scratch, part32 the scan's partials.
+hipError_t launch_ranks(hipStream_t st, const int32_t *ptrI, int32_t N, int32_t s, int32_t *kept,
+                        int32_t *crank, int32_t *part32);
+// orig[rank] = item, where ranks pay
+hipError_t launch_rank_items(hipStream_t st, const int32_t *crank, int32_t N, int32_t *orig);
 
 hipError_t launch_fill_i32(hipStream_t st, int32_t *p, int64_t n, int32_t v);
 hipError_t launch_fill_i64(hipStream_t st, int64_t *p, int64_t n, int64_t v);
@@ -305,6 +316,16 @@ hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int
                             int32_t *hist, int32_t *part32, int32_t *ptrT, int32_t *colT,
                             int32_t *kT, int32_t *posT);
 
+// The filtered member lists of a primal build in one sort: of the nnz
+// incidences (col[k], item[k]) those with item[k] >= 0, by member, items ascending:
+// itm (their items), ptr (n + 1 list pointers) and start[k] = the position after
+// k's own entry (the back-pointer of kept incidence k; start may be null).  item
+// is used up; rsW: one more nnz-entry buffer; *n_dev receives their number.
+hipError_t launch_member_lists(hipStream_t st, const int32_t *col, int32_t *item, int64_t nnz,
+                               int32_t n, int32_t *const rsK[2], int32_t *const rsV[2],
+                               int32_t *rsW, int32_t *hist, int32_t *part32, int32_t *n_dev,
+                               int32_t *ptr, int32_t *itm, int32_t *start);
+
 // The same sort of keys that carry a value v, and w if not null: with p =
 // transpose_passes(n) - 1, the sorted values end in rsV[p & 1] and rsW[p & 1], and
 // ptr[x] (n + 1 entries) is the first key >= x.
@@ -313,23 +334,21 @@ hipError_t launch_sort_values(hipStream_t st, const int32_t *key, const int32_t 
                               int32_t *const rsV[2], int32_t *const rsW[2], int32_t *hist,
                               int32_t *part32, int32_t *ptr);
 
-// s filter: N_s(v) = the items of N(v) with |S| >= s (s_item[it] for item it
-// when s_item is given), every list in its order, written to itmS with list
-// pointers ptrS (M + 1 entries).  pos (nnz + 1 entries) receives the kept
-// entries before each member-list entry; part32 holds the scan's partials.
-// With start given, the back-pointer of every kept entry is written as well:
-// start[inv[p]] = (its position in itmS) + 1, inv mapping member-list
-// positions to item incidences.
-// With err given, nothing is read while kErrColRange is set in *err.
+// s filter of a dual build: N_s(v) = the items of N(v) with |S| >= s, every list
+// in its order, written to itmS with list pointers ptrS (M + 1 entries).  pos
+// (nnz + 1 entries) receives the kept entries before each member-list entry;
+// part32 holds the scan's partials.  The back-pointer of every kept entry is
+// written as well: start[inv[p]] = (its position in itmS) + 1, inv mapping
+// member-list positions to item incidences.
+// Nothing is read while kErrColRange is set in *err.
 // kept (N entries, scratch) receives each item's keep flag first.  With crank
 // given (N + 1 entries), crank[it] = kept items before it, and where ranks pay
 // (ranks_pay), itmS holds ranks and orig[rank] (up to N entries) their items.
 hipError_t launch_filter(hipStream_t st, const int32_t *ptrM, const int32_t *itmM, int32_t M,
                          int64_t nnz, const int32_t *ptrI, int32_t N, int32_t s,
-                         const int32_t *s_item, int32_t *kept, int32_t *pos, int32_t *part32,
-                         int32_t *ptrS, int32_t *itmS, const int32_t *inv, int32_t *start,
-                         int32_t *crank = nullptr, int32_t *orig = nullptr,
-                         const int32_t *err = nullptr);
+                         int32_t *kept, int32_t *pos, int32_t *part32, int32_t *ptrS,
+                         int32_t *itmS, const int32_t *inv, int32_t *start, int32_t *crank,
+                         int32_t *orig, const int32_t *err);
 
 // Per-item exact wedge count W_a, the back-pointer start[k] (first item > a
 // in N_s(v) for member incidence k of a kept item a) and the run totals:

@@ -78,10 +78,17 @@ inline int grid_for(int64_t work, int per_block, int cap = 1 << 20) {
 
 // ------------------------------------------------------------- checks
 
-// Short rows are walked by groups of kGroup lanes (eight rows per wave);
-// longer rows by whole waves, in a second loop that looks at 64 rows at a
-// time and takes the long ones in turn.  Short means at most 32 entries.
+// Short rows are walked by groups of kGroup lanes (eight rows per wave) or, with
+// kLaneRows rows and more, by a lane each; longer rows by whole waves, in a
+// second loop that looks at 64 rows at a time and takes the long ones in turn.
+// Short means at most 32 entries, or kLaneShort for a lane.  What bounds such
+// walks is the latency of their dependent loads: with rows enough for every
+// lane, a lane per row has eight times the rows in flight; with fewer, it
+// would only make the longest chain longer.  5*10^6 rows, 3.7*10^7 entries: k_rows
+// 0.25 -> 0.17 ms, k_cost 0.45 -> 0.38 ms.
 constexpr int kGroup = 8;
+constexpr int kLaneShort = 16;
+constexpr int64_t kLaneRows = 1 << 17;
 
 template <int W, typename T>
 __device__ __forceinline__ T group_sum(T v) {
@@ -128,9 +135,15 @@ __device__ __forceinline__ void for_rows(const int32_t *ptrI, int64_t N, Body bo
     }
 }
 
-// Every row in one launch: body(a, gl, W), W lanes to a row, gl this lane's place.
-template <int SHORT, typename Body>
+// Every row in one launch: body(a, gl, W), W lanes to a row, gl this lane's
+// place.  LANES: a lane per row where the rows are many.
+template <int SHORT, bool LANES, typename Body>
 __device__ __forceinline__ void for_all_rows(const int32_t *ptrI, int64_t N, Body body) {
+    if (LANES && N >= kLaneRows) {
+        for_rows<1, kLaneShort>(ptrI, N, [&](int64_t a, int gl) { body(a, gl, 1); });
+        for_rows<kWave, kLaneShort>(ptrI, N, [&](int64_t a, int gl) { body(a, gl, kWave); });
+        return;
+    }
     for_rows<kGroup, SHORT>(ptrI, N, [&](int64_t a, int gl) { body(a, gl, kGroup); });
     for_rows<kWave, SHORT>(ptrI, N, [&](int64_t a, int gl) { body(a, gl, kWave); });
 }
@@ -157,21 +170,44 @@ __global__ __launch_bounds__(kWave) void k_report(Report R) {
     }
 }
 
-// One wave per row (grid-stride): the row id of every incidence, member range
-// checks and, when asked, the strictly-increasing check of each row.
+// Workgroups of such a launch: as many as rows need, at most `cap`.
+inline int rows_grid(int64_t N, int cap) {
+    return grid_for(N >= kLaneRows ? N : N * kGroup, 256, cap);
+}
+
+// Loads in flight per lane of a row walk.
+constexpr int kRowLoads = 4;
+
+// The row id of every incidence, member range checks and, when asked, the
+// strictly-increasing check of each row.  Rows of fewer than s entries (s_item[i]
+// when given) get -1; with crank, where ranks pay, the others get their rank.
 __global__ __launch_bounds__(256) void k_rows(const int32_t *rp, const int32_t *col, int32_t m,
-                                              int32_t n, int64_t nnz, int check_order,
+                                              int32_t n, int64_t nnz, int check_order, int32_t s,
+                                              const int32_t *s_item, const int32_t *crank,
                                               int32_t *rowid, int32_t *err) {
     int32_t bad = 0;
-    for_all_rows<32>(rp, m, [&](int64_t i, int gl, int W) {
+    crank = ranks_or_null(crank, m);
+    for_all_rows<32, true>(rp, m, [&](int64_t i, int gl, int W) {
         int64_t b = rp[i], e = rp[i + 1];
         if (b < 0) b = 0;
         if (e > nnz) e = nnz;
-        for (int64_t k = b + gl; k < e; k += W) {
-            int32_t v = col[k];
-            rowid[k] = (int32_t)i;
-            if (v < 0 || v >= n) bad |= kErrColRange;
-            if (check_order && k + 1 < e && col[k + 1] <= v) bad |= kErrColOrder;
+        const int32_t id = e - b < (s_item ? s_item[i] : s) ? -1 : crank ? crank[i] : (int32_t)i;
+        for (int64_t k0 = b + gl; k0 < e; k0 += kRowLoads * W) {
+            int32_t v[kRowLoads], next[kRowLoads];
+#pragma unroll
+            for (int q = 0; q < kRowLoads; ++q) {
+                const int64_t k = min(k0 + q * W, e - 1);
+                v[q] = col[k];
+                next[q] = check_order ? col[min(k + 1, e - 1)] : 0;
+            }
+#pragma unroll
+            for (int q = 0; q < kRowLoads; ++q) {
+                const int64_t k = k0 + q * W;
+                if (k >= e) break;
+                rowid[k] = id;
+                if (v[q] < 0 || v[q] >= n) bad |= kErrColRange;
+                if (check_order && k + 1 < e && next[q] <= v[q]) bad |= kErrColOrder;
+            }
         }
     });
     if (bad) atomicOr(err, bad);
@@ -343,6 +379,11 @@ __global__ void k_start_from_map(int64_t nnz, const int32_t *map, int32_t *start
 // and the ballots; so few passes of wide digits.  10^7 keys of 21 bits, counts,
 // scans and moves: 3 passes of 7 bits 0.43 ms, 6 of 4 bits (counters per
 // thread) 0.68 ms.  22,000 keys of 13 bits: 2 passes 25 us, 4 passes 100 us.
+// A primal build's lists are sorted without the items that the filter drops, and
+// carry the item along: 8 B more per key and pass, but no gather of it at the end, no
+// flags, scan and compaction of the lists after.  3.7*10^7 incidences, three
+// quarters kept, 24-bit members: 1.19 ms of scatters where those and the
+// filter's passes took 2.03.
 // 9 bits, as keys of 17 and 18 bits then take two passes and not three: 4.5*10^7
 // of 18 bits with two values 1.14 ms (three passes with one value 1.44).
 constexpr int kRsBits = 9;
@@ -353,13 +394,18 @@ constexpr int kRsWaves = kRsThreads / kWave;
 // Keys per thread: with fewer keys than kRsFewKeys, smaller tiles fill more CUs.
 constexpr int kRsItems = 16, kRsItemsFew = 4;
 constexpr int64_t kRsFewKeys = 1 << 19;
+// What a scatter moves with each key.
+constexpr int kRsOne = 0, kRsTwo = 1, kRsLists = 2;
 
-// Digit counts of each tile, bin-major: hist[bin * ntiles + tile].
+// Digit counts of each tile, bin-major: hist[bin * ntiles + tile].  w2: keys with
+// a negative value there are left out.  n_dev: at most *n_dev keys.
 template <int ITEMS>
-__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const int32_t *keys, int64_t n, int shift,
+__global__ __launch_bounds__(kRsThreads) void k_rs_hist(const int32_t *keys, const int32_t *w2,
+                                                        int64_t n, const int32_t *n_dev, int shift,
                                                         int bits, int32_t *hist, int32_t ntiles) {
     __shared__ int32_t h[kRsWaves][kRsBins];
     const int t = threadIdx.x, w = t / kWave;
+    if (n_dev) n = min(n, (int64_t)*n_dev);
     for (int i = 0; i < kRsWaves; ++i) h[i][t] = h[i][t + kRsThreads] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kRsThreads * ITEMS;
@@ -367,7 +413,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const int32_t *keys, int
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int64_t p = base + i * kRsThreads + t;
-        if (p < n) atomicAdd(&h[w][((uint32_t)keys[p] >> shift) & mask], 1);
+        if (p < n && (!w2 || w2[p] >= 0)) atomicAdd(&h[w][((uint32_t)keys[p] >> shift) & mask], 1);
     }
     __syncthreads();
     for (int d = t; d <= (int)mask; d += kRsThreads) {
@@ -381,13 +427,18 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const int32_t *keys, int
 // first output slot of the tile's keys with that digit.  vin null: the value
 // of key p is p.  With `last`, the values become the final maps instead: kT[q] =
 // value (the incidence), colT[q] = rowid[value] (its item), posT[value] = q (kT,
-// posT may be null).  TWO: a second value moves along (win to wout).
-template <int ITEMS, bool TWO>
+// posT may be null).  kRsTwo: a second value moves along (win to wout); with `last`
+// nothing else is done.  kRsLists: as kRsTwo, but keys with a negative second value are left
+// out; the number of the others goes to *n_dev in the first pass, and is read
+// from there in later ones; in the last, the second value goes to colT[q], and posT[value] = q + 1.
+template <int ITEMS, int MODE>
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
-    const int32_t *kin, const int32_t *vin, const int32_t *win, int64_t n, int shift, int bits,
-    const int32_t *off, int32_t ntiles, int32_t *kout, int32_t *vout, int32_t *wout, int32_t last,
-    const int32_t *rowid, int32_t *colT, int32_t *kT, int32_t *posT) {
+    const int32_t *kin, const int32_t *vin, const int32_t *win, int64_t n, int32_t *n_dev,
+    int32_t first, int shift, int bits, const int32_t *off, int32_t ntiles, int32_t *kout,
+    int32_t *vout, int32_t *wout, int32_t last, const int32_t *rowid, int32_t *colT, int32_t *kT,
+    int32_t *posT) {
     constexpr int TILE = kRsThreads * ITEMS;
+    constexpr bool TWO = MODE != kRsOne, LISTS = MODE == kRsLists;
     __shared__ int32_t cnt[kRsWaves][kRsBins];  // keys of a digit so far; then their place
     __shared__ int32_t sk[TILE], sv[TILE];      // the tile in sorted order
     __shared__ int32_t sw[TWO ? TILE : 1];
@@ -395,9 +446,17 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
     __shared__ int32_t dst[kRsBins];            // output slot less tile position, per digit
     const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
     const uint32_t mask = (1u << bits) - 1u;
+    const int64_t base = (int64_t)blockIdx.x * TILE;
+    if (LISTS) {
+        if (first) {
+            if (blockIdx.x == 0 && t == 0) *n_dev = off[(int64_t)ntiles << bits];
+        } else {
+            n = min(n, (int64_t)*n_dev);
+            if (base >= n) return;
+        }
+    }
     for (int i = 0; i < kRsWaves; ++i) cnt[i][t] = cnt[i][t + kRsThreads] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * TILE;
     const int64_t mine = base + (int64_t)w * ITEMS * kWave + lane;
     int32_t key[ITEMS], val[ITEMS], two[TWO ? ITEMS : 1], rank[ITEMS];
 #pragma unroll
@@ -405,6 +464,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
         const int64_t p = mine + i * kWave;
         key[i] = 0;
         val[i] = (int32_t)p;
+        if (LISTS) two[i] = -1;
         if (p < n) {
             key[i] = kin[p];
             if (vin) val[i] = vin[p];
@@ -413,7 +473,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        const bool ok = mine + i * kWave < n;
+        const bool ok = mine + i * kWave < n && (!LISTS || two[i] >= 0);
         const uint32_t d = ((uint32_t)key[i] >> shift) & mask;
         uint64_t same = __ballot(ok);
         for (int b = 0; b < bits; ++b) {
@@ -447,7 +507,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        if (mine + i * kWave >= n) continue;
+        if (mine + i * kWave >= n || (LISTS && two[i] < 0)) continue;
         const int32_t r = cnt[w][((uint32_t)key[i] >> shift) & mask] + rank[i];
         sk[r] = key[i];
         sv[r] = val[i];
@@ -455,15 +515,18 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
     }
     __syncthreads();
     // each bin's run with consecutive lanes
-    const int32_t tn = (int32_t)(n - base < TILE ? n - base : TILE);
+    const int32_t tn = LISTS ? total : (int32_t)(n - base < TILE ? n - base : TILE);
 #pragma unroll 4
     for (int32_t j = t; j < tn; j += kRsThreads) {
         const int32_t k = sk[j], v = sv[j];
         const int32_t q = dst[((uint32_t)k >> shift) & mask] + j;
         kout[q] = k;
-        if (!last) {
+        if (!last || MODE == kRsTwo) {
             vout[q] = v;
             if (TWO) wout[q] = sw[j];
+        } else if (LISTS) {
+            if (posT) posT[v] = q + 1;
+            colT[q] = sw[j];
         } else {
             if (kT) kT[q] = v;
             if (posT) posT[v] = q;
@@ -474,15 +537,48 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
 
 // Row pointers of the transpose from the sorted members: ptr[v] = first slot
 // with member >= v, for v = 0..n (members outside [0, n) are clamped; they
-// only occur in input that the row checks reject).
-__global__ void k_rs_bounds(const int32_t *sk, int64_t nnz, int32_t n, int32_t *ptr) {
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p <= nnz;
-         p += (int64_t)gridDim.x * blockDim.x) {
+// only occur in input that the row checks reject).  A thread per slot writes the
+// pointers between its member and the one before, and of a long run of members in
+// no list (those of all the items that the filter drops) only the ends: the
+// blocks of kWave members within it a wave writes at once, after a search
+// (left to one thread, such runs took 0.24 ms in a batch of 10 graphs).
+__global__ __launch_bounds__(256) void k_rs_bounds(const int32_t *sk, int64_t nnz, int32_t n,
+                                                   int32_t *ptr, const int32_t *n_dev) {
+    if (n_dev) nnz = min(nnz, (int64_t)*n_dev);
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t nt = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t p = t; p <= nnz; p += nt) {
         int32_t hi = p < nnz ? sk[p] : n;
         int32_t lo = p > 0 ? sk[p - 1] : -1;
         hi = hi < 0 ? 0 : (hi > n ? n : hi);
         lo = lo < -1 ? -1 : (lo > n ? n : lo);
+        if (hi - lo > 2 * kWave) {
+            const int32_t c0 = (lo + kWave) & ~(kWave - 1);  // first block after lo
+            const int32_t c1 = (int32_t)(((int64_t)hi + 1) & ~(int64_t)(kWave - 1));
+            for (int32_t v = lo + 1; v < c0; ++v) ptr[v] = (int32_t)p;
+            lo = c1 - 1;
+        }
         for (int32_t v = lo + 1; v <= hi; ++v) ptr[v] = (int32_t)p;
+    }
+    const int64_t blocks = ((int64_t)n + 1) / kWave;
+    const int lane = lane_id();
+    for (int64_t c0 = t - lane; c0 < blocks; c0 += nt) {
+        const int64_t first = (c0 + lane) * kWave;
+        int32_t lo = 0;
+        bool gap = false;
+        if (c0 + lane < blocks) {
+            int32_t end = (int32_t)nnz;  // first slot with member >= first
+            while (lo < end) {
+                const int32_t mid = lo + ((end - lo) >> 1);
+                if (sk[mid] < first) lo = mid + 1;
+                else end = mid;
+            }
+            gap = lo >= nnz || sk[lo] >= first + kWave - 1;
+        }
+        for (uint64_t m = __ballot(gap); m; m &= m - 1) {
+            const int src = __builtin_ctzll(m);
+            ptr[(c0 + src) * kWave + lane] = __shfl(lo, src, kWave);
+        }
     }
 }
 
@@ -491,30 +587,29 @@ __global__ void k_rs_bounds(const int32_t *sk, int64_t nnz, int32_t n, int32_t *
 // Member-list entries below which the filter compares sizes entry by entry.
 constexpr int64_t kFilterFew = 1 << 20;
 
-// The s filter as a stream compaction: the filtered lists N_s(v), one after
+// The s filter of a dual build, whose item sizes are known once the lists are
+// transposed, as a stream compaction: the filtered lists N_s(v), one after
 // the other, are the kept entries of the member lists in their order, so the
 // position of a kept entry is the number of kept entries before it.
-// kept[it] = 1 if item it has |S| >= s (s_item[it] when given); then
-// keep[p] = kept[itmM[p]] for entry p of the member lists (one gather per
-// entry instead of the item's two list bounds and its s).
-__global__ void k_item_kept(const int32_t *ptrI, int32_t N, int32_t s, const int32_t *s_item,
-                            int32_t *kept) {
+// kept[it] = 1 if item it has |S| >= s; then keep[p] = kept[itmM[p]] for entry p
+// of the member lists (one gather per entry instead of the item's two bounds).
+__global__ void k_item_kept(const int32_t *ptrI, int32_t N, int32_t s, int32_t *kept) {
     for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < N;
          it += (int64_t)gridDim.x * blockDim.x)
-        kept[it] = (ptrI[it + 1] - ptrI[it]) >= (s_item ? s_item[it] : s) ? 1 : 0;
+        kept[it] = ptrI[it + 1] - ptrI[it] >= s ? 1 : 0;
 }
 
 // kept null: the sizes are compared here (short inputs, whose list bounds stay
 // in cache: one launch less).
 __global__ void k_filter_flags(const int32_t *itmM, int64_t nnz, const int32_t *kept,
-                               const int32_t *ptrI, int32_t s, const int32_t *s_item,
-                               int32_t *keep, const int32_t *err) {
+                               const int32_t *ptrI, int32_t s, int32_t *keep,
+                               const int32_t *err) {
     if (err && (*err & kErrColRange)) return;  // items that index nothing
     if (!kept) {
         for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz;
              p += (int64_t)gridDim.x * blockDim.x) {
             const int32_t it = itmM[p];
-            keep[p] = (ptrI[it + 1] - ptrI[it]) >= (s_item ? s_item[it] : s) ? 1 : 0;
+            keep[p] = ptrI[it + 1] - ptrI[it] >= s ? 1 : 0;
         }
         return;
     }
@@ -554,6 +649,16 @@ __global__ void k_filter_scatter(const int32_t *itmM, int64_t nnz, const int32_t
     }
 }
 
+// orig[r] = the kept item with rank r, where ranks pay.
+__global__ void k_rank_items(const int32_t *crank, int32_t N, int32_t *orig) {
+    if (!ranks_or_null(crank, N)) return;
+    for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < N;
+         it += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t r = crank[it];
+        if (crank[it + 1] != r) orig[r] = (int32_t)it;
+    }
+}
+
 // W_a = sum over members v of the number of kept items b > a in N_s(v); 0 for
 // items with |S_a| < s.  For every member incidence k of a kept item,
 // start[k] = index in itmS of the first item > a in N_s(v) (the back-pointer
@@ -567,26 +672,38 @@ __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t
                                               const int32_t *err) {
     if (err && (*err & kErrColRange)) return;  // members that index nothing
     int64_t kept = 0, kept_nnz = 0, wedges = 0;  // counted by each row's first lane
-    for_all_rows<32>(ptrI, N, [&](int64_t a, int gl, int W) {
+    for_all_rows<32, true>(ptrI, N, [&](int64_t a, int gl, int W) {
         const int32_t b = ptrI[a], e = ptrI[a + 1];
         if (e - b < (s_item ? s_item[a] : s)) {
             if (gl == 0) cost[a] = 0;
             return;
         }
         int64_t c = 0;
-        for (int32_t k = b + gl; k < e; k += W) {
-            const int32_t v = memI[k];
-            const int32_t lo = ptrS[v], hi = ptrS[v + 1];
-            int32_t st;
-            if (have_start) {
-                st = start[k];
-            } else {
-                st = full ? lo : upper_bound(itmS, lo, hi, (int32_t)a);
-                start[k] = st;
+        if (have_start) {
+            for (int32_t k0 = b + gl; k0 < e; k0 += kRowLoads * W) {
+                int32_t hi[kRowLoads], st[kRowLoads];
+#pragma unroll
+                for (int q = 0; q < kRowLoads; ++q) {
+                    const int32_t k = min(k0 + q * W, e - 1);
+                    st[q] = start[k];
+                    hi[q] = memI[k];
+                }
+#pragma unroll
+                for (int q = 0; q < kRowLoads; ++q) hi[q] = ptrS[hi[q] + 1];
+#pragma unroll
+                for (int q = 0; q < kRowLoads; ++q)
+                    if (k0 + q * W < e) c += hi[q] - st[q];
             }
-            c += hi - st;
+        } else {
+            for (int32_t k = b + gl; k < e; k += W) {
+                const int32_t v = memI[k];
+                const int32_t lo = ptrS[v], hi = ptrS[v + 1];
+                const int32_t st = full ? lo : upper_bound(itmS, lo, hi, (int32_t)a);
+                start[k] = st;
+                c += hi - st;
+            }
         }
-        c = W == kWave ? wave_sum(c) : group_sum<kGroup>(c);
+        if (W != 1) c = W == kWave ? wave_sum(c) : group_sum<kGroup>(c);
         if (gl == 0) {
             cost[a] = c;
             kept += 1;
@@ -630,7 +747,7 @@ __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t 
                                                      const int32_t *ptrS,
                                                      int32_t *start, int64_t *cost) {
     I.crank = ranks_or_null(I.crank, I.N);
-    for_all_rows<kGroup * kKeysPerLane>(I.ptrI, I.N, [&](int64_t a, int gl, int W) {
+    for_all_rows<kGroup * kKeysPerLane, false>(I.ptrI, I.N, [&](int64_t a, int gl, int W) {
         auto best_of = [&](uint64_t v) { return W == kWave ? group_max<kWave>(v) : group_max<kGroup>(v); };
         const int32_t b = I.ptrI[a], e = I.ptrI[a + 1];
         const int32_t s = I.s_item ? I.s_item[a] : I.s;
@@ -756,13 +873,25 @@ hipError_t launch_report(hipStream_t st, const Report &R) {
 }
 
 hipError_t launch_rows(hipStream_t st, const int32_t *rp, const int32_t *col, int32_t m,
-                       int32_t n, int64_t nnz, int check_order, int32_t *rowid, int32_t *err) {
+                       int32_t n, int64_t nnz, int check_order, int32_t *rowid, int32_t *err,
+                       int32_t s, const int32_t *s_item, const int32_t *crank) {
     if (m <= 0) return hipSuccess;
-    k_rows<<<grid_for((int64_t)m * kGroup, 256, 16384), 256, 0, st>>>(rp, col, m, n, nnz,
-                                                                     check_order, rowid, err);
+    k_rows<<<rows_grid(m, 16384), 256, 0, st>>>(rp, col, m, n, nnz, check_order, s, s_item, crank,
+                                                rowid, err);
     return hipGetLastError();
 }
 
+hipError_t launch_ranks(hipStream_t st, const int32_t *ptrI, int32_t N, int32_t s, int32_t *kept,
+                        int32_t *crank, int32_t *part32) {
+    k_item_kept<<<grid_for(N, 256, 65536), 256, 0, st>>>(ptrI, N, s, kept);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_scan_i32(st, kept, N, crank, part32);
+}
+
+hipError_t launch_rank_items(hipStream_t st, const int32_t *crank, int32_t N, int32_t *orig) {
+    k_rank_items<<<grid_for(N, 256, 65536), 256, 0, st>>>(crank, N, orig);
+    return hipGetLastError();
+}
 
 hipError_t launch_fill_i32(hipStream_t st, int32_t *p, int64_t n, int32_t v) {
     if (n <= 0) return hipSuccess;
@@ -844,11 +973,13 @@ static int key_bits(int32_t n) {
 
 int transpose_passes(int32_t n) { return (key_bits(n) + kRsBits - 1) / kRsBits; }
 
-// The passes of a sort of `keys` in [0, n), each counted, scanned and moved.
-// `move(p, few, ntiles, shift, bits)` launches the scatter of pass p.
+// The passes of a sort of `keys` in [0, n), each counted, scanned and moved:
+// move(p, last, few, keys in, ntiles, shift, bits) launches the scatter of pass p.
+// w, n_dev: see k_rs_hist (w in the first pass, n_dev in later ones).
 template <typename Move>
 static hipError_t rs_passes(hipStream_t st, const int32_t *keys, int64_t nnz, int32_t n,
-                            int32_t *const rsK[2], int32_t *hist, int32_t *part32, Move move) {
+                            int32_t *const rsK[2], int32_t *hist, int32_t *part32,
+                            const int32_t *w, const int32_t *n_dev, Move move) {
     const int passes = transpose_passes(n);
     const int32_t ntiles = (int32_t)rs_tiles(nnz);
     const bool few = nnz < kRsFewKeys;
@@ -858,14 +989,27 @@ static hipError_t rs_passes(hipStream_t st, const int32_t *keys, int64_t nnz, in
         const int32_t *kin = p == 0 ? keys : rsK[(p - 1) & 1];
         const int shift = p * width, bits = std::min(width, total - shift);
         auto *const count = few ? k_rs_hist<kRsItemsFew> : k_rs_hist<kRsItems>;
-        count<<<ntiles, kRsThreads, 0, st>>>(kin, nnz, shift, bits, hist, ntiles);
+        count<<<ntiles, kRsThreads, 0, st>>>(kin, p == 0 ? w : nullptr, nnz, p == 0 ? nullptr : n_dev,
+                                             shift, bits, hist, ntiles);
         e = hipGetLastError();
         if (e == hipSuccess) e = launch_scan_i32(st, hist, (int64_t)ntiles << bits, hist, part32);
         if (e != hipSuccess) break;
-        move(p, p == passes - 1, few, kin, ntiles, shift, bits);
+        move(p, p == passes - 1 ? 1 : 0, few, kin, ntiles, shift, bits);
         e = hipGetLastError();
     }
     return e;
+}
+
+// Scatter of a launch's tile size.
+template <int MODE>
+static auto rs_move(bool few) {
+    return few ? k_rs_scatter<kRsItemsFew, MODE> : k_rs_scatter<kRsItems, MODE>;
+}
+
+static hipError_t rs_bounds(hipStream_t st, const int32_t *sorted, int64_t nnz, int32_t n,
+                            int32_t *ptr, const int32_t *n_dev) {
+    k_rs_bounds<<<grid_for(std::max<int64_t>(nnz, n / kWave) + 1, 256, 65536), 256, 0, st>>>(sorted, nnz, n, ptr, n_dev);
+    return hipGetLastError();
 }
 
 hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int32_t n,
@@ -874,17 +1018,32 @@ hipError_t launch_transpose(hipStream_t st, const int32_t *col, int64_t nnz, int
                             int32_t *kT, int32_t *posT) {
     if (nnz <= 0) return launch_fill_i32(st, ptrT, (int64_t)n + 1, 0);
     const hipError_t e = rs_passes(
-        st, col, nnz, n, rsK, hist, part32,
+        st, col, nnz, n, rsK, hist, part32, nullptr, nullptr,
         [&](int p, int last, bool few, const int32_t *kin, int32_t ntiles, int shift, int bits) {
-            auto *const move = few ? k_rs_scatter<kRsItemsFew, false> : k_rs_scatter<kRsItems, false>;
-            move<<<ntiles, kRsThreads, 0, st>>>(kin, p == 0 ? nullptr : rsV[(p - 1) & 1], nullptr,
-                                                nnz, shift, bits, hist, ntiles, rsK[p & 1],
-                                                rsV[p & 1], nullptr, last, rowid, colT, kT, posT);
+            rs_move<kRsOne>(few)<<<ntiles, kRsThreads, 0, st>>>(
+                kin, p == 0 ? nullptr : rsV[(p - 1) & 1], nullptr, nnz, nullptr, p == 0, shift, bits,
+                hist, ntiles, rsK[p & 1], rsV[p & 1], nullptr, last, rowid, colT, kT, posT);
         });
-    if (e != hipSuccess) return e;
-    k_rs_bounds<<<grid_for(nnz + 1, 256, 65536), 256, 0, st>>>(rsK[(transpose_passes(n) - 1) & 1],
-                                                               nnz, n, ptrT);
-    return hipGetLastError();
+    return e != hipSuccess ? e
+                           : rs_bounds(st, rsK[(transpose_passes(n) - 1) & 1], nnz, n, ptrT, nullptr);
+}
+
+hipError_t launch_member_lists(hipStream_t st, const int32_t *col, int32_t *item, int64_t nnz,
+                               int32_t n, int32_t *const rsK[2], int32_t *const rsV[2],
+                               int32_t *rsW, int32_t *hist, int32_t *part32, int32_t *n_dev,
+                               int32_t *ptr, int32_t *itm, int32_t *start) {
+    if (nnz <= 0) return launch_fill_i32(st, ptr, (int64_t)n + 1, 0);
+    int32_t *const w[2] = {rsW, item};  // the first pass leaves `item` free
+    const hipError_t e = rs_passes(
+        st, col, nnz, n, rsK, hist, part32, item, n_dev,
+        [&](int p, int last, bool few, const int32_t *kin, int32_t ntiles, int shift, int bits) {
+            rs_move<kRsLists>(few)<<<ntiles, kRsThreads, 0, st>>>(
+                kin, p == 0 ? nullptr : rsV[(p - 1) & 1], p == 0 ? item : w[(p - 1) & 1], nnz, n_dev,
+                p == 0, shift, bits, hist, ntiles, rsK[p & 1], rsV[p & 1], w[p & 1], last, nullptr,
+                itm, nullptr, start);
+        });
+    return e != hipSuccess ? e
+                           : rs_bounds(st, rsK[(transpose_passes(n) - 1) & 1], nnz, n, ptr, n_dev);
 }
 
 hipError_t launch_sort_values(hipStream_t st, const int32_t *key, const int32_t *v,
@@ -893,33 +1052,29 @@ hipError_t launch_sort_values(hipStream_t st, const int32_t *key, const int32_t 
                               int32_t *part32, int32_t *ptr) {
     if (nnz <= 0) return launch_fill_i32(st, ptr, (int64_t)n + 1, 0);
     const hipError_t e = rs_passes(
-        st, key, nnz, n, rsK, hist, part32,
+        st, key, nnz, n, rsK, hist, part32, nullptr, nullptr,
         [&](int p, int, bool few, const int32_t *kin, int32_t ntiles, int shift, int bits) {
             const int32_t *vin = p == 0 ? v : rsV[(p - 1) & 1];
             const int32_t *win = p == 0 || !w ? w : rsW[(p - 1) & 1];
-            auto *const move = w ? (few ? k_rs_scatter<kRsItemsFew, true> : k_rs_scatter<kRsItems, true>)
-                                 : (few ? k_rs_scatter<kRsItemsFew, false> : k_rs_scatter<kRsItems, false>);
-            move<<<ntiles, kRsThreads, 0, st>>>(kin, vin, win, nnz, shift, bits, hist, ntiles,
-                                                rsK[p & 1], rsV[p & 1], rsW[p & 1], 0, nullptr,
-                                                nullptr, nullptr, nullptr);
+            (w ? rs_move<kRsTwo>(few) : rs_move<kRsOne>(few))<<<ntiles, kRsThreads, 0, st>>>(
+                kin, vin, win, nnz, nullptr, p == 0, shift, bits, hist, ntiles, rsK[p & 1],
+                rsV[p & 1], rsW[p & 1], 0, nullptr, nullptr, nullptr, nullptr);
         });
-    if (e != hipSuccess) return e;
-    k_rs_bounds<<<grid_for(nnz + 1, 256, 65536), 256, 0, st>>>(rsK[(transpose_passes(n) - 1) & 1],
-                                                               nnz, n, ptr);
-    return hipGetLastError();
+    return e != hipSuccess ? e
+                           : rs_bounds(st, rsK[(transpose_passes(n) - 1) & 1], nnz, n, ptr, nullptr);
 }
 
 hipError_t launch_filter(hipStream_t st, const int32_t *ptrM, const int32_t *itmM, int32_t M,
                          int64_t nnz, const int32_t *ptrI, int32_t N, int32_t s,
-                         const int32_t *s_item, int32_t *kept, int32_t *pos, int32_t *part32,
-                         int32_t *ptrS, int32_t *itmS, const int32_t *inv, int32_t *start,
-                         int32_t *crank, int32_t *orig, const int32_t *err) {
+                         int32_t *kept, int32_t *pos, int32_t *part32, int32_t *ptrS,
+                         int32_t *itmS, const int32_t *inv, int32_t *start, int32_t *crank,
+                         int32_t *orig, const int32_t *err) {
     if (M <= 0) return hipSuccess;
     if (nnz > 0) {
         const bool few = !crank && nnz < kFilterFew;
-        if (!few) k_item_kept<<<grid_for(N, 256, 65536), 256, 0, st>>>(ptrI, N, s, s_item, kept);
+        if (!few) k_item_kept<<<grid_for(N, 256, 65536), 256, 0, st>>>(ptrI, N, s, kept);
         k_filter_flags<<<grid_for(nnz, 256, 65536), 256, 0, st>>>(itmM, nnz, few ? nullptr : kept,
-                                                                 ptrI, s, s_item, pos, err);
+                                                                 ptrI, s, pos, err);
         hipError_t e = hipGetLastError();
         if (e == hipSuccess && crank) e = launch_scan_i32(st, kept, N, crank, part32);
         if (e != hipSuccess) return e;
@@ -940,7 +1095,7 @@ hipError_t launch_cost(hipStream_t st, const int32_t *ptrI, const int32_t *memI,
                        int64_t *cost, int32_t *start, int64_t *totals, int32_t full,
                        int32_t have_start, const int32_t *err) {
     if (N <= 0) return hipSuccess;
-    k_cost<<<grid_for((int64_t)N * kGroup, 256, 4096), 256, 0, st>>>(
+    k_cost<<<rows_grid(N, 4096), 256, 0, st>>>(
         ptrI, memI, N, s, s_item, ptrS, itmS, cost, start, totals, full, have_start, err);
     return hipGetLastError();
 }

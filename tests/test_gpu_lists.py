@@ -1,0 +1,91 @@
+"""Member lists of the kept items alone, rows walked by a lane, a group or a
+wave, and the combined rows of a batch, against the oracle: row lengths around
+the lane's and the group's limits, as many rows as the switch between the two,
+incidences around the sort's tiles and a wave's share, few and many kept."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2010_11448_amd import gen
+
+from helpers import assert_same, to_device
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = np.array([0, 1, 2, 3, 15, 16, 17, 18, 31, 32, 33, 64, 65])
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    from paper_2010_11448_amd import sline
+
+    assert torch.cuda.is_available()
+    c = sline.Context(0)
+    yield c
+    c.close()
+
+
+def rows(size, n: int, seed: int):
+    """A hypergraph with rows of exactly the given lengths (n >= 80): members in
+    even steps round [0, n), half of the rows from one of 64 places in steps
+    of one, so that they overlap."""
+    rng = np.random.default_rng(seed)
+    m = len(size)
+    narrow = rng.integers(0, 2, m) == 0
+    at = np.where(narrow, rng.integers(0, 64, m) * max(1, n // 64) + rng.integers(0, 3, m), rng.integers(0, n, m))
+    step = np.where(narrow, 1, rng.integers(1, max(2, n // 80), m))
+    rp = np.concatenate([[0], np.cumsum(size)])
+    row = np.repeat(np.arange(m), size)
+    v = (at[row] + (np.arange(rp[-1]) - rp[row]) * step[row]) % n
+    key = np.sort(row * n + v)
+    return gen.Hypergraph(rp.astype(np.int32), (key % n).astype(np.int32), m, n)
+
+
+def lengths(m: int, nnz: int, seed: int):
+    """m lengths with a sum of about nnz: mostly 0..3, the others from LENGTHS."""
+    rng = np.random.default_rng(seed)
+    size = rng.choice(LENGTHS[:4], m)
+    at = rng.choice(m, min(m, max(1, nnz // 100)), replace=False)
+    size[at] = rng.choice(LENGTHS, len(at))
+    return size
+
+
+@pytest.mark.parametrize("m,n,nnz", [(131071, 300000, 200000), (131072, 300000, 200000),
+                                     (140000, 5000, 90000), (3000, 1 << 18, 8192),
+                                     (900, 513, 9000), (300000, 1 << 20, 540000)])
+def test_build(ctx, m, n, nnz):
+    import torch
+
+    g = rows(lengths(m, nnz, m + n), n, seed=m)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    for s in (1, 2, 16, 17):
+        print(f"case: m={m} n={n} nnz={len(g.col)} s={s}", flush=True)
+        for dual in (0, 1):
+            ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, dual=dual, threads=8)
+            assert_same(ctx.build(rp, col, g.n_vertices, s, dual), ref, f"m={m} s={s} dual={dual}")
+
+
+@pytest.mark.parametrize("sizes", [(1023, 1, 1024, 0, 1025, 4096, 63, 64, 65), (0, 0, 5), (40000, 3, 40001),
+                                   (1 << 18, 7, 0)], ids=lambda s: "-".join(map(str, s)))
+def test_batch(ctx, sizes):
+    import torch
+
+    graphs = []
+    for q, z in enumerate(sizes):
+        size = lengths(max(1, z // 3), z, q)
+        size = size[np.cumsum(size) <= z]  # then one entry a row, up to z
+        size = np.concatenate([size, np.ones(z - int(size.sum()), dtype=size.dtype)])
+        graphs.append(rows(size, max(80, z // 2), seed=z + q))
+    dev = [(*to_device(g, torch.device("cuda", 0)), g.n_vertices) for g in graphs]
+    for first in (0, 1):
+        dual = [(q + first) % 2 for q in range(len(sizes))]
+        s = [1 + (3 * q + first) % 5 for q in range(len(sizes))]
+        print(f"case: batch {sizes} dual={dual} s={s}", flush=True)
+        got = ctx.build_batch(dev, s, dual)
+        for q, g in enumerate(graphs):
+            ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s[q], dual=dual[q], threads=8)
+            assert_same(got[q], ref, f"graph {q}")

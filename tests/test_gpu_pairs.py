@@ -62,7 +62,7 @@ def test_pairs(ctx, case):
         a, b = pairs(*case, seed=sum(case))
     else:  # a path with as many pairs as items less one, and `case[1]` more
         a, b = chain(N - 1 if case[1] < 0 else N, max(case[1], 0))
-    w = np.random.default_rng(N).integers(1, 1 << 30, len(a)).astype(np.int32)
+    w = np.random.default_rng(N).integers(-(1 << 30), 1 << 30, len(a)).astype(np.int32)
     print(f"case: {case} pairs={len(a)}", flush=True)
     ref = oracle.Pairs(a, b, w)
     L = sline.LineGraph(*[torch.from_numpy(x).cuda() for x in (a, b, w)])
