@@ -538,8 +538,9 @@ __device__ __forceinline__ bool bucket_full(const uint4 &q) {
 // the neighbouring buckets of the run.  Fill mode writes (a, b, w) in b order
 // at task_off[t] + rel; stage mode reserves room in the pool, writes (b, w)
 // there and logs the range (or flags task t when the pool or the log is
-// full).  Leaves the table cleared.
-template <int NT, int RUNCAP>
+// full).  Leaves the table cleared.  FILL: whether the mode is fill, if
+// compiled for one of them (else -1); LISTED: the lists hold every bucket.
+template <int NT, int RUNCAP, int FILL = -1, bool LISTED = false>
 __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S, const Range &R,
                                                int32_t a, int32_t sa, int32_t t, int64_t rel) {
     constexpr int W = NT / kWave;
@@ -583,7 +584,8 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
     int64_t base = 0;
     int32_t shift = 0;  // fill mode, batches written per graph: the graph's item base
     int32_t *dst_a = nullptr, *dst_b = nullptr, *dst_w = nullptr;
-    if (total && A.mode == kModeFill) {
+    const bool fill = FILL < 0 ? A.mode == kModeFill : FILL != 0;
+    if (total && fill) {
         write = true;
         const OutDst od = out_dst(A, a, A.task_off[t] + rel);
         base = od.base;
@@ -625,6 +627,7 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
         // run + (pairs of this wave's buckets before it).  `listed`: the
         // lanes hold the listed buckets, not consecutive ones.
         bool prev_full = R.mul && b0 > 0 && b0 < b1 && bucket_full(t4[b0 - 1]);
+        const bool outs = FILL < 0 ? dst_a != nullptr : FILL != 0;  // ids of items, and a
         auto emit = [&](auto listed, int32_t bk, bool vb) {
             const uint4 q = vb ? t4[bk] : make_uint4(0u, 0u, 0u, 0u);
             const uint32_t wv[4] = {q.x, q.y, q.z, q.w};
@@ -651,8 +654,8 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
                         const uint32_t cnt = (wv[k] >> (j * cbits)) & cm;
                         if (cnt >= s) {
                             const int32_t b = R.lo + (int32_t)(((uint32_t)(4 * bk + k) << R.psh) + j);
-                            if (dst_a) dst_a[base + pos] = a - shift;
-                            dst_b[base + pos] = dst_a ? item_of(A.orig, b) - shift : b;
+                            if (outs) dst_a[base + pos] = a - shift;
+                            dst_b[base + pos] = outs ? item_of(A.orig, b) - shift : b;
                             if (dst_w) dst_w[base + pos] = (int32_t)cnt;
                             ++pos;
                         }
@@ -664,9 +667,9 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     if (ok[k]) {
-                        if (dst_a) dst_a[base + pos] = a - shift;
+                        if (outs) dst_a[base + pos] = a - shift;
                         const int32_t b = R.lo + 4 * bk + k;
-                        dst_b[base + pos] = dst_a ? item_of(A.orig, b) - shift : b;
+                        dst_b[base + pos] = outs ? item_of(A.orig, b) - shift : b;
                         if (dst_w) dst_w[base + pos] = (int32_t)c[k];
                         ++pos;
                     }
@@ -738,16 +741,16 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
                 for (int k = 0; k < 4; ++k) {
                     if (k < n) {
                         const int32_t p = pos + rank[k];
-                        if (dst_a) dst_a[base + p] = a - shift;
+                        if (outs) dst_a[base + p] = a - shift;
                         const int32_t b = R.lo + (int32_t)tag[k] - 1;
-                        dst_b[base + p] = dst_a ? item_of(A.orig, b) - shift : b;
+                        dst_b[base + p] = outs ? item_of(A.orig, b) - shift : b;
                         if (dst_w) dst_w[base + p] = (int32_t)(key[k] & R.cmask);
                     }
                 }
             }
             run += step;
         };
-        if (nact <= LCAP) {
+        if (LISTED || nact <= LCAP) {
             // only the buckets that hold pairs, 64 at a time
             for (int32_t i = 0; i < nact; i += kWave) {
                 const bool vb = i + lane < nact;
@@ -970,7 +973,10 @@ __global__ __launch_bounds__(kWave) void k_count_small(CountArgs A) {
 // 64 wedges and walk and 30 per 64 wedges let through.  So the next item's
 // part of the chain is read while this one is counted, and small items get a
 // single wave, whose barriers cost nothing and whose per-item steps are not
-// repeated by other waves: 4 KB of LDS for up to 256 wedges, 10.8 KB (15 waves
+// repeated by other waves.  FILL: compiled for the fill mode, or for the two
+// others; one kernel for all modes kept twice the arguments, half of them
+// spilled (109 scalar registers, 342 reads of them), and a third more
+// instructions.  4 KB of LDS for up to 256 wedges, 10.8 KB (15 waves
 // per CU) for up to 2048, 40 KB and four waves for up to 8192.
 constexpr int kSieveList = 5 * kWave;  // wedges a wave collects
 
@@ -993,7 +999,7 @@ __device__ __forceinline__ ItemDesc item_desc(const CountArgs &A, int32_t a) {
     return d;
 }
 
-template <int KIND, int NT, int LIM, int CHUNKS, int MINB>
+template <int KIND, int NT, int LIM, int CHUNKS, int MINB, bool FILL>
 __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
     constexpr int NW = NT / kWave;
     constexpr bool SIEVE = KIND != kKindMini;
@@ -1002,6 +1008,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
     constexpr int RUNCAP = ((LIM / 4 / NW + kWave - 1) / kWave * kWave) * NW * 2 / 8;
     constexpr int LISTS = SIEVE ? NW * kSieveList : RUNCAP * 2;
     static_assert(LISTS * sizeof(int32_t) >= RUNCAP * sizeof(int2), "list area");
+    static_assert(RUNCAP * sizeof(int2) / sizeof(uint16_t) >= LIM / 4, "every bucket listed");
     static_assert(!SIEVE || (LIM & (LIM - 1)) == 0, "bits are chosen by a mask");
     __shared__ __align__(16) uint32_t tab[LIM + kWave];  // first walk: `seen`; then the table
     __shared__ __align__(16) uint32_t twice[SIEVE ? LIM : 4];
@@ -1061,7 +1068,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
         const int32_t t = uniform(cur.t), a = uniform(cur.a), s = uniform(cur.s);
         const int32_t size = uniform(cur.size);
         const int32_t first = uniform(cur.first), nend = uniform(cur.nend);
-        const bool skip = A.mode == kModeFill && A.need && !A.need[t];
+        const bool skip = FILL && A.need && !A.need[t];
         map.narrow = NT == kWave || size <= kWave;
         int32_t nv = -1, nb = 0, ne = 0;
         if (!skip) {
@@ -1173,7 +1180,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
                     if (!ok) misc[kMiscOverflow] = 1;
                     __syncthreads();
                     split = misc[kMiscOverflow] != 0;
-                    if (!split) produced += tab_extract<NT, RUNCAP>(A, S, R, a, s, t, produced);
+                    if (!split) produced += tab_extract<NT, RUNCAP, FILL ? 1 : 0, true>(A, S, R, a, s, t, produced);
                     else tab_clear<NT>(tab, R.limit);
                 }
                 __syncthreads();
@@ -1191,7 +1198,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
                 __syncthreads();
             }
             if (sieve) tab_clear<NT>(twice, words);
-            if (A.mode != kModeFill) {
+            if (!FILL) {
                 if (tid == 0) A.task_cnt[t] = produced;
                 my_wedges += total;
                 my_nnz += size;
@@ -1206,7 +1213,7 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
         b = nb;
         e = ne;
     }
-    if (tid == 0 && A.passes && A.mode != kModeFill) {
+    if (tid == 0 && A.passes && !FILL) {
         unsigned long long *wk = stat_row(A);
         if (passes) atomicAdd(&wk[0], (unsigned long long)passes);
         if (KIND != kKindMini) {  // work figures: the kernels of heavier items
@@ -1754,9 +1761,13 @@ hipError_t launch_count(hipStream_t st, const CountArgs &A, hipEvent_t mid) {
         default: k_count_small<1024><<<g[kKindSmall], kWave, 0, st>>>(A); break;
         }
     }
-    if (g[kKindMini] > 0)
-        k_count_item<kKindMini, kWave, 2 * kMiniWedges + kTaskPad, kMiniWedges / kWave, 5>
-            <<<g[kKindMini], kWave, 0, st>>>(A);
+    const bool fill = A.mode == kModeFill;
+    if (g[kKindMini] > 0) {
+        constexpr int LIM = 2 * kMiniWedges + kTaskPad, CHUNKS = kMiniWedges / kWave;
+        auto *const count = fill ? k_count_item<kKindMini, kWave, LIM, CHUNKS, 7, true>
+                                 : k_count_item<kKindMini, kWave, LIM, CHUNKS, 7, false>;
+        count<<<g[kKindMini], kWave, 0, st>>>(A);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (g[kKindGroups] > 0 || g[kKindFlat] > 0) k_reset_queue<<<1, 1, 0, st>>>(A.queue);
@@ -1768,12 +1779,18 @@ hipError_t launch_count(hipStream_t st, const CountArgs &A, hipEvent_t mid) {
         e = launch_count_flat(st, A);
         if (e != hipSuccess) return e;
     }
-    if (g[kKindSieve4] > 0)
-        k_count_item<kKindSieve4, kSieveLarge, kSieveLarge * 16, kSieveLarge * kSieveWedges / kWave, 4>
-            <<<g[kKindSieve4], kSieveLarge, 0, st>>>(A);
-    if (g[kKindSieve1] > 0)
-        k_count_item<kKindSieve1, kSieveSmall, kSieveSmall * 16, kSieveSmall * kSieveWedges / kWave, 4>
-            <<<g[kKindSieve1], kSieveSmall, 0, st>>>(A);
+    if (g[kKindSieve4] > 0) {
+        constexpr int LIM = kSieveLarge * 16, CHUNKS = kSieveLarge * kSieveWedges / kWave;
+        auto *const count = fill ? k_count_item<kKindSieve4, kSieveLarge, LIM, CHUNKS, 4, true>
+                                 : k_count_item<kKindSieve4, kSieveLarge, LIM, CHUNKS, 4, false>;
+        count<<<g[kKindSieve4], kSieveLarge, 0, st>>>(A);
+    }
+    if (g[kKindSieve1] > 0) {
+        constexpr int LIM = kSieveSmall * 16, CHUNKS = kSieveSmall * kSieveWedges / kWave;
+        auto *const count = fill ? k_count_item<kKindSieve1, kSieveSmall, LIM, CHUNKS, 4, true>
+                                 : k_count_item<kKindSieve1, kSieveSmall, LIM, CHUNKS, 4, false>;
+        count<<<g[kKindSieve1], kSieveSmall, 0, st>>>(A);
+    }
     if (g[kKindGroups] > 0) {
         const int gh = g[kKindGroups];
         switch (A.tune.task_slots) {
@@ -1789,17 +1806,29 @@ hipError_t launch_count(hipStream_t st, const CountArgs &A, hipEvent_t mid) {
 }
 
 int32_t set_grids(CountArgs &A, const int64_t *items) {
-    // workgroups a CU holds: tiny four (32 KB of LDS each), item kernels 20 of one
-    // wave (registers), 15 and four (LDS), direct counters two; the hashed
-    // kernels as tuned
+    // workgroups a CU holds: tiny four (32 KB of LDS each), item kernels 28 of one
+    // wave (registers; 20 where items are few, as each costs room in the pool), 15
+    // and four (LDS), direct counters two; the hashed kernels as tuned
     const int per_cu[kKinds] = {A.tune.small_grid_per_cu, A.tune.task_grid_per_cu, 4, 2, 15, 4, 20};
+    // Item kernels share their items out evenly, but not their time: with just the
+    // workgroups that fit, few were left at work in the end (2.1 of 3.75 waves per
+    // SIMD in the mean).  So several rounds of them, as long as each has
+    // kRoundItems items to take; 128 graphs: sieve of one wave 3.4 ms in one
+    // round, 2.3 in four; up to 256 wedges 1.8 and 1.6; 10^6 hyperedges, sieve of
+    // four waves 6.5 and 6.0.  More rounds gained little and cost room
+    // in pool and log.
+    constexpr int kRounds[kKinds] = {1, 1, 2, 1, 6, 4, 5};
+    constexpr int64_t kRoundItems = 8;
     int32_t total = 0;
     for (int k = 0; k < kKinds; ++k) {
         int64_t g = std::max(1, A.n_cu * per_cu[k]);
         if (items) {
             const int64_t n = k == kKindTiny ? (items[k] + kTinyThreads - 1) / kTinyThreads : items[k];
+            g = std::max(g, std::min(g * kRounds[k], n / kRoundItems));
             // items in groups or ranges take several workgroups each
             if (n == 0 || (k != kKindGroups && k != kKindFlat)) g = std::min(g, n);
+        } else {
+            g *= kRounds[k];
         }
         A.grid[k] = (int32_t)g;
         total += (int32_t)g;
