@@ -82,6 +82,7 @@ struct FlatTask {
     int64_t cost;
 };
 
+template <bool FILL, bool ONES>
 __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
     constexpr int NT = kFlatThreads, NW = NT / kWave;
     constexpr int kKeep = kFlatKeep / NT;  // wedges a lane holds (s = 1)
@@ -171,11 +172,11 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
         const int32_t per = flat_ranges_per_task(F, cost);
         const int32_t part = uniform(cur.part);
         const int32_t p0 = part * per, p1 = min(F.ranges, p0 + per);
-        const bool skip = A.mode == kModeFill && A.need && !A.need[t];
+        const bool skip = FILL && A.need && !A.need[t];
         // bits per counter as a shift, counters per word as a shift
         const uint32_t lb = F.lbits, psh = 5u - lb;
-                const bool keep = flat_keeps(s, cost, k1 - k0);
-        if (part == 0 && A.mode != kModeFill) {
+        const bool keep = ONES && flat_keeps(s, cost, k1 - k0);
+        if (part == 0 && !FILL) {
             my_wedges += cost;
             my_nnz += k1 - k0;
         }
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
         // Thread 0: room for `total` pairs of the task.
         auto reserve = [&](int32_t total) {
             bool ok = true;
-            if (A.mode == kModeStage) {
+            if (!FILL && A.mode == kModeStage) {
                 uint64_t off;
                 int32_t rec;
                 ok = stage_reserve(A, pool_cur, log_cur, total, 1, off, rec);
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
                 }
                 sh_off = off;
             }
-            sh_ok = ok && A.mode != kModeCount ? 1 : 0;
+            sh_ok = ok && (FILL || A.mode != kModeCount) ? 1 : 0;
         };
         // Where reserved pairs go.
         struct Dest {
@@ -235,15 +236,12 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
             int32_t shift;
         };
         auto dest = [&]() {
-            Dest d{nullptr, A.pool_b, A.pool_w, (int64_t)sh_off, 0};
-            if (A.mode == kModeFill) {
-                const OutDst od = out_dst(A, a, A.task_off[t] + produced);
-                d = Dest{od.a, od.b, od.w, od.base, od.shift};
-            }
-            return d;
+            if (!FILL) return Dest{nullptr, A.pool_b, A.pool_w, (int64_t)sh_off, 0};
+            const OutDst od = out_dst(A, a, A.task_off[t] + produced);
+            return Dest{od.a, od.b, od.w, od.base, od.shift};
         };
         auto put = [&](const Dest &d, int64_t o, int32_t cand, int32_t w) {
-            if (d.a) {
+            if (FILL) {
                 d.a[o] = a - d.shift;
                 d.b[o] = item_of(A.orig, cand) - d.shift;
             } else {
@@ -496,7 +494,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
                 __syncthreads();
             }
         }
-        if (!skip && A.mode != kModeFill && tid == 0) {
+        if (!skip && !FILL && tid == 0) {
             A.task_cnt[t] = produced;
             my_pairs += produced;
         }
@@ -506,7 +504,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
         r1 = sh_task;
         cur = nxt;
     }
-    if (tid == 0 && A.passes && A.mode != kModeFill) {
+    if (tid == 0 && A.passes && !FILL) {
         unsigned long long *wk = stat_row(A);
         if (passes) atomicAdd(&wk[0], (unsigned long long)passes);
         if (my_nnz) atomicAdd(&wk[1], (unsigned long long)my_nnz);
@@ -526,7 +524,11 @@ hipError_t launch_flat_bounds(hipStream_t st, const int32_t *ptrS, const int32_t
 }
 
 hipError_t launch_count_flat(hipStream_t st, const CountArgs &A) {
-    k_count_flat<<<A.grid[kKindFlat], kFlatThreads, 0, st>>>(A);
+    // A.s is the least s of a batch; only items with s = 1 keep their wedges
+    const bool fill = A.mode == kModeFill, ones = A.s <= 1;
+    auto *const count = fill ? (ones ? k_count_flat<true, true> : k_count_flat<true, false>)
+                             : (ones ? k_count_flat<false, true> : k_count_flat<false, false>);
+    count<<<A.grid[kKindFlat], kFlatThreads, 0, st>>>(A);
     return hipGetLastError();
 }
 
