@@ -168,16 +168,17 @@ struct WedgeMap {
     static constexpr int NW = NT / kWave, PER = CHUNKS / NW;
     static_assert(PER <= kWave && PER * NW == CHUNKS, "a lane per chunk of a run");
 
-    int32_t *adj_all;     // NT: list position less wedge number, per part that has wedges
+    int32_t *adj_all;     // NT: 4 * (list position less wedge number), per part that has wedges
     uint32_t *marks_all;  // 2 * CHUNKS words, all zero between windows
     int32_t *sh;          // 3 * NW
     bool narrow;
     int32_t *adj;
     int32_t off, len, rank, total;  // this thread's part, and all wedges
 
-    // a run: the bits of chunk c0 + lane, the parts before it and the list
-    // position of its first wedge; the chunks that lie in one part (bit per
-    // chunk), chunks and wedges of the run
+    // a run: the bits of chunk c0 + lane but the first (bit i: a part begins at
+    // wedge i + 1), the part of its first wedge and the byte offset of that one's
+    // list entry; the chunks that lie in one part (bit per chunk), chunks and
+    // wedges of the run
     struct Run {
         uint32_t lo, hi;
         int32_t base, pos;
@@ -215,7 +216,7 @@ struct WedgeMap {
                 total += l;
             }
         }
-        if (n > 0) adj[rank] = b - off;
+        if (n > 0) adj[rank] = (int32_t)((uint32_t)(b - off) << 2);
     }
 
     // The wave's run of the window that starts at wedge w0 < total.
@@ -258,37 +259,38 @@ struct WedgeMap {
             r.hi = v.y;
         }
         const int32_t pop = __popc(r.lo) + __popc(r.hi);
-        r.base = before + wave_incl(pop) - pop;
+        r.base = before + wave_incl(pop) - pop + (int32_t)(r.lo & 1u);
+        r.lo = (r.lo >> 1) | (r.hi << 31);
+        r.hi >>= 1;
         r.pos = 0;
-        if (lane < r.nc) r.pos = adj[r.base + (int32_t)(r.lo & 1u)] + r.t0 + lane * kWave;
-        r.whole = __ballot(((r.lo & ~1u) | r.hi) == 0u);
+        if (lane < r.nc) r.pos = adj[r.base] + ((r.t0 + lane * kWave) << 2);
+        r.whole = __ballot((r.lo | r.hi) == 0u);
         return r;
     }
 
-    // List positions of the wedges of chunk u < nc of the run (a lane past the
-    // run's end gets its last wedge's).
-    __device__ __forceinline__ int32_t position(const Run &r, int32_t u, bool full) const {
+    // Byte offsets of the list entries of chunk u < nc of the run (a lane past
+    // the run's end gets its last wedge's).
+    __device__ __forceinline__ uint32_t position(const Run &r, int32_t u, bool full) const {
         if (full && ((r.whole >> u) & 1u))
-            return __builtin_amdgcn_readlane(r.pos, u) + lane_id();
+            return (uint32_t)__builtin_amdgcn_readlane(r.pos, u) + ((uint32_t)lane_id() << 2);
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int32_t)r.lo, u);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int32_t)r.hi, u);
-        const uint64_t m = ((uint64_t)hi << 32) | lo;
-        const int32_t q = __builtin_amdgcn_readlane(r.base, u) + (int32_t)(lo & 1u) +
-                          (int32_t)lanes_below(m >> 1);
-        return adj[q] + r.t0 + (full ? u * kWave + lane_id() : min(u * kWave + lane_id(), r.n - 1));
+        const uint32_t q = __builtin_amdgcn_mbcnt_hi(
+            hi, __builtin_amdgcn_mbcnt_lo(lo, (uint32_t)__builtin_amdgcn_readlane(r.base, u)));
+        const int32_t in = full ? u * kWave + lane_id() : min(u * kWave + lane_id(), r.n - 1);
+        return (uint32_t)adj[q] + ((uint32_t)(r.t0 + in) << 2);
     }
 
     // A list entry; positions lie below 2^30, so a 32-bit offset reaches it.
-    static __device__ __forceinline__ int32_t entry(const int32_t *itmS, int32_t p) {
-        return *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(itmS) +
-                                                  ((uint32_t)p << 2));
+    static __device__ __forceinline__ int32_t entry(const int32_t *itmS, uint32_t at) {
+        return *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(itmS) + at);
     }
 
     // Candidates of chunks u0 .. u0 + K - 1 of the run, -1 past its end.
     template <int K>
     __device__ __forceinline__ void load(const int32_t *itmS, const Run &r, int32_t u0,
                                          int32_t (&j)[K]) const {
-        int32_t p[K];
+        uint32_t p[K];
         if ((u0 + K) * kWave <= r.n) {
 #pragma unroll
             for (int v = 0; v < K; ++v) p[v] = position(r, u0 + v, true);

@@ -21,10 +21,14 @@
 // A counter has 4, 8 or 16 bits, enough for the item's size, which bounds
 // every overlap; a range is as wide as the counters fit in kFlatWords words.
 //
-// What bounds it: LDS atomics and the vector instructions around them (about
-// 20 per 64 wedges), and per range the barriers and the clearing of up to
-// 75 KB.  Two workgroups of 512 threads share a CU, so one counts while the
-// other waits or clears.
+// What bounds it: vector instructions (about 20 per 64 wedges and 250 per wave
+// and range; they fill 54% of the cycles), and the waits of a range that is too
+// short to hide them: LDS reads one after the other, three barriers, lists that
+// are read for the first time.  Two workgroups of 512 threads share a CU, so one
+// counts while the other waits or clears.  A wave's chunks are counted eight at a time,
+// the last ones in groups of eight, four or two: 10^6 hyperedges, s = 2 (8.7*10^9
+// wedges, most of them here): 20.6 ms, 22.0 with eight for all, 24.0 before the
+// kernel was compiled apart for the fill mode and for s = 1.
 #include <algorithm>
 
 #include "sline_count.h"
@@ -68,6 +72,14 @@ __global__ __launch_bounds__(256) void k_flat_bounds(const int32_t *ptrS, const 
             }
         }
     }
+}
+
+// v << n for the low five bits of n: the instruction itself, as the compiler
+// masks n before it where it knows some bit of it.
+__device__ __forceinline__ uint32_t shift_left(uint32_t v, uint32_t n) {
+    uint32_t r;
+    asm("v_lshlrev_b32 %0, %1, %2" : "=v"(r) : "v"(n), "v"(v));
+    return r;
 }
 
 // One member of an item: its walk [st, en) of N_s(v), and the list's row of the
@@ -186,18 +198,19 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
         const uint32_t s_1 = (uint32_t)s - 1u;
 
         // Count wedges, x = candidate - first of the range (>= span: none).
-        auto count = [&](const int32_t (&j)[kLoad], int32_t lo, uint32_t span) {
-            uint32_t x[kLoad], old[kLoad];
+        auto count = [&](const auto &j, int32_t lo, uint32_t span) {
+            constexpr int K = sizeof(j) / sizeof(j[0]);
+            uint32_t x[K], at[K], old[K];
 #pragma unroll
-            for (int u = 0; u < kLoad; ++u) {
+            for (int u = 0; u < K; ++u) {
                 x[u] = (uint32_t)(j[u] - lo);
-                if (x[u] < span)
-                    old[u] = atomicAdd(&ctr[x[u] >> psh], 1u << ((x[u] << lb) & 31u));
+                at[u] = x[u] << lb;  // the counter's bit
+                old[u] = ~0u;        // no count: the item has fewer members than a counter holds
+                if (x[u] < span) old[u] = atomicAdd(&ctr[at[u] >> 5], shift_left(1u, at[u]));
             }
 #pragma unroll
-            for (int u = 0; u < kLoad; ++u) {
-                const bool hit =
-                    x[u] < span && __builtin_amdgcn_ubfe(old[u], x[u] << lb, 1u << lb) == s_1;
+            for (int u = 0; u < K; ++u) {
+                const bool hit = __builtin_amdgcn_ubfe(old[u], at[u], 1u << lb) == s_1;
                 const uint64_t m = __ballot(hit);
                 if (m) {
                     if (hit)
@@ -463,15 +476,42 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
                     for (int32_t w0 = 0; w0 < map.total; w0 += kFlatChunks * kWave) {
                         const auto run = map.window(w0);
                         if (run.nc > 0) {
-                            int32_t ja[kLoad], jb[kLoad];
-                            map.load(A.itmS, run, 0, ja);
-                            // the next chunks are loaded while these are counted
-                            for (int32_t u = 0; u < run.nc; u += 2 * kLoad) {
-                                if (u + kLoad < run.nc) map.load(A.itmS, run, u + kLoad, jb);
-                                count(ja, lo, span);
-                                if (u + kLoad >= run.nc) break;
-                                if (u + 2 * kLoad < run.nc) map.load(A.itmS, run, u + 2 * kLoad, ja);
-                                count(jb, lo, span);
+                            // the next chunks are loaded while these are counted;
+                            // the last ones in as many as there are
+                            int32_t u = 0;
+                            if (run.nc >= kLoad) {
+                                int32_t ja[kLoad], jb[kLoad];
+                                map.load(A.itmS, run, 0, ja);
+                                for (;;) {
+                                    u += kLoad;
+                                    if (u + kLoad > run.nc) {
+                                        count(ja, lo, span);
+                                        break;
+                                    }
+                                    map.load(A.itmS, run, u, jb);
+                                    count(ja, lo, span);
+                                    u += kLoad;
+                                    if (u + kLoad > run.nc) {
+                                        count(jb, lo, span);
+                                        break;
+                                    }
+                                    map.load(A.itmS, run, u, ja);
+                                    count(jb, lo, span);
+                                }
+                            }
+                            const int32_t last = run.nc - u;
+                            if (last > 4) {
+                                int32_t j[8];
+                                map.load(A.itmS, run, u, j);
+                                count(j, lo, span);
+                            } else if (last > 2) {
+                                int32_t j[4];
+                                map.load(A.itmS, run, u, j);
+                                count(j, lo, span);
+                            } else if (last > 0) {
+                                int32_t j[2];
+                                map.load(A.itmS, run, u, j);
+                                count(j, lo, span);
                             }
                         }
                         if (!map.narrow) __syncthreads();  // the map is used again
