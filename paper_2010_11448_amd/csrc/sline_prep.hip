@@ -8,6 +8,8 @@
 // with both adjacencies the counting kernels walk, for an item a, only the
 // items that share a member with it (Sec. IV-B).  Item sizes |S_a| drive the
 // degree-based pruning of Sec. IV-C.
+#include <type_traits>
+
 #include "sline_internal.h"
 
 namespace sl {
@@ -737,31 +739,41 @@ __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t
 // sign bit of start[k].  At least one member stays unflagged, as |S_a| >= s
 // for a kept item.  The item's planning cost becomes the wedges of its
 // inserting members (they fill the table), but at least a third of W_a
-// (every wedge is still read).  A row of at most W * kKeysPerLane members
-// keeps its keys in registers, so the rounds only exchange maxima; longer
-// rows read their members again in every round.  The lane that owns
-// incidence k is the one that flags it.
-constexpr int kKeysPerLane = 4;
+// (every wedge is still read).  A lane looks at each item, and the wave then takes
+// those that the task kernel counts, one after the other: they are few (a
+// group of lanes for every item took 0.31 ms for 5*10^6 of them, this 0.09).  Rows of up to 256 and up to 2048 members keep their keys in registers,
+// so the rounds only exchange maxima; longer rows read their members again in
+// every round (as all above 256 did: one of 2000 members kept the kernel up 0.25 ms).
+// The lane that owns incidence k is the one that flags it.
+constexpr int kKeysFew = 4, kKeysMany = 32;
 
 __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t *memI,
                                                      const int32_t *ptrS,
                                                      int32_t *start, int64_t *cost) {
     I.crank = ranks_or_null(I.crank, I.N);
-    for_all_rows<kGroup * kKeysPerLane, false>(I.ptrI, I.N, [&](int64_t a, int gl, int W) {
-        auto best_of = [&](uint64_t v) { return W == kWave ? group_max<kWave>(v) : group_max<kGroup>(v); };
+    constexpr int W = kWave;
+    const int gl = lane_id();
+    auto best_of = [&](uint64_t v) { return group_max<kWave>(v); };
+    // only items that the task kernel counts: the others count every wedge
+    auto counted = [&](int64_t a) {
+        if (a >= I.N) return false;
+        const int64_t w = cost[a];
+        if (w <= I.small_max) return false;
+        if (I.ptrI[a + 1] - I.ptrI[a] < (I.s_item ? I.s_item[a] : I.s)) return false;
+        int32_t kind, ranges;
+        return direct_tasks(I, (int32_t)a, w, kind, ranges) == 0;
+    };
+    auto mark = [&](int64_t a) {
         const int32_t b = I.ptrI[a], e = I.ptrI[a + 1];
         const int32_t s = I.s_item ? I.s_item[a] : I.s;
-        if (e - b < s) return;
-        // only items that the task kernel counts: the others count every wedge
-        if (cost[a] <= I.small_max) return;
-        int32_t kind, ranges;
-        if (direct_tasks(I, (int32_t)a, cost[a], kind, ranges) > 0) return;
         const int32_t rounds = min(min(s - 1, kMaxLookup), e - b - 1);
         int64_t flagged = 0;
-        if (e - b <= W * kKeysPerLane) {
-            uint64_t key[kKeysPerLane];
+        // the row's keys in K registers of each lane
+        auto keyed = [&](auto per_lane) {
+            constexpr int K = decltype(per_lane)::value;
+            uint64_t key[K];
 #pragma unroll
-            for (int i = 0; i < kKeysPerLane; ++i) {
+            for (int i = 0; i < K; ++i) {
                 const int32_t k = b + gl + i * W;
                 key[i] = 0;
                 if (k < e) {
@@ -774,12 +786,12 @@ __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t 
             for (int32_t r = 0; r < rounds; ++r) {
                 uint64_t best = 0;
 #pragma unroll
-                for (int i = 0; i < kKeysPerLane; ++i) best = key[i] > best ? key[i] : best;
+                for (int i = 0; i < K; ++i) best = key[i] > best ? key[i] : best;
                 best = best_of(best);
                 if ((best >> 32) == 0) break;  // no member with candidates left
                 const int32_t k = INT32_MAX - (int32_t)(uint32_t)best;
 #pragma unroll
-                for (int i = 0; i < kKeysPerLane; ++i) {
+                for (int i = 0; i < K; ++i) {
                     if (key[i] == best) {  // keys are distinct: one owner
                         key[i] = 0;
                         start[k] |= (int32_t)0x80000000u;
@@ -787,6 +799,11 @@ __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t 
                 }
                 flagged += (int64_t)(best >> 32);
             }
+        };
+        if (e - b <= W * kKeysFew) {
+            keyed(std::integral_constant<int, kKeysFew>{});
+        } else if (e - b <= W * kKeysMany) {
+            keyed(std::integral_constant<int, kKeysMany>{});
         } else for (int32_t r = 0; r < rounds; ++r) {
             // best unflagged member: most candidates, then lowest k
             uint64_t best = 0;
@@ -809,7 +826,11 @@ __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t 
             const int64_t least = min(w, (int64_t)kSieveWedges * kSieveLarge + 1);
             cost[a] = max(max(w - flagged, (w + 2) / 3), w > least ? least : (int64_t)0);
         }
-    });
+    };
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
+    for (int64_t base = wave * kWave; base < I.N; base += nwaves * kWave)
+        for (uint64_t m = __ballot(counted(base + gl)); m; m &= m - 1) mark(base + __builtin_ctzll(m));
 }
 
 // Product filter, one block per tile of kFilterTile entries (256 threads x
@@ -1103,7 +1124,7 @@ hipError_t launch_cost(hipStream_t st, const int32_t *ptrI, const int32_t *memI,
 hipError_t launch_mark_lookup(hipStream_t st, const PlanItems &I, const int32_t *memI,
                               const int32_t *ptrS, int32_t *start, int64_t *cost) {
     if (I.N <= 0) return hipSuccess;
-    k_mark_lookup<<<grid_for((int64_t)I.N * kGroup, 256, 16384), 256, 0, st>>>(I, memI, ptrS, start,
+    k_mark_lookup<<<grid_for(I.N, 256, 16384), 256, 0, st>>>(I, memI, ptrS, start,
                                                                               cost);
     return hipGetLastError();
 }

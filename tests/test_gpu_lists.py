@@ -89,3 +89,25 @@ def test_batch(ctx, sizes):
         for q, g in enumerate(graphs):
             ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s[q], dual=dual[q], threads=8)
             assert_same(got[q], ref, f"graph {q}")
+
+
+@pytest.mark.parametrize("k", [2, 64, 255, 256, 257, 2047, 2048, 2049, 3000])
+def test_lookup_members(ctx, k):
+    """Lookup-only members of an item that the hashed task kernel counts: as
+    many members as a lane's registers hold, fewer and more."""
+    import torch
+
+    from test_gpu_direct import hub
+
+    r = min(k, 12)
+    g = hub(2000, k, r, 9000, seed=k)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    base = ctx.tuning()
+    ctx.set_tuning(dense_min_wedges=0)
+    try:
+        for s in sorted({2, 3, r, r + 1}):
+            print(f"case: k={k} s={s}", flush=True)
+            ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, threads=8)
+            assert_same(ctx.build(rp, col, g.n_vertices, s), ref, f"k={k} s={s}")
+    finally:
+        ctx.set_tuning(**base)
