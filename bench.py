@@ -10,11 +10,11 @@ freed before the next call).
 
 The one JSON line carries, beside ``value``:
 
-* ``roofline`` -- the dominant kernel (the workgroup counting kernel
-  k_count_tasks): algorithmic bytes 12*nnz + 4*W + 8*P of the items it counts
-  (their incidences, wedges and the (b, w) pairs it stages) over its run time,
-  HIP events on the library's stream around that kernel alone; HBM traffic
-  from the committed rocprofv3 counter summary of that kernel when the kernel
+* ``roofline`` -- the dominant kernels (the counting kernels of heavy items):
+  algorithmic bytes 12*nnz + 4*W + 8*P of the items they count
+  (their incidences, wedges and the (b, w) pairs they stage) over their run time,
+  HIP events on the library's stream around those kernels; HBM traffic
+  from the committed rocprofv3 counter summary of k_count_tasks when the kernel
   source is unchanged since it was taken (else null).  ``build_frac`` is the
   whole build's share of HBM peak under 12*nnz_s + 4*W_s + 12*|L_s|.
 * ``cpu_baseline`` -- the wedge oracle O3 (the alternative algorithm of
@@ -366,7 +366,7 @@ def bench_plain(args, g, dual, s_list, dev):
                    "s": list(s_list), "dual": dual, "builds_per_step": len(s_list)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_count_tasks (workgroup counting kernel, one launch per build)",
+                     "kernel": "counting kernels of heavy items (k_count_flat, k_count_item, k_count_tasks), one launch each per build",
                      "alg_bytes_per_launch": "12*nnz + 4*W + 8*P over the items it counts",
                      "alg_bytes_mean": alg_bytes / max(launches, 1),
                      "ms_mean": task_ms / max(launches, 1), "launches": launches,

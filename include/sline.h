@@ -130,20 +130,20 @@ typedef struct {
     int64_t n_kept;       /* items with |S| >= s                                  */
     int64_t wedges;       /* W_s: (a, v, b) with a < b, both kept, v shared       */
     int64_t n_pairs;      /* |L_s|                                                */
-    int64_t n_small;      /* items counted by the one-wave kernel                 */
-    int64_t n_heavy;      /* items counted by the workgroup (multi-pass) kernel   */
-    int64_t passes;       /* table passes made by the workgroup kernel            */
+    int64_t n_small;      /* items counted by the kernels for light items         */
+    int64_t n_heavy;      /* items counted by the kernels for heavy items         */
+    int64_t passes;       /* table passes and counter ranges of all kernels       */
     /* stage times in milliseconds, filled when the build had SLINE_PROFILE  */
     double ms_transpose;  /* row checks + transpose (radix sort by member)        */
     double ms_prepare;    /* s filter, per-item wedge counts, buckets             */
     double ms_count;      /* count pass (counting kernels, pairs per item)        */
     double ms_scan;       /* exclusive scan of pairs per item                     */
     double ms_fill;       /* fill pass (counting kernels writing the pairs)       */
-    /* the workgroup counting kernel alone (its count or staging pass)        */
+    /* the counting kernels of heavy items alone (their count or staging pass) */
     int64_t heavy_nnz;    /* incidences of the items it counted                   */
     int64_t heavy_wedges; /* wedges it walked                                     */
     int64_t heavy_pairs;  /* pairs it produced                                    */
-    double ms_tasks;      /* its run time (SLINE_PROFILE)                         */
+    double ms_tasks;      /* their run time (SLINE_PROFILE)                       */
     /* sline_build_spgemm only                                                */
     int64_t product_nnz;  /* entries of the materialized product H H^T          */
     double ms_product;    /* product time (host clock)                          */
@@ -168,20 +168,24 @@ typedef struct {
  *   stage_max_bytes    cap of the staging pool that lets one counting pass
  *                      produce the result; tasks that do not fit are counted
  *                      again (>= 0; 0 = always two passes)
- *   dense_min_wedges   an item whose candidates give at least this many
- *                      wedges per sub-range narrow enough for direct
- *                      (unhashed) counters is cut into such sub-ranges
- *                      (0..2^24; 0 = sub-ranges by wedge count only)
+ *   dense_min_wedges   an item with more wedges than a sieve takes is counted
+ *                      by direct (unhashed) counters when it has at least an
+ *                      eighth of this many wedges per range of candidates
+ *                      that they hold (a sixteenth with s = 1 and at most
+ *                      16384 wedges); other items are cut into unhashed
+ *                      sub-ranges of the task kernel where each gets at
+ *                      least this many (0..2^24; 0 = hash tables alone, for
+ *                      every item, in sub-ranges by wedge count)
  *   small_slots        home slots of the one-wave kernel's LDS table: 512,
  *                      1024 or 2048 (small_max_wedges at most half of it)
  *   task_slots         home slots of the task kernel's LDS table: 4480 or 8960
  *                      (256-thread workgroups, four per CU), 13440 (256
  *                      threads, two per CU) or 17920 (512 threads, two per
  *                      CU); larger tables cut fewer sub-ranges per item
- *   tiny_max_wedges    in builds of at least 32768 items, items with a
- *                      planning cost of at most this (and at most 32 members)
- *                      are counted one per lane, by sorting their candidates
- *                      (0..10; 0 = off) */
+ *   tiny_max_wedges    in builds of at least 32768 items, items with at most
+ *                      this many wedges (three times as many with s > 2; and
+ *                      at most 32 members) are counted one per lane, by
+ *                      sorting their candidates (0..10; 0 = off) */
 typedef struct {
     int32_t small_max_wedges;
     int32_t task_wedges;

@@ -1226,9 +1226,8 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
 
 // --------------------------------------------------------------- tiny
 
-// One lane per tiny item: a single-task item with a planning cost of at most
-// Tuning::tiny_max_wedges (so at most kTinyCap wedges, the planning cost
-// being at least a third of them) and at most kTinyCap members, outside
+// One lane per tiny item: an item with at most Tuning::tiny_max_wedges wedges
+// (three times as many with s > 2, see is_tiny) and at most kTinyCap members, outside
 // product mode.  The lane copies the candidates of all its members' walks
 // into its own column of an LDS buffer, sorts them, and counts each run of
 // equal ids: that count is the overlap.  The candidates come out ascending,

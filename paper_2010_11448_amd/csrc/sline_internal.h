@@ -35,7 +35,7 @@ struct Tuning {
     int32_t dense_min_wedges = 4096;  // cut items into dense sub-ranges when each gets this many wedges
     int32_t small_slots = 1024;  // LDS table of the one-wave kernel: 512, 1024 or 2048 home slots
     int32_t task_slots = 8960;   // LDS table of the task kernel: 4480, 8960, 13440 or 17920 home slots
-    int32_t tiny_max_wedges = 10;  // one-task items up to this planning cost go one per lane (0: off)
+    int32_t tiny_max_wedges = 10;  // items of up to this many wedges go one per lane (0: off)
 };
 
 // Scan tile: 256 threads x 8 items.
@@ -50,9 +50,8 @@ constexpr int kScanTile = kScanThreads * kScanItems;
 // threads, two workgroups per CU.
 constexpr int kTaskThreads = 256;
 // Tiny items (one lane each): at most kTinyCap members and kTinyCap wedges.
-// The planning cost is at least a third of the wedges (lookup-only members
-// lower it no further), so tiny_max_wedges <= kTinyMaxCost keeps every
-// tiny item's wedges within kTinyCap.
+// With s > 2 few wedges make a pair, and up to three times tiny_max_wedges of them
+// are taken, so tiny_max_wedges <= kTinyMaxCost keeps them within kTinyCap.
 constexpr int kTinyCap = 32;
 constexpr int kTinyMaxCost = 10;
 constexpr int kTinyThreads = 256;
@@ -118,6 +117,11 @@ constexpr int32_t kKeepRanks = kFlatWords / 4;  // pairs of a range counted at a
 // wedges in one step of a wave; sieved, with s > 1, up to kSieveWedges * threads
 // (kSieveSmall or kSieveLarge threads); with s = 1, where nothing can be
 // sieved out, up to kOnesWedges.  A member per thread, in a wave per lane.
+// Where the lines lie: a step of a wave is four chunks of 64; a sieve's two bit
+// maps of 16 bits per wedge and its table fill a quarter of a CU's LDS at 8,192
+// wedges, and a larger one would leave too few waves.  10^6 hyperedges, s = 2: 47.8 ms
+// with the sieves, 55.5 with direct counters or hashed tasks for all items above 512
+// wedges (the kernels as they were when the sieves came in).
 constexpr int32_t kMiniWedges = 256;
 constexpr int32_t kSieveSmall = 64, kSieveLarge = 256;
 constexpr int32_t kSieveWedges = 32;
@@ -197,7 +201,13 @@ enum : int32_t {
 
 // Tasks of item a when every wedge of it is counted by one of the kernels
 // without hashed wedge lists (kind: which; ranges: those that stage their pairs
-// by themselves), 0 when it is not.  `cost` is W_a, or the lowered planning
+// by themselves), 0 when it is not.  Direct counters take an item with at
+// least dense_min / 8 wedges per range (512; a sixteenth where it keeps its
+// wedges, s = 1).  Fewer change little, as a range's fixed work is then about what
+// hashing costs; with more, hashing is slower.  Build time with at least 64, 512,
+// 2048 and 8192 wedges a range: 10^6 hyperedges, s = 2: 33.7, 33.8, 35.5, 51.5 ms;
+// s = 8: 6.4, 6.3, 6.5, 7.1; 200,000, s = 1 (half as many): 4.5, 4.6, 4.9, 6.7.
+// `cost` is W_a, or the lowered planning
 // cost of an item that was not to be counted so by its W_a (and is not by less).
 __device__ __forceinline__ int32_t direct_tasks(const PlanItems &I, int32_t a, int64_t cost,
                                                 int32_t &kind, int32_t &ranges) {
