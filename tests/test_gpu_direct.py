@@ -84,3 +84,18 @@ def test_hub(ctx, T, k, r, N):
                 assert_same(ctx.build(rp, col, g.n_vertices, s), ref, what)
             finally:
                 ctx.set_tuning(**base)
+
+
+def test_a_wedge_too_many_for_a_sieve(ctx):
+    """8193 wedges in 17 ranges of 8-bit counters: one too many for the sieve and
+    too few for direct counters, so the task kernel counts them, whatever its
+    lookup-only members lower the planning cost to."""
+    import torch
+
+    T, k, r, N = 2731, 40, 3, 1000000
+    g = hub(T, k, r, N, seed=5)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    for s in (2, 3):
+        ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, threads=8)
+        print(f"case: {r * T} wedges N={N} s={s}", flush=True)
+        assert_same(ctx.build(rp, col, g.n_vertices, s), ref, f"s={s}")
