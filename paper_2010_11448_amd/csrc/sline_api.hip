@@ -1631,13 +1631,15 @@ void plan_enqueue_prep(sline_batch_plan *p, hipStream_t st, int64_t t_cap) {
                              p->K.s_item),
               "row ids");
     member_lists(c, st, L, memI, MT, B.ZT, L.itmS, L.start);
+    // (no list is read by its bounds once the input has been found bad)
     hip_check(c, launch_cost(st, ptrI, memI, NI, p->s_min, p->K.s_item, L.ptrT, L.itmS, L.cost,
-                             L.start, L.totals, 0, 1),
+                             L.start, L.totals, 0, 1, p->d_err),
               "cost");
     const Tuning &tu = p->C.tune;
     const PlanItems PI = plan_items(tu, ptrI, nullptr, p->K.iend, NI, p->s_min, p->K.s_item, false);
     if (p->groups)
-        hip_check(c, launch_mark_lookup(st, PI, memI, L.ptrT, L.start, L.cost), "lookup members");
+        hip_check(c, launch_mark_lookup(st, PI, memI, L.ptrT, L.start, L.cost, p->d_err),
+                  "lookup members");
     plan_enqueue_tasks(p, st, t_cap < 0);
     if (t_cap >= 0)
         hip_check(c, launch_plan_guard(st, L.tbase + NI, t_cap, kErrPlanTasks, p->d_err), "task guard");
@@ -1658,7 +1660,7 @@ void plan_enqueue_count(sline_batch_plan *p, hipStream_t st, int64_t pair_cap) {
                                   TL.tiny_item, TL.big, (int32_t)p->t_cap, L.tcounts, p->d_err),
               "task fill");
     hip_check(c, launch_flat_bounds(st, L.ptrT, L.itmS, (int32_t)p->B.MT, nullptr,
-                                    (int32_t)p->B.NI, L.bnd),
+                                    (int32_t)p->B.NI, L.bnd, p->d_err),
               "list bounds");
     hip_check(c, launch_fill_i32(st, reinterpret_cast<int32_t *>(TL.pool_head), TL.n_zero, 0),
               "zero task arrays");

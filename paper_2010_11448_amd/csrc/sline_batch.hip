@@ -187,6 +187,13 @@ __global__ __launch_bounds__(256) void k_batch_rows(const BatchGraph *gr, const 
         const int64_t z1 = min(z0 + kWaveEntries, ZT);
         int32_t g = __builtin_amdgcn_readfirstlane(find_graph(zb, G, z0));
         for (int64_t at = z0; at < z1; ++g) {
+            if (g >= G) {
+                // rows with bad bounds (reported by k_batch_len) have no
+                // entries, so the graphs may end before ZT: the rest gets a
+                // member that later kernels can index by
+                for (int64_t z = at + lane; z < z1; z += kWave) memC[z] = 0;
+                break;
+            }
             const BatchGraph d = gr[g];
             const int64_t first = zb[g], end = min((int64_t)zb[g + 1], z1);
             const int32_t *from = d.dual ? colT + ptrT[d.vdbase] : d.col;

@@ -45,7 +45,8 @@ constexpr int kFlatChunks = kFlatKeep / kWave;  // 64-wedge chunks marked at a t
 // list's own entries, so rows need no index of their own.  One wave per list.
 __global__ __launch_bounds__(256) void k_flat_bounds(const int32_t *ptrS, const int32_t *itmS,
                                                      int32_t M, const int32_t *crank, int32_t N,
-                                                     int32_t *bnd) {
+                                                     int32_t *bnd, const int32_t *err) {
+    if (err && *err) return;
     crank = ranks_or_null(crank, N);
     const int32_t blocks = flat_blocks(cand_of(crank, N));
     if (blocks < 2) return;  // every item's candidates fit one range of any width
@@ -556,10 +557,11 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
 }  // namespace
 
 hipError_t launch_flat_bounds(hipStream_t st, const int32_t *ptrS, const int32_t *itmS, int32_t M,
-                              const int32_t *crank, int32_t N, int32_t *bnd) {
+                              const int32_t *crank, int32_t N, int32_t *bnd,
+                              const int32_t *err) {
     if (M <= 0 || N <= kFlatBlock) return hipSuccess;
     const int64_t g = std::min<int64_t>(((int64_t)M + 255) / 256, 4096);
-    k_flat_bounds<<<(unsigned)g, 256, 0, st>>>(ptrS, itmS, M, crank, N, bnd);
+    k_flat_bounds<<<(unsigned)g, 256, 0, st>>>(ptrS, itmS, M, crank, N, bnd, err);
     return hipGetLastError();
 }
 

@@ -365,6 +365,7 @@ hipError_t launch_filter(hipStream_t st, const int32_t *ptrM, const int32_t *itm
 // totals[0] = kept items, [1] = kept incidences, [2] = wedges.
 // full != 0 (product mode): start[k] = the first entry of N_s(v) and W_a counts
 // every b in the lists, a itself included.
+// Nothing is read while *err (if given) is not 0.
 hipError_t launch_cost(hipStream_t st, const int32_t *ptrI, const int32_t *memI, int32_t N,
                        int32_t s, const int32_t *s_item, const int32_t *ptrS, const int32_t *itmS,
                        int64_t *cost, int32_t *start, int64_t *totals, int32_t full = 0,
@@ -388,9 +389,10 @@ hipError_t launch_product_filter(hipStream_t st, const int32_t *a, const int32_t
 constexpr int32_t kStartMask = 0x7fffffff;
 constexpr int32_t kMaxLookup = 15;  // lookup-only members per item at most
 // Only items that k_count_tasks counts are marked: every other kernel counts all
-// wedges, and would gain nothing.
+// wedges, and would gain nothing.  Nothing is done while *err (if given) is not 0.
 hipError_t launch_mark_lookup(hipStream_t st, const PlanItems &I, const int32_t *memI,
-                              const int32_t *ptrS, int32_t *start, int64_t *cost);
+                              const int32_t *ptrS, int32_t *start, int64_t *cost,
+                              const int32_t *err = nullptr);
 
 // Tasks: item a with W_a wedges becomes P_a tasks (sub-ranges of its
 // candidate range); ntask[a] = P_a.  Task t of item a (t = tbase[a] + p) is
@@ -422,9 +424,11 @@ hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, const PlanItems
                             const int32_t *abort = nullptr);
 
 // Positions of the multiples of kFlatBlock candidates in the long lists (bnd:
-// as many entries as itmS), for the items counted directly.
+// as many entries as itmS), for the items counted directly.  Nothing is done while
+// *err (if given) is not 0.
 hipError_t launch_flat_bounds(hipStream_t st, const int32_t *ptrS, const int32_t *itmS, int32_t M,
-                              const int32_t *crank, int32_t N, int32_t *bnd);
+                              const int32_t *crank, int32_t N, int32_t *bnd,
+                              const int32_t *err = nullptr);
 
 // Counting-kernel modes.
 enum : int32_t {

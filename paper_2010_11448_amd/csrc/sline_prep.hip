@@ -672,7 +672,7 @@ __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t
                                               int64_t *cost, int32_t *start, int64_t *totals,
                                               int32_t full, int32_t have_start,
                                               const int32_t *err) {
-    if (err && (*err & kErrColRange)) return;  // members that index nothing
+    if (err && *err) return;  // lists or members that index nothing
     int64_t kept = 0, kept_nnz = 0, wedges = 0;  // counted by each row's first lane
     for_all_rows<32, true>(ptrI, N, [&](int64_t a, int gl, int W) {
         const int32_t b = ptrI[a], e = ptrI[a + 1];
@@ -748,8 +748,9 @@ __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t
 constexpr int kKeysFew = 4, kKeysMany = 32;
 
 __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t *memI,
-                                                     const int32_t *ptrS,
-                                                     int32_t *start, int64_t *cost) {
+                                                     const int32_t *ptrS, int32_t *start,
+                                                     int64_t *cost, const int32_t *err) {
+    if (err && *err) return;
     I.crank = ranks_or_null(I.crank, I.N);
     constexpr int W = kWave;
     const int gl = lane_id();
@@ -1123,10 +1124,10 @@ hipError_t launch_cost(hipStream_t st, const int32_t *ptrI, const int32_t *memI,
 }
 
 hipError_t launch_mark_lookup(hipStream_t st, const PlanItems &I, const int32_t *memI,
-                              const int32_t *ptrS, int32_t *start, int64_t *cost) {
+                              const int32_t *ptrS, int32_t *start, int64_t *cost,
+                              const int32_t *err) {
     if (I.N <= 0) return hipSuccess;
-    k_mark_lookup<<<grid_for(I.N, 256, 16384), 256, 0, st>>>(I, memI, ptrS, start,
-                                                                              cost);
+    k_mark_lookup<<<grid_for(I.N, 256, 16384), 256, 0, st>>>(I, memI, ptrS, start, cost, err);
     return hipGetLastError();
 }
 

@@ -247,3 +247,42 @@ def test_batch_with_cached_tuning(ctx, dev, tmp_path):
             assert_same(pres[g], ref, f"cached tuning plan graph {g}")
     finally:
         plan.close()
+
+
+# row_ptr of a graph of m rows and z incidences, bad inside only: rows that the
+# combined lists leave out, at the end or before it, and rows of more than z in all
+BAD_INSIDE = {
+    "above_the_end": lambda rp, m, z: rp.__setitem__(m // 2, z + 7),
+    "above_the_end_in_the_last_row": lambda rp, m, z: rp.__setitem__(m - 1, z + 1),
+    "dips": lambda rp, m, z: rp.__setitem__(m // 2, 0),
+    "negative": lambda rp, m, z: rp.__setitem__(m // 2, -5),
+    "overlaps": lambda rp, m, z: rp.__setitem__(slice(1, 3), rp.new_tensor([z, 0])),
+}
+
+
+@pytest.mark.parametrize("bad", BAD_INSIDE)
+@pytest.mark.parametrize("dual", [0, 1])
+def test_batch_refuses_rows_bad_inside(ctx, dev, bad, dual):
+    """A row_ptr with the right ends but bad inside fails the call, whichever
+    graph of the batch it is in, and the next batch is counted as ever."""
+    from paper_2010_11448_amd import sline
+
+    graphs = [gen.uniform_hypergraph(300, 500, 2, 14, seed) for seed in (1, 2, 3)]
+    ss, duals = [2, 2, 2], [dual, 1 - dual, dual]
+    dg = [to_device(h, dev) for h in graphs]
+    batch = [(rp, col, h.n_vertices) for (rp, col), h in zip(dg, graphs)]
+    for at in range(3):
+        print(f"case: batch, graph {at} {bad}, dual {duals}", flush=True)
+        rp = dg[at][0].clone()
+        BAD_INSIDE[bad](rp, graphs[at].n_edges, int(rp[-1]))
+        broken = list(batch)
+        broken[at] = (rp, dg[at][1], graphs[at].n_vertices)
+        with pytest.raises(sline.SlineError) as ei:
+            ctx.build_batch(broken, ss, duals)
+        assert ei.value.status == sline.SLINE_EINVAL
+        with pytest.raises(sline.SlineError) as ei:
+            sline.BatchPlan(ctx, broken, ss, duals)
+        assert ei.value.status == sline.SLINE_EINVAL
+    for h, d, L in zip(graphs, duals, ctx.build_batch(batch, ss, duals)):
+        ref, _ = oracle.wedge(h.row_ptr, h.col, h.n_edges, h.n_vertices, 2, dual=d, threads=8)
+        assert_same(L, ref, f"after {bad}")

@@ -335,3 +335,32 @@ def test_plan_randomized(ctx, dev, seed):
             _check(plan.run(s2), graphs, s2, duals, f"seed {seed} run {r} s={s2}")
     finally:
         plan.close()
+
+
+from test_gpu_batch import BAD_INSIDE  # noqa: E402
+
+
+@pytest.mark.parametrize("bad", BAD_INSIDE)
+@pytest.mark.parametrize("dual", [0, 1])
+def test_plan_refuses_rows_bad_inside(ctx, dev, bad, dual):
+    """A run whose row_ptr has the planned ends but is bad inside is refused, also
+    when the run after it has other ends; the plan stays usable."""
+    from paper_2010_11448_amd import sline
+
+    graphs = [gen.uniform_hypergraph(300, 500, 2, 14, seed) for seed in (1, 2, 3)]
+    ss, duals = [2, 2, 2], [dual, 1 - dual, dual]
+    dg = [to_device(h, dev) for h in graphs]
+    plan = _plan(ctx, dg, graphs, ss, duals)
+    try:
+        for at in range(3):
+            rp = dg[at][0]
+            keep = rp.clone()
+            BAD_INSIDE[bad](rp, graphs[at].n_edges, int(keep[-1]))
+            print(f"case: plan run, graph {at} {bad}, dual {duals}", flush=True)
+            assert plan.run_raw() == sline.SLINE_EINVAL
+            rp[-1] = rp[-1] - 1
+            assert plan.run_raw() == sline.SLINE_EINVAL
+            rp.copy_(keep)
+            _check(plan.run(), graphs, ss, duals, f"restored after {bad}")
+    finally:
+        plan.close()
