@@ -196,7 +196,11 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
         load_list(mem, F.ranges > 1 && !keep);
         int32_t produced = 0;
         int32_t hits = 0;  // pairs found by this wave
-        const uint32_t s_1 = (uint32_t)s - 1u;
+        // What a counter holds before the add that makes a pair: s - 1, which is less
+        // than the all-ones of a lane without a count as long as s is no more than
+        // the item's size.  An item of fewer members (kept with SLINE_NO_PRUNE)
+        // is in no pair: a value that no counter has.
+        const uint32_t s_1 = s <= k1 - k0 ? (uint32_t)s - 1u : ~0u;
 
         // Count wedges, x = candidate - first of the range (>= span: none).
         auto count = [&](const auto &j, int32_t lo, uint32_t span) {
@@ -206,7 +210,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
             for (int u = 0; u < K; ++u) {
                 x[u] = (uint32_t)(j[u] - lo);
                 at[u] = x[u] << lb;  // the counter's bit
-                old[u] = ~0u;        // no count: the item has fewer members than a counter holds
+                old[u] = ~0u;        // no count: all ones, not s_1
                 if (x[u] < span) old[u] = atomicAdd(&ctr[at[u] >> 5], shift_left(1u, at[u]));
             }
 #pragma unroll

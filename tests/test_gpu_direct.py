@@ -99,3 +99,31 @@ def test_a_wedge_too_many_for_a_sieve(ctx):
         ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, threads=8)
         print(f"case: {r * T} wedges N={N} s={s}", flush=True)
         assert_same(ctx.build(rp, col, g.n_vertices, s), ref, f"s={s}")
+
+
+# members of item 0, one fewer than s, and items after it: counters of 4, 8 and 16
+# bits that are all ones at s - 1, one range of them and two
+UNPRUNED = [(15, 122878), (15, 122882), (255, 61438), (255, 61442), (65535, 30718), (65535, 30722)]
+
+
+@pytest.mark.parametrize("k,N", UNPRUNED, ids=["-".join(map(str, c)) for c in UNPRUNED])
+@pytest.mark.parametrize("variant", ["prune", "f2"])
+def test_fewer_members_than_s(ctx, k, N, variant):
+    """Without degree pruning an item of fewer than s members is counted as well,
+    and is in no pair; two items after it make the only one."""
+    import torch
+    from paper_2010_11448_amd import sline
+
+    s = k + 1
+    flags = sline.SLINE_NO_PRUNE if variant == "prune" else sline.VARIANT_FLAGS[variant]
+    g = hub(9000, k, 3, N, seed=k + N)
+    extra = np.arange(g.n_vertices, g.n_vertices + s, dtype=np.int32)
+    row_ptr = np.append(g.row_ptr, g.row_ptr[-1] + s * np.array([1, 2])).astype(np.int32)
+    g = gen.Hypergraph(row_ptr, np.concatenate([g.col, extra, extra]), g.n_edges + 2, g.n_vertices + s)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, threads=8)
+    assert len(ref.a) == 1
+    for at in (s, s - 1, 3):
+        ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, at, threads=8)
+        print(f"case: {k} members N={N} s={at} flags={flags}", flush=True)
+        assert_same(ctx.build(rp, col, g.n_vertices, at, 0, flags), ref, f"k={k} N={N} s={at}")
