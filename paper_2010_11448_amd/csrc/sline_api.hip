@@ -750,9 +750,10 @@ sline_status noalloc_impl(sline_ctx *c, const sline_csr &H, int32_t s, int32_t d
         sline_ctx *c;
         void *ws, *ws2, *pool;
         size_t ws_bytes, ws2_bytes, pool_bytes;
+        bool pool_fixed;  // the kept pool lies in ws2
         ~Saved() {
             c->fixed = sline_ctx::Fixed{};
-            c->pool_fixed = false;
+            c->pool_fixed = pool_fixed;
             c->ws = ws;
             c->ws_bytes = ws_bytes;
             c->ws2 = ws2;
@@ -760,7 +761,7 @@ sline_status noalloc_impl(sline_ctx *c, const sline_csr &H, int32_t s, int32_t d
             c->pool = pool;
             c->pool_bytes = pool_bytes;
         }
-    } saved{c, c->ws, c->ws2, c->pool, c->ws_bytes, c->ws2_bytes, c->pool_bytes};
+    } saved{c, c->ws, c->ws2, c->pool, c->ws_bytes, c->ws2_bytes, c->pool_bytes, c->pool_fixed};
     c->pool = nullptr;
     c->pool_bytes = 0;
     c->pool_fixed = false;

@@ -133,3 +133,70 @@ def test_refusals(ctx):
     assert "scratch" in sline.sline_last_error(ctx.ctx)
     # the context still works for both entry points afterwards
     _check_against_plain(ctx, g, dev, 2, 1, "after a refusal")
+
+
+class _Recorder:
+    """An allocator that notes every block it hands out, and every release of
+    something that is not one."""
+
+    def __init__(self, device):
+        import torch
+        from paper_2010_11448_amd import sline
+
+        self.live, self.wrong = {}, []
+        cache = torch.cuda
+
+        def alloc(nbytes, stream, user):
+            p = int(cache.caching_allocator_alloc(int(nbytes), device, stream or 0))
+            self.live[p] = int(nbytes)
+            return p
+
+        def free(ptr, nbytes, stream, user):
+            if self.live.get(int(ptr or 0)) != int(nbytes):
+                self.wrong.append((int(ptr or 0), int(nbytes)))
+                return
+            del self.live[int(ptr)]
+            cache.caching_allocator_delete(int(ptr))
+
+        self.keep = (sline.ALLOC_FN(alloc), sline.FREE_FN(free))
+        self.struct = sline.sline_allocator(*self.keep, None)
+
+
+@pytest.mark.parametrize("then", ["build", "noalloc", "destroy"])
+def test_after_a_refused_build(then):
+    """A build refused for its capacity keeps its staged pairs; the call without
+    allocations drops them, and nothing is released that was not allocated."""
+    import torch
+    from paper_2010_11448_amd import sline
+
+    dev = torch.device("cuda", 0)
+    g = gen.uniform_2000(11)
+    rp, col = to_device(g, dev)
+    ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, 1, threads=8)
+    n = len(ref.a)
+    out = torch.empty((3, n), dtype=torch.int32, device=dev)
+    csr = sline.Context.csr(rp, col, g.n_vertices)
+
+    def edges(room):
+        return sline.sline_edges(0, room, *(out[i].data_ptr() for i in range(3)))
+
+    def check(st, e):
+        assert st == sline.SLINE_OK and e.n_pairs == n
+        for i, want in enumerate((ref.a, ref.b, ref.w)):
+            assert np.array_equal(out[i].cpu().numpy(), want)
+
+    rec = _Recorder(0)
+    ctx = sline.sline_create(0, torch.cuda.current_stream(dev).cuda_stream, rec.struct)
+    print(f"case: refused build, noalloc, {then}", flush=True)
+    e = edges(n - 1)
+    assert sline.sline_build(ctx, csr, 1, 0, 0, e) == sline.SLINE_ECAPACITY and e.n_pairs == n
+    held = dict(rec.live)
+    e = edges(n)
+    check(sline.sline_build_noalloc(ctx, csr, 1, 0, 0, e), e)
+    assert rec.live == held
+    if then != "destroy":
+        e = edges(n)
+        call = sline.sline_build if then == "build" else sline.sline_build_noalloc
+        check(call(ctx, csr, 1, 0, 0, e), e)
+    sline.sline_destroy(ctx)
+    assert not rec.wrong and not rec.live
