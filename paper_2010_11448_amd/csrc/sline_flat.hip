@@ -105,7 +105,10 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
     __shared__ int32_t adj[NT];  // the wedge map's positions; hits while pairs are written
     __shared__ __align__(8) uint32_t marks[2 * kFlatChunks];
     __shared__ int32_t msh[3 * NW], wtot[NW];
-    __shared__ int32_t sh_task, sh_hits, sh_ok;
+    // the task after the next one, in two words by turns: a skipped task has no other
+    // barrier, and a late wave may still be reading the word of the task before it
+    __shared__ int32_t sh_task[2];
+    __shared__ int32_t sh_hits, sh_ok;
     __shared__ uint64_t sh_off, pool_cur[3];
     __shared__ int32_t log_cur[3];
     if (count_idle(A)) return;  // uniform: every thread reads the same words
@@ -121,12 +124,12 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
     if (tid == 0) {
         stage_begin(A, kKindFlat, pool_cur, log_cur);
         sh_hits = 0;
-        sh_task = atomicAdd(A.queue + 1, 2);
+        sh_task[0] = atomicAdd(A.queue + 1, 2);
     }
     int64_t passes = 0, my_wedges = 0, my_nnz = 0, my_pairs = 0;  // thread 0's are used
     __syncthreads();
-    int32_t r = sh_task, r1 = r + 1;  // this task and the next in the list
-    __syncthreads();
+    int32_t r = sh_task[0], r1 = r + 1;  // this task and the next in the list
+    int turn = 0;
 
     WedgeMap<NT, kFlatChunks> map;
     map.adj_all = adj;
@@ -543,10 +546,11 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
             A.task_cnt[t] = produced;
             my_pairs += produced;
         }
-        if (tid == 0) sh_task = r2;
+        turn ^= 1;
+        if (tid == 0) sh_task[turn] = r2;
         __syncthreads();
         r = r1;
-        r1 = sh_task;
+        r1 = sh_task[turn];
         cur = nxt;
     }
     if (tid == 0 && A.passes && !FILL) {

@@ -127,3 +127,23 @@ def test_fewer_members_than_s(ctx, k, N, variant):
         ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, at, threads=8)
         print(f"case: {k} members N={N} s={at} flags={flags}", flush=True)
         assert_same(ctx.build(rp, col, g.n_vertices, at, 0, flags), ref, f"k={k} N={N} s={at}")
+
+
+@pytest.mark.parametrize("s", [1, 2, 12])
+@pytest.mark.parametrize("share", [4, 2, 1.25])
+def test_some_tasks_counted_again(ctx, s, share):
+    """A pool that holds a part of the pairs: the fill pass skips the tasks that
+    were staged, one after the other, among those it counts again."""
+    import torch
+
+    g = gen.uniform_hypergraph(3000, 300, 55, 65, seed=7)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, threads=8)
+    base = ctx.tuning()
+    print(f"case: s={s}, pool for 1/{share} of {len(ref.a)} pairs", flush=True)
+    ctx.set_tuning(stage_max_bytes=int(8 * len(ref.a) / share))
+    try:
+        for _ in range(3):
+            assert_same(ctx.build(rp, col, g.n_vertices, s), ref, f"s={s} share={share}")
+    finally:
+        ctx.set_tuning(**base)
