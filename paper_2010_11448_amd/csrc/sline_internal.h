@@ -51,7 +51,8 @@ constexpr int kScanTile = kScanThreads * kScanItems;
 constexpr int kTaskThreads = 256;
 // Tiny items (one lane each): at most kTinyCap members and kTinyCap wedges.
 // With s > 2 few wedges make a pair, and up to three times tiny_max_wedges of them
-// are taken, so tiny_max_wedges <= kTinyMaxCost keeps them within kTinyCap.
+// are taken, so tiny_max_wedges <= kTinyMaxCost keeps them within kTinyCap (by the
+// exact W_a: a planning cost is not lowered to that many, see k_mark_lookup).
 constexpr int kTinyCap = 32;
 constexpr int kTinyMaxCost = 10;
 constexpr int kTinyThreads = 256;
@@ -385,7 +386,8 @@ hipError_t launch_product_filter(hipStream_t st, const int32_t *a, const int32_t
 // before them, every such b is still counted exactly; the others stay below s
 // and are dropped.  The longest lists (most wedges) are chosen; the choice is
 // flagged in the sign bit of start[k], and cost[a] is lowered to the planning
-// cost max(W_a - flagged wedges, W_a / 3).
+// cost max(W_a - flagged wedges, W_a / 3), but not so far that a kernel would be
+// given the item that has no room for W_a wedges.
 constexpr int32_t kStartMask = 0x7fffffff;
 constexpr int32_t kMaxLookup = 15;  // lookup-only members per item at most
 // Only items that k_count_tasks counts are marked: every other kernel counts all

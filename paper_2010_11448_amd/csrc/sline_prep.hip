@@ -823,10 +823,11 @@ __global__ __launch_bounds__(256) void k_mark_lookup(PlanItems I, const int32_t 
         }
         if (gl == 0 && flagged) {
             const int64_t w = cost[a];
-            // an item with too many wedges for the sieve (most + 1 of them is
-            // enough) keeps a cost that is too many as well
-            constexpr int64_t most = (int64_t)kSieveWedges * kSieveLarge;
-            cost[a] = max(max(w - flagged, (w + 2) / 3), w > most ? most + 1 : (int64_t)0);
+            // an item with too many wedges for the sieve keeps a cost that is
+            // too many as well, and one with too many for a lane (which counts
+            // all W_a of a tiny item) likewise
+            constexpr int64_t sieve = (int64_t)kSieveWedges * kSieveLarge, lane = 3 * kTinyMaxCost;
+            cost[a] = max(max(w - flagged, (w + 2) / 3), min(w, (w > sieve ? sieve : lane) + 1));
         }
     };
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;

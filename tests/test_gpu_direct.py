@@ -147,3 +147,24 @@ def test_some_tasks_counted_again(ctx, s, share):
             assert_same(ctx.build(rp, col, g.n_vertices, s), ref, f"s={s} share={share}")
     finally:
         ctx.set_tuning(**base)
+
+
+@pytest.mark.parametrize("small_max", [1, 20, 30])
+@pytest.mark.parametrize("T", [7, 8, 12, 18, 19, 30])
+def test_lowered_cost_of_a_few_wedges(ctx, T, small_max):
+    """Hash tables alone: an item of a few wedges more than small_max_wedges is
+    planned by what its lookup-only members leave, but a lane, which counts every
+    wedge of an item and has room for 32, does not take it for that."""
+    import torch
+
+    g = hub(T, 5, 5, 40000, seed=T)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    base = ctx.tuning()
+    ctx.set_tuning(dense_min_wedges=0, small_max_wedges=small_max)
+    try:
+        for s in (2, 3, 4, 5):
+            ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, threads=8)
+            print(f"case: {5 * T} wedges, small_max={small_max} s={s}", flush=True)
+            assert_same(ctx.build(rp, col, g.n_vertices, s), ref, f"T={T} s={s}")
+    finally:
+        ctx.set_tuning(**base)
