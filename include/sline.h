@@ -40,7 +40,8 @@ enum {
 /* Build flags. */
 enum {
     SLINE_SKIP_VALIDATE = 1u, /* skip the strictly-increasing row check (range
-                                 checks that guard memory always run)       */
+                                 checks that guard memory always run); the
+                                 pairs are unspecified if a row breaks it    */
     SLINE_PROFILE = 2u,       /* time the stages with HIP events on the
                                  context's stream (see sline_stats)          */
     SLINE_NO_WEIGHTS = 4u,    /* pairs only: the w array is neither needed nor

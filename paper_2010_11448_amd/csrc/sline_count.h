@@ -30,6 +30,12 @@ __device__ __forceinline__ void use_ranks(CountArgs &A) {
     if (!A.crank) A.orig = nullptr;
 }
 
+// The item a candidate stands for.  (A row that lists a member twice, let in by
+// SLINE_SKIP_VALIDATE, can leave candidates that are none.)
+__device__ __forceinline__ int32_t item_of(const CountArgs &A, int32_t cand) {
+    return A.orig ? A.orig[min((uint32_t)cand, (uint32_t)A.N - 1u)] : cand;
+}
+
 // Where the pairs of item `item` at combined output position `pos` go: the
 // single output, or (batches written per graph) the arrays of the item's
 // graph at the position inside it, ids to be written less `shift`.

@@ -655,7 +655,7 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
                         if (cnt >= s) {
                             const int32_t b = R.lo + (int32_t)(((uint32_t)(4 * bk + k) << R.psh) + j);
                             if (outs) dst_a[base + pos] = a - shift;
-                            dst_b[base + pos] = outs ? item_of(A.orig, b) - shift : b;
+                            dst_b[base + pos] = outs ? item_of(A, b) - shift : b;
                             if (dst_w) dst_w[base + pos] = (int32_t)cnt;
                             ++pos;
                         }
@@ -669,7 +669,7 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
                     if (ok[k]) {
                         if (outs) dst_a[base + pos] = a - shift;
                         const int32_t b = R.lo + 4 * bk + k;
-                        dst_b[base + pos] = outs ? item_of(A.orig, b) - shift : b;
+                        dst_b[base + pos] = outs ? item_of(A, b) - shift : b;
                         if (dst_w) dst_w[base + pos] = (int32_t)c[k];
                         ++pos;
                     }
@@ -743,7 +743,7 @@ __device__ __forceinline__ int32_t tab_extract(const CountArgs &A, const Smem &S
                         const int32_t p = pos + rank[k];
                         if (outs) dst_a[base + p] = a - shift;
                         const int32_t b = R.lo + (int32_t)tag[k] - 1;
-                        dst_b[base + p] = outs ? item_of(A.orig, b) - shift : b;
+                        dst_b[base + p] = outs ? item_of(A, b) - shift : b;
                         if (dst_w) dst_w[base + p] = (int32_t)(key[k] & R.cmask);
                     }
                 }
@@ -1361,7 +1361,7 @@ __global__ __launch_bounds__(kTinyThreads) void k_count_tiny(CountArgs A) {
                 while (j < nc && col[j * NT] == b) ++j;
                 if (j - i >= sa) {
                     if (dst_a) dst_a[at + q] = a - shift;
-                    dst_b[at + q] = dst_a ? item_of(A.orig, b) - shift : b;
+                    dst_b[at + q] = dst_a ? item_of(A, b) - shift : b;
                     if (dst_w) dst_w[at + q] = j - i;
                     ++q;
                 }
@@ -1671,7 +1671,7 @@ __global__ __launch_bounds__(256) void k_stage_copy(CountArgs A, int32_t n_rec) 
         const OutDst od = out_dst(A, a, dst);
         for (int32_t i = 0; i < rec.n; ++i) {
             od.a[od.base + i] = a - od.shift;
-            od.b[od.base + i] = item_of(A.orig, A.pool_b[rec.off + i]) - od.shift;
+            od.b[od.base + i] = item_of(A, A.pool_b[rec.off + i]) - od.shift;
             if (od.w) od.w[od.base + i] = A.pool_w[rec.off + i];
         }
     }
@@ -1700,7 +1700,7 @@ __global__ __launch_bounds__(256) void k_stage_copy(CountArgs A, int32_t n_rec) 
                 bv[u] = 0;
                 wv[u] = 0;
                 if (i < rec.n) {
-                    bv[u] = item_of(A.orig, A.pool_b[rec.off + i]);
+                    bv[u] = item_of(A, A.pool_b[rec.off + i]);
                     if (od.w) wv[u] = A.pool_w[rec.off + i];
                 }
             }

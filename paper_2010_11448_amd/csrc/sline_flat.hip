@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
         auto put = [&](const Dest &d, int64_t o, int32_t cand, int32_t w) {
             if (FILL) {
                 d.a[o] = a - d.shift;
-                d.b[o] = item_of(A.orig, cand) - d.shift;
+                d.b[o] = item_of(A, cand) - d.shift;
             } else {
                 d.b[o] = cand;
             }
@@ -478,7 +478,10 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
                     int32_t b = mem.st, e = mem.en;
                     if (mem.row >= 0) {
                         b = max(b, ahead);
-                        ahead = e = A.bnd[mem.row + blk1];
+                        ahead = A.bnd[mem.row + blk1];
+                        // the table of a list out of order (SLINE_SKIP_VALIDATE) has
+                        // entries that were never written
+                        e = min(e, ahead);
                     }
                     map.number(b, max(e - b, 0));
                     for (int32_t w0 = 0; w0 < map.total; w0 += kFlatChunks * kWave) {

@@ -94,11 +94,6 @@ __device__ __forceinline__ int32_t cand_end(const int32_t *crank, const int32_t 
     return cand_of(crank, item_end ? item_end[a] : N);
 }
 
-// The item a candidate stands for.
-__device__ __forceinline__ int32_t item_of(const int32_t *orig, int32_t cand) {
-    return orig ? orig[cand] : cand;
-}
-
 // Direct counting (sline_flat.hip): an item's candidate range is cut into
 // ranges of kFlatBlock << k candidates that fit kFlatWords words of counters
 // wide enough for the item's size: 4 bits (k = 2), 8 (k = 1) or 16 (k = 0).

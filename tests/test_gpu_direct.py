@@ -168,3 +168,34 @@ def test_lowered_cost_of_a_few_wedges(ctx, T, small_max):
             assert_same(ctx.build(rp, col, g.n_vertices, s), ref, f"T={T} s={s}")
     finally:
         ctx.set_tuning(**base)
+
+
+@pytest.mark.parametrize("dual", [0, 1])
+@pytest.mark.parametrize("rows", ["shuffled", "repeated"])
+def test_rows_not_checked(ctx, rows, dual):
+    """SLINE_SKIP_VALIDATE lets rows in that are out of order or list a member
+    twice.  The pairs are unspecified then (rows of items out of order still
+    count), but the call returns and the next one counts as ever."""
+    import torch
+    from paper_2010_11448_amd import sline
+
+    g = hub(62000, 255, 4, 140000, seed=1)
+    if dual:
+        v, e = np.repeat(np.arange(g.n_edges), np.diff(g.row_ptr)), g.col
+        o = np.lexsort((v, e))
+        row_ptr = np.concatenate([[0], np.cumsum(np.bincount(e, minlength=g.n_vertices))])
+        g = gen.Hypergraph(row_ptr.astype(np.int32), v[o].astype(np.int32), g.n_vertices, g.n_edges)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    if rows == "shuffled":
+        row = np.repeat(np.arange(g.n_edges), np.diff(g.row_ptr))
+        o = np.lexsort((np.random.default_rng(2).random(len(row)), row))
+        broken = torch.from_numpy(g.col[o]).to(rp.device)
+    else:
+        broken = col // 4 * 4
+    for s in (2, 4):
+        print(f"case: rows {rows}, dual={dual} s={s}", flush=True)
+        L = ctx.build(rp, broken, g.n_vertices, s, dual, sline.SLINE_SKIP_VALIDATE)
+        ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, dual=dual, threads=8)
+        if rows == "shuffled" and not dual:
+            assert_same(L, ref, f"shuffled s={s}")
+        assert_same(ctx.build(rp, col, g.n_vertices, s, dual), ref, f"in order s={s}")
