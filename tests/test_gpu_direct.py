@@ -199,3 +199,43 @@ def test_rows_not_checked(ctx, rows, dual):
         if rows == "shuffled" and not dual:
             assert_same(L, ref, f"shuffled s={s}")
         assert_same(ctx.build(rp, col, g.n_vertices, s, dual), ref, f"in order s={s}")
+
+
+# Sieved or counted directly: as many ranges of direct counters as a sieved item may
+# not have and one more, as few wedges for them as direct counters take and fewer
+RANGES = [(1025, 64, 2, 122879), (1025, 64, 2, 122880), (511, 65, 2, 122879), (512, 65, 2, 122879),
+          (4096, 255, 2, 122879), (2731, 15, 3, 245759), (2731, 15, 3, 245760), (4096, 256, 2, 61439),
+          (4096, 256, 2, 61440)]
+
+
+@pytest.mark.parametrize("T,k,r,N", RANGES, ids=["-".join(map(str, c)) for c in RANGES])
+def test_sieved_or_direct(ctx, T, k, r, N):
+    import torch
+
+    g = hub(T, k, r, N, seed=T + k + N)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    for s in sorted({2, r, r + 1}):
+        ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, threads=8)
+        print(f"case: T={T} k={k} r={r} N={N} s={s}", flush=True)
+        assert_same(ctx.build(rp, col, g.n_vertices, s), ref, f"T={T} k={k} r={r} N={N} s={s}")
+
+
+@pytest.mark.parametrize("order", [1, -1], ids=["ascending", "descending"])
+def test_ids_in_order_of_size(ctx, order):
+    """Hyperedges numbered by size: candidates crowd at one end of every range."""
+    import torch
+
+    st = gen.Stream(3)
+    m, n = 30000, 60000
+    size = np.sort(2 + np.minimum(300, (st.uniform(m) ** -0.8).astype(np.int64)))[::order]
+    row = np.repeat(np.arange(m), size)
+    v = (n * st.uniform(len(row)) ** 3).astype(np.int64)
+    key = np.unique(row * n + v)
+    row_ptr = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=m))])
+    g = gen.Hypergraph(row_ptr.astype(np.int32), (key % n).astype(np.int32), m, n)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    for dual in (0, 1):
+        for s in (2, 3, 5):
+            ref, _ = oracle.wedge(g.row_ptr, g.col, m, n, s, dual=dual, threads=8)
+            print(f"case: order={order} dual={dual} s={s} pairs={len(ref.a)}", flush=True)
+            assert_same(ctx.build(rp, col, n, s, dual), ref, f"order={order} dual={dual} s={s}")
