@@ -1300,7 +1300,7 @@ struct BatchDev {
     const int64_t *ibase, *dbase;
     const int32_t *dual_ids;
     int32_t *zb;   // G + 1 entries
-    int32_t *err;  // CSR rule violations (kErr* bits)
+    int32_t *err;  // CSR rule violations (kErr* bits); then a counter, both zeroed before
 };
 
 // Enqueue the combine stage on `st`: the dual graphs' rows concatenated and
@@ -1312,8 +1312,9 @@ void enqueue_combine(sline_ctx *c, hipStream_t st, int32_t G, const BatchBases &
     hip_check(c, launch_fill_i32(st, X.xcol, B.ZD, 0), "zero dual columns");
     hip_check(c, launch_fill_i32(st, X.rowid, B.ZD, 0), "zero dual rows");
     if (B.GD() > 0 && B.E > 0) {
-        hip_check(c, launch_batch_concat(st, D.gr, D.dual_ids, D.dbase, B.GD(), B.E, X.xcol, X.rowid,
-                                         D.err),
+        // the list of long rows: the sort's buffer is idle, and the flags' second word
+        hip_check(c, launch_batch_concat(st, D.gr, D.dual_ids, D.dbase, B.GD(), B.E, B.ZD, X.xcol,
+                                         X.rowid, X.rsK0, D.err + 1, D.err),
                   "dual rows");
         if (B.ZD > 0) {
             int32_t *const rk[2] = {X.rsK0, X.rsK1};

@@ -71,17 +71,39 @@ __global__ void k_batch_nnz(const BatchGraph *gr, int32_t G, int64_t *nnz, int32
     nnz[g] = z;
 }
 
+// Entries k, k + step, .. of row r of XD, [rb, re) in its graph d.
+__device__ __forceinline__ void concat_row(const BatchGraph *gr, int64_t r, int32_t k, int32_t step,
+                                           int32_t rb, int32_t re, int32_t *xcol, int32_t *xrow,
+                                           int32_t &bad) {
+    const BatchGraph d = *gr;
+    for (; k < re; k += step) {
+        const int32_t v = d.col[k], before = d.col[k > rb ? k - 1 : k];
+        const bool in = v >= 0 && v < d.n;
+        if (!in) bad |= kErrColRange;
+        if (k > rb && before >= v) bad |= kErrColOrder;
+        const int64_t o = d.dzbase + k;
+        xcol[o] = in ? (int32_t)(d.vdbase + v) : 0;
+        xrow[o] = (int32_t)r;
+    }
+}
+
 // Rows of XD (the dual graphs' rows, in graph order): columns shifted by
 // vdbase and the row id of every entry (what the transpose reads); range and
 // order checks.  A wave takes 64 rows: those of up to kShortRow entries a lane
-// each, then the longer ones in turn.  Bounds on latency (a row's graph, its
-// bounds, its entries); a wave per row, which searched the graph for each,
-// took 0.72 ms for 64 graphs of 40,000 rows in the mean, this takes 0.18.
+// each, then those of up to kMidRow in turn; longer ones go to a list, of which
+// every wave of a second kernel takes one (64 such rows in turn would keep the
+// whole batch waiting: 100 rows of 20,000 entries took 5.6 ms, and take 0.11 so).
+// Bounds on latency (a row's graph, its bounds, its entries); a wave per row, which
+// searched the graph for each, took 0.72 ms for 64 graphs of 40,000 rows in the
+// mean, this takes 0.18.
 constexpr int kShortRow = 16;
+constexpr int kMidRow = 256;
 
 __global__ __launch_bounds__(256) void k_batch_concat(const BatchGraph *gr, const int32_t *dual_ids,
                                                       const int64_t *dbase, int32_t GD, int64_t E,
-                                                      int32_t *xcol, int32_t *xrow, int32_t *err) {
+                                                      int32_t *xcol, int32_t *xrow,
+                                                      int32_t *long_rows, int32_t room,
+                                                      int32_t *n_long, int32_t *err) {
     if (*err & kErrPlanShape) return;  // a replayed plan keeps its last lists
     const int lane = lane_id();
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
@@ -103,26 +125,40 @@ __global__ __launch_bounds__(256) void k_batch_concat(const BatchGraph *gr, cons
                 b = en = 0;
             }
         }
-        // entries k, k + step, .. of row r (graph p)
-        auto walk = [&](int32_t p, int64_t r, int32_t k, int32_t step, int32_t rb, int32_t re) {
-            const BatchGraph d = gr[dual_ids[p]];
-            for (; k < re; k += step) {
-                const int32_t v = d.col[k], before = d.col[k > rb ? k - 1 : k];
-                const bool in = v >= 0 && v < d.n;
-                if (!in) bad |= kErrColRange;
-                if (k > rb && before >= v) bad |= kErrColOrder;
-                const int64_t o = d.dzbase + k;
-                xcol[o] = in ? (int32_t)(d.vdbase + v) : 0;
-                xrow[o] = (int32_t)r;
-            }
-        };
+        if (en - b > kMidRow) {
+            // rows that overlap, which another row's bounds give away, may be
+            // more than there is room for
+            const int32_t at = atomicAdd(n_long, 1);
+            if (at < room) long_rows[at] = (int32_t)e;
+            b = en;
+        }
         const bool longer = en - b > kShortRow;
-        if (en > b && !longer) walk(q, e, b, 1, b, en);
+        if (en > b && !longer) concat_row(gr + dual_ids[q], e, b, 1, b, en, xcol, xrow, bad);
         for (uint64_t m = __ballot(longer); m; m &= m - 1) {
             const int src = __builtin_ctzll(m);
             const int32_t rb = __shfl(b, src), re = __shfl(en, src);
-            walk(__shfl(q, src), e0 + src, rb + lane, kWave, rb, re);
+            concat_row(gr + dual_ids[__shfl(q, src)], e0 + src, rb + lane, kWave, rb, re, xcol, xrow,
+                       bad);
         }
+    }
+    if (bad) atomicOr(err, bad);
+}
+
+__global__ __launch_bounds__(256) void k_batch_long(const BatchGraph *gr, const int32_t *dual_ids,
+                                                    const int64_t *dbase, int32_t GD,
+                                                    const int32_t *long_rows, int32_t room,
+                                                    const int32_t *n_long, int32_t *xcol,
+                                                    int32_t *xrow, int32_t *err) {
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
+    const int32_t n = min(*n_long, room);
+    int32_t bad = 0;
+    for (int64_t i = wave_first(wave); i < n; i += nwaves) {
+        const int32_t e = long_rows[i], q = find_graph(dbase, GD, e);
+        const BatchGraph *d = gr + dual_ids[q];
+        const int32_t *rp = d->rp + (e - dbase[q]);
+        const int32_t b = rp[0], en = rp[1];
+        concat_row(d, e, b + lane_id(), kWave, b, en, xcol, xrow, bad);
     }
     if (bad) atomicOr(err, bad);
 }
@@ -313,11 +349,17 @@ hipError_t launch_batch_nnz(hipStream_t st, const BatchGraph *gr, int32_t G, int
 }
 
 hipError_t launch_batch_concat(hipStream_t st, const BatchGraph *gr, const int32_t *dual_ids,
-                               const int64_t *dbase, int32_t GD, int64_t E, int32_t *xcol,
-                               int32_t *xrow, int32_t *err) {
+                               const int64_t *dbase, int32_t GD, int64_t E, int64_t ZD,
+                               int32_t *xcol, int32_t *xrow, int32_t *long_rows, int32_t *n_long,
+                               int32_t *err) {
     if (E <= 0) return hipSuccess;
-    k_batch_concat<<<grid_for(E, 256, 65536), 256, 0, st>>>(gr, dual_ids, dbase, GD, E, xcol,
-                                                                    xrow, err);
+    const int32_t room = (int32_t)(ZD / kMidRow);  // rows of more than kMidRow entries
+    k_batch_concat<<<grid_for(E, 256, 65536), 256, 0, st>>>(gr, dual_ids, dbase, GD, E, xcol, xrow,
+                                                            long_rows, room, n_long, err);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || room == 0) return e;
+    k_batch_long<<<grid_for(room, 4, 2048), 256, 0, st>>>(gr, dual_ids, dbase, GD, long_rows, room,
+                                                          n_long, xcol, xrow, err);
     return hipGetLastError();
 }
 

@@ -111,3 +111,51 @@ def test_lookup_members(ctx, k):
             assert_same(ctx.build(rp, col, g.n_vertices, s), ref, f"k={k} s={s}")
     finally:
         ctx.set_tuning(**base)
+
+
+def distinct_rows(size, n: int, seed: int):
+    rng = np.random.default_rng(seed)
+    row_ptr = np.concatenate([[0], np.cumsum(size)]).astype(np.int32)
+    col = [np.sort(rng.choice(n, k, replace=False)) for k in size]
+    return gen.Hypergraph(row_ptr, np.concatenate(col).astype(np.int32), len(size), n)
+
+
+@pytest.mark.parametrize("sizes", ["one_length", "mixed"])
+def test_batch_of_long_rows(ctx, sizes):
+    """Dual graphs of rows around what a wave takes at once and of many more
+    entries, in one batch and its plan; a bad member or a row out of order at
+    the end of a long row is refused."""
+    import torch
+    from paper_2010_11448_amd import sline
+
+    dev = torch.device("cuda", 0)
+    if sizes == "one_length":
+        graphs = [distinct_rows(np.full(40, k), 9000, k) for k in (255, 256, 257, 2000)]
+    else:
+        some = np.array([0, 1, 16, 17, 255, 256, 257, 300, 3000, 64])
+        graphs = [distinct_rows(np.resize(np.roll(some, k), m), 50000, k) for k, m in ((0, 10), (3, 90), (7, 140))]
+    duals, ss = [1] * len(graphs), [2] * len(graphs)
+    dg = [to_device(g, dev) for g in graphs]
+    batch = [(rp, col, g.n_vertices) for (rp, col), g in zip(dg, graphs)]
+    refs = [oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, 2, dual=1, threads=8)[0] for g in graphs]
+    print(f"case: batch of long rows, {sizes}", flush=True)
+    for L, ref in zip(ctx.build_batch(batch, ss, duals), refs):
+        assert_same(L, ref, "batch")
+    plan = sline.BatchPlan(ctx, batch, ss, duals)
+    try:
+        for L, ref in zip(plan.run(), refs):
+            assert_same(L, ref, "plan")
+        g, (rp, col) = graphs[-1], dg[-1]
+        end = int(g.row_ptr[np.argmax(np.diff(g.row_ptr)) + 1])  # of the longest row
+        keep = int(col[end - 1])
+        for bad in (g.n_vertices, -1, int(col[end - 2])):
+            print(f"case: member {bad} at the end of a long row", flush=True)
+            col[end - 1] = bad
+            assert plan.run_raw() == sline.SLINE_EINVAL
+            with pytest.raises(sline.SlineError):
+                ctx.build_batch(batch, ss, duals)
+        col[end - 1] = keep
+        for L, ref in zip(plan.run(), refs):
+            assert_same(L, ref, "plan, mended")
+    finally:
+        plan.close()
