@@ -1551,6 +1551,7 @@ struct sline_batch_plan {
     BatchBases B;
     int32_t s_min = 1;
     bool groups = true;  // the task kernel has items (its lookup-only members are marked)
+    int64_t items[kKinds] = {};  // items that can come to be of each kind, see plan_grids
     std::vector<std::pair<void *, size_t>> mem;  // device allocations
     // device views
     BatchGraph *d_gr = nullptr;
@@ -1703,6 +1704,33 @@ void plan_enqueue_fill(sline_batch_plan *p, hipStream_t st) {
               "graph pair offsets");
 }
 
+// Items that runs of a plan can have of each kind: with a larger s an item loses
+// wedges and comes to be of the same kind or a lighter one, so no more than the
+// planned run has of that kind and the heavier ones.
+void plan_kinds(sline_batch_plan *p, const int64_t *planned) {
+    constexpr int kWeight[kKinds] = {2, 4, 0, 4, 2, 3, 1};
+    for (int k = 0; k < kKinds; ++k) {
+        p->items[k] = 0;
+        for (int j = 0; j < kKinds; ++j)
+            if (kWeight[j] >= kWeight[k]) p->items[k] += planned[j];
+    }
+}
+
+// The workgroups of a plan's launches, of every kind at least one (each kernel
+// takes items until its list is empty); returns their number.  With the most
+// that are useful of every kind, a plan of four graphs of 1,000 hyperedges held
+// 50 MB for their chunks of pool and log, and cleared most of it in each run.
+int64_t plan_grids(const sline_batch_plan *p, CountArgs &C) {
+    C.n_cu = p->c->n_cu;
+    (void)set_grids(C, p->items);
+    int64_t total = 0;
+    for (int32_t &g : C.grid) {
+        g = (int32_t)std::max<int64_t>(1, std::min<int64_t>(g, p->t_cap));
+        total += g;
+    }
+    return total;
+}
+
 // Counting arguments of the plan's pass (mode, pool and chunks set by the caller).
 CountArgs plan_count_args(sline_batch_plan *p) {
     const Layout &L = p->L;
@@ -1744,10 +1772,9 @@ CountArgs plan_count_args(sline_batch_plan *p) {
     C.need_count = TL.ctrs + 1;
     C.passes = L.passes;
     C.err = L.err;
-    C.n_cu = p->c->n_cu;
     C.abort = p->d_err;
     C.mode = p->pool_cap > 0 ? kModeStage : kModeCount;
-    (void)set_grids(C, nullptr);
+    (void)plan_grids(p, C);
     set_chunks(C);
     return C;
 }
@@ -1928,6 +1955,7 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
     if (B.ZT > 0) {
         const int64_t T = p->host[0], wedges = p->host[3], ranges = p->host[4];
         p->groups = p->host[5 + kKindGroups] > 0;
+        plan_kinds(p, p->host + 5);
         if (T >= INT32_MAX) {
             set_err(c, "too many counting tasks (%s)", std::to_string(T).c_str());
             return SLINE_ENOMEM;
@@ -1935,9 +1963,7 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
         p->t_cap = std::max<int64_t>(T, 1);
         {
             Arena sz;
-            CountArgs all = p->C;
-            all.n_cu = c->n_cu;
-            const int64_t more = ranges + kLogPerWg * set_grids(all, nullptr);
+            const int64_t more = ranges + kLogPerWg * plan_grids(p, p->C);
             (void)plan_tasks(sz, p->t_cap, more);
             Arena A;
             A.base = reinterpret_cast<char *>(plan_alloc(p, sz.off + 4096, "the task arrays"));
@@ -1966,11 +1992,10 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
         // the pool kept for the runs, instead of the W_s / s_min bound: a
         // range that does not fit its workgroup's chunk leaves less than its
         // own size unused, so the pairs take at most twice their number plus
-        // the chunks left partly used at the end (one per workgroup, at most
-        // an eighth of the pool in all); tasks that still find no room are
-        // counted again by the fill pass
-        CountArgs all = p->C;
-        const int64_t groups = set_grids(all, nullptr);
+        // the chunks left partly used at the end (one per workgroup that has
+        // pairs, at most an eighth of the pool in all); tasks that still find no
+        // room are counted again by the fill pass
+        const int64_t groups = std::min(plan_grids(p, p->C), total);
         const int64_t keep = std::min<int64_t>(p->pool_cap, total * 7 / 3 + 512 * groups);
         if (first_pool && keep < p->pool_cap) {
             plan_drop_last(p, first_pool);

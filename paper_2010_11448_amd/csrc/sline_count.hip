@@ -1821,14 +1821,10 @@ int32_t set_grids(CountArgs &A, const int64_t *items) {
     int32_t total = 0;
     for (int k = 0; k < kKinds; ++k) {
         int64_t g = std::max(1, A.n_cu * per_cu[k]);
-        if (items) {
-            const int64_t n = k == kKindTiny ? (items[k] + kTinyThreads - 1) / kTinyThreads : items[k];
-            g = std::max(g, std::min(g * kRounds[k], n / kRoundItems));
-            // items in groups or ranges take several workgroups each
-            if (n == 0 || (k != kKindGroups && k != kKindFlat)) g = std::min(g, n);
-        } else {
-            g *= kRounds[k];
-        }
+        const int64_t n = k == kKindTiny ? (items[k] + kTinyThreads - 1) / kTinyThreads : items[k];
+        g = std::max(g, std::min(g * kRounds[k], n / kRoundItems));
+        // items in groups or ranges take several workgroups each
+        if (n == 0 || (k != kKindGroups && k != kKindFlat)) g = std::min(g, n);
         A.grid[k] = (int32_t)g;
         total += (int32_t)g;
     }

@@ -518,8 +518,8 @@ struct CountArgs {
     const int32_t *abort;
 };
 constexpr int64_t kPoolChunkMin = 256;   // pairs a workgroup reserves at least
-// Workgroups per kind for `items` items of each (null: not known, the most that
-// are useful); returns their number.  Needs tune and n_cu.
+// Workgroups per kind for `items` items of each; returns their number.  Needs tune
+// and n_cu.
 int32_t set_grids(CountArgs &a, const int64_t *items);
 // Chunks of pool and log for the grids, pool_cap, log_cap and mode.
 void set_chunks(CountArgs &a);

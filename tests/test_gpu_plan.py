@@ -364,3 +364,39 @@ def test_plan_refuses_rows_bad_inside(ctx, dev, bad, dual):
             _check(plan.run(), graphs, ss, duals, f"restored after {bad}")
     finally:
         plan.close()
+
+
+def test_small_plan_is_small(ctx, dev):
+    """A plan's task log and pool are sized by its own items: a workgroup, with 32
+    log records of 24 bytes, for no more than each of seven kinds of every task."""
+    graphs = [gen.batch_graph(g, m_cap=1000).graph for g in range(4)]
+    dg = [to_device(h, dev) for h in graphs]
+    plan = _plan(ctx, dg, graphs, [3] * 4, [0] * 4)
+    try:
+        nbytes, tasks, pairs = plan.info()
+        print(f"case: plan of {tasks} tasks, {pairs} pairs: {nbytes} bytes", flush=True)
+        assert nbytes < 7 * tasks * 32 * 24 + (4 << 20)
+        _check(plan.run(), graphs, [3] * 4, [0] * 4, "small plan")
+    finally:
+        plan.close()
+
+
+from test_gpu_direct import hub  # noqa: E402
+
+
+def test_plan_items_change_kind(ctx, dev):
+    """At larger s than planned, items of every kind of kernel come to be of
+    another: no wedges kept, sieved, or fewer wedges."""
+    shapes = [(9000, 15, 3, 20000), (4000, 60, 4, 5000), (300, 20, 2, 900), (100, 64, 3, 4000),
+              (12, 5, 5, 40000), (700, 80, 3, 2000), (9000, 300, 3, 70000)]
+    graphs = [hub(*c, seed=i) for i, c in enumerate(shapes)]
+    dg = [to_device(h, dev) for h in graphs]
+    duals = [0] * len(graphs)
+    for planned in (1, 2):
+        plan = _plan(ctx, dg, graphs, [planned] * len(graphs), duals)
+        try:
+            for s in (planned, planned + 1, 3, 4, planned):
+                print(f"case: planned at s={planned}, run at {s}", flush=True)
+                _check(plan.run([s] * len(graphs)), graphs, [s] * len(graphs), duals, f"s={s}")
+        finally:
+            plan.close()
