@@ -44,7 +44,10 @@ using namespace sl;
 // Host code never passes `scratch` itself to a kernel (on the host it only
 // names the symbol): it uses the device address taken once per device by
 // scratch_address().
-static __device__ __align__(256) unsigned char scratch[SLINE_NOALLOC_SCRATCH_BYTES];
+// Beyond the size that a build's arrays may take it has room for the counters in
+// rows (kSumRows), so that these refuse no build that fits without them.
+constexpr size_t kScratchBytes = SLINE_NOALLOC_SCRATCH_BYTES + (16 << 10);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 
@@ -766,7 +769,7 @@ sline_status noalloc_impl(sline_ctx *c, const sline_csr &H, int32_t s, int32_t d
     c->pool_bytes = 0;
     c->pool_fixed = false;
     c->fixed.base = static_cast<char *>(base);
-    c->fixed.size = SLINE_NOALLOC_SCRATCH_BYTES;
+    c->fixed.size = kScratchBytes;
     c->fixed.used = 0;
     ItemS IS;
     IS.s_min = IS.s_max = s;

@@ -200,3 +200,21 @@ def test_after_a_refused_build(then):
         check(call(ctx, csr, 1, 0, 0, e), e)
     sline.sline_destroy(ctx)
     assert not rec.wrong and not rec.live
+
+
+def test_builds_that_just_fit(ctx):
+    """One hyperedge of two vertices, dual, with as many isolated ones as leave the
+    arrays of the build 128 MiB less a few bytes, and clearly more."""
+    import torch
+    from paper_2010_11448_amd import sline
+
+    dev = torch.device("cuda", 0)
+    rp = torch.tensor([0, 2], dtype=torch.int32, device=dev)
+    out = torch.zeros((3, 4), dtype=torch.int32, device=dev)
+    for n, want in ((5524000, sline.SLINE_OK), (5524832, sline.SLINE_OK), (5530000, sline.SLINE_ENOMEM)):
+        col = torch.tensor([0, n - 1], dtype=torch.int32, device=dev)
+        print(f"case: {n} vertices", flush=True)
+        st, k = ctx.build_noalloc(rp, col, n, 1, 1, 0, out[0], out[1], out[2])
+        assert st == want
+        if st == sline.SLINE_OK:
+            assert k == 1 and out[:, 0].tolist() == [0, n - 1, 1]
