@@ -42,36 +42,61 @@ constexpr int kFlatChunks = kFlatKeep / kWave;  // 64-wedge chunks marked at a t
 // Position of every multiple of kFlatBlock candidates in each list that is at
 // least as long as the table row it needs: bnd[ptrS[v] + r] = the first entry
 // of N_s(v) that is >= r * kFlatBlock, r = 0..blocks.  A row lies over its
-// list's own entries, so rows need no index of their own.  One wave per list.
+// list's own entries, so rows need no index of their own.  The row of the list
+// [b, e), by one wave:
+__device__ __forceinline__ void flat_bounds_row(const int32_t *itmS, int32_t b, int32_t e,
+                                                int32_t blocks, int32_t *bnd) {
+    int32_t last = -1;  // block of the entry before this step's first
+    for (int32_t q = b; q <= e; q += kWave) {
+        const int32_t p = q + lane_id();
+        const int32_t cur = p < e ? itmS[p] / kFlatBlock : blocks;
+        int32_t prev = __shfl_up(cur, 1, kWave);
+        if (lane_id() == 0) prev = last;
+        if (p <= e)
+            for (int32_t x = prev + 1; x <= cur; ++x) bnd[b + x] = p;
+        last = lane63(cur);
+    }
+}
+
+// A wave looks at 64 lists and takes those of up to kMidList entries that need a
+// row; longer ones go to a list of their own, of which every wave of a second
+// kernel takes one.  (64 long lists in turn, as of the only members there are or of
+// hubs with neighbouring ids, would keep the build waiting: 16 lists of 6,250 items,
+// 0.47 ms of a build of 1.34, now 0.92.)
+constexpr int32_t kMidList = 512;
+
 __global__ __launch_bounds__(256) void k_flat_bounds(const int32_t *ptrS, const int32_t *itmS,
                                                      int32_t M, const int32_t *crank, int32_t N,
-                                                     int32_t *bnd, const int32_t *err) {
+                                                     int32_t *bnd, int32_t *long_lists,
+                                                     int32_t *n_long, const int32_t *err) {
     if (err && *err) return;
     crank = ranks_or_null(crank, N);
     const int32_t blocks = flat_blocks(cand_of(crank, N));
     if (blocks < 2) return;  // every item's candidates fit one range of any width
-    const int lane = lane_id();
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
     for (int64_t base = wave * kWave; base < M; base += nwaves * kWave) {
-        const int64_t r = base + lane;
+        const int64_t r = base + lane_id();
         const int32_t b0 = r < M ? ptrS[r] : 0, e0 = r < M ? ptrS[r + 1] : 0;
-        uint64_t m = __ballot(e0 - b0 > blocks);
-        while (m) {
+        const bool row = e0 - b0 > blocks, far = row && e0 - b0 > kMidList;
+        if (far) long_lists[atomicAdd(n_long, 1)] = (int32_t)r;
+        for (uint64_t m = __ballot(row && !far); m; m &= m - 1) {
             const int l = __builtin_ctzll(m);
-            m &= m - 1;
-            const int32_t b = __builtin_amdgcn_readlane(b0, l), e = __builtin_amdgcn_readlane(e0, l);
-            int32_t last = -1;  // block of the entry before this step's first
-            for (int32_t q = b; q <= e; q += kWave) {
-                const int32_t p = q + lane;
-                const int32_t cur = p < e ? itmS[p] / kFlatBlock : blocks;
-                int32_t prev = __shfl_up(cur, 1, kWave);
-                if (lane == 0) prev = last;
-                if (p <= e)
-                    for (int32_t x = prev + 1; x <= cur; ++x) bnd[b + x] = p;
-                last = lane63(cur);
-            }
+            flat_bounds_row(itmS, __builtin_amdgcn_readlane(b0, l), __builtin_amdgcn_readlane(e0, l),
+                            blocks, bnd);
         }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_flat_long(const int32_t *ptrS, const int32_t *itmS,
+                                                   const int32_t *crank, int32_t N, int32_t *bnd,
+                                                   const int32_t *long_lists, const int32_t *n_long) {
+    crank = ranks_or_null(crank, N);
+    const int32_t blocks = flat_blocks(cand_of(crank, N)), n = *n_long;
+    const int32_t nwaves = gridDim.x * (256 / kWave);
+    for (int32_t i = blockIdx.x * (256 / kWave) + wave_id(); i < n; i += nwaves) {
+        const int32_t v = long_lists[i];
+        flat_bounds_row(itmS, uniform(ptrS[v]), uniform(ptrS[v + 1]), blocks, bnd);
     }
 }
 
@@ -568,11 +593,16 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
 }  // namespace
 
 hipError_t launch_flat_bounds(hipStream_t st, const int32_t *ptrS, const int32_t *itmS, int32_t M,
-                              const int32_t *crank, int32_t N, int32_t *bnd,
-                              const int32_t *err) {
+                              const int32_t *crank, int32_t N, int64_t nnz, int32_t *bnd,
+                              int32_t *long_lists, int32_t *n_long, const int32_t *err) {
     if (M <= 0 || N <= kFlatBlock) return hipSuccess;
     const int64_t g = std::min<int64_t>(((int64_t)M + 255) / 256, 4096);
-    k_flat_bounds<<<(unsigned)g, 256, 0, st>>>(ptrS, itmS, M, crank, N, bnd, err);
+    k_flat_bounds<<<(unsigned)g, 256, 0, st>>>(ptrS, itmS, M, crank, N, bnd, long_lists, n_long, err);
+    const hipError_t e = hipGetLastError();
+    const int64_t most = nnz / kMidList;  // lists of more than kMidList entries
+    if (e != hipSuccess || most == 0) return e;
+    k_flat_long<<<(unsigned)std::min<int64_t>((most + 3) / 4, 1024), 256, 0, st>>>(
+        ptrS, itmS, crank, N, bnd, long_lists, n_long);
     return hipGetLastError();
 }
 

@@ -433,11 +433,12 @@ hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, const PlanItems
                             const int32_t *abort = nullptr);
 
 // Positions of the multiples of kFlatBlock candidates in the long lists (bnd:
-// as many entries as itmS), for the items counted directly.  Nothing is done while
-// *err (if given) is not 0.
+// as many entries as itmS, nnz at most), for the items counted directly.  long_lists:
+// scratch of as many; n_long: its length, zeroed by the caller.  Nothing is done
+// while *err (if given) is not 0.
 hipError_t launch_flat_bounds(hipStream_t st, const int32_t *ptrS, const int32_t *itmS, int32_t M,
-                              const int32_t *crank, int32_t N, int32_t *bnd,
-                              const int32_t *err = nullptr);
+                              const int32_t *crank, int32_t N, int64_t nnz, int32_t *bnd,
+                              int32_t *long_lists, int32_t *n_long, const int32_t *err = nullptr);
 
 // Counting-kernel modes.
 enum : int32_t {

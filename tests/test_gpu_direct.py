@@ -239,3 +239,24 @@ def test_ids_in_order_of_size(ctx, order):
             ref, _ = oracle.wedge(g.row_ptr, g.col, m, n, s, dual=dual, threads=8)
             print(f"case: order={order} dual={dual} s={s} pairs={len(ref.a)}", flush=True)
             assert_same(ctx.build(rp, col, n, s, dual), ref, f"order={order} dual={dual} s={s}")
+
+
+@pytest.mark.parametrize("n,at", [(128, 1), (300, 2), (820, 3), (40000, 1)])
+def test_few_long_lists(ctx, n, at):
+    """Member lists of a few hundred to many thousand items, among them those of
+    hubs with neighbouring ids, in several ranges of direct counters."""
+    import torch
+
+    m = 140000
+    st = gen.Stream(n)
+    row = np.repeat(np.arange(m), 3)
+    v = (n * st.uniform(len(row)) ** (4 if n > 1000 else 1)).astype(np.int64)
+    row, v = np.append(row, np.full(40, at)), np.append(v, np.arange(40))  # a larger row
+    key = np.unique(row * n + v)
+    row_ptr = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=m))])
+    g = gen.Hypergraph(row_ptr.astype(np.int32), (key % n).astype(np.int32), m, n)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    for s in (2, 3):
+        ref, _ = oracle.wedge(g.row_ptr, g.col, m, n, s, threads=8)
+        print(f"case: {n} members, s={s}, longest list {np.bincount(g.col).max()}, pairs={len(ref.a)}", flush=True)
+        assert_same(ctx.build(rp, col, n, s), ref, f"n={n} s={s}")
