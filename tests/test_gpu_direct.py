@@ -260,3 +260,42 @@ def test_few_long_lists(ctx, n, at):
         ref, _ = oracle.wedge(g.row_ptr, g.col, m, n, s, threads=8)
         print(f"case: {n} members, s={s}, longest list {np.bincount(g.col).max()}, pairs={len(ref.a)}", flush=True)
         assert_same(ctx.build(rp, col, n, s), ref, f"n={n} s={s}")
+
+
+def near(m: int, n: int, lo: int, hi: int, width: int, far: float, seed: int) -> gen.Hypergraph:
+    """m rows of up to lo..hi members within `width` vertices of the row's own
+    place among n, a share `far` of them anywhere."""
+    st = gen.Stream(seed)
+    size = st.integers(lo, hi, m)
+    row = np.repeat(np.arange(m), size)
+    k = len(row)
+    v = (row * n // m + st.integers(0, width - 1, k)) % n
+    v = np.where(st.uniform(k) < far, st.integers(0, n - 1, k), v)
+    key = np.unique(row * n + v)
+    row_ptr = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=m))])
+    return gen.Hypergraph(row_ptr.astype(np.int32), (key % n).astype(np.int32), m, n)
+
+
+# rows and vertices, sizes, width, share anywhere: candidates that crowd in a small
+# part of the range, all of them or most, for items of few and of many wedges
+NEAR = [(30000, 6000, 5, 30, 400, 0.0), (30000, 6000, 5, 30, 400, 0.05), (60000, 120000, 5, 30, 400, 0.0),
+        (60000, 120000, 5, 30, 400, 0.05), (40000, 8000, 30, 70, 200, 0.02), (20000, 2000, 2, 6, 40, 0.3)]
+
+
+@pytest.mark.parametrize("case", NEAR, ids=["-".join(map(str, c)) for c in NEAR])
+@pytest.mark.parametrize("dual", [0, 1])
+def test_ids_of_neighbours_close(ctx, case, dual):
+    import torch
+
+    g = near(*case, seed=case[0] + dual)
+    rp, col = to_device(g, torch.device("cuda", 0))
+    base = ctx.tuning()
+    for s in (1, 2, 4):
+        ref, _ = oracle.wedge(g.row_ptr, g.col, g.n_edges, g.n_vertices, s, dual=dual, threads=8)
+        for stage in (base["stage_max_bytes"], 0):
+            print(f"case: {case} dual={dual} s={s} stage={stage} pairs={len(ref.a)}", flush=True)
+            ctx.set_tuning(stage_max_bytes=stage)
+            try:
+                assert_same(ctx.build(rp, col, g.n_vertices, s, dual), ref, f"{case} dual={dual} s={s}")
+            finally:
+                ctx.set_tuning(**base)
