@@ -2875,11 +2875,13 @@ sline_status components_impl(sline_ctx *c, int32_t N, const sline_edges *L, int3
     sz.take<int32_t>(4);
     sz.take<unsigned long long>(1);
     sz.take<int32_t>((int64_t)N + 1);
+    sz.take<int32_t>(N);
     Arena A;
     A.base = T.get(sz.off, "components");
     int32_t *err = A.take<int32_t>(4);
     unsigned long long *count = A.take<unsigned long long>(1);
     int32_t *flag = A.take<int32_t>((int64_t)N + 1);
+    int32_t *label = A.take<int32_t>(N);
     hip_check(c, launch_fill_i32(st, err, 4, 0), "zero flags");
     hip_check(c, launch_fill_i64(st, reinterpret_cast<int64_t *>(count), 1, 0), "zero count");
     hip_check(c, launch_fill_i32(st, flag, (int64_t)N + 1, 0), "zero flags");
@@ -2890,7 +2892,7 @@ sline_status components_impl(sline_ctx *c, int32_t N, const sline_edges *L, int3
         set_err(c, "pairs must have 0 <= a < b < n_items and be sorted by (a, b)");
         return SLINE_EINVAL;
     }
-    hip_check(c, launch_components(st, L->a, L->b, n, N, comp), "components");
+    hip_check(c, launch_components(st, L->a, L->b, n, N, comp, label), "components");
     hip_check(c, launch_cc_count(st, comp, flag, N, count), "component count");
     hip_check(c, hipMemcpyAsync(c->host, count, sizeof(int64_t), hipMemcpyDeviceToHost, st),
               "read component count");

@@ -619,9 +619,10 @@ hipError_t launch_adj_fill(hipStream_t st, int64_t n, const int32_t *newid, cons
                            const int32_t *a, const int32_t *b, const int32_t *w, int32_t *ocol,
                            int32_t *ow);
 hipError_t launch_iota(hipStream_t st, int32_t *p, int64_t n);
-// comp[x] = smallest item of x's component in the graph of the pairs.
+// comp[x] = smallest item of x's component in the graph of the pairs; label: N
+// entries of scratch.
 hipError_t launch_components(hipStream_t st, const int32_t *a, const int32_t *b, int64_t n,
-                             int32_t N, int32_t *comp);
+                             int32_t N, int32_t *comp, int32_t *label);
 hipError_t launch_cc_count(hipStream_t st, const int32_t *comp, const int32_t *flag, int32_t N,
                            unsigned long long *count);
 hipError_t launch_gather(hipStream_t st, const int32_t *src, const int32_t *idx, int64_t n,

@@ -177,44 +177,55 @@ __device__ __forceinline__ void st_rel(int32_t *p, int32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Root of x in the union-find forest p: links only ever point to smaller
-// ids, so the walk ends; every node passed is pointed at its grandparent
-// (path halving), which keeps the trees shallow.
-__device__ __forceinline__ int32_t uf_root(int32_t *p, int32_t x) {
-    for (;;) {
-        const int32_t px = ld_rel(p + x);
-        if (px == x) return x;
-        const int32_t gx = ld_rel(p + px);
-        if (gx == px) return px;
-        st_rel(p + x, gx);
-        x = gx;
-    }
-}
-
 __global__ void k_iota(int32_t *p, int64_t n) {
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n;
          x += (int64_t)gridDim.x * blockDim.x)
         p[x] = (int32_t)x;
 }
 
-// Union of the two ends of a pair: the larger root is linked under the smaller
-// with a compare-and-swap that succeeds only while it is still a root, so a
-// component's final root is its smallest item.
+// Union of the two ends of a pair in the forest p, whose links lead to smaller ids: a
+// root is linked to a smaller node of the other end's tree, which need not be a
+// root (as in Sutton, Ben-Nun and Barak, "Optimizing Parallel Graph Connectivity
+// Computation via Subgraph Sampling", 2018).  The compare-and-swap succeeds only while
+// it is still a root, so nothing is lost, and a component's last root is its smallest
+// item.  Nodes passed are pointed at their grandparents.  Of the lanes that have come
+// to the same node the first goes on with it, and the others join what they have
+// below it to what the first has: one lane in the place of 64 that swap one word.
+// Walks to both roots took 70 to 150 ms where the ids of neighbours make a chain (a
+// grid or a path of 10^6 items, both 0.15 ms now), a star of as many 3.5 (0.20).
 __device__ __forceinline__ void uf_union(int32_t *p, int32_t x, int32_t y) {
-    int32_t ra = uf_root(p, x), rb = uf_root(p, y);
-    while (ra != rb) {
-        const int32_t hi = ra > rb ? ra : rb, lo = ra > rb ? rb : ra;
-        const int32_t old = atomicCAS(p + hi, hi, lo);
-        if (old == hi) break;
-        ra = uf_root(p, hi);
-        rb = uf_root(p, lo);
+    int32_t u = ld_rel(p + x), v = ld_rel(p + y);
+    while (u != v) {
+        const int32_t hi = max(u, v), lo = min(u, v);
+        const int32_t first_lo = __builtin_amdgcn_readfirstlane(lo);
+        const bool first = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) ==
+                           (uint32_t)__builtin_ctzll(__ballot(true));
+        if (hi == __builtin_amdgcn_readfirstlane(hi) && !first) {
+            u = lo;
+            v = first_lo;
+            continue;
+        }
+        const int32_t up = ld_rel(p + hi), below = ld_rel(p + lo);
+        if (up == lo) break;
+        if (up == hi) {
+            u = atomicCAS(p + hi, hi, lo);
+            if (u == hi) break;
+            v = lo;  // linked meanwhile: go on from its new parent
+            continue;
+        }
+        u = ld_rel(p + up);
+        v = below;
+        if (u != up) st_rel(p + hi, u);
     }
 }
 
 // The first pair of every item and one in kHookSample: enough to join most of
-// a component, so that after the labels are flattened nearly every other pair
-// has equal ones.
+// a component, so that after the labels are flattened most other pairs have equal
+// ones.  With few pairs the sample is nearly all of them, but flattening it
+// shortens the walks of the rest; with fewer than half as many as items (0.17 ms for
+// 500,000 of 10^6) its launches cost more than that.
 constexpr int kHookSample = 256;
+constexpr int kSampleFrom = 2;
 
 __global__ void k_cc_sample(const int32_t *a, const int32_t *b, int64_t n, int32_t *p) {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
@@ -224,28 +235,33 @@ __global__ void k_cc_sample(const int32_t *a, const int32_t *b, int64_t n, int32
     }
 }
 
-// Every pair, after a flatten: two ends with equal labels are joined already,
-// as a label is always a node of its item's component, also one read from a
-// cache that other links have not reached.  Only the rest walks the forest with
-// reads that pass the caches by: 4.5*10^7 pairs of 200,000 items take 0.20 ms
-// here and 0.25 in the sample, and took 6.5 with such a walk for each.
-__global__ void k_cc_hook(const int32_t *a, const int32_t *b, int64_t n, int32_t *p) {
+// Every pair.  JOINED: label holds the flattened sample, where two ends with equal
+// labels are joined already.  It is a copy that nothing writes to meanwhile: with the
+// labels of p itself, every link threw the line out of the other caches, and 5*10^6
+// pairs of 10^6 items took 2.4 ms (now 0.5 in all).
+template <bool JOINED>
+__global__ void k_cc_hook(const int32_t *a, const int32_t *b, int64_t n, const int32_t *label,
+                          int32_t *p) {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
          e += (int64_t)gridDim.x * blockDim.x) {
         const int32_t x = a[e], y = b[e];
-        if (p[x] != p[y]) uf_union(p, x, y);
+        if (!JOINED || label[x] != label[y]) uf_union(p, x, y);
     }
 }
 
-// Every node at its root.  The walk writes nothing on its way: a halving step
-// here could put back a grandparent read before the node's own thread had
-// stored the root.
-__global__ void k_cc_flatten(int32_t *p, int32_t N) {
+// Every node at its root, also in label if given.  A thread points its own node, and
+// no other, further up the tree until it has come to the root: nothing that it has
+// stored can be put back, and as all threads do so at once, long paths of links get
+// half as long with every step.
+__global__ void k_cc_flatten(int32_t *p, int32_t N, int32_t *label) {
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < N;
          x += (int64_t)gridDim.x * blockDim.x) {
-        int32_t r = (int32_t)x;
-        for (int32_t up = ld_rel(p + r); up != r; up = ld_rel(p + r)) r = up;
-        st_rel(p + x, r);
+        int32_t r = ld_rel(p + x);
+        for (int32_t up = ld_rel(p + r); up != r; up = ld_rel(p + r)) {
+            r = up;
+            st_rel(p + x, r);
+        }
+        if (label) label[x] = r;
     }
 }
 
@@ -495,20 +511,20 @@ hipError_t launch_iota(hipStream_t st, int32_t *p, int64_t n) {
 }
 
 hipError_t launch_components(hipStream_t st, const int32_t *a, const int32_t *b, int64_t n,
-                             int32_t N, int32_t *comp) {
+                             int32_t N, int32_t *comp, int32_t *label) {
     if (N <= 0) return hipSuccess;
     hipError_t e = launch_iota(st, comp, N);
     if (e != hipSuccess) return e;
-    if (n > 0) {
-        if (n > N) {  // else nearly every pair is in the sample
-            k_cc_sample<<<grid_for(n, 256, 65536), 256, 0, st>>>(a, b, n, comp);
-            k_cc_flatten<<<grid_for(N, 256, 65536), 256, 0, st>>>(comp, N);
-        }
-        k_cc_hook<<<grid_for(n, 256, 65536), 256, 0, st>>>(a, b, n, comp);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    if (n > N / kSampleFrom) {
+        k_cc_sample<<<grid_for(n, 256, 65536), 256, 0, st>>>(a, b, n, comp);
+        k_cc_flatten<<<grid_for(N, 256, 65536), 256, 0, st>>>(comp, N, label);
+        k_cc_hook<true><<<grid_for(n, 256, 65536), 256, 0, st>>>(a, b, n, label, comp);
+    } else if (n > 0) {
+        k_cc_hook<false><<<grid_for(n, 256, 65536), 256, 0, st>>>(a, b, n, nullptr, comp);
     }
-    k_cc_flatten<<<grid_for(N, 256, 65536), 256, 0, st>>>(comp, N);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_cc_flatten<<<grid_for(N, 256, 65536), 256, 0, st>>>(comp, N, nullptr);
     return hipGetLastError();
 }
 

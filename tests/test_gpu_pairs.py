@@ -82,3 +82,50 @@ def test_pairs(ctx, case):
         assert np.array_equal(G["col"].cpu().numpy(), col)
         if not flags:
             assert np.array_equal(G["w"].cpu().numpy(), wq)
+
+
+def linked(N: int, *lists):
+    lo = np.concatenate([np.minimum(x, y) for x, y in lists])
+    hi = np.concatenate([np.maximum(x, y) for x, y in lists])
+    key = np.unique((lo * N + hi)[lo < hi])
+    return (key // N).astype(np.int32), (key % N).astype(np.int32)
+
+
+def shapes(N: int):
+    """Pairs whose ids follow their links, in one tree or several."""
+    x = np.arange(N - 1)
+    rng = np.random.default_rng(N)
+    yield "path", linked(N, (x, x + 1))
+    yield "two paths", linked(N, (x[:-1], x[:-1] + 2))
+    yield "evens, then odds", linked(N, (x[:-1], x[:-1] + 2), (np.array([1]), np.array([(N - 1) // 2 * 2])))
+    yield "there and back", linked(N, (x, N - 1 - x), (x, np.maximum(N - 2 - x, 0)))
+    yield "paths of 100", linked(N, (x[x % 100 != 99], x[x % 100 != 99] + 1))
+    yield "band", linked(N, *[(x[: N - k], x[: N - k] + k) for k in range(1, 20)])
+    yield "grid", linked(N, (x, x + 1), (x[: N - 500], x[: N - 500] + 500))
+    yield "tree", linked(N, ((x + 1) // 2, x + 1))
+    yield "hub first", linked(N, (x * 0, x + 1))
+    yield "hub last", linked(N, (x, x * 0 + N - 1))
+    yield "hub between", linked(N, (x, x * 0 + N // 2))
+    yield "two hubs", linked(N, (x[: N // 2], x[: N // 2] * 0 + 7), (x[N // 2 - 9 :], x[N // 2 - 9 :] * 0 + N - 1))
+    p = rng.permutation(N)
+    yield "path in any order", linked(N, (p[:-1], p[1:]))
+    yield "half as many", linked(N, (rng.integers(0, N, N // 2), rng.integers(0, N, N // 2)))
+    yield "twice as many", linked(N, (rng.integers(0, N, 2 * N), rng.integers(0, N, 2 * N)))
+
+
+@pytest.mark.parametrize("N", [70, 2001, 300000])
+def test_components_of_shapes(ctx, N):
+    import torch
+    from paper_2010_11448_amd import sline
+
+    for name, (a, b) in shapes(N):
+        print(f"case: {name}, {N} items, {len(a)} pairs", flush=True)
+        w = np.ones(len(a), dtype=np.int32)
+        want = oracle.components(N, oracle.Pairs(a, b, w))
+        L = sline.LineGraph(*[torch.from_numpy(x).cuda() for x in (a, b, w)])
+        for _ in range(3):
+            comp, count = ctx.components(L, N)
+            assert np.array_equal(comp.cpu().numpy(), want), name
+            present = np.zeros(N, dtype=bool)
+            present[a] = present[b] = True
+            assert count == int(np.sum(present & (want == np.arange(N))))
