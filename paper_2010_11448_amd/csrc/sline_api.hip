@@ -350,6 +350,14 @@ Tuning build_tuning(const Tuning &t, int64_t n_items, int64_t nnz) {
     return u;
 }
 
+// Room for `most` pairs in the chunks of `wgs` workgroups: nearly as many may come
+// (s = 1, or few wedges), and each workgroup may leave part of its chunk unused: with
+// less than an eighth and two smallest chunks each to spare, a build of few
+// pairs would count tasks twice.
+int64_t pool_pairs(int64_t most, int64_t wgs) {
+    return most <= 0 || most >= kPoolSlackMax ? most : most + most / 8 + 2 * kPoolChunkMin * wgs;
+}
+
 // ranks: with room for candidate numbers.  fixed: the arena is a fixed region,
 // where they must not make a build too large that fits without them.
 Layout plan_layout(Arena &A, int64_t m, int64_t n, int64_t nnz, int64_t N, int64_t M, bool dual,
@@ -967,15 +975,10 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
     plan_tasks(tsz, T, more);
     c->no_weights = (flags & SLINE_NO_WEIGHTS) != 0;
     const int64_t pair_bytes = c->no_weights ? 4 : 8;
-    // Staging pool: every pair of L_s accounts for >= s wedges.  Nearly that many
-    // are possible (s = 1, or few wedges), and each workgroup may leave part of
-    // its chunk unused: with less than an eighth and two smallest chunks each to
-    // spare, such a build would count tasks twice.  The product route counts
-    // and fills in two passes (symbolic, then numeric), as SpGEMM does: its
+    // Staging pool: every pair of L_s accounts for >= s wedges.  The product route
+    // counts and fills in two passes (symbolic, then numeric), as SpGEMM does: its
     // product is too large to stage as well.
-    int64_t want_pool = IS.full ? 0 : S.wedges / IS.s_min;
-    if (want_pool > 0 && want_pool < kPoolSlackMax)
-        want_pool += want_pool / 8 + 2 * kPoolChunkMin * wgs;
+    const int64_t want_pool = IS.full ? 0 : pool_pairs(S.wedges / IS.s_min, wgs);
     const int64_t kept_pool =
         std::min<int64_t>(want_pool * pair_bytes, c->tune.stage_max_bytes / pair_bytes * pair_bytes);
     const bool keep_pool = !c->fixed.base && kept_pool > 0 && kept_pool <= kKeptPool;
@@ -1975,7 +1978,7 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
         }
         // 4. one counting pass with a pool of W_s / s_min pairs (every pair
         // of L_s takes at least s wedges): the pair count
-        plan_pool(p, wedges / p->s_min);
+        plan_pool(p, pool_pairs(wedges / p->s_min, plan_grids(p, p->C)));
         void *first_pool = p->pool;
         p->C = plan_count_args(p);
         plan_enqueue_tasks(p, st, false);
@@ -1995,12 +1998,12 @@ sline_status plan_create_impl(sline_ctx *c, int32_t G, const sline_csr *Hs, cons
         p->pair_cap = std::max<int64_t>(total, 1);
         // the pool kept for the runs, instead of the W_s / s_min bound: a
         // range that does not fit its workgroup's chunk leaves less than its
-        // own size unused, so the pairs take at most twice their number plus
-        // the chunks left partly used at the end (one per workgroup that has
-        // pairs, at most an eighth of the pool in all); tasks that still find no
-        // room are counted again by the fill pass
+        // own size unused, so the pairs take at most twice their number, mostly
+        // much less, plus the chunks left partly used at the end (a smallest
+        // one per workgroup that has pairs, or up to a quarter of the pool);
+        // tasks that still find no room are counted again by the fill pass
         const int64_t groups = std::min(plan_grids(p, p->C), total);
-        const int64_t keep = std::min<int64_t>(p->pool_cap, total * 7 / 3 + 512 * groups);
+        const int64_t keep = std::min<int64_t>(p->pool_cap, total * 7 / 3 + kPoolChunkMin * groups);
         if (first_pool && keep < p->pool_cap) {
             plan_drop_last(p, first_pool);
             plan_pool(p, keep);
