@@ -993,7 +993,7 @@ sline_status build_core(sline_ctx *c, const sline_csr &H, int32_t s, int32_t dua
               "task fill");
     if (C.grid[kKindFlat] > 0)
         hip_check(c, launch_flat_bounds(st, ptrS, itmS, (int32_t)M, L.crank, (int32_t)N, nnz, L.bnd,
-                                        L.rsK1, L.queue + 2),
+                                        L.rsK1, L.queue + 2, L.tcounts + kKindFlat * kCountStride),
                   "list bounds");
     mark(c, 2);
     // 7. one counting pass: pairs per task, each range's pairs staged in a pool
@@ -1670,7 +1670,8 @@ void plan_enqueue_count(sline_batch_plan *p, hipStream_t st, int64_t pair_cap) {
                                   TL.tiny_item, TL.big, (int32_t)p->t_cap, L.tcounts, p->d_err),
               "task fill");
     hip_check(c, launch_flat_bounds(st, L.ptrT, L.itmS, (int32_t)p->B.MT, nullptr,
-                                    (int32_t)p->B.NI, p->B.ZT, L.bnd, L.rsK1, L.queue + 2, p->d_err),
+                                    (int32_t)p->B.NI, p->B.ZT, L.bnd, L.rsK1, L.queue + 2,
+                                    L.tcounts + kKindFlat * kCountStride, p->d_err),
               "list bounds");
     hip_check(c, launch_fill_i32(st, reinterpret_cast<int32_t *>(TL.pool_head), TL.n_zero, 0),
               "zero task arrays");

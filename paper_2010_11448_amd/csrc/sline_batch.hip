@@ -89,8 +89,9 @@ __device__ __forceinline__ void concat_row(const BatchGraph *gr, int64_t r, int3
 
 // Rows of XD (the dual graphs' rows, in graph order): columns shifted by
 // vdbase and the row id of every entry (what the transpose reads); range and
-// order checks.  A wave takes 64 rows: those of up to kShortRow entries a lane
-// each, then those of up to kMidRow in turn; longer ones go to a list, of which
+// order checks.  A wave takes 64 rows, or fewer if that leaves waves idle: those of up
+// to kShortRow entries a lane each, then those of up to kMidRow in turn; longer
+// ones go to a list, of which
 // every wave of a second kernel takes one (64 such rows in turn would keep the
 // whole batch waiting: 100 rows of 20,000 entries took 5.6 ms, and take 0.11 so).
 // Bounds on latency (a row's graph, its bounds, its entries); a wave per row, which
@@ -101,7 +102,7 @@ constexpr int kMidRow = 256;
 
 __global__ __launch_bounds__(256) void k_batch_concat(const BatchGraph *gr, const int32_t *dual_ids,
                                                       const int64_t *dbase, int32_t GD, int64_t E,
-                                                      int32_t *xcol, int32_t *xrow,
+                                                      int32_t per, int32_t *xcol, int32_t *xrow,
                                                       int32_t *long_rows, int32_t room,
                                                       int32_t *n_long, int32_t *err) {
     if (*err & kErrPlanShape) return;  // a replayed plan keeps its last lists
@@ -109,10 +110,10 @@ __global__ __launch_bounds__(256) void k_batch_concat(const BatchGraph *gr, cons
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
     int32_t bad = 0;
-    for (int64_t e0 = wave_first(wave * kWave); e0 < E; e0 += nwaves * kWave) {
+    for (int64_t e0 = wave_first(wave * per); e0 < E; e0 += nwaves * per) {
         const int64_t e = e0 + lane;
         int32_t b = 0, en = 0, q = 0;
-        if (e < E) {
+        if (lane < per && e < E) {
             q = wave_graph(dbase, GD, e0, e);
             const BatchGraph *d = gr + dual_ids[q];
             const int32_t *rp = d->rp + (e - dbase[q]);
@@ -125,12 +126,17 @@ __global__ __launch_bounds__(256) void k_batch_concat(const BatchGraph *gr, cons
                 b = en = 0;
             }
         }
-        if (en - b > kMidRow) {
+        const bool far = en - b > kMidRow;
+        if (const uint64_t m = __ballot(far)) {
+            int32_t at = 0;
+            if (lane == 0) at = atomicAdd(n_long, (int32_t)__popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at) +
+                 __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
             // rows that overlap, which another row's bounds give away, may be
             // more than there is room for
-            const int32_t at = atomicAdd(n_long, 1);
-            if (at < room) long_rows[at] = (int32_t)e;
-            b = en;
+            if (far && at < room) long_rows[at] = (int32_t)e;
+            if (far) b = en;
         }
         const bool longer = en - b > kShortRow;
         if (en > b && !longer) concat_row(gr + dual_ids[q], e, b, 1, b, en, xcol, xrow, bad);
@@ -354,8 +360,9 @@ hipError_t launch_batch_concat(hipStream_t st, const BatchGraph *gr, const int32
                                int32_t *err) {
     if (E <= 0) return hipSuccess;
     const int32_t room = (int32_t)(ZD / kMidRow);  // rows of more than kMidRow entries
-    k_batch_concat<<<grid_for(E, 256, 65536), 256, 0, st>>>(gr, dual_ids, dbase, GD, E, xcol, xrow,
-                                                            long_rows, room, n_long, err);
+    const int32_t per = lanes_per_wave(E);
+    k_batch_concat<<<grid_for(E, 4 * per, 65536), 256, 0, st>>>(gr, dual_ids, dbase, GD, E, per, xcol,
+                                                                xrow, long_rows, room, n_long, err);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || room == 0) return e;
     k_batch_long<<<grid_for(room, 4, 2048), 256, 0, st>>>(gr, dual_ids, dbase, GD, long_rows, room,

@@ -58,28 +58,36 @@ __device__ __forceinline__ void flat_bounds_row(const int32_t *itmS, int32_t b, 
     }
 }
 
-// A wave looks at 64 lists and takes those of up to kMidList entries that need a
-// row; longer ones go to a list of their own, of which every wave of a second
-// kernel takes one.  (64 long lists in turn, as of the only members there are or of
+// A wave looks at 64 lists, or at fewer if that leaves waves idle, and takes those of
+// up to kMidList entries that need a row; longer ones go to a list of their own, of
+// which every wave of a second kernel takes one.  (64 long lists in turn, as of the only members there are or of
 // hubs with neighbouring ids, would keep the build waiting: 16 lists of 6,250 items,
 // 0.47 ms of a build of 1.34, now 0.92.)
 constexpr int32_t kMidList = 512;
 
 __global__ __launch_bounds__(256) void k_flat_bounds(const int32_t *ptrS, const int32_t *itmS,
                                                      int32_t M, const int32_t *crank, int32_t N,
-                                                     int32_t *bnd, int32_t *long_lists,
-                                                     int32_t *n_long, const int32_t *err) {
-    if (err && *err) return;
+                                                     int32_t per, int32_t *bnd,
+                                                     int32_t *long_lists, int32_t *n_long,
+                                                     const int32_t *n_flat,
+                                                     const int32_t *err) {
+    if ((err && *err) || *n_flat == 0) return;
     crank = ranks_or_null(crank, N);
     const int32_t blocks = flat_blocks(cand_of(crank, N));
     if (blocks < 2) return;  // every item's candidates fit one range of any width
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
-    for (int64_t base = wave * kWave; base < M; base += nwaves * kWave) {
+    for (int64_t base = wave * per; base < M; base += nwaves * per) {
         const int64_t r = base + lane_id();
-        const int32_t b0 = r < M ? ptrS[r] : 0, e0 = r < M ? ptrS[r + 1] : 0;
+        const bool mine = lane_id() < per && r < M;
+        const int32_t b0 = mine ? ptrS[r] : 0, e0 = mine ? ptrS[r + 1] : 0;
         const bool row = e0 - b0 > blocks, far = row && e0 - b0 > kMidList;
-        if (far) long_lists[atomicAdd(n_long, 1)] = (int32_t)r;
+        if (const uint64_t m = __ballot(far)) {
+            int32_t at = 0;
+            if (lane_id() == 0) at = atomicAdd(n_long, (int32_t)__popcll(m));
+            at = uniform(at) + (int32_t)lanes_below(m);
+            if (far) long_lists[at] = (int32_t)r;
+        }
         for (uint64_t m = __ballot(row && !far); m; m &= m - 1) {
             const int l = __builtin_ctzll(m);
             flat_bounds_row(itmS, __builtin_amdgcn_readlane(b0, l), __builtin_amdgcn_readlane(e0, l),
@@ -594,10 +602,13 @@ __global__ __launch_bounds__(kFlatThreads, 4) void k_count_flat(CountArgs A) {
 
 hipError_t launch_flat_bounds(hipStream_t st, const int32_t *ptrS, const int32_t *itmS, int32_t M,
                               const int32_t *crank, int32_t N, int64_t nnz, int32_t *bnd,
-                              int32_t *long_lists, int32_t *n_long, const int32_t *err) {
+                              int32_t *long_lists, int32_t *n_long, const int32_t *n_flat,
+                              const int32_t *err) {
     if (M <= 0 || N <= kFlatBlock) return hipSuccess;
-    const int64_t g = std::min<int64_t>(((int64_t)M + 255) / 256, 4096);
-    k_flat_bounds<<<(unsigned)g, 256, 0, st>>>(ptrS, itmS, M, crank, N, bnd, long_lists, n_long, err);
+    const int32_t per = lanes_per_wave(M);
+    const int64_t g = std::min<int64_t>(((int64_t)M + 4 * per - 1) / (4 * per), 4096);
+    k_flat_bounds<<<(unsigned)g, 256, 0, st>>>(ptrS, itmS, M, crank, N, per, bnd, long_lists, n_long,
+                                               n_flat, err);
     const hipError_t e = hipGetLastError();
     const int64_t most = nnz / kMidList;  // lists of more than kMidList entries
     if (e != hipSuccess || most == 0) return e;

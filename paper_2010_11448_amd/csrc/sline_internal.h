@@ -38,6 +38,15 @@ struct Tuning {
     int32_t tiny_max_wedges = 10;  // items of up to this many wedges go one per lane (0: off)
 };
 
+// Rows that each wave takes of n, where it looks at a row per lane and walks some of
+// them one after the other: 64, or as few as keep kRowWaves waves at work.
+constexpr int64_t kRowWaves = 8192;
+inline int32_t lanes_per_wave(int64_t n) {
+    int32_t per = kWave;
+    while (per > 1 && n < per * kRowWaves) per /= 2;
+    return per;
+}
+
 // Scan tile: 256 threads x 8 items.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
@@ -434,11 +443,12 @@ hipError_t launch_task_fill(hipStream_t st, const int64_t *cost, const PlanItems
 
 // Positions of the multiples of kFlatBlock candidates in the long lists (bnd:
 // as many entries as itmS, nnz at most), for the items counted directly.  long_lists:
-// scratch of as many; n_long: its length, zeroed by the caller.  Nothing is done
-// while *err (if given) is not 0.
+// scratch of as many; n_long: its length, zeroed by the caller; n_flat: the tasks
+// of those items.  Nothing is done without any, or while *err (if given) is not 0.
 hipError_t launch_flat_bounds(hipStream_t st, const int32_t *ptrS, const int32_t *itmS, int32_t M,
                               const int32_t *crank, int32_t N, int64_t nnz, int32_t *bnd,
-                              int32_t *long_lists, int32_t *n_long, const int32_t *err = nullptr);
+                              int32_t *long_lists, int32_t *n_long, const int32_t *n_flat,
+                              const int32_t *err = nullptr);
 
 // Counting-kernel modes.
 enum : int32_t {
