@@ -14,7 +14,8 @@ __device__ __forceinline__ int wave_id() {
     return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
 }
 
-__device__ __forceinline__ int32_t wave_total(int32_t v) {
+template <typename T>
+__device__ __forceinline__ T wave_total(T v) {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
     return v;

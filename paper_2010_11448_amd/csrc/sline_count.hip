@@ -984,18 +984,17 @@ __global__ __launch_bounds__(kWave) void k_count_small(CountArgs A) {
 constexpr int kSieveList = 5 * kWave;  // wedges a wave collects
 // A hash table holds candidates in their order, and where they crowd in a small part
 // of the range, as with neighbours whose ids are close, probes get long.  So a key
-// that finds no room within kItemProbes buckets of its own ends the pass.  The first
-// time, the range becomes what the candidates span; if that is short enough for
-// direct counters in the table, they count it.  If it is at most kItemNear times
-// as long, it is split in halves until they do; beyond, that would take too
-// many passes, and probes are not limited any more.
-// Without all this, with it, and with 8 buckets, s = 2: 30,000 items of 5 to 30 members
-// within 400 of 6,000 vertices 2.20, 0.96, 1.11 ms (hashed tasks took 1.91), one member
-// in 20 anywhere 1.86, 1.09, 1.28; 300,000 such items of 600,000 vertices 3.43, 1.86,
-// 2.37, one in 20 anywhere 3.29, 3.80, 4.18 (7.87); 128 graphs with members anywhere,
-// replayed, 10.13, 10.24, 10.19.
-constexpr int32_t kItemProbes = 4;
-constexpr uint32_t kItemNear = 16;
+// that finds no room within kItemProbes buckets of its own ends the pass, and another
+// pass measures the range's candidates: if direct counters fit what they span, these
+// count it, else it is split at their mean, which sets few distant candidates apart
+// from the others at once.
+// s = 2, with probes to the end of the table and splits at the middle of the range, and
+// so: 300,000 items of 5 to 30 members within 400 of 60,000 vertices 14.1 and 4.0 ms,
+// one member in 20 anywhere 11.8 and 6.2; 783,766 vertices in cliques of some 500
+// neighbours, s = 8, 8.1 and 4.9 (hashed tasks, with wider counters, took 5.3).  128
+// graphs with members anywhere, replayed, lose 2 % by the code for it (10.12, 10.34); with
+// 4 buckets 10.38, with 2 10.8.
+constexpr int32_t kItemProbes = 8;
 
 // What the counting needs of an item.
 struct ItemDesc {
@@ -1035,7 +1034,8 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
     __shared__ int32_t msh[3 * NW];
     __shared__ int2 stack[kStack];
     __shared__ int32_t misc[kMiscWave + NW];
-    __shared__ int2 bnds[NW];  // each wave's least and largest candidate
+    __shared__ int2 span;    // of a measured range: its least and its largest candidate,
+    __shared__ float2 sums;  // their sum less the range's start, and their number
     __shared__ uint64_t pool_cur[3];
     __shared__ int32_t log_cur[3];
     if (count_idle(A)) return;  // uniform: every thread reads the same words
@@ -1100,10 +1100,11 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
             map.narrow = narrow;
             // call body(j) with kLoad candidates per lane (-1: none), over the
             // wave's chunks; the first ones are loaded
+            // as long as it returns true
             auto walk = [&](bool again, auto body) {
                 for (int32_t u = 0; u < run.nc; u += kLoad) {
                     if (u > 0 || again) map.load(A.itmS, run, u, j);
-                    body();
+                    if (!body()) break;
                 }
             };
             // home slots: two per candidate, and a pair takes two wedges at least
@@ -1132,12 +1133,15 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
                         if (j[u] >= 0 && __builtin_amdgcn_ubfe(old[u], h, 1u))
                             atomicOr(&twice[h >> 5], 1u << (h & 31u));
                     }
+                    return true;
                 });
                 __syncthreads();
                 tab_clear<NT>(tab, words);
             }
             ne = load_end(nv);
             if (tid == 0) {
+                span = make_int2(INT32_MAX, -1);
+                sums = make_float2(0.0f, 0.0f);
                 stack[0] = make_int2(first, nend);
                 misc[kMiscDepth] = 1;
                 misc[kMiscOverflow] = 0;
@@ -1146,26 +1150,49 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
             int32_t produced = 0;
             // the first walk left j at the run's last chunks
             bool again = sieve && run.nc > kLoad;
-            bool tight = false;  // the range is what the candidates span
-            uint32_t least = ~0u;  // of the candidates that went to the table
-            int32_t last = -1;
-            auto add4 = [&](const Range &R, int32_t probes, int32_t x0, int32_t x1, int32_t x2,
-                            int32_t x3) {
-                least = min(min(least, min((uint32_t)x0, (uint32_t)x1)), min((uint32_t)x2, (uint32_t)x3));
-                last = max(max(last, max(x0, x1)), max(x2, x3));
-                return tab_add4(tab, S.spare, R, x0, x1, x2, x3, probes);
+            bool measure = false;  // this pass looks at the candidates of the range alone
+            if (SIEVE && NW == 1 && sieve) {
+                // it starts with that where the last 128 of the first walk are close
+                const int32_t x = wave_least(
+                    (int32_t)min(min((uint32_t)j[0], (uint32_t)j[1]), (uint32_t)INT32_MAX));
+                measure = ~wave_least(~max(j[0], j[1])) - x < want << pack_shift(cb);
+            }
+            // up to four candidates of the range per lane, to the table or measured;
+            // whether the wave's all found room
+            auto take4 = [&](const Range &R, int32_t x0, int32_t x1, int32_t x2, int32_t x3) {
+                if (!measure)
+                    return __ballot(!tab_add4(tab, S.spare, R, x0, x1, x2, x3, kItemProbes)) == 0;
+                const int32_t x[4] = {x0, x1, x2, x3};
+                int32_t least = INT32_MAX, last = -1, count = 0;
+                float sum = 0.0f;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool in = x[u] >= R.lo && x[u] < R.hi;
+                    if (in) least = min(least, x[u]);
+                    if (in) last = max(last, x[u]);
+                    if (in) sum += (float)(x[u] - R.lo);
+                    count += (int32_t)__popcll(__ballot(in));
+                }
+                least = wave_least(least);
+                last = ~wave_least(~last);
+                sum = wave_total(sum);
+                if (lane == 0) {
+                    atomicMin(&span.x, least);
+                    atomicMax(&span.y, last);
+                    atomicAdd(&sums.x, sum);
+                    atomicAdd(&sums.y, (float)count);
+                }
+                return true;
             };
             for (;;) {
                 const int32_t depth = misc[kMiscDepth];
                 const int2 top = depth ? stack[depth - 1] : make_int2(0, 0);
                 if (depth == 0) break;
                 const Range R = make_range(top.x, top.y, want, kTaskPad, cb);
-                bool split = too_wide(R);
-                auto near = [&](uint32_t span) { return span <= ((uint32_t)want << 2) * kItemNear; };
-                const int32_t probes = !tight || near(R.span) ? kItemProbes : kAllProbes;
+                bool split = too_wide(R) && !measure;
                 if (!split) {
-                    ++passes;
-                    bool ok = true;
+                    if (!measure) ++passes;
+                    bool ok = true;  // of the wave
                     if (SIEVE) {
                         int32_t *const mine = list + wid * kSieveList;
                         int32_t n = 0;  // wedges collected
@@ -1186,69 +1213,67 @@ __global__ __launch_bounds__(NT, MINB) void k_count_item(CountArgs A) {
                                 n += __popcll(m);
                                 if (n >= 4 * kWave) {
                                     __builtin_amdgcn_wave_barrier();
-                                    ok &= add4(R, probes, mine[lane], mine[kWave + lane],
-                                               mine[2 * kWave + lane], mine[3 * kWave + lane]);
+                                    ok = ok && take4(R, mine[lane], mine[kWave + lane],
+                                                     mine[2 * kWave + lane], mine[3 * kWave + lane]);
                                     n -= 4 * kWave;
                                     if (lane < n) mine[lane] = mine[4 * kWave + lane];
                                     __builtin_amdgcn_wave_barrier();
                                 }
                             }
+                            return ok;
                         });
                         again = run.nc > kLoad;
                         __builtin_amdgcn_wave_barrier();
-                        if (n > 0) {
+                        if (ok && n > 0) {
                             int32_t x[4];
 #pragma unroll
                             for (int u = 0; u < 4; ++u)
                                 x[u] = u * kWave + lane < n ? mine[u * kWave + lane] : -1;
-                            ok &= add4(R, probes, x[0], x[1], x[2], x[3]);
+                            ok = take4(R, x[0], x[1], x[2], x[3]);
                         }
                     } else {
-                        if (run.nc > 0) ok &= add4(R, probes, j[0], j[1], j[2], j[3]);
+                        if (run.nc > 0) ok = take4(R, j[0], j[1], j[2], j[3]);
                     }
                     if (!ok) misc[kMiscOverflow] = 1;
                     __syncthreads();
                     split = misc[kMiscOverflow] != 0;
-                    if (!split) produced += tab_extract<NT, RUNCAP, FILL ? 1 : 0, true>(A, S, R, a, s, t, produced);
-                    else tab_clear<NT>(tab, R.limit);
-                }
-                const bool tighten = split && !tight && R.mul != 0 && !too_wide(R);
-                if (tighten) {
-                    tight = true;
-                    const int32_t x = wave_least((int32_t)min(least, (uint32_t)INT32_MAX));
-                    const int32_t y = ~wave_least(~last);
-                    if (lane == 0) bnds[wid] = make_int2(x, y);
+                    if (measure) {
+                        // nothing went to the table
+                    } else if (!split) {
+                        produced += tab_extract<NT, RUNCAP, FILL ? 1 : 0, true>(A, S, R, a, s, t, produced);
+                    } else {
+                        tab_clear<NT>(tab, R.limit);
+                    }
                 }
                 __syncthreads();
                 if (tid == 0) {
                     int32_t d = depth - 1;
-                    if (split) {
-                        int2 r = top;
-                        if (tighten) {
-                            r = make_int2(INT32_MAX, -1);
-#pragma unroll
-                            for (int w = 0; w < NW; ++w) {
-                                r.x = min(r.x, bnds[w].x);
-                                r.y = max(r.y, bnds[w].y);
-                            }
-                            r = make_int2(max(r.x, R.lo), min(r.y + 1, R.hi));
-                        }
-                        // a range that is now short enough for direct counters,
-                        // or to be tried with longer probes, goes on whole
-                        const uint32_t span = (uint32_t)(r.y - r.x);
-                        if (tighten && (span <= (uint32_t)want << pack_shift(cb) || !near(span))) {
+                    if (measure) {
+                        // what the candidates span, if direct counters fit it; else
+                        // its parts below and above their mean
+                        const int2 r = make_int2(span.x, span.y + 1);
+                        if (r.x >= r.y) {
+                            // none at all
+                        } else if ((uint32_t)(r.y - r.x) <= (uint32_t)want << pack_shift(cb)) {
                             stack[d++] = r;
                         } else {
-                            const int32_t mid = (int32_t)(((int64_t)r.x + r.y) / 2);
+                            int32_t mid = d < kStack / 2 ? R.lo + (int32_t)(sums.x / sums.y)
+                                                         : (int32_t)(((int64_t)r.x + r.y) / 2);
+                            mid = min(max(mid, r.x + 1), r.y - 1);
                             stack[d] = make_int2(mid, r.y);
                             stack[d + 1] = make_int2(r.x, mid);
                             d += 2;
                         }
+                    } else if (split) {
+                        ++d;  // the range stays, to be measured
                         misc[kMiscOverflow] = 0;
+                        span = make_int2(INT32_MAX, -1);
+                        sums = make_float2(0.0f, 0.0f);
                     }
                     misc[kMiscDepth] = d;
                 }
                 __syncthreads();
+                measure = split && !measure;
             }
             if (sieve) tab_clear<NT>(twice, words);
             if (!FILL) {
