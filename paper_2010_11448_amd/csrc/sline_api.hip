@@ -340,8 +340,10 @@ struct Layout {
 // the items outnumber the lanes of the resident one-wave workgroups several
 // times over (a lane walks its item's lists one entry after another).
 constexpr int64_t kTinyMinItems = 1 << 15;
-// Staging pools below kPoolSlackMax pairs get room to spare (see build_core).
-constexpr int64_t kPoolSlackMax = 1 << 27;
+// Staging pools below kPoolSlackMax pairs get room to spare (see pool_pairs): 8 GB of
+// pairs and 1 GB more.  Larger ones have none: with the result beside them they may
+// already take most of the memory.
+constexpr int64_t kPoolSlackMax = 1 << 30;
 constexpr int64_t kLogPerWg = 32;  // log records for each workgroup's chunks
 Tuning build_tuning(const Tuning &t, int64_t n_items, int64_t nnz) {
     Tuning u = t;
