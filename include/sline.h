@@ -169,10 +169,11 @@ typedef struct {
  *   stage_max_bytes    cap of the staging pool that lets one counting pass
  *                      produce the result; tasks that do not fit are counted
  *                      again (>= 0; 0 = always two passes)
- *   dense_min_wedges   an item with more wedges than a sieve takes is counted
- *                      by direct (unhashed) counters when it has at least an
- *                      eighth of this many wedges per range of candidates
- *                      that they hold (a sixteenth with s = 1 and at most
+ *   dense_min_wedges   an item with more wedges than a sieve takes, or than a
+ *                      sieve of one wave where its candidates fit two ranges
+ *                      of direct (unhashed) counters, is counted by those
+ *                      when it has at least an eighth of this many wedges per
+ *                      range that they hold (a sixteenth with s = 1 and at most
  *                      16384 wedges); other items are cut into unhashed
  *                      sub-ranges of the task kernel where each gets at
  *                      least this many (0..2^24; 0 = hash tables alone, for

@@ -5,15 +5,17 @@
 //   1. row_ptr check, nnz read-back                      (one host sync)
 //   2. row ids, member range / order checks
 //   3. transpose: a stable radix sort of the (member, incidence) pairs,
-//      whose last pass writes the row ids and the position maps; the member
-//      checks are read back                              (one host sync)
+//      whose last pass writes the row ids and the position maps (a primal
+//      build sorts the kept items' incidences alone, so that 5 comes with it)
 //   4. items / member lists chosen by the dual flag (H* swaps the roles, Sec. III)
 //   5. s-filtered member lists N_s(v) (degree-based pruning, Sec. IV-C) and
 //      the back-pointer of every incidence of a kept item
-//   6. exact per-item wedge counts W_a, lookup-only members (s > 1), tasks
-//      (one-wave items and workgroup task groups)       (one host sync)
+//   6. exact per-item wedge counts W_a and tasks, read back with what the member
+//      checks found                                      (one host sync); where
+//      tasks are hashed and s > 1, lookup-only members and the tasks again
+//                                                        (one more)
 //   7. one counting pass staging each range's pairs, exclusive scan of pairs
-//      per task                                          (one host sync)
+//      per task                                         (one host sync)
 //   8. output allocation, staged ranges copied to their offsets, tasks
 //      without room counted again                      (one host sync)
 // sline_build_batch runs the same stages once over many graphs (their items

@@ -22,13 +22,14 @@
 // every overlap; a range is as wide as the counters fit in kFlatWords words.
 //
 // What bounds it: vector instructions (about 20 per 64 wedges and 250 per wave
-// and range; they fill 54% of the cycles), and the waits of a range that is too
-// short to hide them: LDS reads one after the other, three barriers, lists that
+// and range; 56% of a SIMD's cycles by the counters), and the waits of a range that is
+// too short to hide them (54% of a wave's cycles): LDS reads one after the other, three barriers, lists that
 // are read for the first time.  Two workgroups of 512 threads share a CU, so one
 // counts while the other waits or clears.  A wave's chunks are counted eight at a time,
 // the last ones in groups of eight, four or two: 10^6 hyperedges, s = 2 (8.7*10^9
 // wedges, most of them here): 20.6 ms, 22.0 with eight for all, 24.0 before the
-// kernel was compiled apart for the fill mode and for s = 1.
+// kernel was compiled apart for the fill mode and for s = 1 (21.4 since it takes the
+// items of one or two ranges too, of which it relieves the sieves).
 #include <algorithm>
 
 #include "sline_count.h"
@@ -60,9 +61,9 @@ __device__ __forceinline__ void flat_bounds_row(const int32_t *itmS, int32_t b, 
 
 // A wave looks at 64 lists, or at fewer if that leaves waves idle, and takes those of
 // up to kMidList entries that need a row; longer ones go to a list of their own, of
-// which every wave of a second kernel takes one.  (64 long lists in turn, as of the only members there are or of
-// hubs with neighbouring ids, would keep the build waiting: 16 lists of 6,250 items,
-// 0.47 ms of a build of 1.34, now 0.92.)
+// which every wave of a second kernel takes one.  (64 long lists in turn, as of the
+// only members there are or of hubs with neighbouring ids, would keep the build
+// waiting: 16 lists of 6,250 items, 0.47 ms of a build of 1.34, now 0.92.)
 constexpr int32_t kMidList = 512;
 
 __global__ __launch_bounds__(256) void k_flat_bounds(const int32_t *ptrS, const int32_t *itmS,

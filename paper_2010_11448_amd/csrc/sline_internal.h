@@ -70,14 +70,16 @@ constexpr int kTinyThreads = 256;
 // ... in id order and let the member lists hold those ranks: the candidates
 // of an item then lie in a range with no items that cannot be in a pair, so
 // the range is cut into fewer tables.  The price is a look-up per pair to
-// turn ranks back into items (on the 10^6-item power-law graph, 4 of 74 ms
-// at s = 2, where 99.98 % of the items are kept; at s = 8, 15 % kept, the
-// build takes 18.9 instead of 21.7 ms, and 12.4 instead of 13.8 on the dual
-// side).  Ranks are used when at most three in four items are kept (crank[N]
-// counts them; every kernel derives the same answer from it), in builds of one
-// graph with kRankMinItems items or more: a smaller one fits a few tables
-// anyhow, and so does each graph of a batch (128 lognormal graphs of up to
-// 200,000 hyperedges: 11.1 ms with ranks, 10.7 without).
+// turn ranks back into items.  Build time without and with ranks: 10^6-item power
+// law, s = 2 (99.98 % kept) 34.4 and 37.9 ms, s = 3 23.3 and 20.3, s = 8 (15 % kept)
+// 11.0 and 6.0, its dual at s = 8 9.1 and 3.1; 10^6 items of even sizes, 95 %, 74 % and
+// 47 % kept, 14.4 and 14.2, 11.5 and 11.1, 6.45 and 6.57.  Ranks are used when at
+// most three in four items are kept (crank[N] counts them; every kernel derives the
+// same answer from it): what more would bring rests on how sizes and wedges go
+// together, and the line is on the safe side of it.  And in builds of one graph with
+// kRankMinItems items or more, as a smaller one fits a few ranges anyhow (even
+// sizes, 63 % kept: 131,072 items 1.30 and 1.23 ms, 100,000 items 0.968 and
+// 0.972, 50,000 items 0.63 and 0.65), and so does each graph of a batch.
 constexpr int64_t kRankMinItems = 1 << 17;
 __host__ __device__ inline bool ranks_pay(int64_t kept, int64_t N) { return kept * 4 <= N * 3; }
 
@@ -219,8 +221,8 @@ enum : int32_t {
 // least dense_min / 8 wedges per range (512; a sixteenth where it keeps its
 // wedges, s = 1).  Fewer change little, as a range's fixed work is then about what
 // hashing costs; with more, hashing is slower.  Build time with at least 64, 512,
-// 2048 and 8192 wedges a range: 10^6 hyperedges, s = 2: 33.7, 33.8, 35.5, 51.5 ms;
-// s = 8: 6.4, 6.3, 6.5, 7.1; 200,000, s = 1 (half as many): 4.5, 4.6, 4.9, 6.7.
+// 2048 and 8192 wedges a range: 10^6 hyperedges, s = 2: 34.6, 34.6, 36.2, 52.9 ms;
+// s = 8: 6.0, 6.0, 6.1, 7.1; 200,000, s = 1 (half as many): 5.5, 5.5, 5.8, 7.6.
 // `cost` is W_a, or the lowered planning
 // cost of an item that was not to be counted so by its W_a (and is not by less).
 __device__ __forceinline__ int32_t direct_tasks(const PlanItems &I, int32_t a, int64_t cost,
