@@ -23,9 +23,9 @@
 //
 // What bounds it: vector instructions (about 20 per 64 wedges and 250 per wave
 // and range; 56% of a SIMD's cycles by the counters), and the waits of a range that is
-// too short to hide them (54% of a wave's cycles): LDS reads one after the other, three barriers, lists that
-// are read for the first time.  Two workgroups of 512 threads share a CU, so one
-// counts while the other waits or clears.  A wave's chunks are counted eight at a time,
+// too short to hide them (54% of a wave's cycles): LDS reads one after the other,
+// three barriers, lists that are read for the first time.  Two workgroups of 512
+// threads share a CU, so one counts while the other waits or clears.  A wave's chunks are counted eight at a time,
 // the last ones in groups of eight, four or two: 10^6 hyperedges, s = 2 (8.7*10^9
 // wedges, most of them here): 20.6 ms, 22.0 with eight for all, 24.0 before the
 // kernel was compiled apart for the fill mode and for s = 1 (21.4 since it takes the

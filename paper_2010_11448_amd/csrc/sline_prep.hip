@@ -741,8 +741,9 @@ __global__ __launch_bounds__(256) void k_cost(const int32_t *ptrI, const int32_t
 // inserting members (they fill the table), but at least a third of W_a
 // (every wedge is still read).  A lane looks at each item, and the wave then takes
 // those that the task kernel counts, one after the other: they are few (a
-// group of lanes for every item took 0.31 ms for 5*10^6 of them, this 0.09).  Rows of up to 256 and up to 2048 members keep their keys in registers,
-// so the rounds only exchange maxima; longer rows read their members again in
+// group of lanes for every item took 0.31 ms for 5*10^6 of them, this 0.09).  Rows of up to
+// 256 and up to 2048 members keep their keys in registers, so the rounds only
+// exchange maxima; longer rows read their members again in
 // every round (as all above 256 did: one of 2000 members kept the kernel up 0.25 ms).
 // The lane that owns incidence k is the one that flags it.
 constexpr int kKeysFew = 4, kKeysMany = 32;
